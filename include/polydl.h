@@ -27,7 +27,8 @@
  *   - HIP graphs: every entry point may be captured.  Three rules follow from the scratch memory
  *     above.  (1) A call that would have to allocate or grow it while its stream is being
  *     captured returns POLYDL_ERR_UNSUPPORTED and records nothing: run the same call once on
- *     that stream before capturing (or use polydl_conv2d_fwd_noalloc).  (2) A graph keeps the
+ *     that stream before capturing (or use polydl_conv2d_fwd_noalloc).  (A matrix product whose
+ *     variant the library chooses takes its best unsplit variant instead.)  (2) A graph keeps the
  *     scratch addresses of its capture stream; they stay valid for the life of the process.
  *     (3) Replaying the graph, on any stream, uses the scratch memory of the stream it was
  *     CAPTURED on: do not let a replay overlap in time with other split-reduction work of this
@@ -158,7 +159,10 @@ int polydl_conv2d_fwd_tap(int N, int C, int H, int W, int K, int R, int S, int s
 /* ---- matrix product ------------------------------------------------------------------------
  * C[i][j] += sum_k A[i][k] * B[k][j]   (alpha = beta = 1, the reading taken of section "GEMM").
  * Row-major, A is M x K, B is K x N, C is M x N and is read and accumulated into.  K = 0 is
- * allowed (C is left as it is). */
+ * allowed (C is left as it is).  The variants with stage depth 16 and wave tiles up to 64 x 64 split both
+ * operands into three bfloat16 parts each and sum six of their products in float32 (smaller error against
+ * 64 bits than float32 products summed in sequence); tiles that meet values this cannot hold
+ * (infinities, NaN, rows or columns of numbers below 2^-95) are computed from float32 products. */
 int polydl_sgemm(int M, int N, int K, const float *A, const float *B, float *C, void *stream);
 
 /* The general form the text of section "GEMM" states, C = beta*C + alpha*A*B, with both scalars

@@ -158,6 +158,7 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
     if (K == 0 && beta == 1.f) return POLYDL_OK;
     if (!on_gfx950()) return POLYDL_ERR_NO_DEVICE;
     polydl_tile_cfg cfg;
+    bool picked = false;
     if (K == 0) {
         // an empty product: only C = beta*C is left, any variant's epilogue does it
         cfg_of(kVariants[0], 1, 0, 0, &cfg);
@@ -165,6 +166,7 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
         std::lock_guard<std::mutex> lk(g_mu);
         cfg = g_override;
         if (!g_have_override) {
+            picked = true;
             const std::array<int, 3> key = {M, N, K};
             auto it = g_sgemm_plans.find(key);
             if (it != g_sgemm_plans.end()) {
@@ -177,16 +179,28 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
             }
         }
     }
-    const Variant *v = find_variant(cfg);
-    if (!v) return POLYDL_ERR_UNSUPPORTED;
-    // 32-bit byte offsets inside one workgroup's slice of A (bm rows) and of B (bk rows)
-    if ((uint64_t)v->bm * (uint64_t)K * 4 >= 0x7FFFFFF0ull) return POLYDL_ERR_UNSUPPORTED;
-    if ((uint64_t)v->bk * (uint64_t)N * 4 >= 0x7FFFFFF0ull) return POLYDL_ERR_UNSUPPORTED;
-    if ((uint64_t)v->bm * (uint64_t)N * 4 >= 0x7FFFFFF0ull) return POLYDL_ERR_UNSUPPORTED;   // and of C (bm rows)
-    uint64_t tiles = (uint64_t)((M + v->bm - 1) / v->bm) * (uint64_t)((N + v->bn - 1) / v->bn);
-    if (tiles >= 0x7FFFFFFFull || cfg.split_k > 65535 || cfg.raster >= 2) return POLYDL_ERR_UNSUPPORTED;
-    SgemmProblem q{M, N, K, A, B, C, alpha, beta};
-    hipError_t e = v->sgemm(q, cfg.split_k < 1 ? 1 : cfg.split_k, cfg.raster, (hipStream_t)stream);
+    auto launch = [&](hipError_t *e) {
+        const Variant *v = find_variant(cfg);
+        if (!v) return false;
+        // 32-bit byte offsets inside one workgroup's slice of A (bm rows) and of B (bk rows)
+        if ((uint64_t)v->bm * (uint64_t)K * 4 >= 0x7FFFFFF0ull) return false;
+        if ((uint64_t)v->bk * (uint64_t)N * 4 >= 0x7FFFFFF0ull) return false;
+        if ((uint64_t)v->bm * (uint64_t)N * 4 >= 0x7FFFFFF0ull) return false;   // and of C (bm rows)
+        uint64_t tiles = (uint64_t)((M + v->bm - 1) / v->bm) * (uint64_t)((N + v->bn - 1) / v->bn);
+        if (tiles >= 0x7FFFFFFFull || cfg.split_k > 65535 || cfg.raster >= 2) return false;
+        SgemmProblem q{M, N, K, A, B, C, alpha, beta};
+        *e = v->sgemm(q, cfg.split_k < 1 ? 1 : cfg.split_k, cfg.raster, (hipStream_t)stream);
+        return true;
+    };
+    hipError_t e;
+    if (!launch(&e)) return POLYDL_ERR_UNSUPPORTED;
+    if (picked && e != hipSuccess && scratch_refusal() == SCRATCH_CAPTURING) {
+        // the stream is being captured and has no scratch memory for a split reduction yet: the best
+        // variant that needs none (not cached)
+        polydl_model_report rep;
+        SgemmProblem pq{M, N, K, A, B, C};
+        if (!pick_sgemm(pq, &cfg, &rep, true) || !launch(&e)) return POLYDL_ERR_UNSUPPORTED;
+    }
     if (e != hipSuccess) return launch_failed(e);
     std::lock_guard<std::mutex> lk(g_mu);
     g_last = cfg;

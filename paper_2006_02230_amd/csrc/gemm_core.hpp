@@ -101,6 +101,10 @@ struct Tile {
     static constexpr int MIN_WAVES = MB * NB >= 8 ? 2 : 1;
     // where SGEMM runs the split stage schedule (gemm_stage): two chunks per stage, two blocks and more
     static constexpr bool SPLIT_STAGE = BK == 16 && MB * NB >= 2;
+    // tiles whose products are formed on the bfloat16 matrix cores from three-way split operands
+    // (split_core.hpp): two accumulator sets of a wave tile of eight blocks would not fit the registers
+    static constexpr bool SPLIT = BK == 16 && MB * NB <= 4;
+    static constexpr int SPLIT_WAVES = MB * NB == 4 ? 2 : MB * NB == 2 ? 3 : 4;   // waves per SIMD of those kernels
     static constexpr int LDA = BK + 4;                 // LDS row pitch of the A stage [BM][LDA]
     static constexpr int LDB = BN + 4;                 // LDS row pitch of the B stage [BK][LDB]
     static constexpr int A_STAGE = BM * LDA, B_STAGE = BK * LDB;

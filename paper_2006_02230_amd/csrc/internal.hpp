@@ -149,6 +149,11 @@ inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, siz
     return launch_kernel_impl(kernel, grid, block, lds, st, vals, std::index_sequence_for<P...>{});
 }
 
+// Tiles whose products are formed on the bfloat16 matrix cores (Tile::SPLIT), and the LDS of their two stage
+// buffers (SplitTile::SPLIT_BYTES without the bank skews).
+constexpr bool split_products(int bk, int wm, int wn) { return bk == 16 && wm * wn <= 64 * 64; }
+constexpr int split_lds_bytes(int bm, int bn) { return 2 * 6 * 16 * (bm + bn); }
+
 // picker.cpp
 void reuse_bucket(int n, const double *ws, int nlevels, const double *sizes, double *levels, double *mem);
 double reuse_cost(int nlevels, const double *levels, double mem, const double *weights, double mem_weight);
@@ -157,8 +162,9 @@ void model_set_levels(const double *capacity, const double *gbytes_per_s, double
 void model_conv(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads, int reg_class, polydl_model_report *r);
 void model_sgemm(const SgemmProblem &q, const polydl_tile_cfg &cfg, int threads, polydl_model_report *r);
 double model_conv_bf16(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads);   // predicted microseconds
-bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *rep);   // q.pre_act: gather kernel only
-bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_report *rep);
+// no_scratch: only variants that need no scratch memory (nothing split)
+bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *rep, bool no_scratch = false);   // q.pre_act: gather kernel only
+bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_report *rep, bool no_scratch = false);
 struct ConvCandidate { polydl_tile_cfg cfg; polydl_model_report rep; };
 // every (variant, stage depth, split factor, leftover-tile switch) pick_conv ranks, with its model report
 void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out);

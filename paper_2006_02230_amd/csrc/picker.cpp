@@ -118,6 +118,10 @@ struct Cand {
     double gather_elems = 0;     // B elements a thread gathers per stage (im2col addressing in the ALUs)
     double gather_cycles = 0;    // cycles of that addressing per element
     double split_c0 = 0, split_c1 = 0;   // split reduction: microseconds, and microseconds per MB of parts
+    // Tiles whose products run on the bfloat16 matrix cores (split_core.hpp): six 32-cycle instructions per 16
+    // reduction steps instead of eight of 64; split_eff is the matrix-core share of their loop.
+    bool split = false;
+    double split_eff = 0.4;
     bool tail_split = false;     // the kernel cuts the leftover tiles of an unsplit grid (tail_split())
 };
 
@@ -147,9 +151,14 @@ static void model(const Shape &s, const Cand &c, polydl_model_report *r)
     eff *= c.steps_per_stage / (c.steps_per_stage + 1.0 / (mb * nb));
     if (resident < 2) eff *= 0.72;
     else if (resident * mb * nb < 4) eff *= 0.85;   // two small waves leave gaps a third would fill
+    double step_cycles = 64.0;
+    if (c.split) {
+        step_cycles = 24.0;
+        eff = c.split_eff * (resident < 2 ? 0.74 : 1.0);
+    }
     // setup plus an epilogue that grows with the accumulators a lane has to store
     const double overhead = c.wg_overhead_cycles * (0.3 + 0.7 * mb * nb / 2.0);
-    const double wave_cycles = steps * mb * nb * 64.0 / eff + overhead;
+    const double wave_cycles = steps * mb * nb * step_cycles / eff + overhead;
     double mfma_us = waves_on_busiest_simd * wave_cycles / kClockHz * 1e6;
     if (c.rounds) {
         // Resident workgroups per CU, from registers (512 per SIMD lane, at most 8 waves per SIMD)
@@ -424,11 +433,25 @@ void model_sgemm(const SgemmProblem &q, const polydl_tile_cfg &cfg, int threads,
     c.kernel_fixed_us = 6.0;
     // from the kernels' register counts (the eight-block wave tiles are held to 256 registers)
     c.max_waves_per_simd = (cfg.wm * cfg.wn > 64 * 64) ? 2 : ((cfg.wm * cfg.wn == 64 * 64) ? 3 : 4);
+    double part_rate = 1.0, part_us = 0.4, parts_us = 0.0;
+    if (split_products(cfg.bk, cfg.wm, cfg.wn)) {
+        // Fitted to a sweep of 18 sizes from 256^3 to 4096^3, thin and long ones among them: the picks run
+        // within 5 % of the sweep's best.  The smaller the wave tile, the more splitting and the more LDS
+        // reads per matrix instruction; 512 threads split a 256x128 tile's operands once for twice the outputs.
+        const int blocks = cfg.wm * cfg.wn / 1024;
+        c.split = true;
+        c.split_eff = blocks == 1 ? 0.343 : blocks == 2 ? 0.429 : threads == 512 ? 0.654 : 0.572;
+        c.wg_overhead_cycles = 1330;
+        c.max_waves_per_simd = blocks == 1 ? 4 : blocks == 2 ? 3 : 2;
+        c.lds_bytes = split_lds_bytes(cfg.bm, cfg.bn);
+        // the last part of a tile adds all parts alone, at what one compute unit can read (84 GB/s)
+        part_rate = 0.36; part_us = 0.2; parts_us = 1.85 + cfg.split_k * (double)cfg.bm * cfg.bn * 4 / 84.0 * 1e-3;
+    }
     model(s, c, r);
     if (cfg.split_k > 1) {   // every part writes its tile to scratch once, the last one reads them all back
         // plus the hand-over itself (store, count, read back), which no amount of bandwidth shortens
-        r->fixed_us = c.kernel_fixed_us + 2.0 * cfg.split_k * (double)q.M * q.N * 4 / kHbmGBs * 1e-3 +
-                      0.4 * (cfg.split_k - 1);
+        r->fixed_us = c.kernel_fixed_us + 2.0 * part_rate * cfg.split_k * (double)q.M * q.N * 4 / kHbmGBs * 1e-3 +
+                      part_us * (cfg.split_k - 1) + parts_us;
         r->predicted_us = std::max(r->mfma_us, r->mem_us) + r->fixed_us;
     }
 }
@@ -500,6 +523,7 @@ void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out)
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &v = kVariants[i];
         const long stages = (Kg + v.bk - 1) / v.bk;
+        if (v.bm == 256 && v.wm == 64) continue;   // a tile of the matrix product alone
         for (int sk : kSplits) {
             if (sk > stages) break;
             // raster 1: each XCD's workgroups take neighbouring tiles, so filter rows and the input rows
@@ -520,7 +544,7 @@ void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out)
     }
 }
 
-bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep)
+bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep, bool no_scratch)
 {
     std::vector<ConvCandidate> cands;
     conv_candidates(q, &cands);
@@ -533,8 +557,10 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
         return c.cfg.bm * c.cfg.bn < b.cfg.bm * b.cfg.bn;
     };
     const ConvCandidate *b = nullptr;
-    for (const ConvCandidate &c : cands)
+    for (const ConvCandidate &c : cands) {
+        if (no_scratch && (c.cfg.split_k > 1 || c.cfg.raster >= 2)) continue;
         if (!b || before(c, *b)) b = &c;
+    }
     if (!b) return false;
     *best = b->cfg;
     *best_rep = b->rep;
@@ -558,13 +584,14 @@ void sgemm_candidates(const SgemmProblem &q, std::vector<polydl_tile_cfg> *out)
     }
 }
 
-bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep)
+bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep, bool no_scratch)
 {
     bool have = false;
     polydl_model_report rep;
     std::vector<polydl_tile_cfg> cands;
     sgemm_candidates(q, &cands);
     for (const polydl_tile_cfg &c : cands) {
+        if (no_scratch && c.split_k > 1) continue;
         model_sgemm(q, c, (c.bm / c.wm) * (c.bn / c.wn) * 64, &rep);
         if (c.raster == 1) rep.predicted_us *= 0.999;   // ties go to the XCD-aware order
         if (!have || rep.predicted_us < best_rep->predicted_us) { *best = c; *best_rep = rep; have = true; }

@@ -2,6 +2,7 @@
 // "Notation"; two-level tiling as in figure "A code version generated for PolyDL").
 #include "gemm_core.hpp"
 #include "internal.hpp"
+#include "split_core.hpp"
 #include "variants.hpp"
 #include <type_traits>
 
@@ -19,35 +20,14 @@ struct SgemmKArgs {
     unsigned *counters;        // split_k > 1: per tile, how many of its reduction parts have finished
 };
 
-// AVEC / BVEC: 4 when the operand allows 128-bit loads, else 1.  CVEC: the lane's NB adjacent
-// output columns are read and written as one vector when N % NB == 0 and C is 16-byte aligned.
-template <class T, int AVEC, int BVEC, bool CVEC>
-__global__ __launch_bounds__(T::NT, T::MIN_WAVES) void sgemm_kernel(SgemmKArgs p)
+// What follows the reduction: the hand-over of a split reduction's parts, then C = beta*C + alpha*acc.
+// CVEC: the lane's NB adjacent output columns are read and written as one vector when N % NB == 0 and C
+// is 16-byte aligned.
+template <class T, bool CVEC>
+__device__ __forceinline__ void sgemm_finish(const SgemmKArgs &p, v16f (&acc)[T::MB][T::NB], int tid, int m0, int n0,
+                                             int wm0, int wn0)
 {
-    __shared__ __attribute__((aligned(16))) float lds[T::LDS_FLOATS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int tm, tn;
-    tile_coords(blockIdx.x, p.raster, p.tiles_m, p.tiles_n, tm, tn);
-    const int m0 = tm * T::BM, n0 = tn * T::BN;
-    const int wm0 = (wave % T::WAVES_M) * T::WM, wn0 = (wave / T::WAVES_M) * T::WN;
-    const int kbegin = blockIdx.y * p.k_per_split;
-    const int kend = min(p.K, kbegin + p.k_per_split);
-
-    ALoader<T, AVEC> al;
-    BLoaderRows<T, BVEC> bl;
-    al.init(p.A, tid, m0, p.M, p.K, p.K);
-    bl.init(p.B, tid, n0, p.N, p.K, p.N);
-
-    v16f acc[T::MB][T::NB];
-#pragma unroll
-    for (int bi = 0; bi < T::MB; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < T::NB; ++bj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
-
-    if (kbegin < kend) gemm_mainloop<T, T::SPLIT_STAGE>(lds, al, bl, acc, kbegin, kend, tid, wm0, wn0);
-
+    const int lane = tid & 63;
     // With the reduction split over blockIdx.y every part leaves its accumulator tile in scratch
     // memory (thread-contiguous, device-scope stores); the part that arrives last adds all parts
     // in index order and alone updates C, so the result does not depend on the order of arrival.
@@ -123,6 +103,83 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void sgemm_kernel(SgemmKArgs p
     else rows(std::false_type{});
 }
 
+// AVEC / BVEC: 4 when the operand allows 128-bit loads, else 1.
+template <class T, int AVEC, int BVEC, bool CVEC>
+__global__ __launch_bounds__(T::NT, T::MIN_WAVES) void sgemm_kernel(SgemmKArgs p)
+{
+    __shared__ __attribute__((aligned(16))) float lds[T::LDS_FLOATS];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    int tm, tn;
+    tile_coords(blockIdx.x, p.raster, p.tiles_m, p.tiles_n, tm, tn);
+    const int m0 = tm * T::BM, n0 = tn * T::BN;
+    const int wm0 = (wave % T::WAVES_M) * T::WM, wn0 = (wave / T::WAVES_M) * T::WN;
+    const int kbegin = blockIdx.y * p.k_per_split;
+    const int kend = min(p.K, kbegin + p.k_per_split);
+
+    ALoader<T, AVEC> al;
+    BLoaderRows<T, BVEC> bl;
+    al.init(p.A, tid, m0, p.M, p.K, p.K);
+    bl.init(p.B, tid, n0, p.N, p.K, p.N);
+
+    v16f acc[T::MB][T::NB];
+#pragma unroll
+    for (int bi = 0; bi < T::MB; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
+
+    if (kbegin < kend) gemm_mainloop<T, T::SPLIT_STAGE>(lds, al, bl, acc, kbegin, kend, tid, wm0, wn0);
+
+    sgemm_finish<T, CVEC>(p, acc, tid, m0, n0, wm0, wn0);
+}
+
+// The same with the products formed on the bfloat16 matrix cores (split_core.hpp).  Bound: 4096^3 runs the
+// bfloat16 instructions at 1.26 PFLOP/s with random values and 1.72 with zeros -- the clock gives way to
+// power, the vendor's bfloat16 product of that size reaches 1.26 -- and below 2048^3 one wave's instruction
+// issue (8 non-matrix instructions per 32-cycle matrix instruction with one wave per SIMD).  The 256x128 tile
+// with eight waves splits an operand once for twice the outputs: 668 -> 639 us against 128x128.
+// 4096^3 959 -> 639 us, 2048^3 134 -> 100, 1024^3 26 -> 24, 1024 x 32768 x 1024 490 -> 340.
+template <class T, bool CVEC>
+__global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void sgemm_split_kernel(SgemmKArgs p)
+{
+    __shared__ __attribute__((aligned(16))) u32x4 lds[SplitTile<T>::LDS_BYTES / 16];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tm, tn;
+    tile_coords(blockIdx.x, p.raster, p.tiles_m, p.tiles_n, tm, tn);
+    const int m0 = tm * T::BM, n0 = tn * T::BN;
+    const int wm0 = (wave % T::WAVES_M) * T::WM, wn0 = (wave / T::WAVES_M) * T::WN;
+    const int kbegin = blockIdx.y * p.k_per_split;
+    const int kend = min(p.K, kbegin + p.k_per_split);
+
+    v16f acc[T::MB][T::NB];
+    bool redo;
+    {
+        SplitALoader<T> al;
+        SplitBLoaderRows<T> bl;
+        al.init(p.A, tid, m0, p.M, p.K, p.K);
+        bl.init(p.B, tid, n0, p.N, p.K, p.N);
+        SplitAcc<T> sum;
+        sum.clear();
+        if (kbegin < kend) split_mainloop<T>(lds, al, bl, sum, kbegin, kend, tid, wm0, wave / T::WAVES_M);
+        redo = sum.finish(acc) || al.tiny() || bl.tiny();
+    }
+    if (__syncthreads_or(redo)) {   // values the split cannot hold: once more on the fp32 matrix cores
+        ALoader<T, 4, true> al;
+        BLoaderRows<T, 1> bl;
+        al.init(p.A, tid, m0, p.M, p.K, p.K);
+        bl.init(p.B, tid, n0, p.N, p.K, p.N);
+#pragma unroll
+        for (int bi = 0; bi < T::MB; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < T::NB; ++bj)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
+        gemm_mainloop<T, false>(reinterpret_cast<float *>(lds), al, bl, acc, kbegin, kend, tid, wm0, wn0);
+    }
+    sgemm_finish<T, CVEC>(p, acc, tid, m0, n0, wm0, wn0);
+}
+
 template <class T>
 static hipError_t sgemm_launch(const SgemmProblem &q, int split_k, int raster, hipStream_t stream)
 {
@@ -150,9 +207,13 @@ static hipError_t sgemm_launch(const SgemmProblem &q, int split_k, int raster, h
         if (e != hipSuccess) return e;
     }
     dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)split_k), block(T::NT);
+    const bool cvec = (q.N % T::NB == 0) && ((uintptr_t)q.C % 16 == 0);
+    if constexpr (T::SPLIT) {
+        if (cvec) return launch_kernel((sgemm_split_kernel<T, true>), grid, block, 0, stream, a);
+        return launch_kernel((sgemm_split_kernel<T, false>), grid, block, 0, stream, a);
+    } else {
     const bool avec = (q.K % 4 == 0) && ((uintptr_t)q.A % 16 == 0);
     const bool bvec = (q.N % 4 == 0) && ((uintptr_t)q.B % 16 == 0);
-    const bool cvec = (q.N % T::NB == 0) && ((uintptr_t)q.C % 16 == 0);
 #define POLYDL_GO(AV, BV, CV) le = launch_kernel((sgemm_kernel<T, AV, BV, CV>), grid, block, 0, stream, a)
     if (avec && bvec && cvec) POLYDL_GO(4, 4, true);
     else if (avec && bvec) POLYDL_GO(4, 4, false);
@@ -164,6 +225,7 @@ static hipError_t sgemm_launch(const SgemmProblem &q, int split_k, int raster, h
     else POLYDL_GO(1, 1, false);
 #undef POLYDL_GO
     return le;
+    }
 }
 
 #define POLYDL_DEFINE_SGEMM(BM, BN, BK, WM, WN)                                                            \

@@ -9,6 +9,7 @@
     X(128, 64, 16, 64, 32)    \
     X(128, 128, 16, 64, 64)   \
     X(128, 128, 8, 64, 64)    \
+    X(256, 128, 16, 64, 64)   \
     X(128, 256, 16, 64, 128)  \
     X(256, 128, 16, 128, 64)
 
