@@ -27,8 +27,8 @@
  *   - HIP graphs: every entry point may be captured.  Three rules follow from the scratch memory
  *     above.  (1) A call that would have to allocate or grow it while its stream is being
  *     captured returns POLYDL_ERR_UNSUPPORTED and records nothing: run the same call once on
- *     that stream before capturing (or use polydl_conv2d_fwd_noalloc).  (A matrix product whose
- *     variant the library chooses takes its best unsplit variant instead.)  (2) A graph keeps the
+ *     that stream before capturing (or use polydl_conv2d_fwd_noalloc).  (Where the library chooses
+ *     the variant it takes its best unsplit one instead; a variant forced by the caller is refused.)  (2) A graph keeps the
  *     scratch addresses of its capture stream; they stay valid for the life of the process.
  *     (3) Replaying the graph, on any stream, uses the scratch memory of the stream it was
  *     CAPTURED on: do not let a replay overlap in time with other split-reduction work of this
@@ -103,7 +103,9 @@ typedef struct polydl_tile_cfg {
  *   bias K floats or NULL (= none). out N*K*P*Q floats, NKPQ, overwritten.
  *   fuse_relu: 0 = no activation, 1 = ReLU.  (polydl_conv2d_fwd_act takes any polydl_act.)
  * Accumulation is float32 on the matrix cores; the summation order is unspecified but fixed for
- * a given tile configuration, so repeated calls agree bit for bit. */
+ * a given tile configuration, so repeated calls agree bit for bit.  The gather variants (algo 0) with stage
+ * depth 16 and wave tiles up to 64 x 64 form the products of reductions of 128 and more as polydl_sgemm
+ * does (three bfloat16 parts per operand, six products, float32 sums). */
 int polydl_conv2d_fwd(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                       const float *in, const float *wt, const float *bias, float *out,
                       int fuse_relu, void *stream);
@@ -128,9 +130,9 @@ int polydl_conv2d_fwd_pre_act(int N, int C, int H, int W, int K, int R, int S, i
  * hipMalloc.  Same arguments, same variant choice and bit for bit the same result as
  * polydl_conv2d_fwd_act.  The call makes no hipMalloc / hipFree and no call into an allocating
  * library.  The array holds 64 MiB of partial tiles and 16384 arrival counters per device (each
- * device the library runs on keeps its copy until the process ends); a problem whose chosen variant
- * needs more returns POLYDL_ERR_SCRATCH_LIMIT with nothing enqueued (an unsplit variant, forced
- * through polydl_set_tile_override, needs none).  Every call on a device shares that device's
+ * device the library runs on keeps its copy until the process ends), which serves every variant the
+ * library chooses; a forced variant that needs more returns POLYDL_ERR_SCRATCH_LIMIT with nothing
+ * enqueued.  Every call on a device shares that device's
  * array, whatever its stream: the counters a call uses are cleared by a small kernel on its stream
  * first, and two calls that overlap in time on one device race on it -- keep them on one stream or
  * order them with events. */

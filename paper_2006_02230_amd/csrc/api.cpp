@@ -257,45 +257,60 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
         if (!b) return POLYDL_ERR_UNSUPPORTED;
         cfg = b->cfg;
     }
-    if (cfg.layout != 0 && !(cfg.layout == 2 && cfg.algo == 0)) return POLYDL_ERR_UNSUPPORTED;
-    if (cfg.algo == 2) {
-        if (!is_conv_point_cfg(cfg) || !conv_point_fits(q) || !point_aligned) return POLYDL_ERR_UNSUPPORTED;
-        hipError_t pe = conv_point_launch(q, (hipStream_t)stream);
-        if (pe != hipSuccess) return launch_failed(pe);
+    bool no_scratch = false;   // the launch was refused because the stream is being captured and has no scratch memory
+    auto failed = [&](hipError_t e) {
+        no_scratch = scratch_refusal() == SCRATCH_CAPTURING;
+        return launch_failed(e);
+    };
+    auto run = [&]() -> int {
+        if (cfg.layout != 0 && !(cfg.layout == 2 && cfg.algo == 0)) return POLYDL_ERR_UNSUPPORTED;
+        if (cfg.algo == 2) {
+            if (!is_conv_point_cfg(cfg) || !conv_point_fits(q) || !point_aligned) return POLYDL_ERR_UNSUPPORTED;
+            hipError_t pe = conv_point_launch(q, (hipStream_t)stream);
+            if (pe != hipSuccess) return failed(pe);
+            std::lock_guard<std::mutex> lk(g_mu);
+            g_last = cfg;
+            return POLYDL_OK;
+        }
+        if (cfg.algo == 1) {
+            if (pre_act != POLYDL_ACT_NONE) return POLYDL_ERR_UNSUPPORTED;   // a forced patch-kernel variant
+            const PatchVariant *pv = find_patch_variant(cfg);
+            if (!pv) return POLYDL_ERR_UNSUPPORTED;
+            if (cfg.cb == 0) cfg.cb = choose_cb(*pv, q);
+            if (cfg.cb < 2 || (cfg.cb & 1)) return POLYDL_ERR_UNSUPPORTED;
+            const int sk = cfg.split_k < 1 ? 1 : cfg.split_k;
+            if (pv->conv(q, cfg.cb, sk, cfg.raster, nullptr, true) != hipSuccess) return POLYDL_ERR_UNSUPPORTED;
+            hipError_t pe = pv->conv(q, cfg.cb, sk, cfg.raster, (hipStream_t)stream, false);
+            if (pe != hipSuccess) return failed(pe);
+            std::lock_guard<std::mutex> lk(g_mu);
+            g_last = cfg;
+            return POLYDL_OK;
+        }
+        const Variant *v = find_variant(cfg);
+        if (!v) return POLYDL_ERR_UNSUPPORTED;
+        // a tile of bn pixels spans at most bn/PQ + 2 images; their offsets must fit 31 bits
+        const int64_t span = (v->bn / (P * Q) + 2) * CHW * 4;
+        const int64_t span_out = (v->bn / (P * Q) + 2) * (int64_t)K * P * Q * 4;
+        if (span >= 0x7FFFFFF0ll || span_out >= 0x7FFFFFF0ll || (int64_t)v->bm * Kg * 4 >= 0x7FFFFFF0ll)
+            return POLYDL_ERR_UNSUPPORTED;
+        if (cfg.layout == 2) {
+            if (!q.has_tap || !gather_tap_major_fits(q, v->bk)) return POLYDL_ERR_UNSUPPORTED;
+            q.wt_tap = wt_tap;
+        }
+        hipError_t e = v->conv(q, cfg.split_k < 1 ? 1 : cfg.split_k, cfg.raster, (hipStream_t)stream);
+        if (e != hipSuccess) return failed(e);
         std::lock_guard<std::mutex> lk(g_mu);
         g_last = cfg;
         return POLYDL_OK;
+    };
+    int st = run();
+    if (st != POLYDL_OK && no_scratch && !forced) {
+        // the best variant that needs none (not cached); nothing was enqueued so far
+        polydl_model_report rep;
+        if (!pick_conv(q, &cfg, &rep, true)) return st;
+        st = run();
     }
-    if (cfg.algo == 1) {
-        if (pre_act != POLYDL_ACT_NONE) return POLYDL_ERR_UNSUPPORTED;   // a forced patch-kernel variant
-        const PatchVariant *pv = find_patch_variant(cfg);
-        if (!pv) return POLYDL_ERR_UNSUPPORTED;
-        if (cfg.cb == 0) cfg.cb = choose_cb(*pv, q);
-        if (cfg.cb < 2 || (cfg.cb & 1)) return POLYDL_ERR_UNSUPPORTED;
-        const int sk = cfg.split_k < 1 ? 1 : cfg.split_k;
-        if (pv->conv(q, cfg.cb, sk, cfg.raster, nullptr, true) != hipSuccess) return POLYDL_ERR_UNSUPPORTED;
-        hipError_t pe = pv->conv(q, cfg.cb, sk, cfg.raster, (hipStream_t)stream, false);
-        if (pe != hipSuccess) return launch_failed(pe);
-        std::lock_guard<std::mutex> lk(g_mu);
-        g_last = cfg;
-        return POLYDL_OK;
-    }
-    const Variant *v = find_variant(cfg);
-    if (!v) return POLYDL_ERR_UNSUPPORTED;
-    // a tile of bn pixels spans at most bn/PQ + 2 images; their offsets must fit 31 bits
-    const int64_t span = (v->bn / (P * Q) + 2) * CHW * 4;
-    const int64_t span_out = (v->bn / (P * Q) + 2) * (int64_t)K * P * Q * 4;
-    if (span >= 0x7FFFFFF0ll || span_out >= 0x7FFFFFF0ll || (int64_t)v->bm * Kg * 4 >= 0x7FFFFFF0ll)
-        return POLYDL_ERR_UNSUPPORTED;
-    if (cfg.layout == 2) {
-        if (!q.has_tap || !gather_tap_major_fits(q, v->bk)) return POLYDL_ERR_UNSUPPORTED;
-        q.wt_tap = wt_tap;
-    }
-    hipError_t e = v->conv(q, cfg.split_k < 1 ? 1 : cfg.split_k, cfg.raster, (hipStream_t)stream);
-    if (e != hipSuccess) return launch_failed(e);
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_last = cfg;
-    return POLYDL_OK;
+    return st;
 }
 
 }  // namespace polydl

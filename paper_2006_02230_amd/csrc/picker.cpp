@@ -122,6 +122,8 @@ struct Cand {
     // reduction steps instead of eight of 64; split_eff is the matrix-core share of their loop.
     bool split = false;
     double split_eff = 0.4;
+    double tail_us = 4.0;        // leftover tiles cut into parts: the hand-over
+    double sum_us = 0;           // split reduction: the last part of a tile adds all parts alone
     bool tail_split = false;     // the kernel cuts the leftover tiles of an unsplit grid (tail_split())
 };
 
@@ -139,6 +141,7 @@ static void model(const Shape &s, const Cand &c, polydl_model_report *r)
     // (two at a time share its matrix core), so the busiest SIMD sets the time: this is the
     // load-balance requirement on the parallel loops.
     const double steps = std::ceil(s.Kg / 2.0 / c.split_k);               // rank-2 updates per wave
+    const double step_cycles = c.split ? 24.0 : 64.0;                     // matrix-core cycles of one, per block
     const double wgs_on_busiest_cu = std::ceil(wgs / kCUs);
     const double waves_on_busiest_simd = std::ceil(wgs_on_busiest_cu * waves_per_wg / kSimdsPerCU);
     double resident = std::min<double>(c.max_waves_per_simd, std::floor(2.0 * kLevels[1].capacity / c.lds_bytes) *
@@ -151,11 +154,7 @@ static void model(const Shape &s, const Cand &c, polydl_model_report *r)
     eff *= c.steps_per_stage / (c.steps_per_stage + 1.0 / (mb * nb));
     if (resident < 2) eff *= 0.72;
     else if (resident * mb * nb < 4) eff *= 0.85;   // two small waves leave gaps a third would fill
-    double step_cycles = 64.0;
-    if (c.split) {
-        step_cycles = 24.0;
-        eff = c.split_eff * (resident < 2 ? 0.74 : 1.0);
-    }
+    if (c.split) eff = c.split_eff * (resident < 2 ? 0.74 : 1.0);
     // setup plus an epilogue that grows with the accumulators a lane has to store
     const double overhead = c.wg_overhead_cycles * (0.3 + 0.7 * mb * nb / 2.0);
     const double wave_cycles = steps * mb * nb * step_cycles / eff + overhead;
@@ -179,8 +178,8 @@ static void model(const Shape &s, const Cand &c, polydl_model_report *r)
                 per_cu = (wgs - ts.tiles) / kCUs;
                 const double pieces = std::ceil((double)ts.tiles * ts.parts / kCUs);
                 const double simd_share0 = std::ceil(waves_per_wg / kSimdsPerCU);
-                tail_us = 4.0 + pieces * ts.stages_per_part *
-                                    (c.steps_per_stage * mb * nb * 64.0 * simd_share0 / kClockHz * 1e6 / c.eff_sat +
+                tail_us = c.tail_us + pieces * ts.stages_per_part *
+                                    (c.steps_per_stage * mb * nb * step_cycles * simd_share0 / kClockHz * 1e6 / c.eff_sat +
                                      c.gather_elems * c.gather_cycles / kClockHz * 1e6);
             }
         }
@@ -188,7 +187,7 @@ static void model(const Shape &s, const Cand &c, polydl_model_report *r)
         const double rest = per_cu - full_rounds * occ;
         const double stages = std::ceil(steps / c.steps_per_stage);
         const double simd_share = std::ceil(waves_per_wg / kSimdsPerCU);
-        const double t_stage = c.steps_per_stage * mb * nb * 64.0 * simd_share / kClockHz * 1e6 / c.eff_sat +
+        const double t_stage = c.steps_per_stage * mb * nb * step_cycles * simd_share / kClockHz * 1e6 / c.eff_sat +
                                c.gather_elems * c.gather_cycles / kClockHz * 1e6;
         auto round_us = [&](double n) { return c.t_round_us + stages * std::max(n * t_stage, c.t_lat_us); };
         mfma_us = full_rounds * round_us(occ) + (rest > 1e-9 ? round_us(std::ceil(rest - 1e-9)) : 0.0) + tail_us;
@@ -244,7 +243,7 @@ static void model(const Shape &s, const Cand &c, polydl_model_report *r)
         // a layer that mostly writes is slower than that: measured on the pointwise layers of the
         // suite (batch 16 .. 128, either kernel), the output leaves at about 3.15 TB/s
         mem_us = std::max(mem_us, (s.a_bytes + s.b_bytes) / 20000.0 * 1e-3 + s.d_bytes / 3150.0 * 1e-3 + 2.0);
-        if (c.split_k > 1) fixed += c.split_c0 + c.split_c1 * c.split_k * s.d_bytes * 1e-6;
+        if (c.split_k > 1) fixed += c.split_c0 + c.split_c1 * c.split_k * s.d_bytes * 1e-6 + c.sum_us;
     } else if (c.split_k > 1) {
         // every part writes its accumulator tile once, coalesced; the last part of each tile reads
         // them all back and runs the epilogue: no other launch, no pass over the output
@@ -351,16 +350,35 @@ void model_conv(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads, i
         default: c.regs = 228; c.eff_sat = 0.80; c.t_lat_us = 0.4; c.t_round_us = 4; c.gather_cycles = 20; c.split_c0 = 15; c.split_c1 = 1.0; break;
         }
         c.tail_split = cfg.raster >= 2;
+        const bool split = split_products(cfg.bk, cfg.wm, cfg.wn) && (double)q.C * q.R * q.S >= kSplitMinReduction;
+        double point_gather = 0.1, tap_gather = mbn == 11 ? kTapMajorGather11 : (mbn == 21 ? kTapMajorGather21 : kTapMajorGather);
+        if (split) {
+            // fitted to sweeps of 97 problems (the suite at batch 1 .. 64 and the three held-out sets, with and without
+            // the filter copy, reductions of 128 and more; small batches weighted): the picks run within 1.2 % of
+            // the sweep's best on average, 8 % at worst
+            c.split = true;
+            c.lds_bytes = split_lds_bytes(cfg.bm, cfg.bn);
+            point_gather = 0.29;
+            c.tail_us = 9.3;
+            c.split_c1 = 0.078;
+            c.sum_us = c.split_k * (double)cfg.bm * cfg.bn * 4 / (mbn == 11 ? 67.0 : 60.6) * 1e-3;
+            switch (mbn == 22 && threads == 512 ? 0 : mbn) {
+            case 11: c.regs = 128; c.eff_sat = 0.405; c.t_lat_us = 0.333; c.t_round_us = 2.07; c.gather_cycles = 43.4; tap_gather = 0.58; c.split_c0 = 0.85; c.tail_us = 4.8; break;
+            case 12: c.regs = 168; c.eff_sat = 0.476; c.t_lat_us = 0.541; c.t_round_us = 2.07; c.gather_cycles = 46.9; tap_gather = 0.325; c.split_c0 = 2.17; break;
+            case 21: c.regs = 168; c.eff_sat = 0.50; c.t_lat_us = 0.489; c.t_round_us = 2.24; c.gather_cycles = 36.3; tap_gather = 0.845; c.split_c0 = 2.37; break;
+            case 22: c.regs = 256; c.eff_sat = 0.615; c.t_lat_us = 0.772; c.t_round_us = 2.84; c.gather_cycles = 38.5; tap_gather = 0.488; c.split_c0 = 2.44; break;
+            default: c.regs = 256; c.eff_sat = 0.659; c.t_lat_us = 0.361; c.t_round_us = 6.5; c.gather_cycles = 67.3; tap_gather = 0.99; c.split_c0 = 0.45; break;
+            }
+        }
         // 1x1 filters without padding: the channel rides in the instruction's uniform offset and the
         // lanes read a contiguous run of pixels (stride 1); with a stride the lanes' addresses are
         // spread over several times the cache lines and the loads cost what gathered ones do
-        if (point && q.stride == 1) c.gather_cycles *= 0.1;
+        if (point && q.stride == 1) c.gather_cycles *= point_gather;
         // tap by tap over the [K][R][S][C] filter copy: one tap per stage, so the validity bit and
         // the distance are worked out per stage and not per element
         // (with a stride the lanes' addresses spread over twice the cache lines and the cost of
         // the load is in the memory pipeline, which the cheaper addressing does not touch)
-        if (cfg.layout == 2 && q.stride == 1)
-            c.gather_cycles *= mbn == 11 ? kTapMajorGather11 : (mbn == 21 ? kTapMajorGather21 : kTapMajorGather);
+        if (cfg.layout == 2 && q.stride == 1) c.gather_cycles *= tap_gather;
         if (c.split_c1 == 0) c.split_c1 = 0.1;   // scratch tiles, as in the patch kernel
     }
     Shape s = conv_shape(q, cfg.algo, cfg.bn, std::max(2, cfg.cb));
@@ -523,7 +541,7 @@ void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out)
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &v = kVariants[i];
         const long stages = (Kg + v.bk - 1) / v.bk;
-        if (v.bm == 256 && v.wm == 64) continue;   // a tile of the matrix product alone
+        if (v.threads == 512 && Kg < kSplitMinReduction) continue;   // pays through the splitting alone
         for (int sk : kSplits) {
             if (sk > stages) break;
             // raster 1: each XCD's workgroups take neighbouring tiles, so filter rows and the input rows
@@ -559,6 +577,15 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
     const ConvCandidate *b = nullptr;
     for (const ConvCandidate &c : cands) {
         if (no_scratch && (c.cfg.split_k > 1 || c.cfg.raster >= 2)) continue;
+        // the fp32 row-patch kernel is no match for the split products (1.1 .. 1.7 times the time of the best of
+        // those on the suite); its own predictions are not comparable to theirs
+        if (c.cfg.algo == 1 && (int64_t)q.C * q.R * q.S >= kSplitMinReduction && cands.back().cfg.algo == 0) continue;
+        // partial tiles stay within half of the fixed array of the allocation-free call (the other half may
+        // hold a split filter), so that it serves every pick
+        const double tiles = std::ceil((double)q.K / c.cfg.bm) * std::ceil((double)q.N * q.P * q.Q / c.cfg.bn);
+        if (c.cfg.split_k > 1 && (tiles * c.cfg.split_k * c.cfg.bm * c.cfg.bn * 4 > kStaticPartialBytes / 2 ||
+                                  tiles > kStaticCounterBytes / 4))
+            continue;
         if (!b || before(c, *b)) b = &c;
     }
     if (!b) return false;

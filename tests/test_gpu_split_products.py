@@ -87,3 +87,61 @@ def test_sgemm_values_the_split_cannot_hold(P, case, split_k):
         # K sequential fp32 roundings at most (the recomputation's own order)
         assert (np.abs(got[fin] - want[fin]) <= (K + 2) * 2.0 ** -24 * terms[fin]).all(), v
     P.set_tile_override(None)
+
+
+def conv64(x, w, stride, pad):
+    """Plain fp64 convolution and the sum of the terms' magnitudes."""
+    N, C, H, W = x.shape
+    K, _, R, S = w.shape
+    Ph, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (pad, pad), (pad, pad)))
+    out, ab = np.zeros((N, K, Ph, Q)), np.zeros((N, K, Ph, Q))
+    with np.errstate(all="ignore"):
+        for r in range(R):
+            for t in range(S):
+                tap = xp[:, :, r:r + (Ph - 1) * stride + 1:stride, t:t + (Q - 1) * stride + 1:stride]
+                f = w[:, :, r, t].astype(np.float64)
+                out += np.einsum("kc,ncpq->nkpq", f, tap)
+                ab += np.einsum("kc,ncpq->nkpq", np.abs(f), np.abs(tap))
+    return out, ab
+
+
+CONV = [synth.ConvShape("3x3", 2, 24, 9, 11, 70, 3, 3, 1, 1), synth.ConvShape("3x3c16", 3, 32, 7, 7, 130, 3, 3, 1, 1),
+        synth.ConvShape("5x5s2", 1, 16, 13, 10, 33, 5, 5, 2, 2), synth.ConvShape("1x1", 2, 131, 8, 9, 65, 1, 1, 1, 0),
+        synth.ConvShape("1x1s2", 1, 160, 15, 13, 65, 1, 1, 2, 0), synth.ConvShape("8x8", 1, 3, 20, 20, 40, 8, 8, 1, 0),
+        synth.ConvShape("7x7", 1, 11, 18, 17, 64, 7, 7, 2, 3)]
+
+
+@pytest.mark.parametrize("case", ["plain", "inf", "nan", "lowest", "tiny"])
+@pytest.mark.parametrize("s", CONV, ids=lambda s: s.name)
+def test_conv(P, s, case):
+    x, w, _ = synth.conv_inputs(s, seed=11, dist="normal")
+    if case == "inf":
+        x[0, s.C // 2, 4, 5] = np.inf
+    elif case == "nan":
+        w[3, 1, s.R - 1, 0] = np.nan
+    elif case == "lowest":
+        x[0, 1, 3, 4] = np.finfo(np.float32).min
+        w *= np.float32(1e-3)
+    elif case == "tiny":
+        w[2] *= np.float32(1e-36)
+        x *= np.float32(1e20)
+    want, ab = conv64(x, w, s.stride, s.pad)
+    dx, dw = dev(x), dev(w)
+    tap = P.filter_tap_copy(dw)
+    Kg = s.C * s.R * s.S
+    fin = np.isfinite(want)
+    for v in P.variants(0):
+        if v.algo != 0 or v.bk != 16 or v.wm * v.wn > 64 * 64:
+            continue
+        for split_k, raster in ((1, 0), (2, 1), (1, 3)):
+            for layout in ((0, 2) if s.C % 16 == 0 and 2 <= s.R * s.S <= 63 else (0,)):
+                v.split_k, v.raster, v.layout = split_k, raster, layout
+                P.set_tile_override(v)
+                got = host(P.conv2d_fwd(dx, dw, stride=s.stride, pad=s.pad, w_tap=tap if layout else None))
+                assert np.array_equal(np.isnan(got), np.isnan(want)), v
+                assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True), v
+                # as for the matrix product, or Kg sequential roundings where a tile is recomputed
+                bound = (2.0 ** -25 + (Kg / 8 + 3) * 2.0 ** -24) if case == "plain" else (Kg + 2) * 2.0 ** -24
+                assert (np.abs(got[fin] - want[fin]) <= bound * ab[fin]).all(), v
+    P.set_tile_override(None)
