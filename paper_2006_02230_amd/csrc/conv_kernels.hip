@@ -162,7 +162,7 @@ static hipError_t conv_launch(const ConvProblem &q, int split_k, int raster, hip
                      : table ? GATHER_TABLE
                      : a.RS <= 31 ? GATHER_TAPS1 : a.RS <= 63 ? GATHER_TAPS2 : GATHER_ANY;
     if constexpr (T::SPLIT) {
-        if (a.Kg >= kSplitMinReduction) {
+        if (split_pays(q.K, a.RS, a.Kg)) {
 #define POLYDL_GO(MODE) return launch_kernel((conv_split_kernel<T, MODE>), grid, block, 0, stream, a)
             switch (mode) {
             case GATHER_TAPMAJOR: POLYDL_GO(GATHER_TAPMAJOR);
@@ -184,7 +184,7 @@ static hipError_t conv_launch(const ConvProblem &q, int split_k, int raster, hip
         if (mode == GATHER_POINT) POLYDL_GO(1, GATHER_POINT);
         if (mode == GATHER_TABLE) POLYDL_GO(1, GATHER_TABLE);
     }
-    if constexpr (!T::SPLIT) {   // a short reduction of at most 63 taps always fits the table
+    if constexpr (!T::SPLIT) {   // reductions the other tiles come here with fit the table (or take GATHER_ANY)
         if (avec) {
             if (mode == GATHER_TAPS1) POLYDL_GO(4, GATHER_TAPS1);
             if (mode == GATHER_TAPS2) POLYDL_GO(4, GATHER_TAPS2);

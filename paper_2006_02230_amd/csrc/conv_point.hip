@@ -3,21 +3,25 @@
 //   out[n][k][x] = sum_c wt[k][c] * in[n][c][x],   x = 0 .. H*W-1,
 // a GEMM whose reduction (C <= 64) is so short that staging pixels through LDS, a barrier per
 // stage and a tile prologue per workgroup cost more than the arithmetic.  Here
-//   * the whole filter matrix sits in LDS for the life of the workgroup (K*C*4 <= 64 KB), laid
-//     out so that a lane reads the four weights of four consecutive rank-2 updates as one vector;
-//   * a wave owns 64 pixels at a time and loads their C channels from global memory straight
-//     into the registers the matrix instruction reads -- lane j of each half-wave holds pixels
-//     2j and 2j+1 (one 8-byte load per channel pair), the half-waves hold even and odd channels;
+//   * the whole filter matrix sits in LDS for the life of the workgroup, split once into the three bfloat16
+//     parts of split_core.hpp (K*C*6 <= 96 KB) in the order the matrix instruction reads it;
+//   * a wave owns 64 pixels at a time and loads their C channels from global memory straight into
+//     registers -- lane j of each half-wave holds pixels 2j and 2j+1 (one 8-byte load per channel), the
+//     half-waves hold channels 0-7 and 8-15 of every 16 -- where they are split once for all channel groups;
 //   * with those registers it produces the output channels in groups of 32 (accumulators: two
-//     blocks of 32x32, one per pixel of the lane's pair; groups of 64 measured 10 % slower), bias
-//     and activation applied on the way out (section "Operator Fusion"), each lane storing its
-//     two pixels of a channel row as one 8-byte store;
+//     blocks of 32x32, one per pixel of the lane's pair), bias and activation applied on the way out
+//     (section "Operator Fusion"), each lane storing its two pixels of a channel row as one 8-byte store;
 //   * (pixel tile, channel group) units are dealt to the waves of a grid that fits the chip once
 //     in contiguous, equal runs, so a wave reloads pixels only when its run crosses a tile.
 // No barrier after the filter is in LDS; waves never wait for each other.
+//
+// Bound: the bytes written.  With the fp32 instruction the matrix cores needed 21 us of 40 for 64 -> 256 channels
+// at 56x56, batch 32, and hardly overlapped with the stores; the split products need 8: 39.8 -> 31.2 us
+// (44.9 -> 37.8 with operands and outputs that are not in the caches), batch 64 69 -> 58.
 #include <hip/hip_runtime.h>
 #include "gemm_core.hpp"
 #include "internal.hpp"
+#include "split_core.hpp"
 
 namespace polydl {
 
@@ -39,11 +43,10 @@ __device__ __forceinline__ v2f buf_load2(__amdgpu_buffer_rsrc_t r, uint32_t byte
     return __builtin_bit_cast(v2f, v);
 }
 
-// What a finished unit leaves behind until it is stored: its two accumulator blocks, the lane's 16
-// bias values of its channel group, the lane's output offset and the group's first channel.
+// What a finished unit leaves behind until it is stored: its two blocks of sums, bias added, the
+// lane's output offset and the group's first channel.
 struct PointUnit {
     v16f acc[2];
-    v4f bias[4];
     uint32_t vo;
     int k0;
 };
@@ -58,59 +61,93 @@ __device__ __forceinline__ void point_store(__amdgpu_buffer_rsrc_t ro, uint32_t 
 #pragma unroll
     for (int r = first; r < first + count; ++r) {
         const int q = r >> 2, i = r & 3;
-        v2f v = {act_of<ACT>(u.acc[0][r] + u.bias[q][i]), act_of<ACT>(u.acc[1][r] + u.bias[q][i])};
+        v2f v = {act_of<ACT>(u.acc[0][r]), act_of<ACT>(u.acc[1][r])};
         buf_store2(ro, u.vo, (uint32_t)(u.k0 + 8 * q + i) * row_bytes, v);
     }
 }
 
+// The pixels of a tile, split: [pixel of the pair][block of 16 channels][part].
+template <int KB>
+struct PointPixels {
+    u32x4 b[2][KB][3];
+    uint32_t seen[2];      // OR of the bit patterns of the lane's channels of each pixel
+};
+
 // The products of one unit into `cur` and, PENDING, the 16 stores of the unit finished before it
-// (`old`) dealt out between the groups of eight matrix instructions: a wave's stores leave while
-// its own next matrix instructions run instead of after them, in a phase of their own in which
-// the matrix core of the SIMD has nothing to do unless another wave happens to be out of step.
-template <int C8, int ACT, bool PENDING>
-__device__ __forceinline__ void point_unit(const v4f *a_base, int K, const v2f (&b)[C8 * 4], PointUnit &cur,
-                                           __amdgpu_buffer_rsrc_t ro, uint32_t row_bytes, const PointUnit &old)
+// (`old`) dealt out between them: a wave's stores leave while its own next matrix instructions run
+// instead of after them, in a phase of their own in which the matrix core of the SIMD has nothing to do
+// unless another wave happens to be out of step.  True if a sum is not finite.
+template <int KB, int ACT, bool PENDING>
+__device__ __forceinline__ bool point_unit(const u32x4 *a_base, int K, const PointPixels<KB> &px, const v4f (&bias)[4],
+                                           PointUnit &cur, __amdgpu_buffer_rsrc_t ro, uint32_t row_bytes, const PointUnit &old)
 {
+    v16f hi[2], lo[2];
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) cur.acc[nb][r] = 0.f;
-    constexpr int PER = 16 / C8;   // stores per group of eight matrix instructions
+        for (int r = 0; r < 16; ++r) { hi[nb][r] = 0.f; lo[nb][r] = 0.f; }
+    constexpr int PER = 16 / KB;   // stores per block of 16 channels
+    static_for<0, KB>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int kb = decltype(kc)::value;
+        u32x4 a[3];
 #pragma unroll
-    for (int sg = 0; sg < C8; ++sg) {
-        const v4f a = a_base[sg * 2 * K];
+        for (int pl = 0; pl < 3; ++pl) a[pl] = a_base[(kb * 3 + pl) * 2 * K];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            cur.acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[4 * sg + i].x, cur.acc[0], 0, 0, 0);
-            cur.acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[4 * sg + i].y, cur.acc[1], 0, 0, 0);
-        }
+        for (int nb = 0; nb < 2; ++nb) hi[nb] = mfma_bf16(a[0], px.b[nb][kb][0], hi[nb]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) lo[nb] = mfma_bf16(a[1], px.b[nb][kb][0], lo[nb]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) lo[nb] = mfma_bf16(a[0], px.b[nb][kb][1], lo[nb]);
         if constexpr (PENDING) {
-            point_store<ACT>(ro, row_bytes, old, sg * PER, PER);
+            point_store<ACT>(ro, row_bytes, old, kb * PER, PER / 2);
             // keep the stores where they are: left alone, the scheduler moves them all behind the
             // last matrix instruction
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) lo[nb] = mfma_bf16(a[1], px.b[nb][kb][1], lo[nb]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) lo[nb] = mfma_bf16(a[2], px.b[nb][kb][0], lo[nb]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) lo[nb] = mfma_bf16(a[0], px.b[nb][kb][2], lo[nb]);
+        if constexpr (PENDING) {
+            point_store<ACT>(ro, row_bytes, old, kb * PER + PER / 2, PER / 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    });
+    float f = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float v = hi[nb][r] + lo[nb][r];
+            f = __builtin_fmaf(v, 0.f, f);
+            cur.acc[nb][r] = v + bias[r >> 2][r & 3];
+        }
+    return !(f == 0.f);
 }
 
 // A wave's run of units [u, end).  Two unit records take turns: while one collects the products of
 // unit i, the other, holding unit i - 1, is stored.
-template <int C8, int ACT>
-__device__ __forceinline__ void point_run(const ConvPointKArgs &p, const v4f *At, uint32_t u, uint32_t end, int half, int j)
+template <int KB, int ACT>
+__device__ __forceinline__ void point_run(const ConvPointKArgs &p, const u32x4 *At, bool tiny_filter, uint32_t u, uint32_t end,
+                                          int half, int j)
 {
-    const int K = p.K, C = C8 * 8;
+    const int K = p.K, C = KB * 16;
     const uint32_t HW = p.HW, total = (uint32_t)p.N * HW;
     const __amdgpu_buffer_rsrc_t ri = make_rsrc(p.in, (uint64_t)total * C * 4);
     const __amdgpu_buffer_rsrc_t ro = make_rsrc(p.out, (uint64_t)total * K * 4);
     const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.bias, p.bias ? (uint64_t)K * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wt, (uint64_t)K * C * 4);
     const uint32_t row_bytes = HW * 4u;
 
     uint32_t g;
     uint32_t tile = div_by(u, (uint32_t)p.groups, p.recip_groups, g);
-    uint32_t have = 0xFFFFFFFFu, vo = kOobOffset;
-    v2f b[C8 * 4];
-    // pixels of a new tile, the unit's output offset and channel group, its bias values (zeros
-    // without a bias; they are needed only when the unit is stored, one unit later)
+    uint32_t have = 0xFFFFFFFFu, vo = kOobOffset, vi0 = kOobOffset;   // vi0: channel 0 of the lane's pixels
+    PointPixels<KB> px;
+    v4f bias[4];
+    // pixels of a new tile, the unit's output offset and channel group, the lane's 16 bias values (zeros
+    // without a bias; they are needed only when the unit's sums are complete)
     auto open_unit = [&](PointUnit &cur) {
         if (tile != have) {
             // the lane's two pixels: 2j and 2j+1 of the tile, in one image since H*W is even
@@ -118,16 +155,63 @@ __device__ __forceinline__ void point_run(const ConvPointKArgs &p, const v4f *At
             uint32_t x;
             const uint32_t n = div_by(pix0, HW, p.recip_HW, x);
             const bool ok = pix0 < total;
-            const uint32_t vi = ok ? ((n * C + half) * HW + x) * 4u : kOobOffset;
+            vi0 = ok ? (n * C * HW + x) * 4u : kOobOffset;
+            const uint32_t vi = ok ? vi0 + (uint32_t)(8 * half) * row_bytes : kOobOffset;
             vo = ok ? ((n * K + 4u * half) * HW + x) * 4u : kOobOffset;
+            px.seen[0] = 0;
+            px.seen[1] = 0;
+            v2f raw[KB][8];
+            auto fetch = [&](int kb) __attribute__((always_inline)) {
 #pragma unroll
-            for (int s = 0; s < C8 * 4; ++s) b[s] = buf_load2(ri, vi, (uint32_t)(2 * s) * row_bytes);
+                for (int i = 0; i < 8; ++i) raw[kb][i] = buf_load2(ri, vi, (uint32_t)(kb * 16 + i) * row_bytes);
+            };
+            // two blocks in flight: with all of them the registers run out
+            fetch(0);
+            if (KB > 1) fetch(KB > 1 ? 1 : 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) {
+                    SplitUnit<8> s;
+                    s.seen = px.seen[nb];
+                    float v[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = raw[kb][i][nb];
+                    static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { s.template step<decltype(st)::value>(v); });
+                    px.seen[nb] = s.seen;
+#pragma unroll
+                    for (int pl = 0; pl < 3; ++pl) px.b[nb][kb][pl] = (u32x4){s.p[pl][0], s.p[pl][1], s.p[pl][2], s.p[pl][3]};
+                }
+                if (kb + 2 < KB) fetch(kb + 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             have = tile;
         }
         cur.vo = vo;
         cur.k0 = (int)g * 32;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cur.bias[q] = buf_load4(rb, (uint32_t)(g * 32 + 8 * q + 4 * half) * 4u);
+        for (int q = 0; q < 4; ++q) bias[q] = buf_load4(rb, (uint32_t)(g * 32 + 8 * q + 4 * half) * 4u);
+    };
+    // a unit that met values the split cannot hold: once more on the fp32 matrix cores, operands from memory
+    auto check_unit = [&](PointUnit &cur, bool bad) {
+        bad = bad || tiny_filter || split_tiny(px.seen[0]) || split_tiny(px.seen[1]);
+        if (__ballot(bad) == 0) return;
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) cur.acc[nb][r] = 0.f;
+#pragma unroll 1
+        for (int c = 0; c < C; c += 2) {
+            const float a = buf_load1(rw, (uint32_t)((cur.k0 + j) * C + c + half) * 4u);
+            const v2f b = buf_load2(ri, vi0 == kOobOffset ? kOobOffset : vi0 + (uint32_t)(c + half) * row_bytes, 0);
+            cur.acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b.x, cur.acc[0], 0, 0, 0);
+            cur.acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b.y, cur.acc[1], 0, 0, 0);
+        }
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) cur.acc[nb][r] += bias[r >> 2][r & 3];
     };
     auto next_unit = [&]() {
         if (++g == (uint32_t)p.groups) { g = 0; ++tile; }
@@ -135,64 +219,63 @@ __device__ __forceinline__ void point_run(const ConvPointKArgs &p, const v4f *At
     PointUnit A, B;
     uint32_t left = end - u;
     open_unit(A);
-    point_unit<C8, ACT, false>(At + half * K + g * 32 + j, K, b, A, ro, row_bytes, A);
+    check_unit(A, point_unit<KB, ACT, false>(At + half * K + g * 32 + j, K, px, bias, A, ro, row_bytes, A));
     next_unit();
     --left;
     while (left >= 2) {
         open_unit(B);
-        point_unit<C8, ACT, true>(At + half * K + g * 32 + j, K, b, B, ro, row_bytes, A);
+        check_unit(B, point_unit<KB, ACT, true>(At + half * K + g * 32 + j, K, px, bias, B, ro, row_bytes, A));
         next_unit();
         open_unit(A);
-        point_unit<C8, ACT, true>(At + half * K + g * 32 + j, K, b, A, ro, row_bytes, B);
+        check_unit(A, point_unit<KB, ACT, true>(At + half * K + g * 32 + j, K, px, bias, A, ro, row_bytes, B));
         next_unit();
         left -= 2;
     }
     if (left == 1) {
         open_unit(B);
-        point_unit<C8, ACT, true>(At + half * K + g * 32 + j, K, b, B, ro, row_bytes, A);
+        check_unit(B, point_unit<KB, ACT, true>(At + half * K + g * 32 + j, K, px, bias, B, ro, row_bytes, A));
         point_store<ACT>(ro, row_bytes, B, 0, 16);
     } else {
         point_store<ACT>(ro, row_bytes, A, 0, 16);
     }
 }
 
-// C8 = C / 8.  256 threads; LDS holds wt as float4 At[C8][2][K]:
-// At[sg][h][k] = wt[k][8 sg + h + {0, 2, 4, 6}].
-template <int C8>
-__global__ __launch_bounds__(256, 2) void conv_point_kernel(const ConvPointKArgs p)
+// KB = C / 16.  512 threads, one workgroup per compute unit (its eight waves share one copy of the filter).
+// LDS: At[kb][part][half][K] units, channels 16 kb + 8 half + 0..7 of an output channel.
+constexpr int kPointThreads = 512;
+template <int KB>
+__global__ __launch_bounds__(kPointThreads, 2) void conv_point_kernel(const ConvPointKArgs p)
 {
-    __shared__ v4f At[4096];
+    extern __shared__ __attribute__((aligned(16))) u32x4 At[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // the same in all lanes: keeps unit bookkeeping scalar
     const int half = lane >> 5, j = lane & 31;
-    const int K = p.K, C = C8 * 8;
+    const int K = p.K, C = KB * 16;
 
+    bool tiny = false;
     {
-        // filter rows are read as they lie (16 bytes per lane, consecutive lanes consecutive addresses)
-        // and scattered into the layout above one scalar at a time
         const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wt, (uint64_t)K * C * 4);
-        float *At1 = reinterpret_cast<float *>(At);
-        const int count = K * C8 * 2;                       // float4 units of wt
-        for (int idx = tid; idx < count; idx += 256) {
-            const int k = idx / (C8 * 2), c0 = (idx - k * (C8 * 2)) * 4;
-            const v4f v = buf_load4(rw, (uint32_t)idx * 16u);
-            const int sg = c0 >> 3, e0 = (c0 & 7) >> 1;     // c0 is a multiple of 4: components e0 and e0 + 1
-            float *even = At1 + ((sg * 2 + 0) * K + k) * 4 + e0, *odd = At1 + ((sg * 2 + 1) * K + k) * 4 + e0;
-            even[0] = v[0];
-            odd[0] = v[1];
-            even[1] = v[2];
-            odd[1] = v[3];
+        for (int idx = tid; idx < K * KB * 2; idx += kPointThreads) {   // K is a multiple of 64: a wave has one octet
+            const int o = idx / K, k = idx - o * K;
+            const v4f v0 = buf_load4(rw, (uint32_t)(k * C + o * 8) * 4u), v1 = buf_load4(rw, (uint32_t)(k * C + o * 8 + 4) * 4u);
+            const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+            SplitUnit<8> s;
+            static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { s.template step<decltype(st)::value>(v); });
+            tiny |= split_tiny(s.seen);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                At[(((o >> 1) * 3 + pl) * 2 + (o & 1)) * K + k] = (u32x4){s.p[pl][0], s.p[pl][1], s.p[pl][2], s.p[pl][3]};
         }
     }
-    __syncthreads();
+    tiny = __syncthreads_or(tiny);
 
-    const uint32_t w = blockIdx.x * 4u + wave;
+    const uint32_t w = blockIdx.x * (kPointThreads / 64) + wave;
     const uint32_t u = w * p.per + (w < p.rem ? w : p.rem);
     const uint32_t end = u + p.per + (w < p.rem ? 1u : 0u);
     if (u >= end) return;
-    if (p.act == POLYDL_ACT_NONE) point_run<C8, POLYDL_ACT_NONE>(p, At, u, end, half, j);
-    else if (p.act == POLYDL_ACT_RELU) point_run<C8, POLYDL_ACT_RELU>(p, At, u, end, half, j);
-    else point_run<C8, POLYDL_ACT_RELU6>(p, At, u, end, half, j);
+    if (p.act == POLYDL_ACT_NONE) point_run<KB, POLYDL_ACT_NONE>(p, At, tiny, u, end, half, j);
+    else if (p.act == POLYDL_ACT_RELU) point_run<KB, POLYDL_ACT_RELU>(p, At, tiny, u, end, half, j);
+    else point_run<KB, POLYDL_ACT_RELU6>(p, At, tiny, u, end, half, j);
 }
 
 bool conv_point_fits(const ConvProblem &q)
@@ -201,7 +284,7 @@ bool conv_point_fits(const ConvProblem &q)
     if (q.R != 1 || q.S != 1 || q.stride != 1 || q.pad != 0 || q.pre_act != POLYDL_ACT_NONE) return false;
     if (q.C != 16 && q.C != 32 && q.C != 64) return false;
     // at least four channel groups share the pixels a wave holds (with 64 output channels the kernel
-    // measured no faster than the staged one); the filter has to fit the 64 KB of LDS
+    // measured no faster than the staged one); the split filter has to fit 96 KB of LDS
     if (q.K % 64 != 0 || q.K < 128 || (int64_t)q.K * q.C > 16384) return false;
     if (HW % 2 != 0) return false;
     // every byte offset, tile base and unit count stays below 2^31
@@ -215,9 +298,21 @@ void conv_point_shape(const ConvProblem &q, int cus, uint32_t *units, uint32_t *
     const int64_t total = (int64_t)q.N * q.H * q.W;
     const uint32_t tiles = (uint32_t)((total + 63) / 64);
     *units = tiles * (uint32_t)(q.K / 32);
-    const uint32_t fit = (uint32_t)cus * 2u;                 // two workgroups per compute unit (LDS)
-    const uint32_t need = (*units + 3) / 4;
+    const uint32_t fit = (uint32_t)cus;                      // one workgroup per compute unit (LDS)
+    const uint32_t need = (*units + kPointThreads / 64 - 1) / (kPointThreads / 64);
     *workgroups = need < fit ? need : fit;
+}
+
+template <int KB>
+static hipError_t launch_point(const ConvPointKArgs &a, uint32_t wgs, hipStream_t stream)
+{
+    const size_t lds = (size_t)a.K * KB * 16 * 6;
+    if (lds > 64 * 1024) {   // more than the default window has to be asked for
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(conv_point_kernel<KB>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    return launch_kernel(conv_point_kernel<KB>, dim3(wgs), dim3(kPointThreads), lds, stream, a);
 }
 
 hipError_t conv_point_launch(const ConvProblem &q, hipStream_t stream)
@@ -229,17 +324,15 @@ hipError_t conv_point_launch(const ConvProblem &q, hipStream_t stream)
     a.groups = q.K / 32;
     uint32_t wgs;
     conv_point_shape(q, compute_units(), &a.units, &wgs);
-    const uint32_t waves = wgs * 4;
+    const uint32_t waves = wgs * (kPointThreads / 64);
     a.per = a.units / waves;
     a.rem = a.units % waves;
     a.recip_groups = div_recip((uint32_t)a.groups);
     a.recip_HW = div_recip((uint32_t)a.HW);
     a.act = q.act;
-    hipError_t le = hipSuccess;
-    if (q.C == 64) le = launch_kernel(conv_point_kernel<8>, dim3(wgs), dim3(256), 0, stream, a);
-    else if (q.C == 32) le = launch_kernel(conv_point_kernel<4>, dim3(wgs), dim3(256), 0, stream, a);
-    else le = launch_kernel(conv_point_kernel<2>, dim3(wgs), dim3(256), 0, stream, a);
-    return le;
+    if (q.C == 64) return launch_point<4>(a, wgs, stream);
+    if (q.C == 32) return launch_point<2>(a, wgs, stream);
+    return launch_point<1>(a, wgs, stream);
 }
 
 }  // namespace polydl

@@ -155,7 +155,13 @@ constexpr bool split_products(int bk, int wm, int wn) { return bk == 16 && wm * 
 // Convolutions with a shorter reduction keep the fp32 matrix instruction: they are bound by their output, and
 // the longer prologue and the registers of the split kernels cost more than the products give (64 -> 64 channels
 // 1x1 at 56x56, batch 32: 14.3 us against 16.2; 24 -> 144: 18.8 against 24.3; the stem's 147 ties).
-constexpr int kSplitMinReduction = 128;
+// The same holds up to 511 for 1x1 layers of at most 64 output channels, which read four times what they write
+// and have one row of tiles to split the pixels for (256 -> 64 at 56x56, batch 32: 34.3 us against 36.6).
+constexpr int kSplitMinReduction = 128, kSplitMinReductionThin = 512;
+constexpr bool split_pays(int K, int RS, int64_t Kg)
+{
+    return Kg >= (RS == 1 && K <= 64 ? kSplitMinReductionThin : kSplitMinReduction);
+}
 constexpr int split_lds_bytes(int bm, int bn) { return 2 * 6 * 16 * (bm + bn); }
 
 // picker.cpp

@@ -350,7 +350,7 @@ void model_conv(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads, i
         default: c.regs = 228; c.eff_sat = 0.80; c.t_lat_us = 0.4; c.t_round_us = 4; c.gather_cycles = 20; c.split_c0 = 15; c.split_c1 = 1.0; break;
         }
         c.tail_split = cfg.raster >= 2;
-        const bool split = split_products(cfg.bk, cfg.wm, cfg.wn) && (double)q.C * q.R * q.S >= kSplitMinReduction;
+        const bool split = split_products(cfg.bk, cfg.wm, cfg.wn) && split_pays(q.K, q.R * q.S, (int64_t)q.C * q.R * q.S);
         double point_gather = 0.1, tap_gather = mbn == 11 ? kTapMajorGather11 : (mbn == 21 ? kTapMajorGather21 : kTapMajorGather);
         if (split) {
             // fitted to sweeps of 97 problems (the suite at batch 1 .. 64 and the three held-out sets, with and without
@@ -477,7 +477,7 @@ void model_sgemm(const SgemmProblem &q, const polydl_tile_cfg &cfg, int threads,
 static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
 
 // Pointwise kernel (filter resident in LDS, pixels loaded straight into registers): a unit is
-// 64 pixels x 32 output channels, C/2 * 2 matrix instructions; units are dealt to the waves in
+// 64 pixels x 32 output channels, 12 bfloat16 matrix instructions per 16 channels; units are dealt to the waves in
 // equal runs, so the busiest SIMD runs ceil(units / SIMDs) of them one after another.  The tensors
 // are streamed once.
 void model_conv_point(const ConvProblem &q, polydl_model_report *r)
@@ -487,13 +487,12 @@ void model_conv_point(const ConvProblem &q, polydl_model_report *r)
     conv_point_shape(q, kCUs, &units, &wgs);
     const double pixels = (double)q.N * q.H * q.W;
     const double in_bytes = pixels * q.C * 4, out_bytes = pixels * q.K * 4, wt_bytes = (double)q.K * q.C * 4;
-    const double unit_us = (q.C / 2.0) * 2.0 * 64.0 / kClockHz * 1e6;
+    const double unit_us = (q.C / 16.0) * 12.0 * 32.0 / kClockHz * 1e6;
     const double per_simd = std::ceil((double)units / (kCUs * kSimdsPerCU));
     r->mfma_us = per_simd * unit_us / 0.85;
-    // measured over batch sizes 16 .. 128 on 64 -> 64 and 64 -> 256 channels at 56 x 56 (back-to-back
-    // launches on the same buffers): the time follows the bytes written, at 3.3 TB/s; the input,
-    // re-read from the last-level cache, hardly shows
-    r->mem_us = (in_bytes + wt_bytes) / 20000.0 * 1e-3 + out_bytes / 3300.0 * 1e-3;
+    // measured on 64 -> 256 channels at 56 x 56, batch 32 and 64 (back-to-back launches on the same buffers):
+    // the time follows the bytes written, at 4.3 TB/s; the input, re-read from the last-level cache, hardly shows
+    r->mem_us = (in_bytes + wt_bytes) / 20000.0 * 1e-3 + out_bytes / 4300.0 * 1e-3;
     r->fixed_us = 7.0;                               // launch, filling LDS with the filter, first loads, last stores
     r->predicted_us = std::max(r->mfma_us, r->mem_us) + r->fixed_us;
     r->workgroups = (int)wgs;
@@ -541,7 +540,7 @@ void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out)
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &v = kVariants[i];
         const long stages = (Kg + v.bk - 1) / v.bk;
-        if (v.threads == 512 && Kg < kSplitMinReduction) continue;   // pays through the splitting alone
+        if (v.threads == 512 && !split_pays(q.K, q.R * q.S, Kg)) continue;   // pays through the splitting alone
         for (int sk : kSplits) {
             if (sk > stages) break;
             // raster 1: each XCD's workgroups take neighbouring tiles, so filter rows and the input rows
@@ -579,7 +578,7 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
         if (no_scratch && (c.cfg.split_k > 1 || c.cfg.raster >= 2)) continue;
         // the fp32 row-patch kernel is no match for the split products (1.1 .. 1.7 times the time of the best of
         // those on the suite); its own predictions are not comparable to theirs
-        if (c.cfg.algo == 1 && (int64_t)q.C * q.R * q.S >= kSplitMinReduction && cands.back().cfg.algo == 0) continue;
+        if (c.cfg.algo == 1 && split_pays(q.K, q.R * q.S, (int64_t)q.C * q.R * q.S) && cands.back().cfg.algo == 0) continue;
         // partial tiles stay within half of the fixed array of the allocation-free call (the other half may
         // hold a split filter), so that it serves every pick
         const double tiles = std::ceil((double)q.K / c.cfg.bm) * std::ceil((double)q.N * q.P * q.Q / c.cfg.bn);

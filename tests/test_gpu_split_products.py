@@ -145,3 +145,37 @@ def test_conv(P, s, case):
                 bound = (2.0 ** -25 + (Kg / 8 + 3) * 2.0 ** -24) if case == "plain" else (Kg + 2) * 2.0 ** -24
                 assert (np.abs(got[fin] - want[fin]) <= bound * ab[fin]).all(), v
     P.set_tile_override(None)
+
+
+@pytest.mark.parametrize("case", ["plain", "inf", "nan", "lowest", "tiny", "tiny_pixels"])
+@pytest.mark.parametrize("s", [synth.ConvShape("c64", 2, 64, 9, 10, 128, 1, 1, 1, 0), synth.ConvShape("c32", 1, 32, 7, 6, 192, 1, 1, 1, 0),
+                               synth.ConvShape("c16", 3, 16, 5, 4, 256, 1, 1, 1, 0)], ids=lambda s: s.name)
+def test_pointwise_conv(P, s, case):
+    x, w, b = synth.conv_inputs(s, seed=13, dist="normal", bias=True)
+    if case == "inf":
+        x[0, 3, 4, 2] = np.inf
+    elif case == "nan":
+        w[37, 5] = np.nan
+    elif case == "lowest":
+        x[0, 1, 3, 3] = np.finfo(np.float32).min
+        w *= np.float32(1e-3)
+    elif case == "tiny":
+        w[40] *= np.float32(1e-37)
+        x *= np.float32(1e20)
+        b[:] = 0
+    elif case == "tiny_pixels":
+        x[:, :, 2] *= np.float32(1e-37)
+        w *= np.float32(1e20)
+        b[:] = 0
+    want, ab = conv64(x, w, 1, 0)
+    want += b.astype(np.float64)[None, :, None, None]
+    ab += np.abs(b)[None, :, None, None]
+    v = [v for v in P.variants(0) if v.algo == 2][0]
+    P.set_tile_override(v)
+    got = host(P.conv2d_fwd(dev(x), dev(w), dev(b), stride=1, pad=0))
+    P.set_tile_override(None)
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True)
+    bound = (2.0 ** -25 + (s.C / 8 + 4) * 2.0 ** -24) if case == "plain" else (s.C + 3) * 2.0 ** -24
+    assert (np.abs(got[fin] - want[fin]) <= bound * ab[fin]).all()
