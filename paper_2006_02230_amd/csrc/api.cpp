@@ -535,9 +535,11 @@ int polydl_conv2d_fwd_bf16(int N, int C, int H, int W, int K, int R, int S, int 
     uint16_t *in8c = static_cast<uint16_t *>(workspace);
     uint16_t *wt8c = reinterpret_cast<uint16_t *>(static_cast<char *>(workspace) +
                                                   ((size_t)N * cu * H * W * 16 + 255) / 256 * 256);
-    int st = polydl_nchw_to_nchwc_bf16(N, C, H, W, 8, in, in8c, stream);
-    if (st != POLYDL_OK) return st;
-    st = polydl_kcrs_to_kcrsck_bf16(K, C, R, S, 8, 1, wt, wt8c, stream);
+    // the limits of the two layout entry points
+    if (N > 65535 || cu > 65535 || (int64_t)H * W >= (1ll << 31)) return POLYDL_ERR_UNSUPPORTED;
+    if (!on_gfx950()) return POLYDL_ERR_NO_DEVICE;
+    if ((int64_t)K * cu * 8 * R * S >= (1ll << 39) || (int64_t)R * S >= (1ll << 31)) return POLYDL_ERR_UNSUPPORTED;
+    const int st = launched(launch_block8_16bit(in, in8c, N, C, H * W, wt, wt8c, K, R * S, (hipStream_t)stream));
     if (st != POLYDL_OK) return st;
     return polydl_conv2d_fwd_bf16_blocked(N, C, H, W, K, R, S, stride, pad, in8c, wt8c, bias, out, act, stream);
 }

@@ -90,6 +90,8 @@ hipError_t launch_nchwc(const void *src, void *dst, int N, int C, int HW, int b,
                         hipStream_t st);
 hipError_t launch_kcrsck(const void *wt, void *dst, int K, int C, int RS, int bc, int bk, int elem_bytes,
                          hipStream_t st);
+hipError_t launch_block8_16bit(const uint16_t *in, uint16_t *in8c, int N, int C, int HW, const uint16_t *wt, uint16_t *wt8c, int K,
+                               int RS, hipStream_t st);
 hipError_t launch_bias_add(float *y, const float *bias, int K, int PQ, size_t total, hipStream_t st);
 hipError_t launch_act(float *y, size_t total, int act, hipStream_t st);
 hipError_t launch_bnorm_act(const float *x, float *y, const float *gamma, const float *beta, const float *mean,
