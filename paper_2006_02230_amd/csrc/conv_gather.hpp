@@ -345,16 +345,8 @@ __device__ __forceinline__ ConvPart conv_part(const ConvKArgs &p)
     return c;
 }
 
-// A tile whose lanes own single pixels, for store_rows.
-template <class T>
-struct OneColumn {
-    static constexpr int MB = T::MB, NB = 1;
-};
-
 // What follows the reduction: the hand-over of a split reduction's parts, then bias, activation, store.
-// ADJACENT: the lane's NB pixels are neighbours (pixel NB*lane + bj of the wave's columns) and leave as one
-// vector; otherwise block bj's pixel is 32*bj + lane.
-template <class T, bool ADJACENT = true>
+template <class T>
 __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &c, v16f (&acc)[T::MB][T::NB], int tid,
                                             int wm0, int wn0)
 {
@@ -390,7 +382,7 @@ __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &
     // epilogue.  The lane owns NB adjacent pixels starting at colg for 16*MB output channels.
     // Addresses are a per-lane byte offset from the first image the tile touches plus a uniform
     // offset per channel row, so a store costs no address arithmetic.
-    const int colg = n0 + wn0 + (ADJACENT ? T::NB : 1) * (lane & 31);
+    const int colg = n0 + wn0 + T::NB * (lane & 31);
     if (colg >= p.Ng) return;
     const int krow = m0 + wm0 + 4 * (lane >> 5);   // channel of register 0; register r adds 8*(r/4) + r%4
     const uint32_t KPQ = (uint32_t)p.K * (uint32_t)p.PQ;
@@ -408,22 +400,6 @@ __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &
         for (int r = 0; r < 16; ++r)
             bias[bi][r] = buf_load1(rb, (uint32_t)(krow + 32 * bi + 8 * (r >> 2) + (r & 3)) * 4u);
     const uint32_t row_bytes = (uint32_t)p.PQ * 4u;
-    if constexpr (!ADJACENT) {
-#pragma unroll
-        for (int bj = 0; bj < T::NB; ++bj) {
-            const int col = colg + 32 * bj;
-            if (col < p.Ng) {
-                uint32_t q;
-                const uint32_t im = div_by((uint32_t)col, (uint32_t)p.PQ, p.recip_PQ, q) - img0;
-                v16f one[T::MB][1];
-#pragma unroll
-                for (int bi = 0; bi < T::MB; ++bi) one[bi][0] = acc[bi][bj];
-                store_rows_by<OneColumn<T>>(p.act, m0 + T::BM <= p.K, ro, (im * KPQ + (uint32_t)krow * (uint32_t)p.PQ + q) * 4u,
-                                            row_bytes, one, bias, krow, p.K);
-            }
-        }
-        return;
-    }
     // the NB pixels are one vector store when they lie in one image and keep the alignment
     const bool vec = (p.PQ % T::NB == 0) && (((uintptr_t)p.out & 15) == 0);
     if (vec) {

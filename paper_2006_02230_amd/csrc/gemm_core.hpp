@@ -78,14 +78,6 @@ __device__ __forceinline__ void wait_vmcnt0()
     __builtin_amdgcn_s_waitcnt(0x0F70);
 }
 
-// The same until at most N (< 64) of them are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "six bits");
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
-}
-
 // n / d and n % d for any 32-bit n and d >= 1, given recip = floor(2^32 / d) (0xFFFFFFFF for
 // d == 1): umulhi(n, recip) is the quotient or one below it, which one comparison settles.
 __device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t recip, uint32_t &rem)
