@@ -379,6 +379,9 @@ void model_conv(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads, i
         // (with a stride the lanes' addresses spread over twice the cache lines and the cost of
         // the load is in the memory pipeline, which the cheaper addressing does not touch)
         if (cfg.layout == 2 && q.stride == 1) c.gather_cycles *= tap_gather;
+        // and splitting the reduction gains less there than the fit to mostly unstrided layers says: 128 -> 128 3x3/2
+        // on 56x56, batch 32, tile 128x128: two parts 66.9 us, whole tiles 60.1 (stride 1, 28x28: 56.0 and 59.4)
+        if (split && cfg.layout == 2 && q.stride > 1) c.split_c0 += 3;
         if (c.split_c1 == 0) c.split_c1 = 0.1;   // scratch tiles, as in the patch kernel
     }
     Shape s = conv_shape(q, cfg.algo, cfg.bn, std::max(2, cfg.cb));
