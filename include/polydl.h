@@ -164,7 +164,7 @@ int polydl_conv2d_fwd_tap(int N, int C, int H, int W, int K, int R, int S, int s
  * allowed (C is left as it is).  The variants with stage depth 16 and wave tiles up to 64 x 64 split both
  * operands into three bfloat16 parts each and sum six of their products in float32 (smaller error against
  * 64 bits than float32 products summed in sequence); tiles that meet values this cannot hold
- * (infinities, NaN, rows or columns of numbers below 2^-95) are computed from float32 products. */
+ * (infinities, NaN, numbers below 2^-110 with bits under 2^-133) are computed from float32 products. */
 int polydl_sgemm(int M, int N, int K, const float *A, const float *B, float *C, void *stream);
 
 /* The general form the text of section "GEMM" states, C = beta*C + alpha*A*B, with both scalars

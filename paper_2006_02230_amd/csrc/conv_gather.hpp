@@ -302,7 +302,7 @@ struct BLoaderIm2col {
     {
         unit.write(stage + L::A_UNITS, L::B_PLANE, L::B_RUN, lds_off, krow0);
     }
-    __device__ __forceinline__ bool tiny() const { return split_tiny(unit.seen); }
+    __device__ __forceinline__ bool lossy() const { return split_lossy(unit.seen); }
     template <int SET>
     __device__ __forceinline__ void store(float *Bs, int)
     {

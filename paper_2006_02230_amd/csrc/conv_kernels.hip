@@ -69,7 +69,7 @@ __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvK
         SplitAcc<T> sum;
         sum.clear();
         split_mainloop<T>(lds, al, bl, sum, c.kbegin, c.kend, tid, wm0, wave / T::WAVES_M);
-        redo = sum.finish(acc) || al.tiny() || bl.tiny();
+        redo = sum.finish(acc) || al.lossy() || bl.lossy();
     }
     if (__syncthreads_or(redo)) {   // values the split cannot hold: once more on the fp32 matrix cores
         ALoader<T, 4, true> al;

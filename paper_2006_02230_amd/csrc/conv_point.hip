@@ -70,7 +70,7 @@ __device__ __forceinline__ void point_store(__amdgpu_buffer_rsrc_t ro, uint32_t 
 template <int KB>
 struct PointPixels {
     u32x4 b[2][KB][3];
-    uint32_t seen[2];      // OR of the bit patterns of the lane's channels of each pixel
+    uint32_t seen[2];      // SplitUnit::seen of the lane's channels of each pixel
 };
 
 // The products of one unit into `cur` and, PENDING, the 16 stores of the unit finished before it
@@ -130,7 +130,7 @@ __device__ __forceinline__ bool point_unit(const u32x4 *a_base, int K, const Poi
 // A wave's run of units [u, end).  Two unit records take turns: while one collects the products of
 // unit i, the other, holding unit i - 1, is stored.
 template <int KB, int ACT>
-__device__ __forceinline__ void point_run(const ConvPointKArgs &p, const u32x4 *At, bool tiny_filter, uint32_t u, uint32_t end,
+__device__ __forceinline__ void point_run(const ConvPointKArgs &p, const u32x4 *At, bool lossy_filter, uint32_t u, uint32_t end,
                                           int half, int j)
 {
     const int K = p.K, C = KB * 16;
@@ -195,7 +195,7 @@ __device__ __forceinline__ void point_run(const ConvPointKArgs &p, const u32x4 *
     };
     // a unit that met values the split cannot hold: once more on the fp32 matrix cores, operands from memory
     auto check_unit = [&](PointUnit &cur, bool bad) {
-        bad = bad || tiny_filter || split_tiny(px.seen[0]) || split_tiny(px.seen[1]);
+        bad = bad || lossy_filter || split_lossy(px.seen[0]) || split_lossy(px.seen[1]);
         if (__ballot(bad) == 0) return;
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kPointThreads, 2) void conv_point_kernel(const Conv
     const int half = lane >> 5, j = lane & 31;
     const int K = p.K, C = KB * 16;
 
-    bool tiny = false;
+    bool lossy = false;
     {
         const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wt, (uint64_t)K * C * 4);
         for (int idx = tid; idx < K * KB * 2; idx += kPointThreads) {   // K is a multiple of 64: a wave has one octet
@@ -261,21 +261,21 @@ __global__ __launch_bounds__(kPointThreads, 2) void conv_point_kernel(const Conv
             const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
             SplitUnit<8> s;
             static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { s.template step<decltype(st)::value>(v); });
-            tiny |= split_tiny(s.seen);
+            lossy |= split_lossy(s.seen);
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl)
                 At[(((o >> 1) * 3 + pl) * 2 + (o & 1)) * K + k] = (u32x4){s.p[pl][0], s.p[pl][1], s.p[pl][2], s.p[pl][3]};
         }
     }
-    tiny = __syncthreads_or(tiny);
+    lossy = __syncthreads_or(lossy);
 
     const uint32_t w = blockIdx.x * (kPointThreads / 64) + wave;
     const uint32_t u = w * p.per + (w < p.rem ? w : p.rem);
     const uint32_t end = u + p.per + (w < p.rem ? 1u : 0u);
     if (u >= end) return;
-    if (p.act == POLYDL_ACT_NONE) point_run<KB, POLYDL_ACT_NONE>(p, At, tiny, u, end, half, j);
-    else if (p.act == POLYDL_ACT_RELU) point_run<KB, POLYDL_ACT_RELU>(p, At, tiny, u, end, half, j);
-    else point_run<KB, POLYDL_ACT_RELU6>(p, At, tiny, u, end, half, j);
+    if (p.act == POLYDL_ACT_NONE) point_run<KB, POLYDL_ACT_NONE>(p, At, lossy, u, end, half, j);
+    else if (p.act == POLYDL_ACT_RELU) point_run<KB, POLYDL_ACT_RELU>(p, At, lossy, u, end, half, j);
+    else point_run<KB, POLYDL_ACT_RELU6>(p, At, lossy, u, end, half, j);
 }
 
 bool conv_point_fits(const ConvProblem &q)

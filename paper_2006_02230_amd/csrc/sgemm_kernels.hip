@@ -162,7 +162,7 @@ __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void sgemm_split_kernel(Sgem
         SplitAcc<T> sum;
         sum.clear();
         if (kbegin < kend) split_mainloop<T>(lds, al, bl, sum, kbegin, kend, tid, wm0, wave / T::WAVES_M);
-        redo = sum.finish(acc) || al.tiny() || bl.tiny();
+        redo = sum.finish(acc) || al.lossy() || bl.lossy();
     }
     if (__syncthreads_or(redo)) {   // values the split cannot hold: once more on the fp32 matrix cores
         ALoader<T, 4, true> al;

@@ -14,9 +14,9 @@
 // better than fp32; flushing it to a separate sum costs as many registers as the second one.)
 //
 // What the split cannot represent is recomputed with v_mfma_f32_32x32x2_f32 by the workgroup that meets
-// it (`split_needs_fp32`): infinities, NaN and values that round to a bfloat16 infinity leave a non-finite
-// accumulator; a row or column all of whose values lie below 2^-95 would lose the bits under 2^-133,
-// the smallest bfloat16, and is found by OR-ing the bit patterns as they are staged.
+// it: infinities, NaN and values that round to a bfloat16 infinity leave a non-finite accumulator; a value
+// below 2^-110 may have bits under 2^-133, the smallest bfloat16, which its third part drops.  The matrix
+// unit itself keeps bfloat16 subnormals, so every value whose third part is exact is multiplied exactly.
 #pragma once
 #include "gemm_core.hpp"
 #include <type_traits>
@@ -65,13 +65,11 @@ struct SplitTile {
     }
 };
 
-// true if bits (OR of the bit patterns of values staged for one row) shows a nonzero value and none
-// of 2^-95 or more
-__device__ __forceinline__ bool split_tiny(uint32_t bits)
-{
-    const uint32_t m = bits & 0x7FFFFFFFu;
-    return m != 0 && m < (32u << 23);
-}
+// true if bits (OR of the bit patterns of the second remainders, see SplitUnit) shows a value whose three
+// parts do not add up to it.  What is left of a value after two parts has at most seven significant bits and is
+// the third part, unless some of them lie below 2^-133; a float32 is a bfloat16 exactly where its low
+// sixteen bits are zero, for subnormal numbers too.
+__device__ __forceinline__ bool split_lossy(uint32_t bits) { return (bits & 0xFFFFu) != 0; }
 
 // RPT (4 or 8) consecutive reduction values of one row on their way into the three planes.  The splitting
 // goes in steps of about five vector instructions, three per pair of values, so that the main loop can
@@ -81,7 +79,7 @@ struct SplitUnit {
     static constexpr int STEPS = 3 * RPT / 2;
     uint32_t p[3][RPT / 2];
     float rx, ry;
-    uint32_t seen = 0;        // OR of the bit patterns of every value that came through
+    uint32_t seen = 0;        // OR of the bit patterns of what every value left for its third part
     template <int STEP>
     __device__ __forceinline__ void step(const float *v)
     {
@@ -90,15 +88,15 @@ struct SplitUnit {
             p[0][i] = pack_bf16(v[2 * i], v[2 * i + 1]);
             rx = v[2 * i] - __builtin_bit_cast(float, p[0][i] << 16);
             ry = v[2 * i + 1] - __builtin_bit_cast(float, p[0][i] & 0xFFFF0000u);
-            // as an instruction of its own place: the compiler would gather the ORs of a whole stage at
-            // the first use and wait there for loads that are needed much later
-            asm volatile("v_or3_b32 %0, %1, %2, %0" : "+v"(seen) : "v"(v[2 * i]), "v"(v[2 * i + 1]));
         } else if constexpr (PHASE == 1) {
             p[1][i] = pack_bf16(rx, ry);
             rx -= __builtin_bit_cast(float, p[1][i] << 16);
             ry -= __builtin_bit_cast(float, p[1][i] & 0xFFFF0000u);
         } else {
             p[2][i] = pack_bf16(rx, ry);
+            // as an instruction of its own place: the compiler would gather the ORs of a whole stage at
+            // the first use and wait there for loads that are needed much later
+            asm volatile("v_or3_b32 %0, %1, %2, %0" : "+v"(seen) : "v"(rx), "v"(ry));
         }
     }
     // base: first unit of the operand's stage; k_in: reduction index of the first value inside the stage
@@ -222,7 +220,7 @@ struct SplitALoader {
     template <int SET, int STEP>
     __device__ __forceinline__ void step() { unit.template step<STEP>(regs[SET]); }
     __device__ __forceinline__ void write(u32x4 *stage) const { unit.write(stage, L::A_PLANE, L::A_RUN, row, k_in); }
-    __device__ __forceinline__ bool tiny() const { return split_tiny(unit.seen); }
+    __device__ __forceinline__ bool lossy() const { return split_lossy(unit.seen); }
 };
 
 // ---- B operand of a plain GEMM: row-major [Kg][ldb], column index contiguous ------------------
@@ -274,7 +272,7 @@ struct SplitBLoaderRows {
     {
         unit.write(stage + L::A_UNITS, L::B_PLANE, L::B_RUN, pos, row0);
     }
-    __device__ __forceinline__ bool tiny() const { return split_tiny(unit.seen); }
+    __device__ __forceinline__ bool lossy() const { return split_lossy(unit.seen); }
 };
 
 // Software pipeline.  While stage t is multiplied out of LDS buffer t&1, stage t+1 is split from registers into

@@ -179,3 +179,90 @@ def test_pointwise_conv(P, s, case):
     assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True)
     bound = (2.0 ** -25 + (s.C / 8 + 4) * 2.0 ** -24) if case == "plain" else (s.C + 3) * 2.0 ** -24
     assert (np.abs(got[fin] - want[fin]) <= bound * ab[fin]).all()
+
+
+def all_magnitudes(seed, shape, lowest=-149):
+    """Random signs and mantissas, exponents uniform over every float32 number from 2^lowest on, some zeros."""
+    rng = np.random.default_rng(seed)
+    v = np.ldexp(1 + rng.random(shape), rng.integers(lowest, 127, shape)) * rng.choice([-1.0, 1.0], shape)
+    v[rng.random(shape) < 0.05] = 0
+    with np.errstate(under="ignore"):
+        return v.astype(np.float32)
+
+
+# One value of ordinary size beside values whose third bfloat16 part lies below the smallest bfloat16 (2^-133): the
+# small ones must keep all their bits too.  With a single nonzero product per sum the result is exact.
+@pytest.mark.parametrize("split_k", [1, 3])
+@pytest.mark.parametrize("lowest", [-149, -120])
+def test_sgemm_small_values_beside_large_ones(P, split_k, lowest):
+    K = 150
+    eye = np.eye(K, dtype=np.float32)
+    B = all_magnitudes(3, (K, 140), lowest)
+    for v in split_tiles(P):
+        v.split_k = split_k
+        P.set_tile_override(v)
+        for A, X, want in ((eye, B, B), (np.ascontiguousarray(B.T), eye, B.T)):
+            C = dev(np.zeros(want.shape, np.float32))
+            P.sgemm(dev(A), dev(X), C)
+            assert np.array_equal(host(C), want), v
+    P.set_tile_override(None)
+
+
+def test_sgemm_large_value_meets_zero(P):
+    # row 0 of A: 1 and tiny values in one thread's share; B has 0 where A has 1, large values elsewhere
+    M, N, K = 70, 66, 130
+    A, B, _ = synth.sgemm_inputs(M, N, K, seed=21)
+    A[0] *= np.float32(2.0 ** -125)
+    B *= np.float32(2.0 ** 120)
+    A[0, ::8], B[::8] = 1.0, 0.0
+    want = A.astype(np.float64) @ B.astype(np.float64)
+    terms = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)
+    for v in split_tiles(P):
+        P.set_tile_override(v)
+        for a, b, w, t in ((A, B, want, terms), (B.T, A.T, want.T, terms.T)):
+            C = dev(np.zeros(w.shape, np.float32))
+            P.sgemm(dev(a), dev(b), C)
+            assert (np.abs(host(C) - w) <= (K + 2) * 2.0 ** -24 * t).all(), v
+    P.set_tile_override(None)
+
+
+@pytest.mark.parametrize("s", CONV, ids=lambda s: s.name)
+def test_conv_small_values_beside_large_ones(P, s):
+    x = all_magnitudes(5, (s.N, s.C, s.H, s.W))
+    pick = np.zeros((s.K, s.C, s.R, s.S), np.float32)
+    for k in range(s.K):
+        pick[k, k % s.C, s.R // 2, s.S // 2] = 1              # every output is one input value
+    w = all_magnitudes(6, (s.K, s.C, s.R, s.S))
+    dot = np.zeros((s.C, s.C, s.H, s.W), np.float32)
+    for c in range(s.C):
+        dot[c, c, s.H // 2, s.W // 2] = 1                     # every output is one filter value or zero
+    for inp, f in ((x, pick), (dot, w)):
+        want = conv64(inp, f, s.stride, s.pad)[0].astype(np.float32)
+        dx, dw = dev(inp), dev(f)
+        tap = P.filter_tap_copy(dw)
+        for v in P.variants(0):
+            if v.algo != 0 or v.bk != 16 or v.wm * v.wn > 64 * 64:
+                continue
+            for split_k, raster in ((1, 0), (2, 1), (1, 3)):
+                for layout in ((0, 2) if s.C % 16 == 0 and 2 <= s.R * s.S <= 63 else (0,)):
+                    v.split_k, v.raster, v.layout = split_k, raster, layout
+                    P.set_tile_override(v)
+                    got = host(P.conv2d_fwd(dx, dw, stride=s.stride, pad=s.pad, w_tap=tap if layout else None))
+                    assert np.array_equal(got, want), v
+    P.set_tile_override(None)
+
+
+@pytest.mark.parametrize("s", [synth.ConvShape("c64", 2, 64, 9, 10, 128, 1, 1, 1, 0), synth.ConvShape("c32", 1, 32, 7, 6, 192, 1, 1, 1, 0),
+                               synth.ConvShape("c16", 3, 16, 5, 4, 256, 1, 1, 1, 0)], ids=lambda s: s.name)
+def test_pointwise_small_values_beside_large_ones(P, s):
+    x = all_magnitudes(7, (s.N, s.C, s.H, s.W))
+    pick = np.zeros((s.K, s.C, 1, 1), np.float32)
+    pick[np.arange(s.K), np.arange(s.K) % s.C] = 1
+    w = all_magnitudes(8, (s.K, s.C, 1, 1))
+    dot = np.zeros((s.C, s.C, s.H, s.W), np.float32)
+    dot[np.arange(s.C), np.arange(s.C), s.H // 2] = 1
+    P.set_tile_override([v for v in P.variants(0) if v.algo == 2][0])
+    for inp, f in ((x, pick), (dot, w)):
+        got = host(P.conv2d_fwd(dev(inp), dev(f), stride=1, pad=0))
+        assert np.array_equal(got, conv64(inp, f, 1, 0)[0].astype(np.float32))
+    P.set_tile_override(None)
