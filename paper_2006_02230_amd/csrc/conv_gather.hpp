@@ -81,8 +81,9 @@ constexpr int kTableRows = 512;   // 4 KB of LDS
 
 
 // SPLIT: the stage goes to LDS as three bfloat16 planes (split_core.hpp), so a thread's rows of a stage are
-// consecutive; otherwise they lie KSTEP apart.
-template <class T, int MODE, bool SPLIT = false>
+// consecutive; otherwise they lie KSTEP apart.  KTAIL: the reduction may end inside a stage (GATHER_POINT only,
+// every other mode tests each row anyway).
+template <class T, int MODE, bool SPLIT = false, bool KTAIL = true>
 struct BLoaderIm2col {
     typedef SplitTile<T> L;
     static constexpr bool POINT = MODE == GATHER_POINT;
@@ -199,12 +200,15 @@ struct BLoaderIm2col {
     __device__ __forceinline__ void load(int k0, int kend)
     {
         if constexpr (POINT) {
-            // A row at or past kend meets zeros in the filter operand; it reads the last real
-            // channel so that what it multiplies is a finite input value of the same image
+            // A row at or past kend (wave-uniform) meets zeros in the filter operand.  In a stage that is
+            // multiplied it must read as zero, not as a value of another channel, which may be an infinity;
+            // where the reduction is whole stages it only has to stay inside the tensor.
 #pragma unroll
             for (int i = 0; i < ITERS; ++i) {
-                int kg = min(k0 + krow0 + i * KSTEP, kend - 1);  // wave-uniform
-                regs[SET][i] = buf_load1(rsrc, (uint32_t)pix_off, (uint32_t)(kg * HW) * 4u);
+                const int kg = k0 + krow0 + i * KSTEP;
+                if constexpr (KTAIL)
+                    regs[SET][i] = buf_load1(rsrc, (uint32_t)pix_off | (kg < kend ? 0u : kOobOffset), (uint32_t)(kg * HW) * 4u);
+                else regs[SET][i] = buf_load1(rsrc, (uint32_t)pix_off, (uint32_t)(min(kg, kend - 1) * HW) * 4u);
             }
             return;
         }
@@ -279,9 +283,8 @@ struct BLoaderIm2col {
     __device__ __forceinline__ void row()
     {
         if constexpr (POINT) {
-            int kg = s_k0 + krow0 + J;
-            if (!FULL) kg = min(kg, s_kend - 1);
-            regs[SET][J] = buf_load1(rsrc, (uint32_t)pix_off, (uint32_t)(kg * HW) * 4u);
+            const int kg = s_k0 + krow0 + J;
+            regs[SET][J] = buf_load1(rsrc, (uint32_t)pix_off | (FULL || kg < s_kend ? 0u : kOobOffset), (uint32_t)(kg * HW) * 4u);
         } else if constexpr (TAPMAJOR) {
             regs[SET][J] = buf_load1(rsrc, s_off, s_koff + (uint32_t)(J * HW) * 4u);
         } else if constexpr (TABLE) {

@@ -22,9 +22,10 @@ __global__ __launch_bounds__(T::NT) void conv_kernel(ConvKArgs p)
     const int wm0 = (wave % T::WAVES_M) * T::WM, wn0 = (wave / T::WAVES_M) * T::WN;
 
     // AVEC = 1 stands for filter rows that are not a multiple of four floats long or not 16-byte
-    // aligned: vector loads all the same, with the reduction's tail masked
+    // aligned: vector loads all the same, with the reduction's tail masked.  AVEC = 2 (GATHER_POINT): rows as
+    // for 4, but not whole stages long, so that the gather has to mind the tail
     ALoader<T, 4, AVEC == 1> al;
-    BLoaderIm2col<T, MODE> bl;
+    BLoaderIm2col<T, MODE, false, AVEC != 4> bl;
     __shared__ uint2 ktab[MODE == GATHER_TABLE ? kTableRows : 1];
     bl.fill_table(p, tid, ktab);
     al.init(p.wt, tid, c.m0, p.K, p.Kg, p.Kg);
@@ -178,7 +179,8 @@ static hipError_t conv_launch(const ConvProblem &q, int split_k, int raster, hip
 #define POLYDL_GO(AV, MODE) return launch_kernel((conv_kernel<T, AV, MODE>), grid, block, 0, stream, a)
     if (mode == GATHER_TAPMAJOR) POLYDL_GO(4, GATHER_TAPMAJOR);
     if (avec) {
-        if (mode == GATHER_POINT) POLYDL_GO(4, GATHER_POINT);
+        if (mode == GATHER_POINT && a.Kg % T::BK == 0) POLYDL_GO(4, GATHER_POINT);
+        if (mode == GATHER_POINT) POLYDL_GO(2, GATHER_POINT);
         if (mode == GATHER_TABLE) POLYDL_GO(4, GATHER_TABLE);
     } else {
         if (mode == GATHER_POINT) POLYDL_GO(1, GATHER_POINT);

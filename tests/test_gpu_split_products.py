@@ -266,3 +266,22 @@ def test_pointwise_small_values_beside_large_ones(P, s):
         got = host(P.conv2d_fwd(dev(inp), dev(f), stride=1, pad=0))
         assert np.array_equal(got, conv64(inp, f, 1, 0)[0].astype(np.float32))
     P.set_tile_override(None)
+
+
+# The last channel of a reduction that does not fill its last stage: what lies past the end must not meet it.
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+@pytest.mark.parametrize("s", [s for s in CONV if s.R == 1] + [synth.ConvShape("c37", 2, 37, 6, 7, 40, 1, 1, 1, 0)], ids=lambda s: s.name)
+def test_infinity_in_the_last_channel_stays_an_infinity(P, s, value):
+    x, w, _ = synth.conv_inputs(s, seed=17, dist="normal")
+    x[0, s.C - 1, 2, 2] = value
+    want = conv64(x, w, s.stride, s.pad)[0]
+    for v in P.variants(0):
+        if v.algo != 0:
+            continue
+        for split_k in (1, 2):
+            v.split_k = split_k
+            P.set_tile_override(v)
+            got = host(P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad))
+            inf = np.isinf(want)
+            assert inf.any() and np.array_equal(got[inf], want[inf]) and np.isfinite(got[~inf]).all(), v
+    P.set_tile_override(None)
