@@ -35,12 +35,18 @@ const int kNumPatchBf16Variants = (int)(sizeof(kPatchBf16Variants) / sizeof(kPat
 
 static std::mutex g_mu;
 static std::atomic<int> g_last_hip_error{0};
+// The launch that returned e needed scratch memory that cannot be allocated while its stream is being
+// captured.  (The refusal alone may be that of an earlier call: unsplit launches do not reset it.)
+static bool refused_for_capture(hipError_t e)
+{
+    return e == hipErrorStreamCaptureUnsupported && scratch_refusal() == SCRATCH_CAPTURING;
+}
 static int launch_failed(hipError_t e)
 {
     // a launch that needed scratch memory it may not have: not the runtime's refusal
     const int why = scratch_refusal();
     if (e == hipErrorOutOfMemory && why == SCRATCH_TOO_SMALL) return POLYDL_ERR_SCRATCH_LIMIT;
-    if (e == hipErrorStreamCaptureUnsupported && why == SCRATCH_CAPTURING) return POLYDL_ERR_UNSUPPORTED;
+    if (refused_for_capture(e)) return POLYDL_ERR_UNSUPPORTED;
     g_last_hip_error = (int)e;
     return POLYDL_ERR_LAUNCH;
 }
@@ -194,7 +200,7 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
     };
     hipError_t e;
     if (!launch(&e)) return POLYDL_ERR_UNSUPPORTED;
-    if (picked && e != hipSuccess && scratch_refusal() == SCRATCH_CAPTURING) {
+    if (picked && refused_for_capture(e)) {
         // the stream is being captured and has no scratch memory for a split reduction yet: the best
         // variant that needs none (not cached)
         polydl_model_report rep;
@@ -244,25 +250,20 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
             g_conv_plans[key] = cfg;
         }
     }
+    // the pointwise kernel moves pixel pairs as 8-byte words and filter and bias as 16-byte words: tensors
+    // aligned to less take the best of the other candidates (not cached: the plan is about shapes)
     const bool point_aligned = !(((uintptr_t)in | (uintptr_t)out) & 7) && !((uintptr_t)wt & 15) && !((uintptr_t)bias & 15);
     if (!forced && cfg.algo == 2 && !point_aligned) {
-        // the pointwise kernel moves pixel pairs as 8-byte words and filter and bias as 16-byte
-        // words: for tensors aligned to less take the best of the other candidates (not cached:
-        // the plan is about shapes)
-        std::vector<ConvCandidate> cands;
-        conv_candidates(q, &cands);
-        const ConvCandidate *b = nullptr;
-        for (const ConvCandidate &c : cands)
-            if (c.cfg.algo != 2 && (!b || c.rep.predicted_us < b->rep.predicted_us)) b = &c;
-        if (!b) return POLYDL_ERR_UNSUPPORTED;
-        cfg = b->cfg;
+        polydl_model_report rep;
+        if (!pick_conv(q, &cfg, &rep, PickLimits{false, false})) return POLYDL_ERR_UNSUPPORTED;
     }
     bool no_scratch = false;   // the launch was refused because the stream is being captured and has no scratch memory
     auto failed = [&](hipError_t e) {
-        no_scratch = scratch_refusal() == SCRATCH_CAPTURING;
+        no_scratch = refused_for_capture(e);
         return launch_failed(e);
     };
     auto run = [&]() -> int {
+        q.wt_tap = nullptr;    // set below for the variants that read the copy
         if (cfg.layout != 0 && !(cfg.layout == 2 && cfg.algo == 0)) return POLYDL_ERR_UNSUPPORTED;
         if (cfg.algo == 2) {
             if (!is_conv_point_cfg(cfg) || !conv_point_fits(q) || !point_aligned) return POLYDL_ERR_UNSUPPORTED;
@@ -307,7 +308,7 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
     if (st != POLYDL_OK && no_scratch && !forced) {
         // the best variant that needs none (not cached); nothing was enqueued so far
         polydl_model_report rep;
-        if (!pick_conv(q, &cfg, &rep, true)) return st;
+        if (!pick_conv(q, &cfg, &rep, PickLimits{true, point_aligned})) return st;
         st = run();
     }
     return st;

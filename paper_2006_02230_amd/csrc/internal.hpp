@@ -174,8 +174,9 @@ void model_set_levels(const double *capacity, const double *gbytes_per_s, double
 void model_conv(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads, int reg_class, polydl_model_report *r);
 void model_sgemm(const SgemmProblem &q, const polydl_tile_cfg &cfg, int threads, polydl_model_report *r);
 double model_conv_bf16(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads);   // predicted microseconds
-// no_scratch: only variants that need no scratch memory (nothing split)
-bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *rep, bool no_scratch = false);   // q.pre_act: gather kernel only
+// no_scratch: only variants that need no scratch memory (nothing split); pointwise: the pointwise kernel may be picked
+struct PickLimits { bool no_scratch = false, pointwise = true; };
+bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *rep, PickLimits limits = PickLimits());   // q.pre_act: gather kernel only
 bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_report *rep, bool no_scratch = false);
 struct ConvCandidate { polydl_tile_cfg cfg; polydl_model_report rep; };
 // every (variant, stage depth, split factor, leftover-tile switch) pick_conv ranks, with its model report

@@ -564,7 +564,7 @@ void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out)
     }
 }
 
-bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep, bool no_scratch)
+bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep, PickLimits limits)
 {
     std::vector<ConvCandidate> cands;
     conv_candidates(q, &cands);
@@ -578,7 +578,8 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
     };
     const ConvCandidate *b = nullptr;
     for (const ConvCandidate &c : cands) {
-        if (no_scratch && (c.cfg.split_k > 1 || c.cfg.raster >= 2)) continue;
+        if (limits.no_scratch && (c.cfg.split_k > 1 || c.cfg.raster >= 2)) continue;
+        if (!limits.pointwise && c.cfg.algo == 2) continue;
         // the fp32 row-patch kernel is no match for the split products (1.1 .. 1.7 times the time of the best of
         // those on the suite); its own predictions are not comparable to theirs
         if (c.cfg.algo == 1 && split_pays(q.K, q.R * q.S, (int64_t)q.C * q.R * q.S) && cands.back().cfg.algo == 0) continue;

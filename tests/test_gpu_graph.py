@@ -138,3 +138,60 @@ def test_capture_that_would_allocate_is_refused(P):
     import oracle
     want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=1, pad=1, act="relu")
     assert oracle.scaled_error(host(out), want, ab) <= 1e-5
+
+
+def misaligned(a):
+    import torch
+    buf = torch.empty(a.size + 1, dtype=torch.float32, device="cuda")
+    buf[1:].copy_(torch.from_numpy(a.reshape(-1)))
+    return buf[1:].view(a.shape)                    # four bytes off the allocation's alignment
+
+
+@pytest.mark.parametrize("case", ["sgemm", "conv", "conv_tap", "misaligned_pointwise"])
+def test_the_library_choice_is_captured_without_scratch_memory(P, case):
+    # no override, a stream without scratch memory, and a choice that splits its reduction when called
+    # eagerly: the capture records the best variant that needs none
+    import torch
+    import oracle
+    P.set_tile_override(None)
+    if case == "sgemm":
+        M, N, K = 96, 128, 4096
+        A, B, _ = synth.sgemm_inputs(M, N, K, seed=65)
+        want, ab = oracle.gemm(A, B, np.zeros((M, N), np.float32))
+        dA, dB, out = dev(A), dev(B), torch.zeros((M, N), dtype=torch.float32, device="cuda")
+
+        def call():
+            P.sgemm(dA, dB, out, alpha=1.0, beta=0.0)
+    else:
+        s = {"conv": synth.ConvShape("c", 2, 64, 14, 14, 64, 3, 3, 1, 1),
+             "conv_tap": synth.ConvShape("t", 2, 64, 14, 14, 64, 3, 3, 1, 1),
+             "misaligned_pointwise": synth.ConvShape("p", 1, 64, 4, 4, 128, 1, 1, 1, 0)}[case]
+        x, w, b = synth.conv_inputs(s, seed=66, dist="normal", bias=True)
+        want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad, act="relu")
+        dx, dw, db = (misaligned(x) if case.startswith("mis") else dev(x)), dev(w), dev(b)
+        kw = dict(w_tap=P.filter_tap_copy(dw)) if case == "conv_tap" else {}
+        out = torch.empty(want.shape, dtype=torch.float32, device="cuda")
+
+        def call():
+            P.conv2d_fwd(dx, dw, db, out=out, stride=s.stride, pad=s.pad, act="relu", **kw)
+    call()                                  # on the default stream: it has its own scratch memory
+    torch.cuda.synchronize()
+    eager = P.get_last_tile()
+    assert eager.split_k > 1 or eager.raster >= 2, eager
+    fresh = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(fresh):
+        with torch.cuda.graph(graph, stream=fresh):
+            call()
+            captured = P.get_last_tile()
+    assert captured.split_k == 1 and captured.raster < 2, captured
+    for _ in range(3):
+        out.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert oracle.scaled_error(host(out), want, ab) <= 1e-5
+        call()                              # eager work in between
+        torch.cuda.synchronize()
+        assert P.get_last_tile().as_dict() == eager.as_dict()      # the choice for eager calls is unchanged
+        assert oracle.scaled_error(host(out), want, ab) <= 1e-5
