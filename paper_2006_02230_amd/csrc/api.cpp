@@ -188,13 +188,8 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
     auto launch = [&](hipError_t *e) {
         const Variant *v = find_variant(cfg);
         if (!v) return false;
-        // 32-bit byte offsets inside one workgroup's slice of A (bm rows) and of B (bk rows)
-        if ((uint64_t)v->bm * (uint64_t)K * 4 >= 0x7FFFFFF0ull) return false;
-        if ((uint64_t)v->bk * (uint64_t)N * 4 >= 0x7FFFFFF0ull) return false;
-        if ((uint64_t)v->bm * (uint64_t)N * 4 >= 0x7FFFFFF0ull) return false;   // and of C (bm rows)
-        uint64_t tiles = (uint64_t)((M + v->bm - 1) / v->bm) * (uint64_t)((N + v->bn - 1) / v->bn);
-        if (tiles >= 0x7FFFFFFFull || cfg.split_k > 65535 || cfg.raster >= 2) return false;
         SgemmProblem q{M, N, K, A, B, C, alpha, beta};
+        if (!sgemm_tile_in_range(q, v->bm, v->bn, v->bk) || cfg.split_k > 65535 || cfg.raster >= 2) return false;
         *e = v->sgemm(q, cfg.split_k < 1 ? 1 : cfg.split_k, cfg.raster, (hipStream_t)stream);
         return true;
     };
@@ -226,7 +221,6 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
         return POLYDL_ERR_UNSUPPORTED;
     if (!conv_in_range(N, C, H, W, K, R, S, stride, pad, P, Q)) return POLYDL_ERR_UNSUPPORTED;
     if (!on_gfx950()) return POLYDL_ERR_NO_DEVICE;
-    const int64_t Kg = (int64_t)C * R * S, CHW = (int64_t)C * H * W;
     ConvProblem q{N, C, H, W, K, R, S, stride, pad, (int)P, (int)Q, in, wt, bias, out, act, pre_act, arena};
     // a filter copy aligned to less than 16 bytes is ignored: every kernel then reads wt
     q.has_tap = wt_tap && !((uintptr_t)wt_tap & 15);
@@ -289,11 +283,7 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
         }
         const Variant *v = find_variant(cfg);
         if (!v) return POLYDL_ERR_UNSUPPORTED;
-        // a tile of bn pixels spans at most bn/PQ + 2 images; their offsets must fit 31 bits
-        const int64_t span = (v->bn / (P * Q) + 2) * CHW * 4;
-        const int64_t span_out = (v->bn / (P * Q) + 2) * (int64_t)K * P * Q * 4;
-        if (span >= 0x7FFFFFF0ll || span_out >= 0x7FFFFFF0ll || (int64_t)v->bm * Kg * 4 >= 0x7FFFFFF0ll)
-            return POLYDL_ERR_UNSUPPORTED;
+        if (!conv_tile_in_range(q, v->bm, v->bn)) return POLYDL_ERR_UNSUPPORTED;
         if (cfg.layout == 2) {
             if (!q.has_tap || !gather_tap_major_fits(q, v->bk)) return POLYDL_ERR_UNSUPPORTED;
             q.wt_tap = wt_tap;

@@ -49,6 +49,22 @@ inline bool gather_tap_major_fits(const ConvProblem &q, int bk)
     return RS >= 2 && RS <= 63 && q.C % bk == 0 && RS * q.C * q.C < (1ll << 32);
 }
 
+// The kernels' 32-bit byte offsets: inside one workgroup's slice of A (bm rows), of B (bk rows) and of C (bm
+// rows); inside the images a tile of bn pixels touches (at most bn/PQ + 2), read and written, and inside its
+// filter rows.  A launch outside these limits is refused; the picker looks for a tile inside them.
+constexpr int64_t kMaxOffset = 0x7FFFFFF0ll;
+inline bool sgemm_tile_in_range(const SgemmProblem &q, int bm, int bn, int bk)
+{
+    const int64_t tiles = ((int64_t)q.M + bm - 1) / bm * (((int64_t)q.N + bn - 1) / bn);
+    return (int64_t)bm * q.K * 4 < kMaxOffset && (int64_t)bk * q.N * 4 < kMaxOffset && (int64_t)bm * q.N * 4 < kMaxOffset &&
+           tiles < 0x7FFFFFFFll;
+}
+inline bool conv_tile_in_range(const ConvProblem &q, int bm, int bn)
+{
+    const int64_t images = bn / ((int64_t)q.P * q.Q) + 2, Kg = (int64_t)q.C * q.R * q.S;
+    return images * q.C * q.H * q.W * 4 < kMaxOffset && images * q.K * q.P * q.Q * 4 < kMaxOffset && bm * Kg * 4 < kMaxOffset;
+}
+
 // One compiled variant: its tile parameters and the launchers instantiated for it.
 struct Variant {
     int bm, bn, bk, wm, wn;

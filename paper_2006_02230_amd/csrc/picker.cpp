@@ -577,6 +577,7 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
         return c.cfg.bm * c.cfg.bn < b.cfg.bm * b.cfg.bn;
     };
     const ConvCandidate *b = nullptr;
+    bool b_fits = false;       // a variant that can be launched goes before every one that cannot
     for (const ConvCandidate &c : cands) {
         if (limits.no_scratch && (c.cfg.split_k > 1 || c.cfg.raster >= 2)) continue;
         if (!limits.pointwise && c.cfg.algo == 2) continue;
@@ -589,7 +590,11 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
         if (c.cfg.split_k > 1 && (tiles * c.cfg.split_k * c.cfg.bm * c.cfg.bn * 4 > kStaticPartialBytes / 2 ||
                                   tiles > kStaticCounterBytes / 4))
             continue;
-        if (!b || before(c, *b)) b = &c;
+        const bool fits = c.cfg.algo != 0 || conv_tile_in_range(q, c.cfg.bm, c.cfg.bn);
+        if (b && fits != b_fits ? fits : !b || before(c, *b)) {
+            b = &c;
+            b_fits = fits;
+        }
     }
     if (!b) return false;
     *best = b->cfg;
@@ -616,7 +621,7 @@ void sgemm_candidates(const SgemmProblem &q, std::vector<polydl_tile_cfg> *out)
 
 bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep, bool no_scratch)
 {
-    bool have = false;
+    bool have = false, best_fits = false;   // a variant that can be launched goes before every one that cannot
     polydl_model_report rep;
     std::vector<polydl_tile_cfg> cands;
     sgemm_candidates(q, &cands);
@@ -624,7 +629,13 @@ bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_repor
         if (no_scratch && c.split_k > 1) continue;
         model_sgemm(q, c, (c.bm / c.wm) * (c.bn / c.wn) * 64, &rep);
         if (c.raster == 1) rep.predicted_us *= 0.999;   // ties go to the XCD-aware order
-        if (!have || rep.predicted_us < best_rep->predicted_us) { *best = c; *best_rep = rep; have = true; }
+        const bool fits = sgemm_tile_in_range(q, c.bm, c.bn, c.bk);
+        if (have && fits != best_fits ? fits : !have || rep.predicted_us < best_rep->predicted_us) {
+            *best = c;
+            *best_rep = rep;
+            have = true;
+            best_fits = fits;
+        }
     }
     return have;
 }

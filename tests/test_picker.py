@@ -302,3 +302,24 @@ def test_candidates_with_the_filter_copy():
     assert P.model_conv2d(s33, t2).predicted_us < P.model_conv2d(s33, t0).predicted_us
     s2 = (32, 128, 56, 56, 128, 3, 3, 2, 1)
     assert P.model_conv2d(s2, t2).predicted_us == pytest.approx(P.model_conv2d(s2, t0).predicted_us)
+
+
+def launchable(M, N, K, c):
+    # the kernels' 31-bit byte offsets: bm rows of A and of C, bk rows of B
+    limit = 0x7FFFFFF0
+    return c.bm * K * 4 < limit and c.bm * N * 4 < limit and c.bk * N * 4 < limit
+
+
+@pytest.mark.parametrize("big", [2000000, 2100000, 2500000, 3000000, 4000000, 4200000, 8300000])
+def test_very_long_products_get_a_tile_that_can_be_launched(big):
+    for M, N in itertools.product((1, 64, 128, 256, 512, 1024), (1, 16, 64, 256, 512)):
+        for shape in ((M, N, big), (M, big, N), (big, M, N)):
+            tiles = [c for c in P.sgemm_candidates(*shape) if launchable(*shape, c)]
+            cfg, _ = P.pick_sgemm(*shape)
+            assert tiles and launchable(*shape, cfg), (shape, cfg)
+
+
+def test_very_long_reductions_of_a_convolution_get_a_tile_that_can_be_launched():
+    for C, K, N in itertools.product(((1 << 21) - 16, 1 << 21, 3 << 20, (1 << 22) - 16), (64, 128, 256, 512), (8, 256)):
+        cfg, _ = P.pick_conv2d((N, C, 1, 1, K, 1, 1, 1, 0))
+        assert cfg.algo != 0 or cfg.bm * C * 4 < 0x7FFFFFF0, (C, K, N, cfg)
