@@ -127,12 +127,12 @@ int polydl_conv2d_fwd_pre_act(int N, int C, int H, int W, int K, int R, int S, i
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): polydl_conv2d_fwd_act with the scratch memory of split
  * reductions taken from a fixed array inside the library's code object instead of from
- * hipMalloc.  Same arguments, same variant choice and bit for bit the same result as
- * polydl_conv2d_fwd_act.  The call makes no hipMalloc / hipFree and no call into an allocating
+ * hipMalloc.  Same arguments as polydl_conv2d_fwd_act, and bit for bit its result where the variant
+ * that call chooses fits the array (which it does but for large layers with long reductions); else
+ * the best variant that fits.  The call makes no hipMalloc / hipFree and no call into an allocating
  * library.  The array holds 64 MiB of partial tiles and 16384 arrival counters per device (each
- * device the library runs on keeps its copy until the process ends), which serves every variant the
- * library chooses; a forced variant that needs more returns POLYDL_ERR_SCRATCH_LIMIT with nothing
- * enqueued.  Every call on a device shares that device's
+ * device the library runs on keeps its copy until the process ends); a forced variant that needs more
+ * returns POLYDL_ERR_SCRATCH_LIMIT with nothing enqueued.  Every call on a device shares that device's
  * array, whatever its stream: the counters a call uses are cleared by a small kernel on its stream
  * first, and two calls that overlap in time on one device race on it -- keep them on one stream or
  * order them with events. */

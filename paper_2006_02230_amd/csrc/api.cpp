@@ -76,7 +76,7 @@ static bool g_have_override = false;
 static polydl_tile_cfg g_override;
 static polydl_tile_cfg g_last = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 // picks already made, keyed by the problem's dimensions (the ranking depends on nothing else)
-static std::map<std::array<int, 10>, polydl_tile_cfg> g_conv_plans;   // shape, and whether the input is activated on the way in
+static std::map<std::array<int, 10>, polydl_tile_cfg> g_conv_plans;   // shape; input activated on the way in, filter copy, fixed scratch memory
 static std::map<std::array<int, 3>, polydl_tile_cfg> g_sgemm_plans;
 static std::map<std::array<int, 9>, polydl_tile_cfg> g_bf16_plans;
 
@@ -233,7 +233,7 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
     }
     if (!forced) {
         const std::array<int, 10> key = {N, C, H, W, K, R, S, stride, pad,
-                                         (pre_act != POLYDL_ACT_NONE ? 1 : 0) | (q.has_tap ? 2 : 0)};
+                                         (pre_act != POLYDL_ACT_NONE ? 1 : 0) | (q.has_tap ? 2 : 0) | (arena ? 4 : 0)};
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_conv_plans.find(key);
         if (it != g_conv_plans.end()) {

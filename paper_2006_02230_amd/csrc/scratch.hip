@@ -88,7 +88,7 @@ hipError_t splitk_scratch(hipStream_t stream, const ScratchArena *arena, size_t 
         }
         *partials = arena->partials;
         *counters = arena->counters;
-        if (arena->clear_counters && tiles > 0) {
+        if (arena->clear_counters) {
             // the array is shared by every call on this device and keeps what the last one left:
             // a launch that did not run to its end may have left counts behind
             return launch_kernel(zero_words_kernel, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, stream,

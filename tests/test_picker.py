@@ -323,3 +323,10 @@ def test_very_long_reductions_of_a_convolution_get_a_tile_that_can_be_launched()
     for C, K, N in itertools.product(((1 << 21) - 16, 1 << 21, 3 << 20, (1 << 22) - 16), (64, 128, 256, 512), (8, 256)):
         cfg, _ = P.pick_conv2d((N, C, 1, 1, K, 1, 1, 1, 0))
         assert cfg.algo != 0 or cfg.bm * C * 4 < 0x7FFFFFF0, (C, K, N, cfg)
+
+
+@pytest.mark.parametrize("shape", [(32, 2048, 28, 28, 64, 3, 3, 1, 1), (32, 2048, 56, 56, 128, 3, 3, 1, 1)])
+def test_scratch_memory_does_not_keep_the_pick_from_the_best_gather_variant(shape):
+    # layers whose best variant needs tens to hundreds of MiB of partial tiles
+    best = min(P.model_conv2d(shape, c).predicted_us for c in P.conv_candidates(shape) if c.algo == 0)
+    assert P.pick_conv2d(shape)[1].predicted_us <= best * (1 + 1e-6)

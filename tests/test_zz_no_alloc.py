@@ -85,3 +85,22 @@ def test_a_variant_beyond_the_array_is_refused(P):
     P.set_tile_override(None)
     want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=1, pad=1, act="relu")
     assert oracle.scaled_error(got, want, ab) <= FP32_TOL
+
+
+def test_a_choice_beyond_the_array_is_replaced_by_one_that_fits(P):
+    import torch
+    P.set_tile_override(None)
+    s = synth.ConvShape("long", 32, 1024, 28, 28, 128, 3, 3, 1, 1)      # freely chosen: 73 MiB of partial tiles
+    x, w, b = synth.conv_inputs(s, seed=96, dist="normal", bias=True)
+    dx, dw, db = dev(x), dev(w), dev(b)
+
+    def partial_bytes():
+        t = P.get_last_tile()
+        return -(-s.K // t.bm) * -(-(s.N * 28 * 28) // t.bn) * t.split_k * t.bm * t.bn * 4 if t.split_k > 1 else 0
+    ref = P.conv2d_fwd(dx, dw, db, stride=1, pad=1, act="relu")
+    assert partial_bytes() > 64 << 20
+    out = torch.full_like(ref, float("nan"))
+    P.conv2d_fwd_noalloc(dx, dw, db, out, stride=1, pad=1, act="relu")
+    assert partial_bytes() <= 64 << 20
+    # another summation order of 9216 products: FP32_TOL of the terms' magnitudes, which are at least the result's
+    assert float((out - ref).norm() / ref.norm()) <= FP32_TOL
