@@ -284,7 +284,10 @@ struct BLoaderIm2col {
     {
         if constexpr (POINT) {
             const int kg = s_k0 + krow0 + J;
-            regs[SET][J] = buf_load1(rsrc, (uint32_t)pix_off | (FULL || kg < s_kend ? 0u : kOobOffset), (uint32_t)(kg * HW) * 4u);
+            if constexpr (FULL) regs[SET][J] = buf_load1(rsrc, (uint32_t)pix_off, (uint32_t)(kg * HW) * 4u);
+            else if constexpr (KTAIL)
+                regs[SET][J] = buf_load1(rsrc, (uint32_t)pix_off | (kg < s_kend ? 0u : kOobOffset), (uint32_t)(kg * HW) * 4u);
+            else regs[SET][J] = buf_load1(rsrc, (uint32_t)pix_off, (uint32_t)(min(kg, s_kend - 1) * HW) * 4u);
         } else if constexpr (TAPMAJOR) {
             regs[SET][J] = buf_load1(rsrc, s_off, s_koff + (uint32_t)(J * HW) * 4u);
         } else if constexpr (TABLE) {

@@ -50,7 +50,8 @@ __global__ __launch_bounds__(T::NT) void conv_kernel(ConvKArgs p)
 // tiles with fewer reduction parts win (128x128 split 2 where 64x64 with cut leftovers did).  Batch 32, us:
 // 128 -> 128 3x3 with the filter copy 66 -> 56, 512 -> 512 3x3 79 -> 71, 1024 -> 2048 1x1/2 64 -> 55, the stem
 // 89 -> 80, 512 -> 512 3x3 at 28x28 910 -> 690.
-template <class T, int MODE>
+// KTAIL: see BLoaderIm2col.
+template <class T, int MODE, bool KTAIL>
 __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvKArgs p)
 {
     __shared__ __attribute__((aligned(16))) u32x4 lds[SplitTile<T>::LDS_BYTES / 16];
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvK
     bool redo;
     {
         SplitALoader<T> al;
-        BLoaderIm2col<T, MODE, true> bl;
+        BLoaderIm2col<T, MODE, true, KTAIL> bl;
         bl.fill_table(p, tid, ktab);
         al.init(p.wt, tid, c.m0, p.K, p.Kg, p.Kg);
         bl.init(p, tid, c.n0);
@@ -164,14 +165,16 @@ static hipError_t conv_launch(const ConvProblem &q, int split_k, int raster, hip
                      : a.RS <= 31 ? GATHER_TAPS1 : a.RS <= 63 ? GATHER_TAPS2 : GATHER_ANY;
     if constexpr (T::SPLIT) {
         if (split_pays(q.K, a.RS, a.Kg)) {
-#define POLYDL_GO(MODE) return launch_kernel((conv_split_kernel<T, MODE>), grid, block, 0, stream, a)
+#define POLYDL_GO(MODE, KTAIL) return launch_kernel((conv_split_kernel<T, MODE, KTAIL>), grid, block, 0, stream, a)
             switch (mode) {
-            case GATHER_TAPMAJOR: POLYDL_GO(GATHER_TAPMAJOR);
-            case GATHER_POINT: POLYDL_GO(GATHER_POINT);
-            case GATHER_TABLE: POLYDL_GO(GATHER_TABLE);
-            case GATHER_TAPS1: POLYDL_GO(GATHER_TAPS1);
-            case GATHER_TAPS2: POLYDL_GO(GATHER_TAPS2);
-            default: POLYDL_GO(GATHER_ANY);
+            case GATHER_TAPMAJOR: POLYDL_GO(GATHER_TAPMAJOR, true);
+            case GATHER_POINT:
+                if (a.Kg % T::BK == 0) POLYDL_GO(GATHER_POINT, false);
+                POLYDL_GO(GATHER_POINT, true);
+            case GATHER_TABLE: POLYDL_GO(GATHER_TABLE, true);
+            case GATHER_TAPS1: POLYDL_GO(GATHER_TAPS1, true);
+            case GATHER_TAPS2: POLYDL_GO(GATHER_TAPS2, true);
+            default: POLYDL_GO(GATHER_ANY, true);
             }
 #undef POLYDL_GO
         }
