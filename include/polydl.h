@@ -91,9 +91,7 @@ typedef struct polydl_tile_cfg {
                          the output channels 32 at a time.  One variant (bm = wm = 32, bn = wn = 64,
                          bk = 0, split_k = 1, raster = 0, cb = 0); forced on any other problem the
                          call returns POLYDL_ERR_UNSUPPORTED */
-    int cb;           /* algo 1: input channels per stage, even, >= 2; 0 lets the library choose.
-                         algo 0: 2 = products on the float32 matrix instruction in every case (what the
-                         library chooses for short and small problems), 0 = as described below */
+    int cb;           /* algo 1: input channels per stage, even, >= 2; 0 lets the library choose */
 } polydl_tile_cfg;
 
 /* ---- forward convolution ------------------------------------------------------------------
@@ -164,12 +162,9 @@ int polydl_conv2d_fwd_tap(int N, int C, int H, int W, int K, int R, int S, int s
  * C[i][j] += sum_k A[i][k] * B[k][j]   (alpha = beta = 1, the reading taken of section "GEMM").
  * Row-major, A is M x K, B is K x N, C is M x N and is read and accumulated into.  K = 0 is
  * allowed (C is left as it is).  The variants with stage depth 16 and wave tiles up to 64 x 64 split both
- * operands into three bfloat16 parts each and sum six of their products in float32, unless their cb is 2.
- * Measured against 64 bits this has a third of the error of float32 products summed in sequence (mean and
- * largest error below them from reductions of 3 on); a single product is off by up to 2^-23.4 of itself
- * instead of 2^-24.  Tiles that meet values this cannot hold (infinities, NaN, numbers below 2^-110 with
- * bits under 2^-133) are computed from float32 products.  The library chooses float32 products for
- * reductions below 96 and for small products of up to 639 steps. */
+ * operands into three bfloat16 parts each and sum six of their products in float32 (smaller error against
+ * 64 bits than float32 products summed in sequence); tiles that meet values this cannot hold
+ * (infinities, NaN, numbers below 2^-110 with bits under 2^-133) are computed from float32 products. */
 int polydl_sgemm(int M, int N, int K, const float *A, const float *B, float *C, void *stream);
 
 /* The general form the text of section "GEMM" states, C = beta*C + alpha*A*B, with both scalars

@@ -189,7 +189,6 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
         const Variant *v = find_variant(cfg);
         if (!v) return false;
         SgemmProblem q{M, N, K, A, B, C, alpha, beta};
-        q.fp32_products = cfg.cb == kFp32Products;
         if (!sgemm_tile_in_range(q, v->bm, v->bn, v->bk) || cfg.split_k > 65535 || cfg.raster >= 2) return false;
         *e = v->sgemm(q, cfg.split_k < 1 ? 1 : cfg.split_k, cfg.raster, (hipStream_t)stream);
         return true;
@@ -259,7 +258,6 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
     };
     auto run = [&]() -> int {
         q.wt_tap = nullptr;    // set below for the variants that read the copy
-        q.fp32_products = cfg.algo == 0 && cfg.cb == kFp32Products;
         if (cfg.layout != 0 && !(cfg.layout == 2 && cfg.algo == 0)) return POLYDL_ERR_UNSUPPORTED;
         if (cfg.algo == 2) {
             if (!is_conv_point_cfg(cfg) || !conv_point_fits(q) || !point_aligned) return POLYDL_ERR_UNSUPPORTED;

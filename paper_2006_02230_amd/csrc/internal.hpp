@@ -25,7 +25,6 @@ struct SgemmProblem {
     float *C;
     float alpha = 1.f, beta = 1.f;   // C = beta*C + alpha*A*B
     const ScratchArena *arena = nullptr;
-    bool fp32_products = false;      // the variant's cb is kFp32Products
 };
 
 struct ConvProblem {
@@ -40,12 +39,7 @@ struct ConvProblem {
     // launchers read wt_tap instead of wt when it is set; the picker only looks at has_tap.
     const float *wt_tap = nullptr;
     bool has_tap = false;
-    bool fp32_products = false;            // gather kernel: the variant's cb is kFp32Products
 };
-
-// polydl_tile_cfg::cb of an algo 0 variant: products on the fp32 matrix instruction also where the tile would
-// form them from split operands.
-constexpr int kFp32Products = 2;
 
 // Whether the gather kernel can walk the reduction tap by tap (tile layout 2; bk = stage depth): 2..63 taps,
 // whole stages inside one tap, and C * (C*R*S) below 2^32 for its exact division by C.
@@ -187,18 +181,6 @@ constexpr bool split_pays(int K, int RS, int64_t Kg)
     return Kg >= (RS == 1 && K <= 64 ? kSplitMinReductionThin : kSplitMinReduction);
 }
 constexpr int split_lds_bytes(int bm, int bn) { return 2 * 6 * 16 * (bm + bn); }
-
-// Matrix products that are short or small are better off on the fp32 matrix instruction.  Below 96 reduction steps a
-// product is bound by its operands and its output and gains nothing (4096 x 4096 x 32: 21.8 us against 26.2, x 128: 36
-// against 29), and a sum of one or two products would be rounded worse than fp32 rounds it (largest error at
-// K = 1: 8.8e-8 of the product against 5.9e-8; from K = 3 on below fp32's).  Small products of up to 639 steps are
-// a launch's latency, to which the split adds its longer prologue (1024 x 1024 x 192: 9.9 us against 10.7); rows that
-// are no multiple of four floats long, which the fp32 kernels load dword by dword, move that line (1013 x 1507 x 240:
-// 15.1 us against 14.2).
-constexpr bool sgemm_split_pays(int M, int N, int K)
-{
-    return K >= 640 || (K >= 96 && (int64_t)M * N * K >= (N % 4 || K % 4 ? 200000000ll : 450000000ll));
-}
 
 // picker.cpp
 void reuse_bucket(int n, const double *ws, int nlevels, const double *sizes, double *levels, double *mem);

@@ -455,16 +455,14 @@ void model_sgemm(const SgemmProblem &q, const polydl_tile_cfg &cfg, int threads,
     // from the kernels' register counts (the eight-block wave tiles are held to 256 registers)
     c.max_waves_per_simd = (cfg.wm * cfg.wn > 64 * 64) ? 2 : ((cfg.wm * cfg.wn == 64 * 64) ? 3 : 4);
     double part_rate = 1.0, part_us = 0.4, parts_us = 0.0;
-    // (the fit holds for small products on the fp32 instruction too, where the latency of a launch decides)
-    const bool small = (double)q.M * q.N < (q.K >= 96 ? 3e6 : 1e6);
-    if (split_products(cfg.bk, cfg.wm, cfg.wn) && (sgemm_split_pays(q.M, q.N, q.K) || small)) {
+    if (split_products(cfg.bk, cfg.wm, cfg.wn)) {
         // Fitted to a sweep of 18 sizes from 256^3 to 4096^3, thin and long ones among them: the picks run
         // within 5 % of the sweep's best.  The smaller the wave tile, the more splitting and the more LDS
         // reads per matrix instruction; 512 threads split a 256x128 tile's operands once for twice the outputs.
         const int blocks = cfg.wm * cfg.wn / 1024;
         c.split = true;
         c.split_eff = blocks == 1 ? 0.343 : blocks == 2 ? 0.429 : threads == 512 ? 0.654 : 0.572;
-        c.wg_overhead_cycles = blocks == 4 ? 3000 : 1330;
+        c.wg_overhead_cycles = 1330;
         c.max_waves_per_simd = blocks == 1 ? 4 : blocks == 2 ? 3 : 2;
         c.lds_bytes = split_lds_bytes(cfg.bm, cfg.bn);
         // the last part of a tile adds all parts alone, at what one compute unit can read (84 GB/s)
@@ -609,18 +607,15 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
 void sgemm_candidates(const SgemmProblem &q, std::vector<polydl_tile_cfg> *out)
 {
     out->clear();
-    const bool pays = sgemm_split_pays(q.M, q.N, q.K);
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &v = kVariants[i];
         const long stages = ((long)q.K + v.bk - 1) / v.bk;
-        const bool split = split_products(v.bk, v.wm, v.wn);
-        if (v.threads == 512 && !pays) continue;   // pays through the splitting alone
         // long, skinny reductions (few output tiles) want many parts
         static const int kSgemmSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
         for (int sk : kSgemmSplits) {
             if (sk > stages) break;
             for (int raster = 0; raster < 2; ++raster)
-                out->push_back(polydl_tile_cfg{v.bm, v.bn, v.bk, v.wm, v.wn, sk, 0, raster, 0, split && !pays ? kFp32Products : 0});
+                out->push_back(polydl_tile_cfg{v.bm, v.bn, v.bk, v.wm, v.wn, sk, 0, raster, 0, 0});
         }
     }
 }

@@ -199,27 +199,3 @@ def test_argument_errors(P):
     assert P.lib.polydl_sgemm_ex(4, 4, 0, 2.0, z, z, 1.0, one, z) == 0   # K = 0, beta = 1: C unchanged, untouched
     assert P.lib.polydl_sgemm_ex(0, 4, 4, 1.0, one, one, 1.0, one, z) == -2
     assert P.lib.polydl_sgemm_ex(4, 4, 4, 1.0, one, z, 1.0, one, z) == -1
-
-
-@pytest.mark.parametrize("M,N,K", SHAPES + [(257, 129, 95), (64, 200, 639)])
-def test_float32_products_forced(P, M, N, K):
-    # cb = 2: the fp32 matrix instruction on the tiles that else split their operands; one product is rounded once
-    A, B, C0 = synth.sgemm_inputs(M, N, K, seed=M + N + K, c0="random")
-    want, ab = oracle.gemm(A, B, C0)
-    for v in P.variants(1):
-        if v.bk != 16 or v.wm * v.wn > 64 * 64:
-            continue
-        for split_k, raster in ((1, 0), (3, 1)):
-            v.split_k, v.raster, v.cb = split_k, raster, 2
-            P.set_tile_override(v)
-            assert oracle.scaled_error(run_sgemm(P, A, B, C0), want, ab) <= FP32_TOL, v
-            assert P.get_last_tile().cb == 2
-            if K == 1:
-                assert np.array_equal(run_sgemm(P, A, B, np.zeros_like(C0)), A * B), v
-    P.set_tile_override(None)
-
-
-@pytest.mark.parametrize("M,N", [(1, 1), (64, 64), (1000, 700), (2048, 1024)])
-def test_one_product_is_rounded_once(P, M, N):
-    A, B, _ = synth.sgemm_inputs(M, N, 1, seed=77)
-    assert np.array_equal(run_sgemm(P, A, B, np.zeros((M, N), np.float32)), A * B)

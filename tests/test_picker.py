@@ -330,16 +330,3 @@ def test_scratch_memory_does_not_keep_the_pick_from_the_best_gather_variant(shap
     # layers whose best variant needs tens to hundreds of MiB of partial tiles
     best = min(P.model_conv2d(shape, c).predicted_us for c in P.conv_candidates(shape) if c.algo == 0)
     assert P.pick_conv2d(shape)[1].predicted_us <= best * (1 + 1e-6)
-
-
-def test_short_and_small_products_stay_on_the_fp32_instruction():
-    # cb = 2 marks the form: reductions below 96, and up to 639 for products of less than 4.5e8
-    # multiply-adds (2e8 where rows are no whole vectors)
-    splits = lambda c: c.bk == 16 and c.wm * c.wn <= 64 * 64
-    for M, N, K, fp32 in ((4096, 4096, 1, True), (4096, 4096, 95, True), (4096, 4096, 96, False), (1024, 1024, 192, True),
-                          (1024, 1024, 428, True), (1024, 1024, 430, False), (64, 64, 639, True), (64, 64, 640, False), (1013, 1507, 240, False),
-                          (500, 1507, 240, True)):
-        cfg, _ = P.pick_sgemm(M, N, K)
-        assert not splits(cfg) or (cfg.cb == 2) == fp32, (M, N, K, cfg)
-        for c in P.sgemm_candidates(M, N, K):
-            assert c.cb == (2 if fp32 and splits(c) else 0)
