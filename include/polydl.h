@@ -162,9 +162,11 @@ int polydl_conv2d_fwd_tap(int N, int C, int H, int W, int K, int R, int S, int s
  * C[i][j] += sum_k A[i][k] * B[k][j]   (alpha = beta = 1, the reading taken of section "GEMM").
  * Row-major, A is M x K, B is K x N, C is M x N and is read and accumulated into.  K = 0 is
  * allowed (C is left as it is).  The variants with stage depth 16 and wave tiles up to 64 x 64 split both
- * operands into three bfloat16 parts each and sum six of their products in float32 (smaller error against
- * 64 bits than float32 products summed in sequence); tiles that meet values this cannot hold
- * (infinities, NaN, numbers below 2^-110 with bits under 2^-133) are computed from float32 products. */
+ * operands into three bfloat16 parts each and sum six of their products in float32 (K >= 3).  Measured
+ * against 64 bits the error is a third of that of float32 products summed in sequence at K = 16 and more;
+ * a product that stands alone in its sum is off by up to 2^-23.4 of itself instead of 2^-24.  Tiles that meet
+ * values this cannot hold (infinities, NaN, numbers below 2^-110 with bits under 2^-133) are computed from
+ * float32 products. */
 int polydl_sgemm(int M, int N, int K, const float *A, const float *B, float *C, void *stream);
 
 /* The general form the text of section "GEMM" states, C = beta*C + alpha*A*B, with both scalars

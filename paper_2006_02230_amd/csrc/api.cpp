@@ -77,7 +77,7 @@ static polydl_tile_cfg g_override;
 static polydl_tile_cfg g_last = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 // picks already made, keyed by the problem's dimensions (the ranking depends on nothing else)
 static std::map<std::array<int, 10>, polydl_tile_cfg> g_conv_plans;   // shape; input activated on the way in, filter copy, fixed scratch memory
-static std::map<std::array<int, 3>, polydl_tile_cfg> g_sgemm_plans;
+static std::map<std::array<int, 4>, polydl_tile_cfg> g_sgemm_plans;   // M, N, K, whether C is read
 static std::map<std::array<int, 9>, polydl_tile_cfg> g_bf16_plans;
 
 static const Variant *find_variant(const polydl_tile_cfg &c)
@@ -173,13 +173,13 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
         cfg = g_override;
         if (!g_have_override) {
             picked = true;
-            const std::array<int, 3> key = {M, N, K};
+            const std::array<int, 4> key = {M, N, K, beta != 0.f};
             auto it = g_sgemm_plans.find(key);
             if (it != g_sgemm_plans.end()) {
                 cfg = it->second;
             } else {
                 polydl_model_report rep;
-                SgemmProblem pq{M, N, K, A, B, C};
+                SgemmProblem pq{M, N, K, A, B, C, alpha, beta};
                 if (!pick_sgemm(pq, &cfg, &rep)) return POLYDL_ERR_UNSUPPORTED;
                 g_sgemm_plans[key] = cfg;
             }
@@ -199,7 +199,7 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
         // the stream is being captured and has no scratch memory for a split reduction yet: the best
         // variant that needs none (not cached)
         polydl_model_report rep;
-        SgemmProblem pq{M, N, K, A, B, C};
+        SgemmProblem pq{M, N, K, A, B, C, alpha, beta};
         if (!pick_sgemm(pq, &cfg, &rep, true) || !launch(&e)) return POLYDL_ERR_UNSUPPORTED;
     }
     if (e != hipSuccess) return launch_failed(e);

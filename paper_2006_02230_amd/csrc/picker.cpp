@@ -122,6 +122,8 @@ struct Cand {
     // reduction steps instead of eight of 64; split_eff is the matrix-core share of their loop.
     bool split = false;
     double split_eff = 0.4;
+    double split_overhead = 0;   // cycles of a workgroup's prologue and epilogue (SGEMM)
+    double read_overhead = 0;    // and of an epilogue that reads C first
     double tail_us = 4.0;        // leftover tiles cut into parts: the hand-over
     double sum_us = 0;           // split reduction: the last part of a tile adds all parts alone
     bool tail_split = false;     // the kernel cuts the leftover tiles of an unsplit grid (tail_split())
@@ -154,10 +156,10 @@ static void model(const Shape &s, const Cand &c, polydl_model_report *r)
     eff *= c.steps_per_stage / (c.steps_per_stage + 1.0 / (mb * nb));
     if (resident < 2) eff *= 0.72;
     else if (resident * mb * nb < 4) eff *= 0.85;   // two small waves leave gaps a third would fill
-    if (c.split) eff = c.split_eff * (resident < 2 ? 0.74 : 1.0);
+    if (c.split) eff = c.split_eff * (resident < 2 ? 0.666 : 1.0);
     // setup plus an epilogue that grows with the accumulators a lane has to store
-    const double overhead = c.wg_overhead_cycles * (0.3 + 0.7 * mb * nb / 2.0);
-    const double wave_cycles = steps * mb * nb * step_cycles / eff + overhead;
+    const double overhead = c.split ? c.split_overhead : c.wg_overhead_cycles * (0.3 + 0.7 * mb * nb / 2.0);
+    const double wave_cycles = steps * mb * nb * step_cycles / eff + overhead + c.read_overhead;
     double mfma_us = waves_on_busiest_simd * wave_cycles / kClockHz * 1e6;
     if (c.rounds) {
         // Resident workgroups per CU, from registers (512 per SIMD lane, at most 8 waves per SIMD)
@@ -454,19 +456,25 @@ void model_sgemm(const SgemmProblem &q, const polydl_tile_cfg &cfg, int threads,
     c.kernel_fixed_us = 6.0;
     // from the kernels' register counts (the eight-block wave tiles are held to 256 registers)
     c.max_waves_per_simd = (cfg.wm * cfg.wn > 64 * 64) ? 2 : ((cfg.wm * cfg.wn == 64 * 64) ? 3 : 4);
+    if (q.beta != 0.f && cfg.wm * cfg.wn >= 64 * 64) c.read_overhead = cfg.wm * cfg.wn > 64 * 64 ? 8844 : 7789;
     double part_rate = 1.0, part_us = 0.4, parts_us = 0.0;
-    if (split_products(cfg.bk, cfg.wm, cfg.wn)) {
-        // Fitted to a sweep of 18 sizes from 256^3 to 4096^3, thin and long ones among them: the picks run
-        // within 5 % of the sweep's best.  The smaller the wave tile, the more splitting and the more LDS
-        // reads per matrix instruction; 512 threads split a 256x128 tile's operands once for twice the outputs.
+    if (split_products(cfg.bk, cfg.wm, cfg.wn) && q.K >= kSgemmSplitMinReduction) {
+        // Fitted to sweeps of 1142 sizes, 64 .. 4096 by 64 .. 4096 by 8 .. 32768, odd ones and accumulated ones among them:
+        // the picks run within 1 % of the sweep's best on average, 24 % at worst (64x64x8).  The smaller the wave tile, the more
+        // splitting and the more LDS reads per matrix instruction; 512 threads split a 256x128 tile's operands
+        // once for twice the outputs.  Large tiles pay for their epilogue, most of all where C is read: few
+        // workgroups then wait for row after row (1418x747x39, accumulated: 64x64 10.6 us, 128x128 22).
         const int blocks = cfg.wm * cfg.wn / 1024;
+        const int k = blocks == 1 ? 0 : blocks == 2 ? 1 : threads == 512 ? 3 : 2;
+        static const double kEff[] = {0.339, 0.449, 0.595, 0.648}, kStore[] = {1012, 1942, 9413, 4443}, kRead[] = {2110, 5074, 12511, 10714};
         c.split = true;
-        c.split_eff = blocks == 1 ? 0.343 : blocks == 2 ? 0.429 : threads == 512 ? 0.654 : 0.572;
-        c.wg_overhead_cycles = 1330;
+        c.split_eff = kEff[k];
+        c.split_overhead = kStore[k];
+        c.read_overhead = q.beta != 0.f ? kRead[k] : 0;
         c.max_waves_per_simd = blocks == 1 ? 4 : blocks == 2 ? 3 : 2;
         c.lds_bytes = split_lds_bytes(cfg.bm, cfg.bn);
-        // the last part of a tile adds all parts alone, at what one compute unit can read (84 GB/s)
-        part_rate = 0.36; part_us = 0.2; parts_us = 1.85 + cfg.split_k * (double)cfg.bm * cfg.bn * 4 / 84.0 * 1e-3;
+        // the last part of a tile adds all parts alone, at what one compute unit can read (60 GB/s)
+        part_rate = 0.19; part_us = 0.215; parts_us = 1.36 + cfg.split_k * (double)cfg.bm * cfg.bn * 4 / 59.6 * 1e-3;
     }
     model(s, c, r);
     if (cfg.split_k > 1) {   // every part writes its tile to scratch once, the last one reads them all back
@@ -610,6 +618,7 @@ void sgemm_candidates(const SgemmProblem &q, std::vector<polydl_tile_cfg> *out)
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &v = kVariants[i];
         const long stages = ((long)q.K + v.bk - 1) / v.bk;
+        if (v.threads == 512 && q.K < kSgemmSplitMinReduction) continue;   // pays through the splitting alone
         // long, skinny reductions (few output tiles) want many parts
         static const int kSgemmSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
         for (int sk : kSgemmSplits) {
@@ -622,7 +631,8 @@ void sgemm_candidates(const SgemmProblem &q, std::vector<polydl_tile_cfg> *out)
 
 bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_report *best_rep, bool no_scratch)
 {
-    bool have = false, best_fits = false;   // a variant that can be launched goes before every one that cannot
+    bool have = false;
+    int best_order = 0;
     polydl_model_report rep;
     std::vector<polydl_tile_cfg> cands;
     sgemm_candidates(q, &cands);
@@ -630,12 +640,15 @@ bool pick_sgemm(const SgemmProblem &q, polydl_tile_cfg *best, polydl_model_repor
         if (no_scratch && c.split_k > 1) continue;
         model_sgemm(q, c, (c.bm / c.wm) * (c.bn / c.wn) * 64, &rep);
         if (c.raster == 1) rep.predicted_us *= 0.999;   // ties go to the XCD-aware order
-        const bool fits = sgemm_tile_in_range(q, c.bm, c.bn, c.bk);
-        if (have && fits != best_fits ? fits : !have || rep.predicted_us < best_rep->predicted_us) {
+        // a variant that can be launched goes before every one that cannot, and the smaller error of split
+        // operands before the 128x256 tile's speed on short products (4096x4096x32: 21 us against 24.5)
+        const int order = 2 * sgemm_tile_in_range(q, c.bm, c.bn, c.bk) +
+                          (split_products(c.bk, c.wm, c.wn) && q.K >= kSgemmSplitMinReduction);
+        if (have && order != best_order ? order > best_order : !have || rep.predicted_us < best_rep->predicted_us) {
             *best = c;
             *best_rep = rep;
             have = true;
-            best_fits = fits;
+            best_order = order;
         }
     }
     return have;

@@ -209,9 +209,11 @@ static hipError_t sgemm_launch(const SgemmProblem &q, int split_k, int raster, h
     dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)split_k), block(T::NT);
     const bool cvec = (q.N % T::NB == 0) && ((uintptr_t)q.C % 16 == 0);
     if constexpr (T::SPLIT) {
-        if (cvec) return launch_kernel((sgemm_split_kernel<T, true>), grid, block, 0, stream, a);
-        return launch_kernel((sgemm_split_kernel<T, false>), grid, block, 0, stream, a);
-    } else {
+        if (q.K >= kSgemmSplitMinReduction) {
+            if (cvec) return launch_kernel((sgemm_split_kernel<T, true>), grid, block, 0, stream, a);
+            return launch_kernel((sgemm_split_kernel<T, false>), grid, block, 0, stream, a);
+        }
+    }
     const bool avec = (q.K % 4 == 0) && ((uintptr_t)q.A % 16 == 0);
     const bool bvec = (q.N % 4 == 0) && ((uintptr_t)q.B % 16 == 0);
 #define POLYDL_GO(AV, BV, CV) le = launch_kernel((sgemm_kernel<T, AV, BV, CV>), grid, block, 0, stream, a)
@@ -225,7 +227,6 @@ static hipError_t sgemm_launch(const SgemmProblem &q, int split_k, int raster, h
     else POLYDL_GO(1, 1, false);
 #undef POLYDL_GO
     return le;
-    }
 }
 
 #define POLYDL_DEFINE_SGEMM(BM, BN, BK, WM, WN)                                                            \

@@ -199,3 +199,12 @@ def test_argument_errors(P):
     assert P.lib.polydl_sgemm_ex(4, 4, 0, 2.0, z, z, 1.0, one, z) == 0   # K = 0, beta = 1: C unchanged, untouched
     assert P.lib.polydl_sgemm_ex(0, 4, 4, 1.0, one, one, 1.0, one, z) == -2
     assert P.lib.polydl_sgemm_ex(4, 4, 4, 1.0, one, z, 1.0, one, z) == -1
+
+
+@pytest.mark.parametrize("M,N", [(1, 1), (64, 64), (1000, 700), (2048, 1024)])
+def test_one_product_is_rounded_once(P, M, N):
+    A, B, _ = synth.sgemm_inputs(M, N, 1, seed=77)
+    for v in [None] + P.variants(1):
+        P.set_tile_override(v)
+        assert np.array_equal(run_sgemm(P, A, B, np.zeros((M, N), np.float32)), A * B), v
+    P.set_tile_override(None)

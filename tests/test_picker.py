@@ -330,3 +330,18 @@ def test_scratch_memory_does_not_keep_the_pick_from_the_best_gather_variant(shap
     # layers whose best variant needs tens to hundreds of MiB of partial tiles
     best = min(P.model_conv2d(shape, c).predicted_us for c in P.conv_candidates(shape) if c.algo == 0)
     assert P.pick_conv2d(shape)[1].predicted_us <= best * (1 + 1e-6)
+
+
+@pytest.mark.parametrize("M,N,K", [(1418, 747, 39), (1128, 3015, 33), (3515, 3099, 35), (1024, 4096, 48)])
+def test_short_accumulated_products_stay_on_small_tiles(M, N, K):
+    # C is read row by row in the epilogue: few large tiles wait for it (1418x747x39: 64x64 10.6 us, 128x128 22)
+    cfg, _ = P.pick_sgemm(M, N, K)
+    assert cfg.bm * cfg.bn <= 64 * 128, cfg
+
+
+def test_products_of_three_terms_and_more_split_their_operands():
+    # smaller error than the fp32 instruction's, whatever the size; one and two terms keep that instruction
+    for M, N in itertools.product((1, 64, 1000, 4096), (1, 64, 1000, 4096)):
+        for K in (3, 8, 32, 500, 4096):
+            c, _ = P.pick_sgemm(M, N, K)
+            assert c.bk == 16 and c.wm * c.wn <= 64 * 64, (M, N, K, c)
