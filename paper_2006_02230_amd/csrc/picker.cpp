@@ -576,12 +576,22 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
 {
     std::vector<ConvCandidate> cands;
     conv_candidates(q, &cands);
+    auto tiles = [&](const ConvCandidate &c) {
+        return std::ceil((double)q.K / c.cfg.bm) * std::ceil((double)q.N * q.P * q.Q / c.cfg.bn);
+    };
+    auto part_bytes = [&](const ConvCandidate &c) {
+        return c.cfg.split_k > 1 ? tiles(c) * c.cfg.split_k * c.cfg.bm * c.cfg.bn * 4 : 0.0;
+    };
+    // Parts of more than 32 MiB leave the caches, and splitting that far gains less than predicted: where it
+    // was predicted 1 .. 4 % faster it was 5 .. 14 % slower (116 -> 317 3x3 on 28x28, batch 17: 78 us whole, 91 in three
+    // parts), where 5 % and more, faster.
+    auto rank = [&](const ConvCandidate &c) { return c.rep.predicted_us * (part_bytes(c) > 32 * 1024 * 1024 ? 1.05 : 1.0); };
     // Equal predictions are candidates held by the same data floor: of those the smaller workgroup
     // tile goes first (more workgroups, so more independent loads in flight and a shorter last round).
-    auto before = [](const ConvCandidate &c, const ConvCandidate &b) {
-        const double tie = 1e-6 * b.rep.predicted_us;
-        if (c.rep.predicted_us < b.rep.predicted_us - tie) return true;
-        if (c.rep.predicted_us > b.rep.predicted_us + tie) return false;
+    auto before = [&](const ConvCandidate &c, const ConvCandidate &b) {
+        const double c_us = rank(c), b_us = rank(b), tie = 1e-6 * b_us;
+        if (c_us < b_us - tie) return true;
+        if (c_us > b_us + tie) return false;
         return c.cfg.bm * c.cfg.bn < b.cfg.bm * b.cfg.bn;
     };
     const ConvCandidate *b = nullptr;
@@ -595,10 +605,7 @@ bool pick_conv(const ConvProblem &q, polydl_tile_cfg *best, polydl_model_report 
         // a call that brings its own scratch memory gets the best variant that fits it.  (Held to 32 MiB, as
         // other calls once were, 2048 -> 64 channels 3x3 on 28x28, batch 32, took 635 us instead of 467, and
         // 2048 -> 128 on 56x56 3312 instead of 2860.)
-        if (q.arena && c.cfg.split_k > 1) {
-            const double tiles = std::ceil((double)q.K / c.cfg.bm) * std::ceil((double)q.N * q.P * q.Q / c.cfg.bn);
-            if (tiles * c.cfg.split_k * c.cfg.bm * c.cfg.bn * 4 > q.arena->partial_bytes || tiles > q.arena->ncounters) continue;
-        }
+        if (q.arena && c.cfg.split_k > 1 && (part_bytes(c) > q.arena->partial_bytes || tiles(c) > q.arena->ncounters)) continue;
         const bool fits = c.cfg.algo != 0 || conv_tile_in_range(q, c.cfg.bm, c.cfg.bn);
         if (b && fits != b_fits ? fits : !b || before(c, *b)) {
             b = &c;
