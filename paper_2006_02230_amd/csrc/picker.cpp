@@ -354,33 +354,47 @@ void model_conv(const ConvProblem &q, const polydl_tile_cfg &cfg, int threads, i
         c.tail_split = cfg.raster >= 2;
         const bool split = split_products(cfg.bk, cfg.wm, cfg.wn) && split_pays(q.K, q.R * q.S, (int64_t)q.C * q.R * q.S);
         double point_gather = 0.1, tap_gather = mbn == 11 ? kTapMajorGather11 : (mbn == 21 ? kTapMajorGather21 : kTapMajorGather);
+        double table_gather = 1, taps_gather = 1, taps_lat = 1;   // the split kernels': row table, and KCRS order
         if (split) {
             // fitted to sweeps of 97 problems (the suite at batch 1 .. 64 and the three held-out sets, with and without
             // the filter copy, reductions of 128 and more; small batches weighted): the picks run within 1.2 % of
-            // the sweep's best on average, 8 % at worst
+            // the sweep's best on average, 8 % at worst.  The factors of short reductions (row table,
+            // tiles of one and two blocks a wave) and of layers of at most 64 output channels in the KCRS order come
+            // from 339 more layers of 16 .. 1024 channels on 7x7 .. 112x112 at batch 1 .. 64: the fit had too few of
+            // those and left the reduction of 128 -> 64 3x3 on 56x56, batch 8, whole (56.5 us; in three parts 46.9).
+            // For the others the same factors gained as much as they lost.
             c.split = true;
             c.lds_bytes = split_lds_bytes(cfg.bm, cfg.bn);
             point_gather = 0.29;
+            if (mbn != 22) table_gather = 0.72;
             c.tail_us = 9.3;
             c.split_c1 = 0.078;
             c.sum_us = c.split_k * (double)cfg.bm * cfg.bn * 4 / (mbn == 11 ? 67.0 : 60.6) * 1e-3;
             switch (mbn == 22 && threads == 512 ? 0 : mbn) {
-            case 11: c.regs = 128; c.eff_sat = 0.405; c.t_lat_us = 0.333; c.t_round_us = 2.07; c.gather_cycles = 43.4; tap_gather = 0.58; c.split_c0 = 0.85; c.tail_us = 4.8; break;
-            case 12: c.regs = 168; c.eff_sat = 0.476; c.t_lat_us = 0.541; c.t_round_us = 2.07; c.gather_cycles = 46.9; tap_gather = 0.325; c.split_c0 = 2.17; break;
-            case 21: c.regs = 168; c.eff_sat = 0.50; c.t_lat_us = 0.489; c.t_round_us = 2.24; c.gather_cycles = 36.3; tap_gather = 0.845; c.split_c0 = 2.37; break;
-            case 22: c.regs = 256; c.eff_sat = 0.615; c.t_lat_us = 0.772; c.t_round_us = 2.84; c.gather_cycles = 38.5; tap_gather = 0.488; c.split_c0 = 2.44; break;
-            default: c.regs = 256; c.eff_sat = 0.659; c.t_lat_us = 0.361; c.t_round_us = 6.5; c.gather_cycles = 67.3; tap_gather = 0.99; c.split_c0 = 0.45; break;
+            case 11: c.regs = 128; taps_gather = 1.08; taps_lat = 0.99; c.eff_sat = 0.405; c.t_lat_us = 0.333; c.t_round_us = 2.07; c.gather_cycles = 43.4; tap_gather = 0.58; c.split_c0 = 0.85; c.tail_us = 4.8; break;
+            case 12: c.regs = 168; taps_gather = 1.02; taps_lat = 1.34; c.eff_sat = 0.476; c.t_lat_us = 0.541; c.t_round_us = 2.07; c.gather_cycles = 46.9; tap_gather = 0.325; c.split_c0 = 2.17; break;
+            case 21: c.regs = 168; taps_gather = 1.16; taps_lat = 1.07; c.eff_sat = 0.50; c.t_lat_us = 0.489; c.t_round_us = 2.24; c.gather_cycles = 36.3; tap_gather = 0.845; c.split_c0 = 2.37; break;
+            case 22: c.regs = 256; taps_gather = 1.24; taps_lat = 1.16; c.eff_sat = 0.615; c.t_lat_us = 0.772; c.t_round_us = 2.84; c.gather_cycles = 38.5; tap_gather = 0.488; c.split_c0 = 2.44; break;
+            default: c.regs = 256; taps_gather = 0.89; taps_lat = 0.98; c.eff_sat = 0.659; c.t_lat_us = 0.361; c.t_round_us = 6.5; c.gather_cycles = 67.3; tap_gather = 0.99; c.split_c0 = 0.45; break;
             }
         }
         // 1x1 filters without padding: the channel rides in the instruction's uniform offset and the
         // lanes read a contiguous run of pixels (stride 1); with a stride the lanes' addresses are
         // spread over several times the cache lines and the loads cost what gathered ones do
-        if (point && q.stride == 1) c.gather_cycles *= point_gather;
-        // tap by tap over the [K][R][S][C] filter copy: one tap per stage, so the validity bit and
-        // the distance are worked out per stage and not per element
-        // (with a stride the lanes' addresses spread over twice the cache lines and the cost of
-        // the load is in the memory pipeline, which the cheaper addressing does not touch)
-        if (cfg.layout == 2 && q.stride == 1) c.gather_cycles *= tap_gather;
+        if (point) {
+            if (q.stride == 1) c.gather_cycles *= point_gather;
+        } else if (cfg.layout == 2 && q.stride == 1) {
+            // tap by tap over the [K][R][S][C] filter copy: one tap per stage, so the validity bit and
+            // the distance are worked out per stage and not per element
+            // (with a stride the lanes' addresses spread over twice the cache lines and the cost of
+            // the load is in the memory pipeline, which the cheaper addressing does not touch)
+            c.gather_cycles *= tap_gather;
+        } else if (split && gather_table_fits(q, cfg.bk)) {
+            c.gather_cycles *= table_gather;
+        } else if (q.K <= 64) {   // one row of tiles
+            c.gather_cycles *= taps_gather;
+            c.t_lat_us *= taps_lat;
+        }
         // and splitting the reduction gains less there than the fit to mostly unstrided layers says: 128 -> 128 3x3/2
         // on 56x56, batch 32, tile 128x128: two parts 66.9 us, whole tiles 60.1 (stride 1, 28x28: 56.0 and 59.4)
         if (split && cfg.layout == 2 && q.stride > 1) c.split_c0 += 3;
