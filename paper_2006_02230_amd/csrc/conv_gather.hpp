@@ -67,8 +67,8 @@ __device__ __forceinline__ uint32_t outside_bits(int lo, int hi, int n)
 //               stage shares one tap: its validity bit and its distance are found once per stage,
 //               not per element, and the channel rides in the uniform offset.  In that copy the
 //               filter rows are contiguous in the walked order, so they load as in a plain GEMM.
-//  GATHER_TABLE  filters of at most 63 taps with a short reduction (C*R*S + 2 stages at most kTableRows
-//               rows; the stem layer): as GATHER_TAPS2, but the (c, r, s) split of a reduction row is
+//  GATHER_TABLE  filters of at most 63 taps with a short reduction (gather_table_fits(); the stem
+//               layer): as GATHER_TAPS2, but the (c, r, s) split of a reduction row is
 //               not redone by every wave for every element.  The workgroup writes (distance of the
 //               row's tap and channel in bytes, tap number) of every row into LDS once; a load then
 //               reads its row's entry (one address per stage, constant offsets), adds the distance
@@ -77,7 +77,6 @@ __device__ __forceinline__ uint32_t outside_bits(int lo, int hi, int n)
 //               scalar unit of a compute unit serves four SIMDs, and at 18 scalar instructions per
 //               matrix instruction (the stem layer) it, not the matrix cores, set the pace.
 enum { GATHER_ANY = 0, GATHER_POINT = 1, GATHER_TAPS1 = 2, GATHER_TAPS2 = 3, GATHER_TAPMAJOR = 4, GATHER_TABLE = 5 };
-constexpr int kTableRows = 512;   // 4 KB of LDS
 
 
 // SPLIT: the stage goes to LDS as three bfloat16 planes (split_core.hpp), so a thread's rows of a stage are

@@ -1,4 +1,4 @@
-// Forward convolution as an implicit GEMM on the fp32 matrix cores.
+// Forward convolution as an implicit GEMM on the matrix cores, fp32 or bfloat16 with split operands.
 //
 // The paper's convolution nest (figure "The 2-D Convolution code") contains a GEMM in its three
 // inner loops; here the whole nest is one GEMM  out[K][N*P*Q] = wt[K][C*R*S] * X[C*R*S][N*P*Q]
@@ -156,9 +156,7 @@ static hipError_t conv_launch(const ConvProblem &q, int split_k, int raster, hip
         if (!gather_tap_major_fits(q, T::BK) || ((uintptr_t)q.wt_tap & 15)) return hipErrorInvalidValue;
         a.wt = q.wt_tap;
     }
-    // the table covers every row a load can ask for: the reduction rounded up to whole stages and the
-    // two stages the loads run ahead
-    const bool table = a.RS <= 63 && (stages + 2) * T::BK <= kTableRows;
+    const bool table = gather_table_fits(q, T::BK);
     const int mode = (q.R == 1 && q.S == 1 && q.pad == 0) ? GATHER_POINT
                      : tapmajor ? GATHER_TAPMAJOR
                      : table ? GATHER_TABLE

@@ -16,8 +16,8 @@
 // No barrier after the filter is in LDS; waves never wait for each other.
 //
 // Bound: the bytes written.  With the fp32 instruction the matrix cores needed 21 us of 40 for 64 -> 256 channels
-// at 56x56, batch 32, and hardly overlapped with the stores; the split products need 8: 39.8 -> 31.2 us
-// (44.9 -> 37.8 with operands and outputs that are not in the caches), batch 64 69 -> 58.
+// at 56x56, batch 32, and hardly overlapped with the stores; the split products need 8: 40 -> 32 us back to
+// back on the same tensors (44.9 -> 37.8 with operands and outputs that are not in the caches), batch 64 69 -> 58.
 #include <hip/hip_runtime.h>
 #include "gemm_core.hpp"
 #include "internal.hpp"

@@ -95,11 +95,11 @@ struct Tile {
     static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN;
     static constexpr int NT = WAVES_M * WAVES_N * 64;
     static constexpr int MB = WM / 32, NB = WN / 32;  // 32x32 MFMA blocks per wave tile
-    // Waves per SIMD the SGEMM kernel's register allocation is held to: the eight-block wave tiles need 128
+    // Waves per SIMD the fp32 SGEMM kernel's register allocation is held to: the eight-block wave tiles need 128
     // accumulator registers and end a handful of registers above the 256 that still let two
     // waves share a SIMD; bounded, the few excess values (epilogue addresses) go to scratch.
     static constexpr int MIN_WAVES = MB * NB >= 8 ? 2 : 1;
-    // where SGEMM runs the split stage schedule (gemm_stage): two chunks per stage, two blocks and more
+    // where the fp32 SGEMM kernel runs the split stage schedule (gemm_stage): two chunks per stage, two blocks and more
     static constexpr bool SPLIT_STAGE = BK == 16 && MB * NB >= 2;
     // tiles whose products are formed on the bfloat16 matrix cores from three-way split operands
     // (split_core.hpp): two accumulator sets of a wave tile of eight blocks would not fit the registers
@@ -265,8 +265,9 @@ struct BLoaderRows {
 // Two schedules.  The plain one: per chunk of eight reduction rows read the fragments, multiply;
 // copy the next stage to LDS; barrier.  The split one, see gemm_stage: the stage is multiplied in
 // two phases of one chunk each, the fragments of a phase are read from LDS one phase ahead into
-// StageFrags.  SGEMM runs the split schedule on wave tiles of two 32x32 blocks and more, where one
-// to three waves share a SIMD (measured at 2048^3 and 4096^3: 2-8 % faster on the 128x64, 128x128 and
+// StageFrags.  The fp32 SGEMM kernel runs the split schedule on wave tiles of two 32x32 blocks and more, where one
+// to three waves share a SIMD (measured at 2048^3 and 4096^3, before those tiles' products moved to the bfloat16
+// matrix cores where K >= 3: 2-8 % faster on the 128x64, 128x128 and
 // larger tiles, no change with 32x32 wave tiles, slower with a single chunk per stage).  The
 // convolution kernels keep the plain one: over the suite and 28 further layer shapes the split
 // schedule gave the same total (single layers 8 % faster or 6 % slower), because many waves share

@@ -49,6 +49,16 @@ inline bool gather_tap_major_fits(const ConvProblem &q, int bk)
     return RS >= 2 && RS <= 63 && q.C % bk == 0 && RS * q.C * q.C < (1ll << 32);
 }
 
+// Whether the gather kernel keeps a table of the reduction's rows in LDS (kTableRows of 8 bytes): at most 63 taps, and
+// every row a load can ask for -- the reduction rounded up to whole stages and the two stages the loads run
+// ahead -- has an entry.
+constexpr int kTableRows = 512;
+inline bool gather_table_fits(const ConvProblem &q, int bk)
+{
+    const int64_t RS = (int64_t)q.R * q.S, stages = (q.C * RS + bk - 1) / bk;
+    return RS <= 63 && (stages + 2) * bk <= kTableRows;
+}
+
 // The kernels' 32-bit byte offsets: inside one workgroup's slice of A (bm rows), of B (bk rows) and of C (bm
 // rows); inside the images a tile of bn pixels touches (at most bn/PQ + 2), read and written, and inside its
 // filter rows.  A launch outside these limits is refused; the picker looks for a tile inside them.
@@ -204,7 +214,7 @@ void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out);
 void sgemm_candidates(const SgemmProblem &q, std::vector<polydl_tile_cfg> *out);
 
 // conv_point.hip: pointwise convolution with the filter resident in LDS (cfg.algo == 2; one variant:
-// 32 output channels x 64 pixels per wave and unit, 256 threads)
+// 32 output channels x 64 pixels per wave and unit, 512 threads)
 bool conv_point_fits(const ConvProblem &q);
 void conv_point_shape(const ConvProblem &q, int cus, uint32_t *units, uint32_t *workgroups);
 hipError_t conv_point_launch(const ConvProblem &q, hipStream_t stream);

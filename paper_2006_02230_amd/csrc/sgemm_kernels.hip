@@ -1,4 +1,4 @@
-// SGEMM C += A*B on the fp32 matrix cores (figure "Matrix multiplication code", section
+// SGEMM C += A*B on the matrix cores, fp32 or bfloat16 with split operands (figure "Matrix multiplication code", section
 // "Notation"; two-level tiling as in figure "A code version generated for PolyDL").
 #include "gemm_core.hpp"
 #include "internal.hpp"
@@ -139,7 +139,8 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void sgemm_kernel(SgemmKArgs p
 // power, the vendor's bfloat16 product of that size reaches 1.26 -- and below 2048^3 one wave's instruction
 // issue (8 non-matrix instructions per 32-cycle matrix instruction with one wave per SIMD).  The 256x128 tile
 // with eight waves splits an operand once for twice the outputs: 668 -> 639 us against 128x128.
-// 4096^3 959 -> 639 us, 2048^3 134 -> 100, 1024^3 26 -> 24, 1024 x 32768 x 1024 490 -> 340.
+// 4096^3 959 -> 640 .. 670 us (the card's power decides), 2048^3 134 -> 100, 1024^3 26 -> 24, 1024 x 32768 x 1024
+// 490 .. 510 -> 340 .. 370.
 template <class T, bool CVEC>
 __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void sgemm_split_kernel(SgemmKArgs p)
 {

@@ -1,9 +1,11 @@
 // GEMM main loop with fp32 operands multiplied on the bfloat16 matrix cores.
 //
 // An fp32 value is the exact sum of three bfloat16 values (8 + 8 + 8 significand bits, each rounded
-// to nearest): x = x0 + x1 + x2.  Of the nine products of two such sums the six with weights down to
-// 2^-18 are formed; the three left out together are below 2^-26 of the product, a quarter of the
-// rounding of one fp32 addition.  v_mfma_f32_32x32x16_bf16 does 16 times the work per cycle of
+// to nearest): x = x0 + x1 + x2 (G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019).  Of the nine products of two such
+// sums the six with weights down to 2^-18 are formed; the three left out together come to 2^-24 of the product
+// at worst (1 + 2^-8 - 2^-17 squared), what one fp32 addition may round, and on uniform values to less than
+// 2^-26 of it in 97 of 100.  v_mfma_f32_32x32x16_bf16 does 16 times the work per cycle of
 // v_mfma_f32_32x32x2_f32, so six of them still leave 2.7 times the fp32 rate.
 //
 // Sums.  The products x0*y0 go to one accumulator, the five small ones to a second; both are added
@@ -357,7 +359,7 @@ __device__ __forceinline__ void split_mainloop(u32x4 *lds, AL &al, BL &bl, Split
         split_stage<T, 0, true>(lds, al, bl, acc, k0, kend, tid, wm0, wave_col);
         split_stage<T, 1, true>(lds, al, bl, acc, k0 + BK, kend, tid, wm0, wave_col);
     }
-    // at most four stages are left
+    // at most five stages are left
     for (; k0 + BK < kend; k0 += 2 * BK) {
         split_stage<T, 0, false>(lds, al, bl, acc, k0, kend, tid, wm0, wave_col);
         split_stage<T, 1, false>(lds, al, bl, acc, k0 + BK, kend, tid, wm0, wave_col);

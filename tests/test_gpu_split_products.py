@@ -27,9 +27,11 @@ def split_tiles(P):
 # one stage, its boundary, the boundaries of the unrolled pipeline, long
 @pytest.mark.parametrize("K", [1, 15, 16, 17, 33, 48, 64, 79, 80, 81, 97, 576, 2500])
 def test_sgemm_error_against_64_bits(P, K):
-    # The six products kept leave out less than 2^-25 of a product; every main accumulator step rounds once
-    # per eight terms (<= 2^-24 of the running sum).  Worst case over the terms' magnitudes:
-    # 2^-25 + (K/8 + 2) * 2^-24, plus the final rounding; fp32 in sequence would be allowed K * 2^-24.
+    # The six products kept leave out 2^-24 of a product at worst; the main accumulator rounds once per eight
+    # terms (<= 2^-24 of the running sum), at the end the two accumulators are added (once more), and the small
+    # one holds at most 2^-7 of the terms, so its own roundings stay below half of one of these: in all
+    # (1 + K/8 + 1 + 1/2) * 2^-24, and the last part of a block of eight.  fp32 in sequence would be
+    # allowed K * 2^-24.
     for v in split_tiles(P):
         for M, N in ((v.bm, v.bn), (v.bm + 1, v.bn - 1)):
             A, B, _ = synth.sgemm_inputs(M, N, K, seed=K)
