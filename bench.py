@@ -19,6 +19,7 @@ sys.path.insert(0, ROOT)
 
 FP32_MFMA_PEAK_TFLOPS = 157.3   # MI355X dense fp32 matrix peak
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # dense bf16 matrix peak
+SPLIT_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS / 6   # fp32 products formed as six bf16 products each
 HBM_PEAK_GBS = 8000.0
 
 # HBM-side bytes of one pass over the suite (all kernels of the eight layers, batch 32), from the L2
@@ -44,6 +45,15 @@ def csrc_digest():
             h.update(f.encode())
             h.update(open(os.path.join(d, f), "rb").read())
     return h.hexdigest()
+
+
+def products_peak(tile, reduction, thin=False):
+    """Peak of the instruction that forms the products: tiles of stage depth 16 and wave tiles up to 64x64 split
+    fp32 operands for the bf16 matrix cores from a reduction of 128 on (512 for 1x1 layers of at most 64 output
+    channels: thin; 3 for SGEMM, whose caller passes no less), the pointwise kernel always."""
+    split = tile.algo == 2 or (tile.algo == 0 and tile.bk == 16 and tile.wm * tile.wn <= 64 * 64 and
+                               reduction >= (512 if thin else 128))
+    return SPLIT_PEAK_TFLOPS if split else FP32_MFMA_PEAK_TFLOPS
 
 
 def conv_flops(s, P, Q):
@@ -302,16 +312,20 @@ def main():
     rows = []
     sweep_dump = []
     kern_ms_sum = 0.0
+    peak_ms_sum = 0.0    # the layers' nominal flops at the peak of the instruction each one runs on
     for L in ([] if args.no_layer_rows else layers):
         i = L["index"]
         reps = 30
         ms = time_calls(torch, lambda L=L: run_layer(L), reps)
+        sh = L["shape"]
+        peak = products_peak(P.get_last_tile(), sh.C * sh.R * sh.S, thin=sh.R * sh.S == 1 and sh.K <= 64)
         tile = P.get_last_tile().as_dict()
         tf = L["flops"] / (ms * 1e-3) / 1e12
         ai = L["flops"] / L["bytes"]
-        ceiling = min(FP32_MFMA_PEAK_TFLOPS, ai * HBM_PEAK_GBS / 1e3)
+        ceiling = min(peak, ai * HBM_PEAK_GBS / 1e3)
+        peak_ms_sum += L["flops"] / (peak * 1e12) * 1e3
         rows.append(dict(layer=i, shape=[L["shape"].C, L["shape"].K, L["shape"].H, L["shape"].R, L["shape"].stride],
-                         us=round(ms * 1e3, 2), tflops=round(tf, 2), frac_mfma=round(tf / FP32_MFMA_PEAK_TFLOPS, 4),
+                         us=round(ms * 1e3, 2), tflops=round(tf, 2), frac_mfma=round(tf / peak, 4),
                          frac_roofline=round(tf / ceiling, 4), gbs=round(L["bytes"] / (ms * 1e-3) / 1e9, 1),
                          tile=tile))
         kern_ms_sum += ms
@@ -394,6 +408,7 @@ def main():
     if args.no_layer_rows:
         kern_ms_sum = e0.elapsed_time(e1) / args.steps
     achieved = total_flops / (kern_ms_sum * 1e-3) / 1e12
+    mfma_peak = total_flops / (peak_ms_sum * 1e-3) / 1e12 if peak_ms_sum else FP32_MFMA_PEAK_TFLOPS
 
     # the same suite without the filter copies (polydl_conv2d_fwd_act on NCHW / KCRS alone): the step
     # timed the same way, and each layer's launch time
@@ -412,7 +427,7 @@ def main():
             k_us.append(round(time_calls(torch, lambda L=L: run_layer(L, tap=False), 30) * 1e3, 2))
         kcrs_only = dict(ms_per_step=round(k_ms, 4), value=round(total_flops / (k_ms * 1e-3) / 1e12, 3),
                          layers_us=k_us, achieved=round(total_flops / (sum(k_us) * 1e-6) / 1e12, 3),
-                         frac=round(total_flops / (sum(k_us) * 1e-6) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4))
+                         frac=round(total_flops / (sum(k_us) * 1e-6) / 1e12 / mfma_peak, 4))
 
     sg = []
     if not args.no_sgemm:
@@ -423,7 +438,7 @@ def main():
             ms = time_calls(torch, lambda: P.sgemm(dA, dB, dC), 20 if n >= 2048 else 100)
             tf = 2.0 * n ** 3 / (ms * 1e-3) / 1e12
             sg.append(dict(n=n, us=round(ms * 1e3, 2), tflops=round(tf, 2),
-                           frac_mfma=round(tf / FP32_MFMA_PEAK_TFLOPS, 4), tile=P.get_last_tile().as_dict()))
+                           frac_mfma=round(tf / products_peak(P.get_last_tile(), 128), 4), tile=P.get_last_tile().as_dict()))
             if args.sweep:
                 # every candidate the SGEMM picker ranks; candidates the model puts beyond 4x its best
                 # prediction are not timed (they would take most of the sweep's time and none is near)
@@ -462,7 +477,7 @@ def main():
             ms = time_calls(torch, lambda: P.sgemm(dA, dB, dC), 10)
             tf = 2.0 * M * N * K / (ms * 1e-3) / 1e12
             sg.append(dict(mnk=[M, N, K], us=round(ms * 1e3, 2), tflops=round(tf, 2),
-                           frac_mfma=round(tf / FP32_MFMA_PEAK_TFLOPS, 4), tile=P.get_last_tile().as_dict()))
+                           frac_mfma=round(tf / products_peak(P.get_last_tile(), 128), 4), tile=P.get_last_tile().as_dict()))
             del dA, dB, dC
 
     # the same suite with bfloat16 inputs (fp32 accumulate and output) at batch 64: operands already in
@@ -689,8 +704,8 @@ def main():
         fl = conv_flops(s, Pq, Qq)
         cfg1 = dict(workload="configs[0]: N=1 C=K=64 56x56 3x3 s1 p1, no bias, U[-1,1), seed 0",
                     us=round(ms * 1e3, 2), tflops=round(fl / (ms * 1e-3) / 1e12, 2),
-                    frac_mfma=round(fl / (ms * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4),
-                    mfma_time_at_peak_us=round(fl / (FP32_MFMA_PEAK_TFLOPS * 1e12) * 1e6, 2),
+                    frac_mfma=round(fl / (ms * 1e-3) / 1e12 / products_peak(P.get_last_tile(), 64 * 9), 4),
+                    mfma_time_at_peak_us=round(fl / (products_peak(P.get_last_tile(), 64 * 9) * 1e12) * 1e6, 2),
                     tile=P.get_last_tile().as_dict())
         if not args.no_cpu:
             import ctypes
@@ -754,12 +769,14 @@ def main():
                               else "KCRS only (polydl_conv2d_fwd_act)",
                    "frac_of_fp32_mfma_peak": round(value / FP32_MFMA_PEAK_TFLOPS, 4),
                    "clock_warm_ms": args.clock_warm_ms},
-        "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": FP32_MFMA_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": round(achieved / FP32_MFMA_PEAK_TFLOPS, 4), "traffic": traffic,
+        "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(mfma_peak, 1),
+                     "peak_source": "the layers' nominal flops at the peak of the instruction each runs on: %.1f TFLOP/s fp32, "
+                                    "%.1f for fp32 operands split for the bf16 one" % (FP32_MFMA_PEAK_TFLOPS, SPLIT_PEAK_TFLOPS),
+                     "unit": "TFLOP/s", "frac": round(achieved / mfma_peak, 4), "traffic": traffic,
                      "traffic_unit": "bytes per suite pass (L2 fetch + write-back); algorithmic: %d" % total_bytes,
                      "traffic_source": "not measured in this run: counters of an earlier rocprofv3 --pmc run of the "
                                        "same kernel sources (digest checked), null when the sources have changed",
-                     "kernel": "polydl::conv_kernel / polydl::conv_patch_kernel as picked per layer (all 8 "
+                     "kernel": "polydl::conv_split_kernel / conv_kernel / conv_point_kernel as picked per layer (all 8 "
                                "layers, nominal 2*N*K*P*Q*C*R*S flops / sum of per-layer mean launch durations)"},
         "cpu_baseline": cpu,
         "layers": rows,
