@@ -362,18 +362,10 @@ __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &
     if (parts > 1) {
         __shared__ unsigned s_arrived;
         constexpr size_t TILE = (size_t)T::BM * T::BN;
-        constexpr int NT = T::NT;
         const int slot = c.tile - c.first_split_tile;   // scratch tiles and counters are numbered over the split tiles
         float *tile0 = p.partials + (size_t)slot * parts * TILE;
         float *mine = tile0 + (size_t)part * TILE;
-#pragma unroll
-        for (int bi = 0; bi < T::MB; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < T::NB; ++bj)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    __hip_atomic_store(mine + ((bi * T::NB + bj) * 16 + r) * NT + tid, acc[bi][bj][r], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+        store_partial_tile<T>(mine, tid, acc);
         wait_vmcnt0();   // vmcnt(0): this wave's device-scope stores have completed
         __syncthreads();
         if (tid == 0)
@@ -382,7 +374,7 @@ __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &
         if (__builtin_amdgcn_readfirstlane(s_arrived) != (unsigned)parts - 1u) return;   // not the last part
         if (tid == 0)               // leave the counter at zero for the next launch
             __hip_atomic_store(p.counters + slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sum_partial_tiles<T>(tile0, parts, TILE, tid, acc);
+        sum_partial_tiles<T, kPartsAhead<T>>(tile0, parts, tid, acc);
     }
     // epilogue.  The lane owns NB adjacent pixels starting at colg for 16*MB output channels.
     // Addresses are a per-lane byte offset from the first image the tile touches plus a uniform

@@ -476,14 +476,7 @@ __global__ __launch_bounds__(T::NT) void conv_patch_kernel(ConvPatchKArgs p)
         constexpr size_t TILE = (size_t)T::BM * T::BN;
         float *tile0 = p.partials + (size_t)cut_tile * p.split_k * TILE;
         float *mine = tile0 + (size_t)part * TILE;
-#pragma unroll
-        for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < NB; ++bj)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    __hip_atomic_store(mine + ((bi * NB + bj) * 16 + r) * NT + tid, acc[bi][bj][r], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+        store_partial_tile<T>(mine, tid, acc);
         // The tile is written and read back with device-scope accesses, which go past the caches
         // that are not shared by the whole device.  A full release/acquire fence pair would do
         // too, but costs a write-back of the whole L2 per workgroup.  Instead: wait until this
@@ -497,7 +490,7 @@ __global__ __launch_bounds__(T::NT) void conv_patch_kernel(ConvPatchKArgs p)
         if (__builtin_amdgcn_readfirstlane(s_arrived) != (unsigned)p.split_k - 1u) return;   // not the last part
         if (tid == 0)               // leave the counter at zero for the next launch
             __hip_atomic_store(p.counters + cut_tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sum_partial_tiles<T>(tile0, p.split_k, TILE, tid, acc);
+        sum_partial_tiles<T, 1>(tile0, p.split_k, tid, acc);
     }
     // Addresses are a per-lane byte offset from the first image the tile touches plus a uniform
     // offset per channel row; biases of channels at or past K (and of a missing bias vector) read

@@ -433,40 +433,79 @@ __device__ __forceinline__ void gemm_mainloop(float *lds, AL &al, BL &bl, v16f (
         gemm_stage<T, 0, SPLIT>(As, Bs, al, bl, acc, f, k0, kend, tid, wm0, wn0);
 }
 
-// Sum of the `parts` partial accumulator tiles of one output tile, in index order (so the result
-// does not depend on which part arrived last).  Tiles lie TILE floats apart, each in register
-// order (thread-contiguous).  The loads are device-scope.  (Requesting part i+1 before part i is
-// added measured no faster: other workgroups fill the compute unit while the last one of a tile sums.)
+// Partial accumulator tiles of a split reduction, in register order: WIDTH registers of a lane together, the lanes' groups
+// consecutive.  Stores and loads are device-scope (sc1).  WIDTH 4: 128-bit accesses, a quarter of the instructions of the
+// hand-over (64x64 tiles in 4 parts, 12.8 -> 12.1 us for a layer of one image; 8 parts of 128x2048x4096 27.0 -> 24.3 with
+// AHEAD below).  Workgroups of 512 threads keep single words: with the wide ones 1024 -> 2048 1x1/2 in two parts
+// of 256x128 tiles was 1.7 % slower (53.1 -> 54.0 us).
+constexpr int kDeviceScope = 16;   // sc1 in the cache policy of a raw buffer access
 template <class T>
-__device__ __forceinline__ void sum_partial_tiles(const float *tile0, int parts, size_t TILE, int tid,
-                                                  v16f (&acc)[T::MB][T::NB])
+constexpr int kPartialWidth = T::NT > 256 ? 1 : 4;
+
+template <class T>
+__device__ __forceinline__ void store_partial_tile(float *mine, int tid, const v16f (&acc)[T::MB][T::NB])
 {
-    constexpr int R = T::MB * T::NB * 16, NT = T::NT;
-    auto fetch = [&](float (&dst)[R], int sp) {
-        const float *part = tile0 + (size_t)sp * TILE + tid;
-#pragma unroll
-        for (int i = 0; i < R; ++i) dst[i] = __hip_atomic_load(part + (size_t)i * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto add = [&](const float (&src)[R]) {
-#pragma unroll
-        for (int bi = 0; bi < T::MB; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < T::NB; ++bj)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[bi][bj][r] += src[(bi * T::NB + bj) * 16 + r];
-    };
+    constexpr int W = kPartialWidth<T>;
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(mine, (uint64_t)T::BM * T::BN * 4);
 #pragma unroll
     for (int bi = 0; bi < T::MB; ++bi)
 #pragma unroll
         for (int bj = 0; bj < T::NB; ++bj)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
-    float a[R];
-    for (int sp = 0; sp < parts; ++sp) {
-        fetch(a, sp);
-        add(a);
+            for (int i = 0; i < 16; i += W) {
+                const int unit = ((bi * T::NB + bj) * 16 + i) * T::NT * 4;
+                if constexpr (W == 4) {
+                    const v4f v = {acc[bi][bj][i], acc[bi][bj][i + 1], acc[bi][bj][i + 2], acc[bi][bj][i + 3]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), r, 16 * tid, unit, kDeviceScope);
+                } else {
+                    const float f = acc[bi][bj][i];   // a bit cast of the element itself would take element 0
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, f), r, 4 * tid, unit, kDeviceScope);
+                }
+            }
+}
+
+// Sum of the `parts` partial tiles of one output tile, in index order (so the result does not depend on which
+// part arrived last).  AHEAD parts are requested together: a grid that hands over small tiles has nothing else to do
+// meanwhile, and part by part every one cost a round trip (64x64 tiles: 0.4 us each; 8 parts 3.2 us).
+template <class T, int AHEAD>
+__device__ __forceinline__ void sum_partial_tiles(const float *tile0, int parts, int tid, v16f (&acc)[T::MB][T::NB])
+{
+    constexpr int W = kPartialWidth<T>, U = T::MB * T::NB * 16 / W;   // accesses of a lane per part
+    constexpr uint32_t TILE_BYTES = (uint32_t)T::BM * T::BN * 4;
+#pragma unroll
+    for (int bi = 0; bi < T::MB; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[bi][bj][i] = 0.f;
+    for (int sp = 0; sp < parts; sp += AHEAD) {
+        const __amdgpu_buffer_rsrc_t r = make_rsrc(tile0 + (size_t)sp * (T::BM * T::BN), (uint64_t)AHEAD * TILE_BYTES);
+        float v[AHEAD][U][W];
+#pragma unroll
+        for (int n = 0; n < AHEAD; ++n) {
+            // parts past the last one are out of range: no access, zeros (a sum that starts at +0 is never -0)
+            const int off = sp + n < parts ? 4 * W * tid : (int)kOobOffset;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int unit = n * (int)TILE_BYTES + u * W * T::NT * 4;
+                if constexpr (W == 4) {
+                    const v4f f = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, off, unit, kDeviceScope));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[n][u][i] = f[i];
+                } else {
+                    v[n][u][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, unit, kDeviceScope));
+                }
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < AHEAD; ++n)
+#pragma unroll
+            for (int e = 0; e < U * W; ++e) acc[e / 16 / T::NB][e / 16 % T::NB][e % 16] += v[n][e / W][e % W];
     }
 }
+// AHEAD of the kernels that work on 1, 2 and 4 blocks a wave, within the registers their main loops take anyway
+template <class T>
+constexpr int kPartsAhead = T::MB * T::NB == 1 ? 4 : T::MB * T::NB == 2 ? 3 : 1;
 
 // Row (inside the workgroup tile) of accumulator register r of row block bi for this lane: a
 // 32x32 result keeps column lane%32 in every register and row 8*(r/4) + 4*(lane/32) + r%4 in

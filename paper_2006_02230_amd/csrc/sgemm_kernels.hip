@@ -35,17 +35,9 @@ __device__ __forceinline__ void sgemm_finish(const SgemmKArgs &p, v16f (&acc)[T:
     if (p.split_k > 1) {
         __shared__ unsigned s_arrived;
         constexpr size_t TILE = (size_t)T::BM * T::BN;
-        constexpr int NT = T::NT;
         float *tile0 = p.partials + (size_t)blockIdx.x * p.split_k * TILE;
         float *mine = tile0 + (size_t)blockIdx.y * TILE;
-#pragma unroll
-        for (int bi = 0; bi < T::MB; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < T::NB; ++bj)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    __hip_atomic_store(mine + ((bi * T::NB + bj) * 16 + r) * NT + tid, acc[bi][bj][r], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+        store_partial_tile<T>(mine, tid, acc);
         wait_vmcnt0();   // vmcnt(0): this wave's device-scope stores have completed
         __syncthreads();
         if (tid == 0)
@@ -54,7 +46,7 @@ __device__ __forceinline__ void sgemm_finish(const SgemmKArgs &p, v16f (&acc)[T:
         if (__builtin_amdgcn_readfirstlane(s_arrived) != (unsigned)p.split_k - 1u) return;   // not the last part
         if (tid == 0)               // leave the counter at zero for the next launch
             __hip_atomic_store(p.counters + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sum_partial_tiles<T>(tile0, p.split_k, TILE, tid, acc);
+        sum_partial_tiles<T, kPartsAhead<T>>(tile0, p.split_k, tid, acc);
     }
     // epilogue: C = beta*C + alpha*acc (alpha = beta = 1 rounds exactly like C += acc).  C is
     // addressed by a per-lane byte offset of the lane's first row and column inside the tile's row

@@ -287,3 +287,23 @@ def test_infinity_in_the_last_channel_stays_an_infinity(P, s, value):
             inf = np.isinf(want)
             assert inf.any() and np.array_equal(got[inf], want[inf]) and np.isfinite(got[~inf]).all(), v
     P.set_tile_override(None)
+
+
+@pytest.mark.parametrize("parts", [2, 3, 4, 5, 7, 8, 9, 13])
+def test_sum_of_any_number_of_parts(P, parts):
+    # the last part of a tile requests several parts together: counts at and beside its multiples; C is read, ragged rows.
+    # Every part's length differs from the others' sum, so a part left out or counted twice shows.
+    import torch
+    g = np.random.default_rng(parts)
+    M, N, K = 300, 141, 16 * 13 * 3 + 5
+    A, B, C0 = (g.uniform(-1, 1, s).astype(np.float32) for s in ((M, K), (K, N), (M, N)))
+    want = A.astype(np.float64) @ B + C0
+    ab = np.abs(A).astype(np.float64) @ np.abs(B) + np.abs(C0)
+    for v in P.variants(1):
+        v.split_k, v.raster = parts, 1
+        P.set_tile_override(v)
+        first = host(P.sgemm(dev(A), dev(B), dev(C0)))
+        # K fp32 roundings bound either instruction, two more for the parts' sum and C
+        assert (np.abs(first - want) <= (K + parts + 2) * 2.0 ** -24 * ab).all(), v
+        assert np.array_equal(first, host(P.sgemm(dev(A), dev(B), dev(C0)))), v
+    P.set_tile_override(None)
