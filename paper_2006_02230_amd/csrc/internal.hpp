@@ -226,6 +226,10 @@ inline bool is_conv_point_cfg(const polydl_tile_cfg &c)
            c.layout == 0 && c.raster == 0 && c.cb == 0;
 }
 
+// conv_thin.hip: short reductions into at most 64 output channels, no reduction split and no scratch memory
+bool conv_thin_pays(const ConvProblem &q);
+hipError_t conv_thin_launch(const ConvProblem &q, hipStream_t stream);
+
 // reuse_analyse.cpp (arguments already validated)
 int reuse_analyse(int nloops, const int *extents, const int *parallel, int nrefs, const polydl_loop_ref *refs,
                   int max_deps, polydl_reuse_dep *deps, int *ndeps);

@@ -1,0 +1,70 @@
+"""Short reductions into at most 64 output channels (first layers), with enough pixels for the kernel that keeps the whole
+split filter in LDS: edges of its units, steps and tap masks against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import FP32_TOL, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2006_02230_amd as p
+    p.set_tile_override(None)
+    yield p
+
+
+# 98304 pixels (1536 units of 64) and more take the kernel on a card of 256 compute units
+SHAPES = [synth.ConvShape("first_layer", 2, 3, 450, 451, 64, 7, 7, 2, 3),        # odd rows, a last unit of 4 pixels
+          synth.ConvShape("two_steps", 1, 2, 320, 321, 50, 3, 3, 1, 1),          # 18 rows: the second step nearly empty
+          synth.ConvShape("63_taps", 1, 6, 318, 331, 33, 7, 9, 1, 4),            # every mask bit; 378 rows, the longest
+          synth.ConvShape("strided_45_taps", 3, 4, 560, 549, 64, 5, 9, 3, 3),
+          synth.ConvShape("no_padding", 4, 8, 161, 163, 64, 3, 3, 1, 0),
+          synth.ConvShape("small_images", 2100, 5, 7, 7, 17, 3, 3, 1, 1),        # a unit touches three images
+          synth.ConvShape("1x1", 40, 131, 50, 50, 64, 1, 1, 1, 0),
+          synth.ConvShape("1x1_strided_padded", 11, 130, 190, 191, 20, 1, 1, 2, 1),
+          synth.ConvShape("one_unit_less", 24, 16, 64, 64, 64, 3, 3, 1, 1),      # 1536 units; 23 images: the picked tile
+          synth.ConvShape("below", 23, 16, 64, 64, 64, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=lambda s: s.name)
+def test_against_the_oracle(P, s):
+    x, w, b = synth.conv_inputs(s, seed=3 + len(s.name), dist="normal", bias=True)
+    dx, dw, db = dev(x), dev(w), dev(b)
+    for act, bias, pre in (("relu6", True, None), ("none", False, "relu")):
+        want, ab = oracle.conv2d_fwd(np.maximum(x, 0) if pre else x, w, bias=b if bias else None, stride=s.stride, pad=s.pad, act=act)
+        got = host(P.conv2d_fwd(dx, dw, db if bias else None, stride=s.stride, pad=s.pad, act=act, pre_act=pre))
+        assert oracle.scaled_error(got, want, ab) <= FP32_TOL, (act, pre)
+
+
+@pytest.mark.parametrize("case", ["inf", "nan_filter", "lowest", "tiny", "tiny_filter"])
+def test_values_the_split_cannot_hold(P, case):
+    s = synth.ConvShape("v", 3, 3, 381, 379, 60, 5, 5, 2, 2)
+    x, w, _ = synth.conv_inputs(s, seed=5, dist="normal")
+    if case == "inf":
+        x[1, 2, 0, 378] = np.inf
+    elif case == "nan_filter":
+        w[7, 1, 2, 0] = np.nan
+    elif case == "lowest":
+        x[0, 1, 3, 3] = np.finfo(np.float32).min
+        w *= np.float32(1e-3)
+    elif case == "tiny":
+        x[2, :, 100:] *= np.float32(1e-37)
+        w *= np.float32(1e20)
+    elif case == "tiny_filter":
+        w[40] *= np.float32(1e-37)
+        x *= np.float32(1e20)
+    # the padding is zeros that are multiplied like any other value
+    want, ab = oracle.conv2d_fwd(np.pad(x, ((0, 0), (0, 0), (s.pad, s.pad), (s.pad, s.pad))), w, stride=s.stride, pad=0)
+    got = host(P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad))
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True)
+    # 75 sequential roundings where a unit is recomputed with fp32 instructions, the last one of the store
+    assert (np.abs(got[fin] - want[fin]) <= (75 + 2) * 2.0 ** -24 * ab[fin]).all()
