@@ -67,15 +67,20 @@ __device__ __forceinline__ uint32_t outside_bits(int lo, int hi, int n)
 //               stage shares one tap: its validity bit and its distance are found once per stage,
 //               not per element, and the channel rides in the uniform offset.  In that copy the
 //               filter rows are contiguous in the walked order, so they load as in a plain GEMM.
-//  GATHER_TABLE  filters of at most 63 taps with a short reduction (gather_table_fits(); the stem
-//               layer): as GATHER_TAPS2, but the (c, r, s) split of a reduction row is
-//               not redone by every wave for every element.  The workgroup writes (distance of the
+//  GATHER_TABLE  filters of at most 63 taps with a short reduction (gather_table_fits()), on the fp32
+//               instruction: as GATHER_TAPS2, but the (c, r, s) split of a reduction row is not redone by every wave for every element.  The workgroup writes (distance of the
 //               row's tap and channel in bytes, tap number) of every row into LDS once; a load then
 //               reads its row's entry (one address per stage, constant offsets), adds the distance
 //               to the lane's offset and shifts the lane's 64 tap bits by the tap number.  Same
 //               vector instructions per element as GATHER_TAPS2, a tenth of its scalar ones: the one
 //               scalar unit of a compute unit serves four SIMDs, and at 18 scalar instructions per
 //               matrix instruction (the stem layer) it, not the matrix cores, set the pace.
+//  With SPLIT, GATHER_TAPS1 / GATHER_TAPS2 read their rows from a table as well, of any reduction's length: a stage is 16
+//               rows, so the rows' taps repeat every R*S stages, 16 channels further on.  The table holds one such period
+//               (or a part's stages, if fewer), the 16 channels per period ride in the uniform offset, and only the
+//               stage number is divided, once per stage.  Batch 32 with the filter in KCRS order only: 512 -> 512 3x3
+//               on 7x7 70.1 -> 64.4 us (8.4 scalar instructions per matrix instruction before), 83 -> 201 3x3 on 35x29,
+//               batch 7, 30.8 -> 28.6, one 64 -> 64 3x3 image 12.1 -> 11.05.
 enum { GATHER_ANY = 0, GATHER_POINT = 1, GATHER_TAPS1 = 2, GATHER_TAPS2 = 3, GATHER_TAPMAJOR = 4, GATHER_TABLE = 5 };
 
 
@@ -89,12 +94,16 @@ struct BLoaderIm2col {
     static constexpr bool TAPMAJOR = MODE == GATHER_TAPMAJOR;
     static constexpr bool TABLE = MODE == GATHER_TABLE;
     static constexpr bool TAPS = MODE == GATHER_TAPS1 || MODE == GATHER_TAPS2 || TAPMAJOR || TABLE;
+    static constexpr int AHEAD = 3;   // stages behind the last one that a load may ask for, at most
     static constexpr int LAST_BIT = MODE == GATHER_TAPS1 ? 31 : 63;   // never a tap: always set
     static constexpr int KSTEP = T::NT / T::BN;  // reduction rows covered by one pass of the workgroup
     static constexpr int ITERS = T::BK / KSTEP;
     static_assert(T::BK % KSTEP == 0, "stage depth must be a multiple of the rows loaded per pass");
     static_assert(!SPLIT || ITERS == 4 || ITERS == 8, "whole quads");
     static constexpr int RPT = ITERS;
+    static constexpr bool PERIODIC = SPLIT && (MODE == GATHER_TAPS1 || MODE == GATHER_TAPS2);
+    static constexpr int TABLE_ROWS = PERIODIC ? LAST_BIT * 16 : MODE == GATHER_TABLE ? kTableRows : 1;
+    static_assert(!PERIODIC || T::BK == 16, "a period is R*S stages of 16 rows");
     SplitUnit<SPLIT ? RPT : 4> unit;                                 // SPLIT: the values on their way into the planes
     float regs[2][ITERS];
     __amdgpu_buffer_rsrc_t rsrc;
@@ -103,13 +112,24 @@ struct BLoaderIm2col {
     int krow0, lds_off;
     int RS, S, HW, W, pre_act, C;
     uint32_t magic_RS, magic_S, one_RS, one_S, magic_C;
-    const uint2 *tab;   // GATHER_TABLE: per reduction row (byte distance, tap number), in LDS
+    const uint2 *tab;   // GATHER_TABLE, PERIODIC: per reduction row (byte distance, tap number), in LDS
 
     // GATHER_TABLE: the workgroup fills the table (rows at or past the end of the reduction get the
     // bit that is always set); the caller puts a barrier between this and the first load.
-    __device__ __forceinline__ void fill_table(const ConvKArgs &p, int tid, uint2 *t)
+    // PERIODIC: the rows of the stages from kbegin on, those the loads run ahead included, at most one period.
+    __device__ __forceinline__ void fill_table(const ConvKArgs &p, int tid, uint2 *t, int kbegin, int kend)
     {
         tab = t;
+        if constexpr (PERIODIC) {
+            const int first = kbegin >> 4, stages = min(p.RS, ((kend - kbegin + 15) >> 4) + AHEAD);
+            for (int e = tid; e < stages * 16; e += T::NT) {
+                const uint32_t st = (uint32_t)(first + (e >> 4)), phase = st - fast_div(st, p.magic_RS, p.one_RS) * (uint32_t)p.RS;
+                const uint32_t row = phase * 16u + (uint32_t)(e & 15);
+                const uint32_t c = fast_div(row, p.magic_RS, p.one_RS), rs = row - c * (uint32_t)p.RS;
+                const uint32_t r = fast_div(rs, p.magic_S, p.one_S), sx = rs - r * (uint32_t)p.S;
+                t[row] = (uint2){(c * (uint32_t)p.HW + r * (uint32_t)p.W + sx) * 4u, rs};
+            }
+        }
         if constexpr (TABLE) {
             // every row a load can ask for: the reduction rounded up to whole stages and the two
             // stages the loads run ahead (the launcher checked that the table holds them)
@@ -260,8 +280,8 @@ struct BLoaderIm2col {
     }
     // the steps of split_core.hpp's main loop; a stage is fetched row by row
     int s_k0, s_kend;
-    uint32_t s_off, s_koff;          // GATHER_TAPMAJOR: the stage's lane offset and first row's distance
-    const uint2 *s_row;              // GATHER_TABLE: the stage's first entry
+    uint32_t s_off, s_koff;          // GATHER_TAPMAJOR: the stage's lane offset and first row's distance; PERIODIC: its period's distance
+    const uint2 *s_row;              // PERIODIC: the stage's first entry
     template <bool FULL>
     __device__ __forceinline__ void begin(int k0, int kend)
     {
@@ -276,7 +296,11 @@ struct BLoaderIm2col {
             s_off = (uint32_t)pix_off | (((word >> (t & 31u)) & 1u) << 31);
             s_koff = ((c0 + (uint32_t)krow0) * (uint32_t)HW + r * (uint32_t)W + sx) * 4u;
         }
-        if constexpr (TABLE) s_row = tab + (k0 + krow0);
+        if constexpr (PERIODIC) {
+            const uint32_t st = (uint32_t)k0 >> 4, period = fast_div(st, magic_RS, one_RS);
+            s_row = tab + ((st - period * (uint32_t)RS) * 16u + (uint32_t)krow0);
+            s_koff = period * 16u * (uint32_t)HW * 4u;
+        }
     }
     template <int SET, bool FULL, int J>
     __device__ __forceinline__ void row()
@@ -289,10 +313,13 @@ struct BLoaderIm2col {
             else regs[SET][J] = buf_load1(rsrc, (uint32_t)pix_off, (uint32_t)(min(kg, s_kend - 1) * HW) * 4u);
         } else if constexpr (TAPMAJOR) {
             regs[SET][J] = buf_load1(rsrc, s_off, s_koff + (uint32_t)(J * HW) * 4u);
-        } else if constexpr (TABLE) {
+        } else if constexpr (PERIODIC) {
             const uint2 e = s_row[J];
-            const uint64_t taps = ((uint64_t)smask << 32) | rmask;
-            regs[SET][J] = buf_load1(rsrc, ((uint32_t)pix_off + e.x) | ((uint32_t)(taps >> e.y) << 31));
+            // a row at or past kend takes the bit that is always set
+            const uint32_t tap = FULL || s_k0 + krow0 + J < s_kend ? e.y : (uint32_t)LAST_BIT;
+            // bit 0 counts: the shift below drops the rest
+            const uint32_t outside = MODE == GATHER_TAPS1 ? rmask >> tap : (uint32_t)((((uint64_t)smask << 32) | rmask) >> tap);
+            regs[SET][J] = buf_load1(rsrc, ((uint32_t)pix_off + e.x) | (outside << 31), s_koff);
         } else {
             regs[SET][J] = gather<FULL>((uint32_t)(s_k0 + krow0 + J), s_kend);
         }

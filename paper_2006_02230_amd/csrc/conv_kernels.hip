@@ -27,7 +27,7 @@ __global__ __launch_bounds__(T::NT) void conv_kernel(ConvKArgs p)
     ALoader<T, 4, AVEC == 1> al;
     BLoaderIm2col<T, MODE, false, AVEC != 4> bl;
     __shared__ uint2 ktab[MODE == GATHER_TABLE ? kTableRows : 1];
-    bl.fill_table(p, tid, ktab);
+    bl.fill_table(p, tid, ktab, c.kbegin, c.kend);
     al.init(p.wt, tid, c.m0, p.K, p.Kg, p.Kg);
     bl.init(p, tid, c.n0);
     if constexpr (MODE == GATHER_TABLE) __syncthreads();
@@ -55,7 +55,8 @@ template <class T, int MODE, bool KTAIL>
 __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvKArgs p)
 {
     __shared__ __attribute__((aligned(16))) u32x4 lds[SplitTile<T>::LDS_BYTES / 16];
-    __shared__ uint2 ktab[MODE == GATHER_TABLE ? kTableRows : 1];
+    typedef BLoaderIm2col<T, MODE, true, KTAIL> Gather;
+    __shared__ __attribute__((aligned(16))) uint2 ktab[Gather::TABLE_ROWS];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const ConvPart c = conv_part<T>(p);
     const int wm0 = (wave % T::WAVES_M) * T::WM, wn0 = (wave / T::WAVES_M) * T::WN;
@@ -63,11 +64,11 @@ __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvK
     bool redo;
     {
         SplitALoader<T> al;
-        BLoaderIm2col<T, MODE, true, KTAIL> bl;
-        bl.fill_table(p, tid, ktab);
+        Gather bl;
+        bl.fill_table(p, tid, ktab, c.kbegin, c.kend);
         al.init(p.wt, tid, c.m0, p.K, p.Kg, p.Kg);
         bl.init(p, tid, c.n0);
-        if constexpr (MODE == GATHER_TABLE) __syncthreads();
+        if constexpr (Gather::PERIODIC) __syncthreads();
         SplitAcc<T> sum;
         sum.clear();
         split_mainloop<T>(lds, al, bl, sum, c.kbegin, c.kend, tid, wm0, wave / T::WAVES_M);
@@ -76,7 +77,6 @@ __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvK
     if (__syncthreads_or(redo)) {   // values the split cannot hold: once more on the fp32 matrix cores
         ALoader<T, 4, true> al;
         BLoaderIm2col<T, MODE> bl;
-        bl.tab = ktab;
         al.init(p.wt, tid, c.m0, p.K, p.Kg, p.Kg);
         bl.init(p, tid, c.n0);
 #pragma unroll
@@ -169,10 +169,10 @@ static hipError_t conv_launch(const ConvProblem &q, int split_k, int raster, hip
             case GATHER_POINT:
                 if (a.Kg % T::BK == 0) POLYDL_GO(GATHER_POINT, false);
                 POLYDL_GO(GATHER_POINT, true);
-            case GATHER_TABLE: POLYDL_GO(GATHER_TABLE, true);
-            case GATHER_TAPS1: POLYDL_GO(GATHER_TAPS1, true);
-            case GATHER_TAPS2: POLYDL_GO(GATHER_TAPS2, true);
-            default: POLYDL_GO(GATHER_ANY, true);
+            default:
+                if (a.RS <= 31) POLYDL_GO(GATHER_TAPS1, true);
+                if (a.RS <= 63) POLYDL_GO(GATHER_TAPS2, true);
+                POLYDL_GO(GATHER_ANY, true);
             }
 #undef POLYDL_GO
         }

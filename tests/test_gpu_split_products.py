@@ -307,3 +307,28 @@ def test_sum_of_any_number_of_parts(P, parts):
         assert (np.abs(first - want) <= (K + parts + 2) * 2.0 ** -24 * ab).all(), v
         assert np.array_equal(first, host(P.sgemm(dev(A), dev(B), dev(C0)))), v
     P.set_tile_override(None)
+
+
+# filters of 1, 3, 4, 9, 25, 31, 32, 49 and 63 taps: the row table repeats every so many stages; channel counts that end the
+# reduction inside a stage and inside a period, parts that begin inside one and are shorter or longer than one
+@pytest.mark.parametrize("R,S,C", [(1, 1, 160), (1, 3, 90), (2, 2, 61), (3, 3, 16), (3, 3, 83), (5, 5, 37), (1, 31, 6), (4, 8, 9), (7, 7, 21), (7, 9, 5)])
+def test_row_table_of_any_reduction(P, R, S, C):
+    s = synth.ConvShape("t", 2, C, 13, 17, 70, R, S, 1, min(R, S) // 2 + (R == S == 1))
+    s = s if S <= 17 else synth.ConvShape("t", 2, C, 3, 40, 70, R, S, 2, 1)
+    x, w, _ = synth.conv_inputs(s, seed=R * S + C, dist="normal")
+    x[1, C - 1, 2, 3] = np.inf                    # the last channel's value reaches its own outputs only
+    x[0, 0, 0, 0] = np.nan
+    want, ab = conv64(x, w, s.stride, s.pad)
+    dx, dw = dev(x), dev(w)
+    fin = np.isfinite(want)
+    for v in P.variants(0):
+        if v.algo != 0 or v.bk != 16 or v.wm * v.wn > 64 * 64:
+            continue
+        for split_k in (1, 2, 5, 16):
+            v.split_k, v.raster = split_k, 1
+            P.set_tile_override(v)
+            got = host(P.conv2d_fwd(dx, dw, stride=s.stride, pad=s.pad))
+            assert np.array_equal(np.isnan(got), np.isnan(want)), v
+            assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True), v
+            assert (np.abs(got[fin] - want[fin]) <= (C * R * S + 2) * 2.0 ** -24 * ab[fin]).all(), v
+    P.set_tile_override(None)
