@@ -94,7 +94,6 @@ struct BLoaderIm2col {
     static constexpr bool TAPMAJOR = MODE == GATHER_TAPMAJOR;
     static constexpr bool TABLE = MODE == GATHER_TABLE;
     static constexpr bool TAPS = MODE == GATHER_TAPS1 || MODE == GATHER_TAPS2 || TAPMAJOR || TABLE;
-    static constexpr int AHEAD = 3;   // stages behind the last one that a load may ask for, at most
     static constexpr int LAST_BIT = MODE == GATHER_TAPS1 ? 31 : 63;   // never a tap: always set
     static constexpr int KSTEP = T::NT / T::BN;  // reduction rows covered by one pass of the workgroup
     static constexpr int ITERS = T::BK / KSTEP;
@@ -102,7 +101,7 @@ struct BLoaderIm2col {
     static_assert(!SPLIT || ITERS == 4 || ITERS == 8, "whole quads");
     static constexpr int RPT = ITERS;
     static constexpr bool PERIODIC = SPLIT && (MODE == GATHER_TAPS1 || MODE == GATHER_TAPS2);
-    static constexpr int TABLE_ROWS = PERIODIC ? LAST_BIT * 16 : MODE == GATHER_TABLE ? kTableRows : 1;
+    static constexpr int TABLE_ROWS = PERIODIC ? (LAST_BIT + 2) * 16 : MODE == GATHER_TABLE ? kTableRows : 1;
     static_assert(!PERIODIC || T::BK == 16, "a period is R*S stages of 16 rows");
     SplitUnit<SPLIT ? RPT : 4> unit;                                 // SPLIT: the values on their way into the planes
     float regs[2][ITERS];
@@ -116,18 +115,33 @@ struct BLoaderIm2col {
 
     // GATHER_TABLE: the workgroup fills the table (rows at or past the end of the reduction get the
     // bit that is always set); the caller puts a barrier between this and the first load.
-    // PERIODIC: the rows of the stages from kbegin on, those the loads run ahead included, at most one period.
+    // PERIODIC: the rows of the part's stages, at most one period; behind that the last stage as it ends, and one of
+    // rows that lie outside, for the loads that run ahead.
     __device__ __forceinline__ void fill_table(const ConvKArgs &p, int tid, uint2 *t, int kbegin, int kend)
     {
         tab = t;
         if constexpr (PERIODIC) {
-            const int first = kbegin >> 4, stages = min(p.RS, ((kend - kbegin + 15) >> 4) + AHEAD);
-            for (int e = tid; e < stages * 16; e += T::NT) {
-                const uint32_t st = (uint32_t)(first + (e >> 4)), phase = st - fast_div(st, p.magic_RS, p.one_RS) * (uint32_t)p.RS;
-                const uint32_t row = phase * 16u + (uint32_t)(e & 15);
+            const uint32_t period = (uint32_t)p.RS * 16u;
+            auto phase_row = [&](int k) __attribute__((always_inline)) {   // of the stage that begins at row k (uniform)
+                const uint32_t st = (uint32_t)k >> 4;
+                return (st - fast_div(st, p.magic_RS, p.one_RS) * (uint32_t)p.RS) * 16u;
+            };
+            const int last = (kend - 1) & ~15;
+            const uint32_t first = phase_row(kbegin), first_of_last = phase_row(last);
+            const uint32_t rows = min((uint32_t)(last - kbegin) + 16u, period);
+            for (uint32_t e = tid; e < rows + 32u; e += T::NT) {
+                uint32_t row = first + e, at;
+                if (row >= period) row -= period;
+                at = row;
+                bool in = true;
+                if (e >= rows) {      // behind the period: the last stage once more, its rows past kend outside, and a stage of such rows
+                    row = first_of_last + ((e - rows) & 15u);
+                    at = period + (e - rows);
+                    in = last + (int)(e - rows) < kend;
+                }
                 const uint32_t c = fast_div(row, p.magic_RS, p.one_RS), rs = row - c * (uint32_t)p.RS;
                 const uint32_t r = fast_div(rs, p.magic_S, p.one_S), sx = rs - r * (uint32_t)p.S;
-                t[row] = (uint2){(c * (uint32_t)p.HW + r * (uint32_t)p.W + sx) * 4u, rs};
+                t[at] = (uint2){(c * (uint32_t)p.HW + r * (uint32_t)p.W + sx) * 4u, in ? rs : (uint32_t)LAST_BIT};
             }
         }
         if constexpr (TABLE) {
@@ -298,7 +312,9 @@ struct BLoaderIm2col {
         }
         if constexpr (PERIODIC) {
             const uint32_t st = (uint32_t)k0 >> 4, period = fast_div(st, magic_RS, one_RS);
-            s_row = tab + ((st - period * (uint32_t)RS) * 16u + (uint32_t)krow0);
+            uint32_t at = (st - period * (uint32_t)RS) * 16u;
+            if (!FULL && k0 + 16 > kend) at = (uint32_t)RS * 16u + (k0 >= kend ? 16u : 0u);
+            s_row = tab + (at + (uint32_t)krow0);
             s_koff = period * 16u * (uint32_t)HW * 4u;
         }
     }
@@ -315,10 +331,8 @@ struct BLoaderIm2col {
             regs[SET][J] = buf_load1(rsrc, s_off, s_koff + (uint32_t)(J * HW) * 4u);
         } else if constexpr (PERIODIC) {
             const uint2 e = s_row[J];
-            // a row at or past kend takes the bit that is always set
-            const uint32_t tap = FULL || s_k0 + krow0 + J < s_kend ? e.y : (uint32_t)LAST_BIT;
             // bit 0 counts: the shift below drops the rest
-            const uint32_t outside = MODE == GATHER_TAPS1 ? rmask >> tap : (uint32_t)((((uint64_t)smask << 32) | rmask) >> tap);
+            const uint32_t outside = MODE == GATHER_TAPS1 ? rmask >> e.y : (uint32_t)((((uint64_t)smask << 32) | rmask) >> e.y);
             regs[SET][J] = buf_load1(rsrc, ((uint32_t)pix_off + e.x) | (outside << 31), s_koff);
         } else {
             regs[SET][J] = gather<FULL>((uint32_t)(s_k0 + krow0 + J), s_kend);
