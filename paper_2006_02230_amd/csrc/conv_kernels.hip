@@ -48,8 +48,8 @@ __global__ __launch_bounds__(T::NT) void conv_kernel(ConvKArgs p)
 // kSplitMinReduction and more.  Bound: the gathering and splitting of every input value once per tap, beside
 // matrix instructions that leave two to three times less time for it than the fp32 ones did; hence larger
 // tiles with fewer reduction parts win (128x128 split 2 where 64x64 with cut leftovers did).  Batch 32, us:
-// 128 -> 128 3x3 with the filter copy 66 -> 56, 512 -> 512 3x3 79 -> 71, 1024 -> 2048 1x1/2 64 -> 55, the stem
-// 89 -> 80, 512 -> 512 3x3 at 28x28 910 -> 690.
+// 128 -> 128 3x3 with the filter copy 66 -> 54, 512 -> 512 3x3 79 -> 64, 1024 -> 2048 1x1/2 64 -> 53,
+// 512 -> 512 3x3 at 28x28 910 -> 690 (power).
 // KTAIL: see BLoaderIm2col.
 template <class T, int MODE, bool KTAIL>
 __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvKArgs p)

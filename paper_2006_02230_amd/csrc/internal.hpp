@@ -180,7 +180,8 @@ inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, siz
 // Tiles whose products are formed on the bfloat16 matrix cores (Tile::SPLIT), and the LDS of their two stage
 // buffers (SplitTile::SPLIT_BYTES without the bank skews).
 constexpr bool split_products(int bk, int wm, int wn) { return bk == 16 && wm * wn <= 64 * 64; }
-// Convolutions with a shorter reduction keep the fp32 matrix instruction: they are bound by their output, and
+// Convolutions with a shorter reduction keep the fp32 matrix instruction on these tiles (not in conv_thin.hip, whose
+// operands stay in registers): they are bound by their output, and
 // the longer prologue and the registers of the split kernels cost more than the products give (64 -> 64 channels
 // 1x1 at 56x56, batch 32: 14.3 us against 16.2; 24 -> 144: 18.8 against 24.3; the stem's 147 ties).
 // The same holds up to 511 for 1x1 layers of at most 64 output channels, which read four times what they write
