@@ -106,8 +106,8 @@ typedef struct polydl_tile_cfg {
  * a given tile configuration, so repeated calls agree bit for bit.  The gather variants (algo 0) with stage
  * depth 16 and wave tiles up to 64 x 64 form the products of reductions of 128 and more as polydl_sgemm
  * does (three bfloat16 parts per operand, six products, float32 sums).  So do, unless a variant is forced, layers of
- * at most 64 output channels with reductions of 16 .. 384 and many pixels (first layers), which have a kernel of their
- * own where the pick is an unsplit gather variant; polydl_get_last_tile then still reports that pick. */
+ * at most 64 output channels with reductions of 24 .. 384 and many pixels (first layers), which have a kernel of their
+ * own where the pick is an unsplit variant of algo 0 or 1; polydl_get_last_tile then still reports that pick. */
 int polydl_conv2d_fwd(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                       const float *in, const float *wt, const float *bias, float *out,
                       int fuse_relu, void *stream);

@@ -267,6 +267,13 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
             g_last = cfg;
             return POLYDL_OK;
         }
+        if (!forced && cfg.algo != 2 && cfg.split_k <= 1 && conv_thin_pays(q)) {
+            const hipError_t te = conv_thin_launch(q, (hipStream_t)stream);
+            if (te != hipSuccess) return failed(te);
+            std::lock_guard<std::mutex> lk(g_mu);
+            g_last = cfg;
+            return POLYDL_OK;
+        }
         if (cfg.algo == 1) {
             if (pre_act != POLYDL_ACT_NONE) return POLYDL_ERR_UNSUPPORTED;   // a forced patch-kernel variant
             const PatchVariant *pv = find_patch_variant(cfg);
@@ -283,13 +290,6 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
         }
         const Variant *v = find_variant(cfg);
         if (!v) return POLYDL_ERR_UNSUPPORTED;
-        if (!forced && cfg.split_k <= 1 && conv_thin_pays(q)) {
-            const hipError_t te = conv_thin_launch(q, (hipStream_t)stream);
-            if (te != hipSuccess) return failed(te);
-            std::lock_guard<std::mutex> lk(g_mu);
-            g_last = cfg;
-            return POLYDL_OK;
-        }
         if (!conv_tile_in_range(q, v->bm, v->bn)) return POLYDL_ERR_UNSUPPORTED;
         if (cfg.layout == 2) {
             if (!q.has_tap || !gather_tap_major_fits(q, v->bk)) return POLYDL_ERR_UNSUPPORTED;

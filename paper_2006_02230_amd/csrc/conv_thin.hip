@@ -300,14 +300,16 @@ static size_t thin_lds_bytes(int steps) { return (size_t)steps * 384 * 16 + (siz
 // bits, 24 steps the LDS.  Below 6 units per compute unit (of its eight waves) the picked tile is faster: 7x7 3 -> 64 stride 2
 // with 980 units 18.3 us against 21.5 here, 1568: 27.9 and 22.9, 6272: 76 and 61, 16072: 194 and 146; 3x3 16 -> 64 on 56x56
 // with 1274: 19.4 and 20.4, 1813: 25.3 and 21.8; 5x5 6 -> 32 with 1511: 22.4 and 20.0, 16002: 162 and 122; 3x3 3 -> 32 with
-// 9016: 49 and 32.  Nine shapes of 16 .. 384 reduction rows and 1500 .. 16000 units: 1.0 .. 1.5 times as fast.
+// 9016: 49 and 32.  Twenty shapes of 24 .. 384 reduction rows and 1536 .. 16000 units: 1.0 .. 1.5 times as fast, whether the
+// pick was a gather or a row-patch variant (18 rows, 1600 units: 11.7 and 12.0).  Below 128 rows, where the picks use the fp32
+// instruction, the error against 64 bits falls with it (72 rows 1.56e-7 -> 0.58e-7).
 // 1x1 layers read their pixels in whole lines, which the staged kernel does as well: below 128 channels it is the faster
 // one (64 -> 64 on 56x56 with 2401 units 17.9 us against 21.0), above it as fast with three units a wave and more
 // (256 -> 64 with 1813 units 40.7 and 30.6, 3087: 60.5 and 54, 6223: 122.8 and 125).
 bool conv_thin_pays(const ConvProblem &q)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S, PQ = (int64_t)q.P * q.Q, units = ((int64_t)q.N * PQ + 63) / 64, cus = compute_units();
-    if (q.K > kThinRows || q.R * q.S > 63 || Kg < 16 || Kg > 24 * 16 || units < 6 * cus) return false;
+    if (q.K > kThinRows || q.R * q.S > 63 || Kg < 24 || Kg > 24 * 16 || units < 6 * cus) return false;
     if (q.R * q.S == 1 && (Kg < 128 || units > 16 * cus)) return false;
     // the images 64 pixels touch, read and written, within 31-bit offsets
     const int64_t images = 64 / PQ + 2;

@@ -22,7 +22,7 @@ def P():
 
 # 98304 pixels (1536 units of 64) and more take the kernel on a card of 256 compute units
 SHAPES = [synth.ConvShape("first_layer", 2, 3, 450, 451, 64, 7, 7, 2, 3),        # odd rows, a last unit of 4 pixels
-          synth.ConvShape("two_steps", 1, 2, 320, 321, 50, 3, 3, 1, 1),          # 18 rows: the second step nearly empty
+          synth.ConvShape("two_steps", 1, 3, 320, 321, 50, 3, 3, 1, 1),          # 27 rows
           synth.ConvShape("63_taps", 1, 6, 318, 331, 33, 7, 9, 1, 4),            # every mask bit; 378 rows, the longest
           synth.ConvShape("strided_45_taps", 3, 4, 560, 549, 64, 5, 9, 3, 3),
           synth.ConvShape("no_padding", 4, 8, 161, 163, 64, 3, 3, 1, 0),
@@ -68,3 +68,13 @@ def test_values_the_split_cannot_hold(P, case):
     assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True)
     # 75 sequential roundings where a unit is recomputed with fp32 instructions, the last one of the store
     assert (np.abs(got[fin] - want[fin]) <= (75 + 2) * 2.0 ** -24 * ab[fin]).all()
+
+
+def test_short_reduction_into_many_channels(P):
+    # the fp32 gather kernel with its row table on a grid that fills the card: padding at every image border reads as zero
+    s = synth.ConvShape("b", 64, 3, 28, 15, 512, 5, 5, 1, 2)
+    x, w, b = synth.conv_inputs(s, seed=9, dist="normal", bias=True)
+    want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad)
+    dx, dw, db = dev(x), dev(w), dev(b)
+    for _ in range(4):
+        assert oracle.scaled_error(host(P.conv2d_fwd(dx, dw, db, stride=s.stride, pad=s.pad)), want, ab) <= FP32_TOL
