@@ -45,8 +45,8 @@ struct ThinWave {
     uint32_t seen;
 };
 
-// loads the value of one row (byte distance and tap number from the table) of pixel block NB
-__device__ __forceinline__ float thin_load(const ThinPixel &px, __amdgpu_buffer_rsrc_t ri, uint32_t dist, uint32_t tap)
+// loads the value of one row (tap number and byte distance from the table; why in this order: conv_gather.hpp)
+__device__ __forceinline__ float thin_load(const ThinPixel &px, __amdgpu_buffer_rsrc_t ri, uint32_t tap, uint32_t dist)
 {
     const uint64_t taps = ((uint64_t)px.hi << 32) | px.lo;
     return buf_load1(ri, (px.off + dist) | ((uint32_t)(taps >> tap) << 31));   // the shift drops the other bits
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, j = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int steps = p.steps;
-    uint2 *tab = reinterpret_cast<uint2 *>(At + steps * 384);     // (byte distance, tap number) of every row, three steps more than there are
+    uint2 *tab = reinterpret_cast<uint2 *>(At + steps * 384);     // (tap number, byte distance) of every row, three steps more than there are
     float *bias = reinterpret_cast<float *>(tab + (steps + 3) * 16);
 
     // Three octets of a filter row in flight per thread (rows need not be aligned: buffer loads only need dwords).  Value by
@@ -131,12 +131,12 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
         }
     }
     for (int kg = tid; kg < (steps + 3) * 16; kg += kThinThreads) {
-        uint2 e = {0u, 63u};      // never a tap: always outside
+        uint2 e = {63u, 0u};      // never a tap: always outside
         if (kg < p.Kg) {
             const uint32_t c = fast_div((uint32_t)kg, p.magic_RS, p.one_RS), rs = (uint32_t)kg - c * (uint32_t)p.RS;
             const uint32_t r = fast_div(rs, p.magic_S, p.one_S), s = rs - r * (uint32_t)p.S;
-            e.x = (c * (uint32_t)p.HW + r * (uint32_t)p.W + s) * 4u;
-            e.y = rs;
+            e.x = rs;
+            e.y = (c * (uint32_t)p.HW + r * (uint32_t)p.W + s) * 4u;
         }
         tab[kg] = e;
     }
@@ -253,8 +253,7 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
                     a[mb] = 32 * mb + j < p.K && kk < p.Kg ? p.wt[(size_t)(32 * mb + j) * p.Kg + kk] : 0.f;
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb) {
-                    const uint64_t taps = ((uint64_t)px[nb].hi << 32) | px[nb].lo;
-                    b[nb] = apply_act(buf_load1(ri, (px[nb].off + e.x) | ((uint32_t)(taps >> e.y) << 31)), p.pre_act);
+                    b[nb] = apply_act(thin_load(px[nb], ri, e.x, e.y), p.pre_act);
                 }
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb)
