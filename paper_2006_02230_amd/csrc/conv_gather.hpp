@@ -399,10 +399,9 @@ __device__ __forceinline__ ConvPart conv_part(const ConvKArgs &p)
     return c;
 }
 
-// What follows the reduction: the hand-over of a split reduction's parts, then bias, activation, store.
-// SPLIT: of the kernels on split operands.  The fp32 kernels keep the hand-over in single words they always had: with the
-// wide one their code gave wrong values at image borders (3 -> 512 5x5 on 28x15), for a reason not found yet.
-template <class T, bool SPLIT>
+// What follows the reduction: the hand-over of a split reduction's parts (AHEAD of them requested together), then bias,
+// activation, store.
+template <class T, int AHEAD>
 __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &c, v16f (&acc)[T::MB][T::NB], int tid,
                                             int wm0, int wn0)
 {
@@ -416,17 +415,7 @@ __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &
         const int slot = c.tile - c.first_split_tile;   // scratch tiles and counters are numbered over the split tiles
         float *tile0 = p.partials + (size_t)slot * parts * TILE;
         float *mine = tile0 + (size_t)part * TILE;
-        if constexpr (SPLIT) store_partial_tile<T>(mine, tid, acc);
-        else {
-#pragma unroll
-            for (int bi = 0; bi < T::MB; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < T::NB; ++bj)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        __hip_atomic_store(mine + ((bi * T::NB + bj) * 16 + r) * T::NT + tid, acc[bi][bj][r], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-        }
+        store_partial_tile<T>(mine, tid, acc);
         wait_vmcnt0();   // vmcnt(0): this wave's device-scope stores have completed
         __syncthreads();
         if (tid == 0)
@@ -435,8 +424,7 @@ __device__ __forceinline__ void conv_finish(const ConvKArgs &p, const ConvPart &
         if (__builtin_amdgcn_readfirstlane(s_arrived) != (unsigned)parts - 1u) return;   // not the last part
         if (tid == 0)               // leave the counter at zero for the next launch
             __hip_atomic_store(p.counters + slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if constexpr (SPLIT) sum_partial_tiles<T, kPartsAhead<T>>(tile0, parts, tid, acc);
-        else sum_partial_words<T>(tile0, parts, TILE, tid, acc);
+        sum_partial_tiles<T, AHEAD>(tile0, parts, tid, acc);
     }
     // epilogue.  The lane owns NB adjacent pixels starting at colg for 16*MB output channels.
     // Addresses are a per-lane byte offset from the first image the tile touches plus a uniform

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(T::NT) void conv_kernel(ConvKArgs p)
             for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
 
     gemm_mainloop<T, false>(lds, al, bl, acc, c.kbegin, c.kend, tid, wm0, wn0);
-    conv_finish<T, false>(p, c, acc, tid, wm0, wn0);
+    conv_finish<T, 1>(p, c, acc, tid, wm0, wn0);
 }
 
 // The same with the products formed on the bfloat16 matrix cores (split_core.hpp), for reductions of
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvK
                 for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
         gemm_mainloop<T, false>(reinterpret_cast<float *>(lds), al, bl, acc, c.kbegin, c.kend, tid, wm0, wn0);
     }
-    conv_finish<T, true>(p, c, acc, tid, wm0, wn0);
+    conv_finish<T, kPartsAhead<T>>(p, c, acc, tid, wm0, wn0);
 }
 
 template <class T>

@@ -435,7 +435,7 @@ __device__ __forceinline__ void gemm_mainloop(float *lds, AL &al, BL &bl, v16f (
 
 // Partial accumulator tiles of a split reduction, in register order: WIDTH registers of a lane together, the lanes' groups
 // consecutive.  Stores and loads are device-scope (sc1).  WIDTH 4: 128-bit accesses, a quarter of the instructions of the
-// hand-over (64x64 tiles in 4 parts, 12.8 -> 12.1 us for a layer of one image; 8 parts of 128x2048x4096 27.0 -> 24.3 with
+// hand-over (64x64 tiles in 4 parts, 12.8 -> 12.1 us for a layer of one image; 8 parts of 128x2048x4096 26.5 -> 23.8 with
 // AHEAD below).  Workgroups of 512 threads keep single words: with the wide ones 1024 -> 2048 1x1/2 in two parts
 // of 256x128 tiles was 1.7 % slower (53.1 -> 54.0 us).
 constexpr int kDeviceScope = 16;   // sc1 in the cache policy of a raw buffer access
@@ -503,44 +503,11 @@ __device__ __forceinline__ void sum_partial_tiles(const float *tile0, int parts,
             for (int e = 0; e < U * W; ++e) acc[e / 16 / T::NB][e / 16 % T::NB][e % 16] += v[n][e / W][e % W];
     }
 }
-// AHEAD of the kernels that work on 1, 2 and 4 blocks a wave, within the registers their main loops take anyway
+// AHEAD of the split-operand kernels of 1, 2 and 4 blocks a wave, within the registers their main loops take anyway.  The fp32
+// convolution kernels request one part at a time: their main loops are smaller, and with more the 64x64 tile took 70
+// registers instead of 63 (7 waves a SIMD instead of 8).
 template <class T>
 constexpr int kPartsAhead = T::MB * T::NB == 1 ? 4 : T::MB * T::NB == 2 ? 3 : 1;
-
-// The same over tiles of single words (fp32 convolution kernels): sum of the `parts` partial accumulator tiles of one output tile, in index order (so the result
-// does not depend on which part arrived last).  Tiles lie TILE floats apart, each in register
-// order (thread-contiguous).  The loads are device-scope.  (Requesting part i+1 before part i is
-// added measured no faster: other workgroups fill the compute unit while the last one of a tile sums.)
-template <class T>
-__device__ __forceinline__ void sum_partial_words(const float *tile0, int parts, size_t TILE, int tid,
-                                                  v16f (&acc)[T::MB][T::NB])
-{
-    constexpr int R = T::MB * T::NB * 16, NT = T::NT;
-    auto fetch = [&](float (&dst)[R], int sp) {
-        const float *part = tile0 + (size_t)sp * TILE + tid;
-#pragma unroll
-        for (int i = 0; i < R; ++i) dst[i] = __hip_atomic_load(part + (size_t)i * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto add = [&](const float (&src)[R]) {
-#pragma unroll
-        for (int bi = 0; bi < T::MB; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < T::NB; ++bj)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[bi][bj][r] += src[(bi * T::NB + bj) * 16 + r];
-    };
-#pragma unroll
-    for (int bi = 0; bi < T::MB; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < T::NB; ++bj)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
-    float a[R];
-    for (int sp = 0; sp < parts; ++sp) {
-        fetch(a, sp);
-        add(a);
-    }
-}
 
 // Row (inside the workgroup tile) of accumulator register r of row block bi for this lane: a
 // 32x32 result keeps column lane%32 in every register and row 8*(r/4) + 4*(lane/32) + r%4 in

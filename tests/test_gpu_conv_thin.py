@@ -78,3 +78,22 @@ def test_short_reduction_into_many_channels(P):
     dx, dw, db = dev(x), dev(w), dev(b)
     for _ in range(4):
         assert oracle.scaled_error(host(P.conv2d_fwd(dx, dw, db, stride=s.stride, pad=s.pad)), want, ab) <= FP32_TOL
+
+
+@pytest.mark.parametrize("C", [3, 4], ids=["filter_rows_of_75", "filter_rows_of_100"])   # dword and 128-bit filter loads
+def test_short_reduction_on_every_tile(P, C):
+    # every fp32 gather variant on a grid of several rounds: whole tiles, cut leftover tiles, two parts; every output compared
+    import torch
+    s = synth.ConvShape("b", 64, C, 28, 15, 512, 5, 5, 1, 2)
+    x, w, b = synth.conv_inputs(s, seed=11 + C, dist="normal", bias=True)
+    want, ab = (torch.from_numpy(a).cuda() for a in oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad))
+    dx, dw, db = dev(x), dev(w), dev(b)
+    for v in P.variants(0):
+        if v.algo != 0:
+            continue
+        for v.split_k, v.raster in ((1, 1), (1, 3), (2, 1)):
+            P.set_tile_override(v)
+            first = P.conv2d_fwd(dx, dw, db, stride=s.stride, pad=s.pad)
+            assert bool(((first.double() - want).abs() <= FP32_TOL * ab).all()), v
+            assert torch.equal(first, P.conv2d_fwd(dx, dw, db, stride=s.stride, pad=s.pad)), v
+    P.set_tile_override(None)
