@@ -16,7 +16,11 @@
 // Bound: 24 matrix instructions a step (768 cycles a wave, two waves a SIMD) take 1.3 .. 1.7 us: the card's power (the
 // products of the first figure come to 0.8 PFLOP/s), 145 vector instructions, and 16 gathered loads whose lanes touch six
 // lines each.  Loads two steps ahead instead of one (16 more registers, a few spilled outside the loop) were 3 .. 5 % slower.
-// Up to 16 of 64 reduction rows more than the layer has are multiplied (whole pairs of steps).
+// Up to 31 reduction rows more than the layer has are multiplied (whole pairs of steps).
+// Values the split cannot hold (thin_redo): a filter with one sends every unit through the fp32 instruction, from the filter in
+// LDS: 3 -> 64 7x7/2 above 107 us (value by value from memory 207; the staged tiles 173), 32 -> 64 3x3 on 56x56 56 (120; 80),
+// 3 -> 64 3x3 on 112x112 34 (48; 32.5).  A pixel with one sends its block of 32 pixels there: 78 (112; 74), 39.5 (70; 37.5),
+// 27.5 (35; 32).
 #include "conv_gather.hpp"
 
 namespace polydl {
@@ -42,7 +46,7 @@ struct ThinWave {
     u32x4 a[2][2], b[2][2][3];    // two filter planes in turn [..][row block]; pixel planes [step parity][pixel block][plane]
     float raw[2][8];              // values of the next step
     uint4 row[2];                 // two table entries, of rows whose values are loaded next, and the two behind them
-    uint32_t seen;
+    uint32_t seen[2];             // per pixel block
 };
 
 // loads the value of one row (tap number and byte distance from the table; why in this order: conv_gather.hpp)
@@ -64,8 +68,8 @@ __device__ __forceinline__ void thin_step(ThinWave &w, const ThinPixel (&px)[2],
         for (int i = 0; i < 16; ++i) w.raw[i / 8][i % 8] = apply_act(w.raw[i / 8][i % 8], pre_act);
     }
     SplitUnit<8> u[2];
-    u[0].seen = w.seen;
-    u[1].seen = 0;
+    u[0].seen = w.seen[0];
+    u[1].seen = w.seen[1];
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, 24>([&](auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value, P = i / 4, mb = i % 4 / 2, nb = i % 2;
@@ -90,7 +94,72 @@ __device__ __forceinline__ void thin_step(ThinWave &w, const ThinPixel (&px)[2],
     for (int n = 0; n < 2; ++n)
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) w.b[S ^ 1][n][pl] = (u32x4){u[n].p[pl][0], u[n].p[pl][1], u[n].p[pl][2], u[n].p[pl][3]};
-    w.seen = u[0].seen | u[1].seen;
+    w.seen[0] = u[0].seen;
+    w.seen[1] = u[1].seen;
+}
+
+// Pixel blocks NB0 .. NB0 + NBS - 1 on the fp32 matrix cores, for values the split cannot hold.  The two halves of the wave take
+// the rows they have in the planes too.  LOSSY: the filter lies in LDS as it is, 64 values a row; otherwise its planes add up
+// to it.  16 reduction rows a step, the pixels of the next one requested before this one's products.
+template <bool LOSSY, int NB0, int NBS>
+__device__ __forceinline__ void thin_redo(v16f (&acc)[2][2], const ThinPixel (&px)[2], __amdgpu_buffer_rsrc_t ri, const u32x4 *at0,
+                                          const float *filter, const uint4 *tab0, int steps, int pre_act)
+{
+    float raw[2][NBS][8];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int n = 0; n < NBS; ++n)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mb][NB0 + n][r] = 0.f;
+    auto load = [&](auto set, int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 e = tab0[8 * t + i];
+#pragma unroll
+            for (int n = 0; n < NBS; ++n) {
+                raw[decltype(set)::value][n][2 * i] = thin_load(px[NB0 + n], ri, e.x, e.y);
+                raw[decltype(set)::value][n][2 * i + 1] = thin_load(px[NB0 + n], ri, e.z, e.w);
+            }
+        }
+    };
+    auto step = [&](auto set, int t) __attribute__((always_inline)) {
+        constexpr int S = decltype(set)::value;
+        load(std::integral_constant<int, S ^ 1>{}, t + 1);   // the table holds three steps more
+        float a[2][8];
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+            if constexpr (LOSSY) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) a[mb][i] = filter[(16 * t + i) * kThinRows + 32 * mb];
+            } else {
+                const u32x4 *at = at0 + t * 384 + 32 * mb;
+                const u32x4 hi = at[0], mid = at[128], lo = at[256];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    auto low = [](uint32_t w) __attribute__((always_inline)) { return __builtin_bit_cast(float, w << 16); };
+                    auto high = [](uint32_t w) __attribute__((always_inline)) { return __builtin_bit_cast(float, w & 0xFFFF0000u); };
+                    a[mb][2 * i] = low(hi[i]) + (low(mid[i]) + low(lo[i]));
+                    a[mb][2 * i + 1] = high(hi[i]) + (high(mid[i]) + high(lo[i]));
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int n = 0; n < NBS; ++n) {
+                const float b = apply_act(raw[S][n][i], pre_act);
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+                    acc[mb][NB0 + n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mb][i], b, acc[mb][NB0 + n], 0, 0, 0);
+            }
+    };
+    load(std::integral_constant<int, 0>{}, 0);
+#pragma unroll 1
+    for (int t = 0; t < steps; t += 2) {
+        step(std::integral_constant<int, 0>{}, t);
+        step(std::integral_constant<int, 1>{}, t + 1);
+    }
 }
 
 __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArgs p)
@@ -104,32 +173,39 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
 
     // Three octets of a filter row in flight per thread (rows need not be aligned: buffer loads only need dwords).  Value by
     // value, with a wait per octet, this took 12 us of every launch.
-    bool lossy = false;
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.wt, (uint64_t)p.K * p.Kg * 4);
-    for (int idx0 = tid; idx0 < steps * 2 * kThinRows; idx0 += 3 * kThinThreads) {
-        v4f raw[3][2];
+    auto filter_octets = [&](auto &&use) __attribute__((always_inline)) {
+        for (int idx0 = tid; idx0 < steps * 2 * kThinRows; idx0 += 3 * kThinThreads) {
+            v4f raw[3][2];
 #pragma unroll
-        for (int n = 0; n < 3; ++n) {
-            const int idx = idx0 + n * kThinThreads, o = idx / kThinRows, k = idx % kThinRows;
+            for (int n = 0; n < 3; ++n) {
+                const int idx = idx0 + n * kThinThreads, o = idx / kThinRows, k = idx % kThinRows;
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                raw[n][h] = buf_load4(rw, k < p.K && 8 * o + 4 * h < p.Kg ? (uint32_t)(k * p.Kg + 8 * o + 4 * h) * 4u : kOobOffset);
+                for (int h = 0; h < 2; ++h)
+                    raw[n][h] = buf_load4(rw, k < p.K && 8 * o + 4 * h < p.Kg ? (uint32_t)(k * p.Kg + 8 * o + 4 * h) * 4u : kOobOffset);
+            }
+#pragma unroll
+            for (int n = 0; n < 3; ++n) {
+                const int idx = idx0 + n * kThinThreads, o = idx / kThinRows, k = idx % kThinRows;
+                if (idx >= steps * 2 * kThinRows) break;
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = 8 * o + i < p.Kg ? raw[n][i / 4][i % 4] : 0.f;   // not the next row's
+                use(o, k, v);
+            }
         }
+    };
+    bool lossy = false;
+    filter_octets([&](int o, int k, const float (&v)[8]) __attribute__((always_inline)) {
+        SplitUnit<8> s;
+        static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { s.template step<decltype(st)::value>(v); });
+        // or an infinity, a NaN, a value that rounds to an infinity: its remainder's exponent is all ones (so may be that of
+        // several remainders together, from values of 2^17 on; then the filter is only used as it is without need)
+        lossy |= split_lossy(s.seen) || (s.seen & 0x7F800000u) == 0x7F800000u;
 #pragma unroll
-        for (int n = 0; n < 3; ++n) {
-            const int idx = idx0 + n * kThinThreads, o = idx / kThinRows, k = idx % kThinRows;
-            if (idx >= steps * 2 * kThinRows) break;
-            float v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = 8 * o + i < p.Kg ? raw[n][i / 4][i % 4] : 0.f;   // not the next row's
-            SplitUnit<8> s;
-            static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { s.template step<decltype(st)::value>(v); });
-            lossy |= split_lossy(s.seen);
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl)
-                At[((o >> 1) * 3 + pl) * 128 + (o & 1) * 64 + k] = (u32x4){s.p[pl][0], s.p[pl][1], s.p[pl][2], s.p[pl][3]};
-        }
-    }
+        for (int pl = 0; pl < 3; ++pl)
+            At[((o >> 1) * 3 + pl) * 128 + (o & 1) * 64 + k] = (u32x4){s.p[pl][0], s.p[pl][1], s.p[pl][2], s.p[pl][3]};
+    });
     for (int kg = tid; kg < (steps + 3) * 16; kg += kThinThreads) {
         uint2 e = {63u, 0u};      // never a tap: always outside
         if (kg < p.Kg) {
@@ -142,11 +218,20 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
     }
     if (tid < kThinRows) bias[tid] = p.bias && tid < p.K ? p.bias[tid] : 0.f;
     lossy = __syncthreads_or(lossy);
+    float *filter = reinterpret_cast<float *>(At);
+    if (lossy) {   // uniform: a filter value the split cannot hold; the planes make room for the filter as it is
+        filter_octets([&](int o, int k, const float (&v)[8]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) filter[(8 * o + i) * kThinRows + k] = v[i];
+        });
+        __syncthreads();
+    }
 
     // the wave's run of units, and what is left over one each, to first waves of workgroups before second ones
     const uint32_t first = (blockIdx.x * (kThinThreads / 64) + wave) * p.per, extra = (uint32_t)wave * gridDim.x + blockIdx.x;
     const uint32_t count = p.per + (extra < p.rem ? 1u : 0u);
     const u32x4 *at0 = At + half * 64 + j;
+    const float *filter0 = filter + half * 8 * kThinRows + j;   // the lane's values of step t: filter0[(16 t + i) * 64]
     const uint4 *tab0 = reinterpret_cast<const uint4 *>(tab + 8 * half);   // the lane's rows of step t: tab0 + 8 t
     const uint32_t KPQ = (uint32_t)p.K * (uint32_t)p.PQ;
     const int lead = (p.pad * p.W + p.pad) * 4;   // tap (0,0) may lie this far before the image
@@ -177,90 +262,73 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
                 px[nb].hi = (uint32_t)(taps >> 32) | 0x80000000u;
             }
         }
-        ThinWave w;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) { w.hi[mb][nb][r] = 0.f; w.lo[mb][nb][r] = 0.f; }
-        w.seen = 0;
-        auto load_all = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint4 e = tab0[8 * t + i];
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    w.raw[nb][2 * i] = thin_load(px[nb], ri, e.x, e.y);
-                    w.raw[nb][2 * i + 1] = thin_load(px[nb], ri, e.z, e.w);
-                }
-            }
-        };
-        load_all(0);
-        w.a[0][0] = at0[0];
-        w.a[0][1] = at0[32];
-        if (p.pre_act != POLYDL_ACT_NONE) {   // uniform
-#pragma unroll
-            for (int i = 0; i < 16; ++i) w.raw[i / 8][i % 8] = apply_act(w.raw[i / 8][i % 8], p.pre_act);
-        }
-#pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            SplitUnit<8> s;
-            s.seen = w.seen;
-            static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { s.template step<decltype(st)::value>(w.raw[n]); });
-            w.seen = s.seen;
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) w.b[0][n][pl] = (u32x4){s.p[pl][0], s.p[pl][1], s.p[pl][2], s.p[pl][3]};
-        }
-        load_all(1);
-        const u32x4 *at = at0;
-        const uint4 *tb = tab0 + 8 * 2;
-        w.row[0] = tb[0];
-        // in pairs, one set of pixel planes each; what the last step prepares is never multiplied
-        for (int t = 0; t < steps; t += 2) {
-            thin_step<0>(w, px, ri, at, tb, p.pre_act);
-            thin_step<1>(w, px, ri, at + 384, tb + 8, p.pre_act);
-            at += 768;
-            tb += 16;
-        }
-
         v16f acc[2][2];
-        float f = 0.f;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    acc[mb][nb][r] = w.hi[mb][nb][r] + w.lo[mb][nb][r];
-                    f = __builtin_fmaf(acc[mb][nb][r], 0.f, f);
-                }
-        if (__ballot(lossy || !(f == 0.f) || split_lossy(w.seen)) != 0) {
-            // values the split cannot hold: the unit once more on the fp32 matrix cores, operands from memory
+        bool again[2] = {false, false};
+        if (__builtin_expect(!lossy, 1)) {
+            ThinWave w;
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
-#pragma unroll 1
-            for (int k = 0; k < p.Kg; k += 2) {
-                const int kk = k + half;
-                const uint2 e = tab[kk];
-                float a[2], b[2];
+                    for (int r = 0; r < 16; ++r) { w.hi[mb][nb][r] = 0.f; w.lo[mb][nb][r] = 0.f; }
+            auto load_all = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
-                    a[mb] = 32 * mb + j < p.K && kk < p.Kg ? p.wt[(size_t)(32 * mb + j) * p.Kg + kk] : 0.f;
+                for (int i = 0; i < 4; ++i) {
+                    const uint4 e = tab0[8 * t + i];
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    b[nb] = apply_act(thin_load(px[nb], ri, e.x, e.y), p.pre_act);
+                    for (int nb = 0; nb < 2; ++nb) {
+                        w.raw[nb][2 * i] = thin_load(px[nb], ri, e.x, e.y);
+                        w.raw[nb][2 * i + 1] = thin_load(px[nb], ri, e.z, e.w);
+                    }
                 }
+            };
+            load_all(0);
+            w.a[0][0] = at0[0];
+            w.a[0][1] = at0[32];
+            if (p.pre_act != POLYDL_ACT_NONE) {   // uniform
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
+                for (int i = 0; i < 16; ++i) w.raw[i / 8][i % 8] = apply_act(w.raw[i / 8][i % 8], p.pre_act);
+            }
 #pragma unroll
-                    for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mb], b[nb], acc[mb][nb], 0, 0, 0);
+            for (int n = 0; n < 2; ++n) {
+                SplitUnit<8> s;
+                static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { s.template step<decltype(st)::value>(w.raw[n]); });
+                w.seen[n] = s.seen;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) w.b[0][n][pl] = (u32x4){s.p[pl][0], s.p[pl][1], s.p[pl][2], s.p[pl][3]};
+            }
+            load_all(1);
+            const u32x4 *at = at0;
+            const uint4 *tb = tab0 + 8 * 2;
+            w.row[0] = tb[0];
+            // in pairs, one set of pixel planes each; what the last step prepares is never multiplied
+            for (int t = 0; t < steps; t += 2) {
+                thin_step<0>(w, px, ri, at, tb, p.pre_act);
+                thin_step<1>(w, px, ri, at + 384, tb + 8, p.pre_act);
+                at += 768;
+                tb += 16;
+            }
+            float f[2] = {0.f, 0.f};
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        acc[mb][nb][r] = w.hi[mb][nb][r] + w.lo[mb][nb][r];
+                        f[nb] = __builtin_fmaf(acc[mb][nb][r], 0.f, f[nb]);
+                    }
+            if (__builtin_expect(__ballot(!(f[0] + f[1] == 0.f) || split_lossy(w.seen[0] | w.seen[1])) != 0, 0)) {
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) again[nb] = __ballot(!(f[nb] == 0.f) || split_lossy(w.seen[nb])) != 0;
             }
         }
+        // all uniform
+        if (__builtin_expect(lossy, 0)) thin_redo<true, 0, 2>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
+        else if (__builtin_expect(again[0] && again[1], 0)) thin_redo<false, 0, 2>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
+        else if (__builtin_expect(again[0], 0)) thin_redo<false, 0, 1>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
+        else if (__builtin_expect(again[1], 0)) thin_redo<false, 1, 1>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
         // bias, activation, store: the lane's channels are 32 mb + 8 (r / 4) + 4 half + r % 4; a half-wave stores 128 consecutive bytes
         const uint64_t oskip = (uint64_t)img0 * KPQ * 4;
         const __amdgpu_buffer_rsrc_t ro = make_rsrc(reinterpret_cast<char *>(p.out) + oskip, p.out_bytes - oskip);

@@ -97,3 +97,38 @@ def test_short_reduction_on_every_tile(P, C):
             assert bool(((first.double() - want).abs() <= FP32_TOL * ab).all()), v
             assert torch.equal(first, P.conv2d_fwd(dx, dw, db, stride=s.stride, pad=s.pad)), v
     P.set_tile_override(None)
+
+
+# two steps, the most steps, an odd number of pairs; 98304 pixels and a few
+REDO = [synth.ConvShape("two_steps", 1, 3, 320, 321, 64, 3, 3, 1, 1), synth.ConvShape("24_steps", 1, 6, 318, 331, 33, 7, 9, 1, 4),
+        synth.ConvShape("six_steps", 9, 9, 105, 105, 40, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("where", ["first_block", "second_block", "both_blocks", "filter_tiny", "filter_rounds_to_inf"])
+@pytest.mark.parametrize("s", REDO, ids=lambda s: s.name)
+def test_recomputed_pixel_blocks(P, s, where):
+    # which of a unit's two blocks of 32 pixels is recomputed, and from which copy of the filter; the rest of the unit stays
+    x, w, b = synth.conv_inputs(s, seed=21, dist="normal", bias=True)
+    before = None
+    if where == "filter_rounds_to_inf":
+        x *= np.float32(1e-3)
+        w[3, 1, 0, 0] = np.finfo(np.float32).max    # its first part is an infinity
+    elif where == "filter_tiny":
+        w[s.K - 1] *= np.float32(1e-36)
+        w[0] *= np.float32(2.0 ** 40)
+    else:
+        before = host(P.conv2d_fwd(dev(x), dev(w), dev(b), stride=s.stride, pad=s.pad, pre_act="relu6"))
+        # one pixel per recomputed block, far from the others' taps; stride 1 and padding: outputs lie where the inputs do
+        for q in {"first_block": [8], "second_block": [40], "both_blocks": [8, 55]}[where]:
+            r, c = divmod((s.H // 2 * s.W // 64) * 64 + q, s.W)
+            x[0, :, r, c] = np.float32(1.17e-38) * np.float32(1.3)
+    want, ab = oracle.conv2d_fwd(np.clip(x, 0, 6), w, bias=b, stride=s.stride, pad=s.pad)
+    got = host(P.conv2d_fwd(dev(x), dev(w), dev(b), stride=s.stride, pad=s.pad, pre_act="relu6"))
+    # one rounding per product and addition of a sequential sum bounds either instruction
+    assert (np.abs(got - want) <= (s.C * s.R * s.S + 2) * 2.0 ** -24 * ab).all()
+    if before is not None:
+        far = np.ones(got.shape, bool)
+        for q in (8, 40, 55):
+            r, c = divmod((s.H // 2 * s.W // 64) * 64 + q, s.W)
+            far[0, :, max(0, r - s.R):r + s.R + 1] = False
+        assert np.array_equal(got[far], before[far])
