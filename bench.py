@@ -50,8 +50,8 @@ def csrc_digest():
 def products_peak(tile, reduction, thin=False):
     """Peak of the instruction that forms the products: tiles of stage depth 16 and wave tiles up to 64x64 split
     fp32 operands for the bf16 matrix cores from a reduction of 128 on (512 for 1x1 layers of at most 64 output
-    channels: thin; 3 for SGEMM, whose caller passes no less), the pointwise kernel always."""
-    split = tile.algo == 2 or (tile.algo == 0 and tile.bk == 16 and tile.wm * tile.wn <= 64 * 64 and
+    channels: thin; 3 for SGEMM, whose caller passes no less), the pointwise and the first-layer kernel always."""
+    split = tile.algo in (2, 3) or (tile.algo == 0 and tile.bk == 16 and tile.wm * tile.wn <= 64 * 64 and
                                reduction >= (512 if thin else 128))
     return SPLIT_PEAK_TFLOPS if split else FP32_MFMA_PEAK_TFLOPS
 
@@ -348,11 +348,12 @@ def main():
                             cold_frac_roofline=round(L["flops"] / (cms * 1e-3) / 1e12 / ceiling, 4))
             del sets
         if args.sweep:
-            # every candidate the picker ranks, timed; the model's prediction beside it
+            # every candidate the picker ranks, and the first-layer kernel where it took their place, timed; the model's
+            # prediction beside it
             shape = tuple(L["shape"])[1:]
             cands = []
             t_sweep = time.perf_counter()
-            for v in P.conv_candidates(shape, tap=L["wt"] is not None):
+            for v in P.conv_candidates(shape, tap=L["wt"] is not None) + ([P.TileCfg(**tile)] if tile["algo"] == 3 else []):
                 try:
                     P.set_tile_override(v)
                     run_layer(L)
@@ -776,7 +777,7 @@ def main():
                      "traffic_unit": "bytes per suite pass (L2 fetch + write-back); algorithmic: %d" % total_bytes,
                      "traffic_source": "not measured in this run: counters of an earlier rocprofv3 --pmc run of the "
                                        "same kernel sources (digest checked), null when the sources have changed",
-                     "kernel": "polydl::conv_split_kernel / conv_kernel / conv_point_kernel as picked per layer (all 8 "
+                     "kernel": "polydl::conv_split_kernel / conv_kernel / conv_point_kernel / conv_thin_kernel as picked per layer (all 8 "
                                "layers, nominal 2*N*K*P*Q*C*R*S flops / sum of per-layer mean launch durations)"},
         "cpu_baseline": cpu,
         "layers": rows,

@@ -90,7 +90,14 @@ typedef struct polydl_tile_cfg {
                          stays in LDS, a wave loads 64 pixels straight into registers and forms
                          the output channels 32 at a time.  One variant (bm = wm = 32, bn = wn = 64,
                          bk = 0, split_k = 1, raster = 0, cb = 0); forced on any other problem the
-                         call returns POLYDL_ERR_UNSUPPORTED */
+                         call returns POLYDL_ERR_UNSUPPORTED;
+                         3: first-layer kernel for K <= 64, at most 63 taps and C*R*S <= 384: the
+                         split filter stays in LDS, a wave gathers 64 pixels' values straight into
+                         registers.  One variant (bm = bn = wm = wn = 64, bk = 0, split_k = 1,
+                         raster = 0, cb = 0), not enumerated and not ranked: unless a variant is forced
+                         it takes the place of an unsplit pick of algo 0 or 1 where it is known to be
+                         faster (reductions of 24 and more, many pixels); forced on any other problem
+                         the call returns POLYDL_ERR_UNSUPPORTED */
     int cb;           /* algo 1: input channels per stage, even, >= 2; 0 lets the library choose */
 } polydl_tile_cfg;
 
@@ -105,9 +112,8 @@ typedef struct polydl_tile_cfg {
  * Accumulation is float32 on the matrix cores; the summation order is unspecified but fixed for
  * a given tile configuration, so repeated calls agree bit for bit.  The gather variants (algo 0) with stage
  * depth 16 and wave tiles up to 64 x 64 form the products of reductions of 128 and more as polydl_sgemm
- * does (three bfloat16 parts per operand, six products, float32 sums).  So do, unless a variant is forced, layers of
- * at most 64 output channels with reductions of 24 .. 384 and many pixels (first layers), which have a kernel of their
- * own where the pick is an unsplit variant of algo 0 or 1; polydl_get_last_tile then still reports that pick. */
+ * does (three bfloat16 parts per operand, six products, float32 sums), and so do the pointwise and the first-layer
+ * kernel (algo 2 and 3). */
 int polydl_conv2d_fwd(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                       const float *in, const float *wt, const float *bias, float *out,
                       int fuse_relu, void *stream);
@@ -120,8 +126,9 @@ int polydl_conv2d_fwd_act(int N, int C, int H, int W, int K, int R, int S, int s
  * case of section "Operator Fusion": an element-wise operator fused with the heavy operator that
  * follows it): out = act(conv(pre_act(in)) + bias), where pre_act (a polydl_act) is applied to
  * every input element as it is read, so the activated input is never written to memory.  Padding
- * contributes zeros (ReLU and ReLU6 of zero).  Served by the gather kernel (algo 0) only: with a
- * forced algo 1 or algo 2 variant and pre_act != POLYDL_ACT_NONE the call returns POLYDL_ERR_UNSUPPORTED. */
+ * contributes zeros (ReLU and ReLU6 of zero).  Served by the gather and the first-layer kernel (algo 0
+ * and 3) only: with a forced algo 1 or algo 2 variant and pre_act != POLYDL_ACT_NONE the call returns
+ * POLYDL_ERR_UNSUPPORTED. */
 int polydl_conv2d_fwd_pre_act(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                               const float *in, const float *wt, const float *bias, float *out,
                               int pre_act /* polydl_act */, int act /* polydl_act */, void *stream);

@@ -258,6 +258,8 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
     };
     auto run = [&]() -> int {
         q.wt_tap = nullptr;    // set below for the variants that read the copy
+        // the first-layer kernel is not among the ranked candidates: it takes the place of an unsplit pick
+        if (!forced && cfg.algo != 2 && cfg.split_k <= 1 && conv_thin_pays(q)) cfg = conv_thin_cfg();
         if (cfg.layout != 0 && !(cfg.layout == 2 && cfg.algo == 0)) return POLYDL_ERR_UNSUPPORTED;
         if (cfg.algo == 2) {
             if (!is_conv_point_cfg(cfg) || !conv_point_fits(q) || !point_aligned) return POLYDL_ERR_UNSUPPORTED;
@@ -267,7 +269,8 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
             g_last = cfg;
             return POLYDL_OK;
         }
-        if (!forced && cfg.algo != 2 && cfg.split_k <= 1 && conv_thin_pays(q)) {
+        if (cfg.algo == 3) {
+            if (!is_conv_thin_cfg(cfg) || !conv_thin_fits(q)) return POLYDL_ERR_UNSUPPORTED;
             const hipError_t te = conv_thin_launch(q, (hipStream_t)stream);
             if (te != hipSuccess) return failed(te);
             std::lock_guard<std::mutex> lk(g_mu);
@@ -648,14 +651,20 @@ int polydl_model_conv2d(int N, int C, int H, int W, int K, int R, int S, int str
     int64_t P, Q;
     if (!conv_dims(N, C, H, W, K, R, S, stride, pad, &P, &Q)) return POLYDL_ERR_BAD_DIMENSION;
     if (!cfg || !report) return POLYDL_ERR_NULL_POINTER;
-    const bool known = cfg->algo == 2 ? is_conv_point_cfg(*cfg)
-                                      : (cfg->algo == 1 ? find_patch_variant(*cfg) != nullptr
-                                                        : (cfg->algo == 0 && find_variant(*cfg) != nullptr));
+    const bool known = cfg->algo == 3   ? is_conv_thin_cfg(*cfg)
+                       : cfg->algo == 2 ? is_conv_point_cfg(*cfg)
+                       : cfg->algo == 1 ? find_patch_variant(*cfg) != nullptr
+                                        : (cfg->algo == 0 && find_variant(*cfg) != nullptr);
     if (!known || !conv_in_range(N, C, H, W, K, R, S, stride, pad, P, Q)) return POLYDL_ERR_UNSUPPORTED;
     ConvProblem q{N, C, H, W, K, R, S, stride, pad, (int)P, (int)Q, nullptr, nullptr, nullptr, nullptr, 0};
     if (cfg->algo == 2) {
         if (!conv_point_fits(q)) return POLYDL_ERR_UNSUPPORTED;
         model_conv_point(q, report);
+        return POLYDL_OK;
+    }
+    if (cfg->algo == 3) {
+        if (!conv_thin_fits(q)) return POLYDL_ERR_UNSUPPORTED;
+        model_conv_thin(q, report);
         return POLYDL_OK;
     }
     int rc = 0;
@@ -863,10 +872,10 @@ int polydl_set_tile_override(const polydl_tile_cfg *cfg)
         g_have_override = false;
         return POLYDL_OK;
     }
-    const bool known = cfg->algo == 2 ? is_conv_point_cfg(*cfg)
-                                      : (cfg->algo == 1 ? (find_patch_variant(*cfg) != nullptr ||
-                                                           find_patch_bf16_variant(*cfg) != nullptr)
-                                                        : (cfg->algo == 0 && find_variant(*cfg) != nullptr));
+    const bool known = cfg->algo == 3   ? is_conv_thin_cfg(*cfg)
+                       : cfg->algo == 2 ? is_conv_point_cfg(*cfg)
+                       : cfg->algo == 1 ? (find_patch_variant(*cfg) != nullptr || find_patch_bf16_variant(*cfg) != nullptr)
+                                        : (cfg->algo == 0 && find_variant(*cfg) != nullptr);
     if (!known || cfg->split_k < 1 || cfg->layout < 0 || cfg->layout > 2 || (cfg->layout == 2 && cfg->algo != 0) ||
         cfg->raster < 0 ||
         cfg->raster > 3 || (cfg->raster >= 2 && cfg->algo != 0) || cfg->cb < 0 || (cfg->cb & 1))

@@ -363,8 +363,16 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
 // the last step reads ahead half a plane past the filter: the room behind it is kept
 static size_t thin_lds_bytes(int steps) { return (size_t)steps * 384 * 16 + (size_t)(steps + 3) * 16 * 8 + kThinRows * 4 + 2048; }
 
-// Where the kernel is the faster one.  Limits: 64 output channels are what a wave's accumulators hold, 63 taps the mask
-// bits, 24 steps the LDS.  Below 6 units per compute unit (of its eight waves) the picked tile is faster: 7x7 3 -> 64 stride 2
+// 64 output channels are what a wave's accumulators hold, 63 taps the mask bits, 24 steps the LDS; the images 64 pixels touch, read
+// and written, lie within 31-bit offsets.
+bool conv_thin_fits(const ConvProblem &q)
+{
+    const int64_t RS = (int64_t)q.R * q.S, PQ = (int64_t)q.P * q.Q, images = 64 / PQ + 2;
+    return q.K <= kThinRows && RS <= 63 && q.C * RS <= 24 * 16 &&
+           images * q.C * q.H * q.W * 4 + ((int64_t)q.pad * q.W + q.pad) * 4 < kMaxOffset && images * q.K * PQ * 4 < kMaxOffset;
+}
+
+// Where the kernel is the faster one.  Below 6 units per compute unit (of its eight waves) the picked tile is faster: 7x7 3 -> 64 stride 2
 // with 980 units 18.3 us against 21.5 here, 1568: 27.9 and 22.9, 6272: 76 and 61, 16072: 194 and 146; 3x3 16 -> 64 on 56x56
 // with 1274: 19.4 and 20.4, 1813: 25.3 and 21.8; 5x5 6 -> 32 with 1511: 22.4 and 20.0, 16002: 162 and 122; 3x3 3 -> 32 with
 // 9016: 49 and 32.  Twenty shapes of 24 .. 384 reduction rows and 1536 .. 16000 units: 1.0 .. 1.5 times as fast, whether the
@@ -376,11 +384,8 @@ static size_t thin_lds_bytes(int steps) { return (size_t)steps * 384 * 16 + (siz
 bool conv_thin_pays(const ConvProblem &q)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S, PQ = (int64_t)q.P * q.Q, units = ((int64_t)q.N * PQ + 63) / 64, cus = compute_units();
-    if (q.K > kThinRows || q.R * q.S > 63 || Kg < 24 || Kg > 24 * 16 || units < 6 * cus) return false;
-    if (q.R * q.S == 1 && (Kg < 128 || units > 16 * cus)) return false;
-    // the images 64 pixels touch, read and written, within 31-bit offsets
-    const int64_t images = 64 / PQ + 2;
-    return images * q.C * q.H * q.W * 4 + ((int64_t)q.pad * q.W + q.pad) * 4 < kMaxOffset && images * q.K * PQ * 4 < kMaxOffset;
+    if (!conv_thin_fits(q) || Kg < 24 || units < 6 * cus) return false;
+    return q.R * q.S != 1 || (Kg >= 128 && units <= 16 * cus);
 }
 
 hipError_t conv_thin_launch(const ConvProblem &q, hipStream_t stream)

@@ -227,8 +227,18 @@ inline bool is_conv_point_cfg(const polydl_tile_cfg &c)
            c.layout == 0 && c.raster == 0 && c.cb == 0;
 }
 
-// conv_thin.hip: short reductions into at most 64 output channels, no reduction split and no scratch memory
-bool conv_thin_pays(const ConvProblem &q);
+// conv_thin.hip: short reductions into at most 64 output channels, no reduction split and no scratch memory (cfg.algo == 3; one
+// variant: 64 output channels x 64 pixels per wave and unit, 512 threads).  Not ranked: it takes the place of an unsplit pick
+// where conv_thin_pays().
+bool conv_thin_fits(const ConvProblem &q);
+bool conv_thin_pays(const ConvProblem &q);   // and fits
+void model_conv_thin(const ConvProblem &q, polydl_model_report *r);
+inline polydl_tile_cfg conv_thin_cfg() { return polydl_tile_cfg{64, 64, 0, 64, 64, 1, 0, 0, 3, 0}; }
+inline bool is_conv_thin_cfg(const polydl_tile_cfg &c)
+{
+    return c.algo == 3 && c.bm == 64 && c.bn == 64 && c.bk == 0 && c.wm == 64 && c.wn == 64 && c.split_k <= 1 &&
+           c.layout == 0 && c.raster == 0 && c.cb == 0;
+}
 hipError_t conv_thin_launch(const ConvProblem &q, hipStream_t stream);
 
 // reuse_analyse.cpp (arguments already validated)

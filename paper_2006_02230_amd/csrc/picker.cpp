@@ -535,6 +535,38 @@ void model_conv_point(const ConvProblem &q, polydl_model_report *r)
     for (int i = 0; i < 4; ++i) { r->ws[i] = ws[i]; r->ws_level[i] = placed[i]; r->ws_traffic[i] = moved[i]; }
 }
 
+// First-layer kernel (split filter resident in LDS, pixels gathered straight into registers): units of 64 pixels, dealt evenly to
+// the waves, two of which share a SIMD.  Fitted to 1916 launches of 24 .. 384 reduction rows and 1536 .. 40000 units, operands in the
+// cache: 11 % off in the mean, 25 % below to 14 % above for eight of ten.
+void model_conv_thin(const ConvProblem &q, polydl_model_report *r)
+{
+    std::memset(r, 0, sizeof(*r));
+    const double Kg = (double)q.C * q.R * q.S, steps = std::ceil(Kg / 32) * 2, pixels = (double)q.N * q.P * q.Q;
+    const double units = std::ceil(pixels / 64), waves = std::min(kCUs * 8.0, std::ceil(units / 8) * 8);
+    const double in_bytes = (double)q.N * q.C * q.H * q.W * 4, out_bytes = pixels * q.K * 4, wt_bytes = q.K * Kg * 4;
+    // a last round of at most half the waves finds the SIMDs to itself
+    const double full = std::floor(units / waves), rest = units / waves - full;
+    const double rounds = full + (rest <= 0 ? 0.0 : rest <= 0.5 ? 0.26 : 1.0);
+    r->mfma_us = rounds * (steps * 1.36 + 2.6 + 0.4 * q.K / 64.0);
+    r->mem_us = in_bytes / 5400.0 * 1e-3 + out_bytes / 3460.0 * 1e-3;
+    r->fixed_us = 5.6;                               // launch, splitting the filter into LDS, first loads, last stores
+    r->predicted_us = std::max(r->mfma_us, r->mem_us) + r->fixed_us;
+    r->workgroups = (int)(waves / 8);
+    r->simd_load = std::ceil(units / (waves / 2));
+    // reuses: accumulators of a unit; its pixels' values, reused by the channels; the filter's planes in LDS, read by every unit;
+    // the tensors themselves
+    const double planes = steps * 16 * 64 * 6;
+    const double ws[4] = {2 * 64.0 * 64 * 4, 64.0 * Kg * 4, planes, in_bytes + out_bytes + wt_bytes};
+    const double moved[4] = {0, units * 64.0 * Kg * 4, units * planes, in_bytes + out_bytes + wt_bytes};
+    double sizes[4], weights[4];
+    for (int i = 0; i < 4; ++i) { sizes[i] = kLevels[i].capacity; weights[i] = 1.0 / kLevels[i].gbytes_per_s; }
+    int placed[4];
+    bucket_placed(4, ws, 4, sizes, r->level_bytes, &r->mem_bytes, placed);
+    r->eq1_cost = reuse_cost(4, r->level_bytes, r->mem_bytes, weights, 1.0 / kHbmGBs);
+    r->n_ws = 4;
+    for (int i = 0; i < 4; ++i) { r->ws[i] = ws[i]; r->ws_level[i] = placed[i]; r->ws_traffic[i] = moved[i]; }
+}
+
 void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out)
 {
     out->clear();

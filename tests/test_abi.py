@@ -56,3 +56,20 @@ def test_variant_table(lib):
     bad = p.TileCfg(17, 64, 16, 32, 32, 1, 0, 0, 0, 0)
     assert lib.polydl_set_tile_override(ctypes.byref(bad)) == -3
     assert lib.polydl_set_tile_override(None) == 0
+
+
+def test_first_layer_kernel_as_an_override(lib):
+    # reported by polydl_get_last_tile, so accepted as an override; not enumerated; modelled on the problems it serves
+    import paper_2006_02230_amd as p
+    thin = p.TileCfg(64, 64, 0, 64, 64, 1, 0, 0, 3, 0)
+    assert lib.polydl_set_tile_override(ctypes.byref(thin)) == 0
+    assert lib.polydl_set_tile_override(None) == 0
+    for field, value in (("bm", 32), ("bn", 128), ("bk", 16), ("wm", 32), ("wn", 32), ("split_k", 2), ("layout", 2), ("raster", 1), ("cb", 2)):
+        other = p.TileCfg(64, 64, 0, 64, 64, 1, 0, 0, 3, 0)
+        setattr(other, field, value)
+        assert lib.polydl_set_tile_override(ctypes.byref(other)) == -3, field
+    t = [p.model_conv2d((n, 3, 224, 224, 64, 7, 7, 2, 3), thin).predicted_us for n in (1, 32, 64, 128)]
+    assert 0 < t[0] < t[1] < t[2] < t[3] and 50 < t[1] < 80       # 62 us measured
+    for shape in ((32, 3, 56, 56, 65, 3, 3, 1, 1), (32, 3, 56, 56, 64, 8, 8, 1, 1), (32, 43, 56, 56, 64, 3, 3, 1, 1)):
+        with pytest.raises(p.PolydlError):
+            p.model_conv2d(shape, thin)

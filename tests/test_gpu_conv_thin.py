@@ -80,6 +80,89 @@ def test_short_reduction_into_many_channels(P):
         assert oracle.scaled_error(host(P.conv2d_fwd(dx, dw, db, stride=s.stride, pad=s.pad)), want, ab) <= FP32_TOL
 
 
+THIN = dict(bm=64, bn=64, bk=0, wm=64, wn=64, split_k=1, layout=0, raster=0, algo=3, cb=0)
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=lambda s: s.name)
+def test_the_kernel_that_ran_is_reported(P, s):
+    x, w, _ = synth.conv_inputs(s, seed=4, dist="normal")
+    dx, dw = dev(x), dev(w)
+    first = P.conv2d_fwd(dx, dw, stride=s.stride, pad=s.pad)
+    ran = P.get_last_tile()
+    if s.name == "below":
+        assert ran.algo != 3
+    else:
+        assert ran.as_dict() == THIN
+    # what is reported can be forced, modelled, and gives the same bits
+    assert P.model_conv2d(tuple(s)[1:], ran).predicted_us > 0
+    P.set_tile_override(ran)
+    assert (P.conv2d_fwd(dx, dw, stride=s.stride, pad=s.pad) == first).all()
+    assert P.get_last_tile().as_dict() == ran.as_dict()
+    P.set_tile_override(None)
+
+
+# fewer pixels than a unit, fewer units than waves, one channel in and out, a filter larger than the image, 63 and 1 taps
+FORCED = [synth.ConvShape("one_pixel", 1, 5, 3, 3, 7, 3, 3, 1, 0), synth.ConvShape("one_unit", 1, 1, 8, 8, 1, 1, 1, 1, 0),
+          synth.ConvShape("units_65", 3, 7, 37, 37, 64, 5, 5, 1, 2), synth.ConvShape("large_filter", 2, 6, 5, 4, 33, 9, 7, 1, 4),
+          synth.ConvShape("strided_past_the_end", 2, 42, 11, 13, 64, 3, 3, 4, 1), synth.ConvShape("1x1_384", 3, 384, 9, 7, 64, 1, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("s", FORCED + SHAPES, ids=lambda s: s.name)
+def test_forced_on_any_problem_it_fits(P, s):
+    x, w, b = synth.conv_inputs(s, seed=5, dist="normal", bias=True)
+    want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad, act="relu")
+    P.set_tile_override(P.TileCfg(**THIN))
+    got = host(P.conv2d_fwd(dev(x), dev(w), dev(b), stride=s.stride, pad=s.pad, act="relu"))
+    P.set_tile_override(None)
+    assert oracle.scaled_error(got, want, ab) <= FP32_TOL
+
+
+def test_forced_on_a_problem_it_does_not_fit(P):
+    for s in (synth.ConvShape("65_channels", 1, 3, 9, 9, 65, 3, 3, 1, 1), synth.ConvShape("64_taps", 1, 3, 9, 9, 8, 8, 8, 1, 4),
+              synth.ConvShape("387_rows", 1, 43, 9, 9, 8, 3, 3, 1, 1)):
+        x, w, _ = synth.conv_inputs(s, seed=6, dist="normal")
+        P.set_tile_override(P.TileCfg(**THIN))
+        with pytest.raises(P.PolydlError):
+            P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad)
+        P.set_tile_override(None)
+
+
+def test_through_every_entry_captured_and_misaligned(P):
+    import torch
+    s = SHAPES[0]
+    x, w, b = synth.conv_inputs(s, seed=8, dist="normal", bias=True)
+    want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad, act="relu")
+    kw = dict(stride=s.stride, pad=s.pad, act="relu")
+    dx, dw, db = dev(x), dev(w), dev(b)
+    eager = P.conv2d_fwd(dx, dw, db, **kw)
+    assert oracle.scaled_error(host(eager), want, ab) <= FP32_TOL
+
+    def ran(out):
+        assert P.get_last_tile().as_dict() == THIN
+        assert torch.equal(out, eager)
+
+    ran(P.conv2d_fwd(dx, dw, db, w_tap=P.filter_tap_copy(dw), **kw))
+    ran(P.conv2d_fwd_noalloc(dx, dw, db, torch.full_like(eager, -1.0), **kw))
+
+    def off_by_one(t):       # four bytes past the allocation's alignment
+        v = torch.empty(t.numel() + 1, device="cuda")[1:].view(t.shape)
+        return v.copy_(t)
+
+    ran(P.conv2d_fwd(off_by_one(dx), off_by_one(dw), off_by_one(db), out=off_by_one(eager).fill_(-1.0), **kw))
+
+    out = torch.empty_like(eager)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        P.conv2d_fwd(dx, dw, db, out=out, **kw)
+    for rep in range(4):
+        out.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        ran(out)
+        P.conv2d_fwd(dx, dw, db, **kw)       # eager work between the replays
+
+
 @pytest.mark.parametrize("C", [3, 4], ids=["filter_rows_of_75", "filter_rows_of_100"])   # dword and 128-bit filter loads
 def test_short_reduction_on_every_tile(P, C):
     # every fp32 gather variant on a grid of several rounds: whole tiles, cut leftover tiles, two parts; every output compared
