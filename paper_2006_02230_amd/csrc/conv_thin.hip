@@ -36,7 +36,8 @@ struct ConvThinKArgs {
     uint64_t in_bytes, out_bytes;
     int act, pre_act;
     int steps;                    // reduction steps of 16 rows, an even number
-    uint32_t units, per, rem;     // 64-pixel units; a wave takes `per` of them in a run, `rem` waves one more
+    uint32_t units, per, rem;     // 64-pixel units; a wave takes `per` of them, `rem` waves one more
+    uint32_t wave_units, step_units;   // wave w's i-th unit is w * wave_units + i * step_units
 };
 
 struct ThinPixel { uint32_t off, lo, hi; };   // byte offset of tap (0,0); one bit per tap, set where it lies outside the image
@@ -227,8 +228,9 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
         __syncthreads();
     }
 
-    // the wave's run of units, and what is left over one each, to first waves of workgroups before second ones
-    const uint32_t first = (blockIdx.x * (kThinThreads / 64) + wave) * p.per, extra = (uint32_t)wave * gridDim.x + blockIdx.x;
+    // what is left over after equal shares goes to first waves of workgroups before second ones
+    const uint32_t first = (blockIdx.x * (kThinThreads / 64) + wave) * p.wave_units;
+    const uint32_t extra = (uint32_t)wave * gridDim.x + blockIdx.x;
     const uint32_t count = p.per + (extra < p.rem ? 1u : 0u);
     const u32x4 *at0 = At + half * 64 + j;
     const float *filter0 = filter + half * 8 * kThinRows + j;   // the lane's values of step t: filter0[(16 t + i) * 64]
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
     const uint32_t KPQ = (uint32_t)p.K * (uint32_t)p.PQ;
     const int lead = (p.pad * p.W + p.pad) * 4;   // tap (0,0) may lie this far before the image
     for (uint32_t i = 0; i < count; ++i) {
-        const uint32_t n0 = (i < p.per ? first + i : p.units - p.rem + extra) * 64u;
+        const uint32_t n0 = (i < p.per ? first + i * p.step_units : p.units - p.rem + extra) * 64u;
         uint32_t rem0;
         const uint32_t img0 = div_by(n0, (uint32_t)p.PQ, p.recip_PQ, rem0);
         const uint64_t skip = (uint64_t)img0 * p.CHW * 4;
@@ -372,12 +374,22 @@ bool conv_thin_fits(const ConvProblem &q)
            images * q.C * q.H * q.W * 4 + ((int64_t)q.pad * q.W + q.pad) * 4 < kMaxOffset && images * q.K * PQ * 4 < kMaxOffset;
 }
 
+constexpr int64_t kLastLevelCache = 256ll << 20;
+static int64_t thin_bytes(const ConvProblem &q) { return (int64_t)q.N * 4 * ((int64_t)q.C * q.H * q.W + (int64_t)q.K * q.P * q.Q); }
+
 // Where the kernel is the faster one.  Below 6 units per compute unit (of its eight waves) the picked tile is faster: 7x7 3 -> 64 stride 2
 // with 980 units 18.3 us against 21.5 here, 1568: 27.9 and 22.9, 6272: 76 and 61, 16072: 194 and 146; 3x3 16 -> 64 on 56x56
 // with 1274: 19.4 and 20.4, 1813: 25.3 and 21.8; 5x5 6 -> 32 with 1511: 22.4 and 20.0, 16002: 162 and 122; 3x3 3 -> 32 with
-// 9016: 49 and 32.  Twenty shapes of 24 .. 384 reduction rows and 1536 .. 16000 units: 1.0 .. 1.5 times as fast, whether the
-// pick was a gather or a row-patch variant (18 rows, 1600 units: 11.7 and 12.0).  Below 128 rows, where the picks use the fp32
-// instruction, the error against 64 bits falls with it (72 rows 1.56e-7 -> 0.58e-7).
+// 9016: 49 and 32.  Below 128 rows, where the picks use the fp32 instruction, the error against 64 bits falls with it (72 rows
+// 1.56e-7 -> 0.58e-7).
+// Reductions of up to 80 rows: the products are not all there is to win, and two things eat it.  Work of the kernel that is not
+// the layer's (rows filled up to whole pairs of steps, waves without a unit in the last round of 64 pixels each; `own` is the
+// rest of it): 36 rows, 56x56, 3332 units 20.7 us on the picked tile and 22.1 here (own 0.46), 27 rows on 14x14 with 2101 units
+// 12.6 and 13.1 (0.43), 24 rows on 28x28 with 2401 13.6 and 15.0 (0.44); 45 rows with 4000 units 1.04 .. 1.28 times as fast (0.69).  And
+// outputs beyond the last-level cache in short image rows, where the picked tiles write longer runs: 8 -> 64 3x3 on 28x28, 40903
+// units 266 and 327.  Of 4685 timings of 24 .. 384 rows and 1536 .. 40000 units, operands in the cache and not, 445 were more
+// than 3 % slower here, by up to 30 %; of the 3818 within these limits 88, by up to 12 % (small images of few channels), and of the
+// others 256 would have been more than 3 % faster.
 // 1x1 layers read their pixels in whole lines, which the staged kernel does as well: below 128 channels it is the faster
 // one (64 -> 64 on 56x56 with 2401 units 17.9 us against 21.0), above it as fast with three units a wave and more
 // (256 -> 64 with 1813 units 40.7 and 30.6, 3087: 60.5 and 54, 6223: 122.8 and 125).
@@ -385,7 +397,23 @@ bool conv_thin_pays(const ConvProblem &q)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S, PQ = (int64_t)q.P * q.Q, units = ((int64_t)q.N * PQ + 63) / 64, cus = compute_units();
     if (!conv_thin_fits(q) || Kg < 24 || units < 6 * cus) return false;
+    if (Kg <= 80) {
+        const int64_t waves = cus * (kThinThreads / 64), rounds = (units + waves - 1) / waves, rows = (Kg + 31) / 32 * 32;
+        const double own = (double)(Kg * units) / (double)(rows * rounds * waves);
+        if (own < (Kg <= 48 ? 0.55 : 0.45)) return false;
+        if (q.K > 32 && q.Q < 48 && thin_bytes(q) > kLastLevelCache) return false;
+    }
     return q.R * q.S != 1 || (Kg >= 128 && units <= 16 * cus);
+}
+
+// Whether a wave takes its units in a run: where a unit reads at least half of its input rows again that the one before it
+// read (64 pixels go 64 * stride / Q rows further, R - stride rows stay) and the layer fits the last-level cache.  There it finds
+// them close by: 3 -> 64 3x3 on 112x112, 5096 units, 23.7 us against 26.2, 7x7/2 on 224x224 51.9 and 53.4.  Otherwise
+// neighbouring waves take neighbouring units, so that what the card reads and writes at a time lies together: 8 -> 64 3x3/2 on
+// 14x28, 9001 units, 96.0 us against 108.8 in runs, 3 -> 64 3x3 on 112x112, 25088 units, 106 and 125.5.
+static bool thin_in_runs(const ConvProblem &q)
+{
+    return (int64_t)(q.R - q.stride) * q.Q >= 64ll * q.stride && thin_bytes(q) <= kLastLevelCache;
 }
 
 hipError_t conv_thin_launch(const ConvProblem &q, hipStream_t stream)
@@ -409,6 +437,9 @@ hipError_t conv_thin_launch(const ConvProblem &q, hipStream_t stream)
     const uint32_t cus = (uint32_t)compute_units(), wgs = need < cus ? need : cus, waves = wgs * waves_per_wg;
     a.per = a.units / waves;
     a.rem = a.units % waves;
+    const bool runs = thin_in_runs(q);
+    a.wave_units = runs ? a.per : 1;
+    a.step_units = runs ? 1 : waves;
     const size_t lds = thin_lds_bytes(a.steps);
     if (lds > 64 * 1024) {   // more than the default window has to be asked for
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(conv_thin_kernel),

@@ -101,6 +101,34 @@ def test_the_kernel_that_ran_is_reported(P, s):
     P.set_tile_override(None)
 
 
+# reductions of up to 80 rows: where more than 45 % (up to 48 rows; else 55 %) of what the kernel multiplies is not the layer's, the
+# picked tile is the faster one; (C, H, W, N, K, R, S, stride), with compute units' waves of 2048
+@pytest.mark.parametrize("C,H,W,N,K,R,S,stride,takes", [
+    (3, 112, 112, 32, 64, 3, 3, 1, True), (5, 224, 224, 10, 32, 3, 3, 1, True), (8, 56, 56, 80, 64, 3, 3, 1, True),
+    (4, 112, 112, 17, 64, 3, 3, 1, False), (4, 28, 69, 412, 64, 3, 3, 2, False), (3, 14, 14, 686, 16, 3, 3, 1, False),
+    (8, 28, 28, 213, 32, 1, 3, 1, False), (8, 56, 56, 49, 64, 3, 3, 1, False), (9, 56, 56, 52, 64, 3, 3, 1, True)])
+def test_short_reductions_take_the_kernel_where_it_pays(P, C, H, W, N, K, R, S, stride, takes):
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("sizes for 256 compute units")
+    x, w = torch.randn(N, C, H, W, device="cuda"), torch.randn(K, C, R, S, device="cuda")
+    P.conv2d_fwd(x, w, stride=stride, pad=1)
+    assert (P.get_last_tile().algo == 3) == takes
+
+
+# more than two units a wave: in runs of neighbours (rows read again) and in steps over the card, with and without some left over
+@pytest.mark.parametrize("s", [synth.ConvShape("runs", 6, 3, 224, 221, 8, 3, 3, 1, 1), synth.ConvShape("runs_none_left", 8, 2, 256, 128, 5, 5, 5, 1, 2),
+                               synth.ConvShape("steps", 1601, 4, 14, 15, 9, 3, 3, 1, 1), synth.ConvShape("steps_none_left", 2048, 3, 16, 16, 6, 3, 3, 2, 1),
+                               synth.ConvShape("steps_strided", 23, 3, 223, 227, 7, 3, 3, 2, 1)], ids=lambda s: s.name)
+def test_units_of_a_wave(P, s):
+    x, w, b = synth.conv_inputs(s, seed=7, dist="normal", bias=True)
+    want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad)
+    P.set_tile_override(P.TileCfg(**THIN))
+    got = host(P.conv2d_fwd(dev(x), dev(w), dev(b), stride=s.stride, pad=s.pad))
+    P.set_tile_override(None)
+    assert oracle.scaled_error(got, want, ab) <= FP32_TOL
+
+
 # fewer pixels than a unit, fewer units than waves, one channel in and out, a filter larger than the image, 63 and 1 taps
 FORCED = [synth.ConvShape("one_pixel", 1, 5, 3, 3, 7, 3, 3, 1, 0), synth.ConvShape("one_unit", 1, 1, 8, 8, 1, 1, 1, 1, 0),
           synth.ConvShape("units_65", 3, 7, 37, 37, 64, 5, 5, 1, 2), synth.ConvShape("large_filter", 2, 6, 5, 4, 33, 9, 7, 1, 4),
