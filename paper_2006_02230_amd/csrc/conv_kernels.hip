@@ -49,7 +49,8 @@ __global__ __launch_bounds__(T::NT) void conv_kernel(ConvKArgs p)
 // matrix instructions that leave two to three times less time for it than the fp32 ones did; hence larger
 // tiles with fewer reduction parts win (128x128 split 2 where 64x64 with cut leftovers did).  Batch 32, us:
 // 128 -> 128 3x3 with the filter copy 66 -> 54, 512 -> 512 3x3 79 -> 64, 1024 -> 2048 1x1/2 64 -> 53,
-// 512 -> 512 3x3 at 28x28 910 -> 690 (power).
+// 512 -> 512 3x3 at 28x28 910 -> 620 .. 690.  Launched back to back the small ones run at 2.1 .. 2.3 GHz with the matrix
+// cores busy a third of the cycles, the last one at 1.95 GHz (power) with 0.56; without load on the card it is 2.4 GHz.
 // KTAIL: see BLoaderIm2col.
 template <class T, int MODE, bool KTAIL>
 __global__ __launch_bounds__(T::NT, T::SPLIT_WAVES) void conv_split_kernel(ConvKArgs p)

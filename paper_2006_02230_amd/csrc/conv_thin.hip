@@ -11,11 +11,12 @@
 //     splits them there into the operand of the matrix instruction: no LDS, no barrier;
 //   * one step's 24 matrix instructions have the splitting of the next step's values, the loads of the step after that and
 //     the filter reads dealt out between them: six vector instructions each, what is free there.
-// 3 -> 64 channels 7x7/2 on 224x224, batch 32: 80 -> 64 us (batch 64: 146 -> 112); 3x3 3 -> 32 of the same, batch 32, on
+// 3 -> 64 channels 7x7/2 on 224x224, batch 32: 80 -> 62 us (batch 64: 146 -> 112); 3x3 3 -> 32 of the same, batch 32, on
 // the fp32 instruction before: 35.5 -> 25 us.
-// Bound: 24 matrix instructions a step (768 cycles a wave, two waves a SIMD) take 1.3 .. 1.7 us: the card's power (the
-// products of the first figure come to 0.8 PFLOP/s), 145 vector instructions, and 16 gathered loads whose lanes touch six
-// lines each.  Loads two steps ahead instead of one (16 more registers, a few spilled outside the loop) were 3 .. 5 % slower.
+// Bound: the two waves of a SIMD share its issue.  On that layer a SIMD's matrix instructions take 47 thousand cycles and its
+// other vector instructions 60 thousand (10 per matrix instruction: 6 in a step, the rest by the unit and by the filter) of the
+// 120 thousand that the layer lasts, at 2.0 GHz (2.4 where power allows; the products come to 0.8 PFLOP/s); then come the
+// gathered loads, whose lanes touch six lines each.  Loads two steps ahead instead of one (16 more registers, a few spilled outside the loop) were 3 .. 5 % slower.
 // Up to 31 reduction rows more than the layer has are multiplied (whole pairs of steps).
 // Values the split cannot hold (thin_redo): a filter with one sends every unit through the fp32 instruction, from the filter in
 // LDS: 3 -> 64 7x7/2 above 107 us (value by value from memory 207; the staged tiles 173), 32 -> 64 3x3 on 56x56 56 (120; 80),
