@@ -40,7 +40,8 @@ def import_sweeps(paths, out_path=DATA):
     problems = []
     for path in paths:
         for layer in json.load(open(path)):
-            rows = [[c["cfg"][f] for f in CFG_FIELDS] + [c["us"]] for c in layer["candidates"]]
+            # a sweep also times the first-layer kernel (algo 3) where it runs; tournaments are among the ranked candidates
+            rows = [[c["cfg"][f] for f in CFG_FIELDS] + [c["us"]] for c in layer["candidates"] if c["cfg"]["algo"] != 3]
             problems.append({"shape": layer["shape"], "rows": rows})
     os.makedirs(os.path.dirname(out_path), exist_ok=True)
     with open(out_path, "w") as f:

@@ -66,6 +66,18 @@ def test_packed_sweep_file_round_trip(tmp_path):
     assert sorted(zip(I, J)) == [(0, 1), (0, 2), (1, 0), (1, 2), (2, 0), (2, 1)]
 
 
+def test_only_ranked_candidates_are_imported(tmp_path):
+    # a sweep also times the first-layer kernel, which no tournament can pick
+    shape = [32, 3, 224, 224, 64, 7, 7, 2, 3]
+    cfgs = [P.TileCfg(64, 128, 16, 32, 64, 1, 0, 1, 0, 0), P.TileCfg(64, 64, 0, 64, 64, 1, 0, 0, 3, 0), P.TileCfg(64, 64, 16, 32, 32, 1, 0, 1, 0, 0)]
+    src, packed = tmp_path / "s.json", tmp_path / "packed.json"
+    src.write_text(json.dumps([{"layer": 0, "shape": shape, "picked": cfgs[1].as_dict(), "picked_us": 60.0,
+                                "candidates": [{"us": 60.0 + i, "cfg": c.as_dict()} for i, c in enumerate(cfgs)]}]))
+    assert T.import_sweeps([str(src)], str(packed)) == (1, 2)
+    _, us, _, _, got, _ = T.load_table(str(packed))
+    assert list(us) == [60.0, 62.0] and [c.algo for c in got] == [0, 0]
+
+
 def test_split_is_seeded_and_about_seventy_percent():
     a, b = T.split_mask(5000, 0), T.split_mask(5000, 0)
     assert np.array_equal(a, b) and not np.array_equal(a, T.split_mask(5000, 1))
