@@ -19,7 +19,7 @@
 // gathered loads, whose lanes touch six lines each.  Loads two steps ahead instead of one (16 more registers, a few spilled outside the loop) were 3 .. 5 % slower.
 // Up to 31 reduction rows more than the layer has are multiplied (whole pairs of steps).
 // Values the split cannot hold (thin_redo): a filter with one sends every unit through the fp32 instruction, from the filter in
-// LDS: 3 -> 64 7x7/2 above 107 us (value by value from memory 207; the staged tiles 173), 32 -> 64 3x3 on 56x56 56 (120; 80),
+// LDS: 3 -> 64 7x7/2 above 107 us (value by value from memory 207; the staged tiles 173), 32 -> 64 3x3 on 56x56 58 (120; 80),
 // 3 -> 64 3x3 on 112x112 34 (48; 32.5).  A pixel with one sends its block of 32 pixels there: 78 (112; 74), 39.5 (70; 37.5),
 // 27.5 (35; 32).
 #include "conv_gather.hpp"
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
     if (tid < kThinRows) bias[tid] = p.bias && tid < p.K ? p.bias[tid] : 0.f;
     lossy = __syncthreads_or(lossy);
     float *filter = reinterpret_cast<float *>(At);
-    if (lossy) {   // uniform: a filter value the split cannot hold; the planes make room for the filter as it is
+    if (__builtin_expect(lossy, 0)) {   // uniform: a filter value the split cannot hold; the planes make room for the filter as it is
         filter_octets([&](int o, int k, const float (&v)[8]) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) filter[(8 * o + i) * kThinRows + k] = v[i];
@@ -266,8 +266,9 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
             }
         }
         v16f acc[2][2];
-        bool again[2] = {false, false};
-        if (__builtin_expect(!lossy, 1)) {
+        if (__builtin_expect(lossy, 0)) {   // uniform, as below
+            thin_redo<true, 0, 2>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
+        } else {
             ThinWave w;
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
@@ -322,16 +323,17 @@ __global__ __launch_bounds__(kThinThreads, 2) void conv_thin_kernel(ConvThinKArg
                         acc[mb][nb][r] = w.hi[mb][nb][r] + w.lo[mb][nb][r];
                         f[nb] = __builtin_fmaf(acc[mb][nb][r], 0.f, f[nb]);
                     }
+            // Rare, and all of it in here and expected not to be taken: the code then lies behind the stores, not in the middle of what
+            // every unit runs (3 -> 64 3x3 on 112x112, batch 32: 26.7 -> 26.3 us).
             if (__builtin_expect(__ballot(!(f[0] + f[1] == 0.f) || split_lossy(w.seen[0] | w.seen[1])) != 0, 0)) {
+                bool again[2];
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb) again[nb] = __ballot(!(f[nb] == 0.f) || split_lossy(w.seen[nb])) != 0;
+                if (again[0] && again[1]) thin_redo<false, 0, 2>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
+                else if (again[0]) thin_redo<false, 0, 1>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
+                else if (again[1]) thin_redo<false, 1, 1>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
             }
         }
-        // all uniform
-        if (__builtin_expect(lossy, 0)) thin_redo<true, 0, 2>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
-        else if (__builtin_expect(again[0] && again[1], 0)) thin_redo<false, 0, 2>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
-        else if (__builtin_expect(again[0], 0)) thin_redo<false, 0, 1>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
-        else if (__builtin_expect(again[1], 0)) thin_redo<false, 1, 1>(acc, px, ri, at0, filter0, tab0, steps, p.pre_act);
         // bias, activation, store: the lane's channels are 32 mb + 8 (r / 4) + 4 half + r % 4; a half-wave stores 128 consecutive bytes
         const uint64_t oskip = (uint64_t)img0 * KPQ * 4;
         const __amdgpu_buffer_rsrc_t ro = make_rsrc(reinterpret_cast<char *>(p.out) + oskip, p.out_bytes - oskip);
