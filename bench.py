@@ -26,12 +26,12 @@ HBM_PEAK_GBS = 8000.0
 # fetch and write-back counters of two rocprofv3 --pmc runs, each scaled by what the same counter
 # reads for a plain 256 MiB elementwise copy.  Valid only for the kernel sources they were taken
 # with: their digest is kept beside them and the bench line reports null when it no longer matches.
-HBM_TRAFFIC = {"csrc_sha256": "f4c22141f7f92fa7d75ef20e8c024b0ee268647b6aa48e0e1b0ad0f106197cc5", "batch": 32, "filters": "tap", "fetch_bytes": 569714888, "write_bytes": 408686348}
+HBM_TRAFFIC = {"csrc_sha256": "fc9d1608064d9bf8614b39db481fd41cd20c9437c99c0dd6bdb4c7a878ece5bc", "batch": 32, "filters": "tap", "fetch_bytes": 568619856, "write_bytes": 408620298}
 
 
 # L2 fetch + write-back bytes of config 4 from two rocprofv3 --pmc runs of `bench.py --copy-probe --counter-pass
 # fusion` (same scaling as above): the fused launch, and the convolution + bias + activation launches it replaces.
-FUSION_TRAFFIC = {"csrc_sha256": "f4c22141f7f92fa7d75ef20e8c024b0ee268647b6aa48e0e1b0ad0f106197cc5", "fused_bytes": 84719101, "separate_bytes": 110430945}
+FUSION_TRAFFIC = {"csrc_sha256": "fc9d1608064d9bf8614b39db481fd41cd20c9437c99c0dd6bdb4c7a878ece5bc", "fused_bytes": 84488297, "separate_bytes": 110209248}
 
 COLD_ROTATION_BYTES = 640 * 1000 * 1000
 
