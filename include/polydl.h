@@ -70,7 +70,12 @@ typedef enum polydl_act { POLYDL_ACT_NONE = 0, POLYDL_ACT_RELU = 1, POLYDL_ACT_R
  * bm tiles output channels and bn tiles output pixels; for SGEMM bm tiles M and bn tiles N. */
 typedef struct polydl_tile_cfg {
     int bm, bn, bk;   /* workgroup tile: bm x bn outputs, bk reduction elements per stage      */
-    int wm, wn;       /* wave tile (multiples of 32); the workgroup has (bm/wm)*(bn/wn) waves  */
+    int wm, wn;       /* wave tile (multiples of 32); the workgroup has (bm/wm)*(bn/wn) waves.
+                         64x64x16 with wave tile 64x64 and 32x32x16 with 32x32 (SGEMM and algo 0,
+                         raster 1; filters of at most 63 taps) are the tiles of small problems: the
+                         eight waves of a workgroup share a tile's reduction and meet in LDS.  They
+                         are not enumerated and not ranked: unless a variant is forced they take the
+                         place of a pick where they are predicted to be well below it              */
     int split_k;      /* >= 1: the reduction is cut into this many parts (one workgroup each);  */
     int layout;       /* 0: read NCHW / KCRS directly; 1: via blocked NCHWc / KCRSck copies;
                          2: gather kernel reading the filter's [K][R][S][C] copy, reduction walked
@@ -112,8 +117,8 @@ typedef struct polydl_tile_cfg {
  * Accumulation is float32 on the matrix cores; the summation order is unspecified but fixed for
  * a given tile configuration, so repeated calls agree bit for bit.  The gather variants (algo 0) with stage
  * depth 16 and wave tiles up to 64 x 64 form the products of reductions of 128 and more as polydl_sgemm
- * does (three bfloat16 parts per operand, six products, float32 sums), and so do the pointwise and the first-layer
- * kernel (algo 2 and 3). */
+ * does (three bfloat16 parts per operand, six products, float32 sums), and so do the tiles of small problems (of any
+ * reduction), the pointwise and the first-layer kernel (algo 2 and 3). */
 int polydl_conv2d_fwd(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                       const float *in, const float *wt, const float *bias, float *out,
                       int fuse_relu, void *stream);

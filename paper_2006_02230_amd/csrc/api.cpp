@@ -181,11 +181,18 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
                 polydl_model_report rep;
                 SgemmProblem pq{M, N, K, A, B, C, alpha, beta};
                 if (!pick_sgemm(pq, &cfg, &rep)) return POLYDL_ERR_UNSUPPORTED;
+                sgemm_wave_pick(pq, rep.predicted_us, false, &cfg);
                 g_sgemm_plans[key] = cfg;
             }
         }
     }
     auto launch = [&](hipError_t *e) {
+        if (is_wave_cfg(cfg)) {
+            SgemmProblem q{M, N, K, A, B, C, alpha, beta};
+            if (!sgemm_wave_fits(q, cfg.bm)) return false;
+            *e = sgemm_wave_launch(q, cfg.bm, cfg.split_k, (hipStream_t)stream);
+            return true;
+        }
         const Variant *v = find_variant(cfg);
         if (!v) return false;
         SgemmProblem q{M, N, K, A, B, C, alpha, beta};
@@ -200,7 +207,9 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
         // variant that needs none (not cached)
         polydl_model_report rep;
         SgemmProblem pq{M, N, K, A, B, C, alpha, beta};
-        if (!pick_sgemm(pq, &cfg, &rep, true) || !launch(&e)) return POLYDL_ERR_UNSUPPORTED;
+        if (!pick_sgemm(pq, &cfg, &rep, true)) return POLYDL_ERR_UNSUPPORTED;
+        sgemm_wave_pick(pq, rep.predicted_us, true, &cfg);
+        if (!launch(&e)) return POLYDL_ERR_UNSUPPORTED;
     }
     if (e != hipSuccess) return launch_failed(e);
     std::lock_guard<std::mutex> lk(g_mu);
@@ -231,6 +240,13 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
         forced = g_have_override;
         cfg = g_override;
     }
+    // the first-layer kernel and the single waves are not among the ranked candidates: they take the place of a pick
+    auto choose = [&](PickLimits limits) {
+        polydl_model_report rep;
+        if (!pick_conv(q, &cfg, &rep, limits)) return false;
+        if (cfg.algo == 2 || cfg.split_k > 1 || !conv_thin_pays(q)) conv_wave_pick(q, rep.predicted_us, limits.no_scratch, &cfg);
+        return true;
+    };
     if (!forced) {
         const std::array<int, 10> key = {N, C, H, W, K, R, S, stride, pad,
                                          (pre_act != POLYDL_ACT_NONE ? 1 : 0) | (q.has_tap ? 2 : 0) | (arena ? 4 : 0)};
@@ -239,18 +255,14 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
         if (it != g_conv_plans.end()) {
             cfg = it->second;
         } else {
-            polydl_model_report rep;
-            if (!pick_conv(q, &cfg, &rep)) return POLYDL_ERR_UNSUPPORTED;
+            if (!choose(PickLimits())) return POLYDL_ERR_UNSUPPORTED;
             g_conv_plans[key] = cfg;
         }
     }
     // the pointwise kernel moves pixel pairs as 8-byte words and filter and bias as 16-byte words: tensors
     // aligned to less take the best of the other candidates (not cached: the plan is about shapes)
     const bool point_aligned = !(((uintptr_t)in | (uintptr_t)out) & 7) && !((uintptr_t)wt & 15) && !((uintptr_t)bias & 15);
-    if (!forced && cfg.algo == 2 && !point_aligned) {
-        polydl_model_report rep;
-        if (!pick_conv(q, &cfg, &rep, PickLimits{false, false})) return POLYDL_ERR_UNSUPPORTED;
-    }
+    if (!forced && cfg.algo == 2 && !point_aligned && !choose(PickLimits{false, false})) return POLYDL_ERR_UNSUPPORTED;
     bool no_scratch = false;   // the launch was refused because the stream is being captured and has no scratch memory
     auto failed = [&](hipError_t e) {
         no_scratch = refused_for_capture(e);
@@ -258,8 +270,7 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
     };
     auto run = [&]() -> int {
         q.wt_tap = nullptr;    // set below for the variants that read the copy
-        // the first-layer kernel is not among the ranked candidates: it takes the place of an unsplit pick
-        if (!forced && cfg.algo != 2 && cfg.split_k <= 1 && conv_thin_pays(q)) cfg = conv_thin_cfg();
+        if (!forced && cfg.algo != 2 && cfg.split_k <= 1 && !is_wave_cfg(cfg) && conv_thin_pays(q)) cfg = conv_thin_cfg();
         if (cfg.layout != 0 && !(cfg.layout == 2 && cfg.algo == 0)) return POLYDL_ERR_UNSUPPORTED;
         if (cfg.algo == 2) {
             if (!is_conv_point_cfg(cfg) || !conv_point_fits(q) || !point_aligned) return POLYDL_ERR_UNSUPPORTED;
@@ -291,14 +302,16 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
             g_last = cfg;
             return POLYDL_OK;
         }
+        const bool wave = is_wave_cfg(cfg);
         const Variant *v = find_variant(cfg);
-        if (!v) return POLYDL_ERR_UNSUPPORTED;
-        if (!conv_tile_in_range(q, v->bm, v->bn)) return POLYDL_ERR_UNSUPPORTED;
+        if (!v && !wave) return POLYDL_ERR_UNSUPPORTED;
+        if (wave ? !conv_wave_fits(q, cfg.bm) : !conv_tile_in_range(q, v->bm, v->bn)) return POLYDL_ERR_UNSUPPORTED;
         if (cfg.layout == 2) {
-            if (!q.has_tap || !gather_tap_major_fits(q, v->bk)) return POLYDL_ERR_UNSUPPORTED;
+            if (!q.has_tap || !gather_tap_major_fits(q, cfg.bk)) return POLYDL_ERR_UNSUPPORTED;
             q.wt_tap = wt_tap;
         }
-        hipError_t e = v->conv(q, cfg.split_k < 1 ? 1 : cfg.split_k, cfg.raster, (hipStream_t)stream);
+        const int parts = cfg.split_k < 1 ? 1 : cfg.split_k;
+        hipError_t e = wave ? conv_wave_launch(q, cfg.bm, parts, (hipStream_t)stream) : v->conv(q, parts, cfg.raster, (hipStream_t)stream);
         if (e != hipSuccess) return failed(e);
         std::lock_guard<std::mutex> lk(g_mu);
         g_last = cfg;
@@ -307,8 +320,7 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
     int st = run();
     if (st != POLYDL_OK && no_scratch && !forced) {
         // the best variant that needs none (not cached); nothing was enqueued so far
-        polydl_model_report rep;
-        if (!pick_conv(q, &cfg, &rep, PickLimits{true, point_aligned})) return st;
+        if (!choose(PickLimits{true, point_aligned})) return st;
         st = run();
     }
     return st;
@@ -654,7 +666,7 @@ int polydl_model_conv2d(int N, int C, int H, int W, int K, int R, int S, int str
     const bool known = cfg->algo == 3   ? is_conv_thin_cfg(*cfg)
                        : cfg->algo == 2 ? is_conv_point_cfg(*cfg)
                        : cfg->algo == 1 ? find_patch_variant(*cfg) != nullptr
-                                        : (cfg->algo == 0 && find_variant(*cfg) != nullptr);
+                                        : (cfg->algo == 0 && (find_variant(*cfg) != nullptr || is_wave_cfg(*cfg)));
     if (!known || !conv_in_range(N, C, H, W, K, R, S, stride, pad, P, Q)) return POLYDL_ERR_UNSUPPORTED;
     ConvProblem q{N, C, H, W, K, R, S, stride, pad, (int)P, (int)Q, nullptr, nullptr, nullptr, nullptr, 0};
     if (cfg->algo == 2) {
@@ -665,6 +677,11 @@ int polydl_model_conv2d(int N, int C, int H, int W, int K, int R, int S, int str
     if (cfg->algo == 3) {
         if (!conv_thin_fits(q)) return POLYDL_ERR_UNSUPPORTED;
         model_conv_thin(q, report);
+        return POLYDL_OK;
+    }
+    if (is_wave_cfg(*cfg)) {
+        if (!conv_wave_fits(q, cfg->bm)) return POLYDL_ERR_UNSUPPORTED;
+        model_conv_wave(q, *cfg, report);
         return POLYDL_OK;
     }
     int rc = 0;
@@ -678,8 +695,12 @@ int polydl_model_sgemm(int M, int N, int K, const polydl_tile_cfg *cfg, polydl_m
 {
     if (M <= 0 || N <= 0 || K <= 0) return POLYDL_ERR_BAD_DIMENSION;
     if (!cfg || !report) return POLYDL_ERR_NULL_POINTER;
-    if (!find_variant(*cfg)) return POLYDL_ERR_UNSUPPORTED;
     SgemmProblem q{M, N, K, nullptr, nullptr, nullptr};
+    if (is_wave_cfg(*cfg) && sgemm_wave_fits(q, cfg->bm)) {
+        model_sgemm_wave(q, *cfg, report);
+        return POLYDL_OK;
+    }
+    if (!find_variant(*cfg)) return POLYDL_ERR_UNSUPPORTED;
     model_sgemm(q, *cfg, threads_of(*cfg), report);
     return POLYDL_OK;
 }
@@ -875,7 +896,7 @@ int polydl_set_tile_override(const polydl_tile_cfg *cfg)
     const bool known = cfg->algo == 3   ? is_conv_thin_cfg(*cfg)
                        : cfg->algo == 2 ? is_conv_point_cfg(*cfg)
                        : cfg->algo == 1 ? (find_patch_variant(*cfg) != nullptr || find_patch_bf16_variant(*cfg) != nullptr)
-                                        : (cfg->algo == 0 && find_variant(*cfg) != nullptr);
+                                        : (cfg->algo == 0 && (find_variant(*cfg) != nullptr || is_wave_cfg(*cfg)));
     if (!known || cfg->split_k < 1 || cfg->layout < 0 || cfg->layout > 2 || (cfg->layout == 2 && cfg->algo != 0) ||
         cfg->raster < 0 ||
         cfg->raster > 3 || (cfg->raster >= 2 && cfg->algo != 0) || cfg->cb < 0 || (cfg->cb & 1))

@@ -1,0 +1,218 @@
+// Convolution of small layers as products of single waves (wave_core.hpp).  The implicit GEMM, and the ways a load finds its
+// element, are those of conv_gather.hpp; here the values of a row go to LDS as they are loaded, a lane per pixel.
+#include "conv_gather.hpp"
+#include "wave_core.hpp"
+
+namespace polydl {
+
+struct ConvWaveKArgs {
+    const float *in, *wt, *bias;
+    float *out;
+    int C, H, W, K, R, S, stride, pad;
+    int PQ, Q, RS, HW, CHW, Kg, Ng;
+    uint32_t magic_C, magic_RS, one_RS, magic_S, one_S;   // for fast_div()
+    uint32_t recip_PQ, recip_Q;                           // for div_by()
+    uint64_t in_bytes, out_bytes;
+    int act, pre_act;
+    WaveOrder order;
+    WaveParts parts;
+};
+
+// B operand: rows of the im2col matrix.  MODE: GATHER_POINT, GATHER_TAPS1, GATHER_TAPS2 or GATHER_TAPMAJOR.  A lane loads one pixel: with
+// 64 pixels a tile a row per load, with 32 two rows, the second in the upper half-wave.
+template <class T, int MODE>
+struct WaveBGather {
+    static constexpr bool POINT = MODE == GATHER_POINT, TAPMAJOR = MODE == GATHER_TAPMAJOR;
+    static constexpr bool TABLE = MODE == GATHER_TAPS1 || MODE == GATHER_TAPS2;
+    static constexpr int LAST_BIT = MODE == GATHER_TAPS1 ? 31 : 63;   // never a tap: always set
+    static constexpr int ROWS = 64 / T::WN, LOADS = 16 / ROWS;
+    // TABLE: (tap number, byte distance) of the rows of one period of RS steps, then the last step's as it ends
+    static constexpr int TABLE_ROWS = TABLE ? (LAST_BIT + 1) * 16 : 1;
+    const char *base;
+    uint32_t bytes;
+    uint32_t pix_off, lo, hi;         // byte offset of tap (0,0), or out of range; one bit per tap, set where it lies outside the image
+    int half_row;                     // ROWS == 2: the lane's row of a load
+    int C, HW, W, S, RS, Kg, pre_act;
+    uint32_t magic_C, magic_RS, one_RS, magic_S, one_S;
+    const uint2 *tab, *row;
+    uint32_t off, koff;               // of the step being fetched
+    int k0;
+
+    static __device__ __forceinline__ void fill_table(const ConvWaveKArgs &p, int tid, uint2 *t)
+    {
+        if constexpr (TABLE) {
+            const uint32_t period = (uint32_t)p.RS * 16u, last = (uint32_t)(p.Kg - 1) & ~15u;
+            const uint32_t st = last >> 4, first_of_last = (st - fast_div(st, p.magic_RS, p.one_RS) * (uint32_t)p.RS) * 16u;
+            for (uint32_t e = tid; e < period + 16u; e += kWaveThreads) {
+                const uint32_t r16 = e < period ? e : first_of_last + (e - period);
+                const bool in = e < period || last + (e - period) < (uint32_t)p.Kg;
+                const uint32_t c = fast_div(r16, p.magic_RS, p.one_RS), rs = r16 - c * (uint32_t)p.RS;
+                const uint32_t r = fast_div(rs, p.magic_S, p.one_S), s = rs - r * (uint32_t)p.S;
+                t[e] = (uint2){in ? rs : (uint32_t)LAST_BIT, (c * (uint32_t)p.HW + r * (uint32_t)p.W + s) * 4u};
+            }
+        }
+    }
+    __device__ __forceinline__ void init(const ConvWaveKArgs &p, int n0, int lane, const uint2 *t)
+    {
+        C = p.C; HW = p.HW; W = p.W; S = p.S; RS = p.RS; Kg = p.Kg; pre_act = p.pre_act;
+        magic_C = p.magic_C; magic_RS = p.magic_RS; one_RS = p.one_RS; magic_S = p.magic_S; one_S = p.one_S;
+        tab = t;
+        half_row = ROWS == 2 ? lane >> 5 : 0;
+        uint32_t rem0;
+        const int img0 = (int)div_by((uint32_t)n0, (uint32_t)p.PQ, p.recip_PQ, rem0);
+        const uint64_t skip = (uint64_t)img0 * p.CHW * 4;
+        // tap (0,0) lies up to pad rows and columns before the image: the descriptor starts that much earlier
+        const int lead = POINT ? 0 : (p.pad * p.W + p.pad) * 4;
+        base = reinterpret_cast<const char *>(p.in) + skip - lead;
+        const uint64_t left = p.in_bytes - skip + lead;
+        bytes = left > kMaxRecords ? (uint32_t)kMaxRecords : (uint32_t)left;
+        const int col = n0 + lane % T::WN;
+        pix_off = kOobOffset;
+        lo = hi = 0xFFFFFFFFu;
+        if (col < p.Ng) {
+            uint32_t pq, q;
+            const int img = (int)div_by((uint32_t)col, (uint32_t)p.PQ, p.recip_PQ, pq), oh = (int)div_by(pq, (uint32_t)p.Q, p.recip_Q, q);
+            const int ih0 = oh * p.stride - p.pad, iw0 = (int)q * p.stride - p.pad;
+            pix_off = (uint32_t)(((img - img0) * p.CHW + ih0 * p.W + iw0) * 4 + lead);
+            if constexpr (!POINT) {
+                constexpr int MAX = MODE == GATHER_TAPS1 ? 31 : 32;
+                const uint32_t rows_out = outside_bits<MAX>(-ih0, p.H - ih0, p.R), cols_out = outside_bits<MAX>(-iw0, p.W - iw0, p.S);
+                const uint32_t all_cols = low_bits<MAX>(p.S);
+                uint64_t taps = 0;
+                for (int r = 0; r < p.R; ++r) taps |= (uint64_t)((rows_out >> r) & 1u ? all_cols : cols_out) << (r * p.S);
+                lo = (uint32_t)taps;
+                hi = (uint32_t)(taps >> 32);
+                if constexpr (MODE == GATHER_TAPS1) lo |= 1u << 31;
+                else hi |= 1u << 31;
+            }
+        }
+        if constexpr (TABLE) {   // such a pixel's bits are all set
+            if (col >= p.Ng) pix_off = 0;
+        } else if constexpr (ROWS == 2) {
+            if (col < p.Ng) pix_off += (uint32_t)(half_row * p.HW) * 4u;
+        }
+    }
+    __device__ __forceinline__ void begin(int t)
+    {
+        k0 = 16 * t;
+        if constexpr (TAPMAJOR) {   // one tap for the whole step
+            const uint32_t tap = __umulhi((uint32_t)k0, magic_C), c0 = (uint32_t)k0 - tap * (uint32_t)C;
+            const uint32_t r = fast_div(tap, magic_S, one_S), s = tap - r * (uint32_t)S;
+            const uint32_t word = tap < 32u ? lo : hi;
+            off = pix_off | (((word >> (tap & 31u)) & 1u) << 31);
+            koff = (c0 * (uint32_t)HW + r * (uint32_t)W + s) * 4u;
+        }
+        if constexpr (TABLE) {
+            const uint32_t period = fast_div((uint32_t)t, magic_RS, one_RS);
+            row = tab + (k0 + 16 > Kg ? (uint32_t)RS * 16u : ((uint32_t)t - period * (uint32_t)RS) * 16u) + half_row;
+            koff = period * 16u * (uint32_t)HW * 4u;
+        }
+    }
+    template <int N>
+    __device__ __forceinline__ void load(int, bool live, v4f *dst) const
+    {
+        v4f *at = dst + N * 16;
+        if constexpr (POINT) {
+            const int k = k0 + N * ROWS;
+            if constexpr (ROWS == 1) lds_load<4>(raw_rsrc(base, live && k < Kg ? bytes : 0u), at, pix_off, (uint32_t)(k * HW) * 4u);
+            else lds_load<4>(raw_rsrc(base, live ? bytes : 0u), at, k + half_row < Kg ? pix_off : kOobOffset, (uint32_t)(k * HW) * 4u);
+        } else if constexpr (TAPMAJOR) {
+            lds_load<4>(raw_rsrc(base, live ? bytes : 0u), at, off, koff + (uint32_t)(N * ROWS * HW) * 4u);
+        } else {
+            const uint2 e = row[N * ROWS];
+            // bit 0 counts: the shift below drops the rest
+            const uint32_t outside = MODE == GATHER_TAPS1 ? lo >> e.x : (uint32_t)((((uint64_t)hi << 32) | lo) >> e.x);
+            lds_load<4>(raw_rsrc(base, live ? bytes : 0u), at, (pix_off + e.y) | (outside << 31), koff);
+        }
+    }
+    __device__ __forceinline__ void finish(float (&v)[8]) const
+    {
+        if (pre_act != POLYDL_ACT_NONE) {   // uniform
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = apply_act(v[i], pre_act);
+        }
+    }
+};
+
+template <class T, int MODE>
+__global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void conv_wave_kernel(ConvWaveKArgs p)
+{
+    typedef WaveBGather<T, MODE> Gather;
+    extern __shared__ __attribute__((aligned(16))) v4f slices[];
+    __shared__ __attribute__((aligned(16))) uint2 tab[Gather::TABLE_ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tm, tn;
+    wave_tile(p.order, blockIdx.x, tm, tn);
+    const int m0 = tm * T::WM, n0 = tn * T::WN;
+    const int first = blockIdx.y * p.parts.part_steps, last = min(p.parts.steps, first + p.parts.part_steps);
+    v16f acc[T::MB][T::NB];
+    {
+        WaveA<T> al;
+        Gather bl;
+        Gather::fill_table(p, tid, tab);
+        al.init(p.wt, m0, p.K, p.Kg, lane);
+        bl.init(p, n0, lane, tab);
+        if constexpr (Gather::TABLE) __syncthreads();
+        wave_products<T>(al, bl, acc, first + wave, last, p.Kg, slices + wave * T::SLICE, lane);
+    }
+    wave_finish<T>(slices, acc, p.parts, wave, lane, [&](int u, const v4f (&v)[T::NB]) __attribute__((always_inline)) {
+        const int ch = m0 + 32 * (u / 4) + 8 * (u % 4) + 4 * (lane >> 5), col = n0 + (lane & 31);
+        const uint32_t KPQ = (uint32_t)p.K * (uint32_t)p.PQ, row_bytes = (uint32_t)p.PQ * 4u;
+        uint32_t rem0;
+        const uint32_t img0 = div_by((uint32_t)n0, (uint32_t)p.PQ, p.recip_PQ, rem0);
+        const uint64_t skip = (uint64_t)img0 * KPQ * 4;
+        const __amdgpu_buffer_rsrc_t ro = make_rsrc(reinterpret_cast<char *>(p.out) + skip, p.out_bytes - skip);
+        const v4f bias = buf_load4(make_rsrc(p.bias, p.bias ? (uint64_t)p.K * 4 : 0), (uint32_t)ch * 4u);   // zero past K
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj) {
+            uint32_t pq;
+            const uint32_t img = div_by((uint32_t)(col + 32 * bj), (uint32_t)p.PQ, p.recip_PQ, pq);
+            const uint32_t off = col + 32 * bj < p.Ng ? ((img - img0) * KPQ + (uint32_t)ch * (uint32_t)p.PQ + pq) * 4u : kOobOffset;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                buf_store1(ro, ch + e < p.K ? off : kOobOffset, e * row_bytes, apply_act(v[bj][e] + bias[e], p.act));
+        }
+    });
+}
+
+template <class T>
+static hipError_t conv_wave_launch_t(const ConvProblem &q, int parts, hipStream_t stream)
+{
+    ConvWaveKArgs a;
+    a.in = static_cast<const float *>(q.in); a.wt = q.wt_tap ? q.wt_tap : static_cast<const float *>(q.wt);
+    a.bias = q.bias; a.out = q.out;
+    a.C = q.C; a.H = q.H; a.W = q.W; a.K = q.K; a.R = q.R; a.S = q.S;
+    a.stride = q.stride; a.pad = q.pad; a.Q = q.Q;
+    a.PQ = q.P * q.Q; a.RS = q.R * q.S; a.HW = q.H * q.W; a.CHW = q.C * q.H * q.W;
+    a.Kg = q.C * a.RS; a.Ng = q.N * a.PQ;
+    a.magic_C = div_magic((uint32_t)q.C);
+    a.magic_RS = div_magic((uint32_t)a.RS); a.one_RS = a.RS == 1 ? 0xFFFFFFFFu : 0u;
+    a.magic_S = div_magic((uint32_t)q.S); a.one_S = q.S == 1 ? 0xFFFFFFFFu : 0u;
+    a.recip_PQ = div_recip((uint32_t)a.PQ); a.recip_Q = div_recip((uint32_t)q.Q);
+    a.in_bytes = (uint64_t)q.N * a.CHW * 4;
+    a.out_bytes = (uint64_t)q.N * q.K * a.PQ * 4;
+    a.act = q.act; a.pre_act = q.pre_act;
+    const int tiles_m = (q.K + T::WM - 1) / T::WM, tiles_n = (a.Ng + T::WN - 1) / T::WN, tiles = tiles_m * tiles_n;
+    a.order = wave_order((uint32_t)tiles_m, (uint32_t)tiles_n);
+    const hipError_t e = wave_parts(a.Kg, parts, tiles, sizeof(float) * T::WM * T::WN, q.arena, stream, &a.parts);
+    if (e != hipSuccess) return e;
+    void (*kern)(ConvWaveKArgs) = q.R == 1 && q.S == 1 && q.pad == 0 ? conv_wave_kernel<T, GATHER_POINT>
+                                  : q.wt_tap ? conv_wave_kernel<T, GATHER_TAPMAJOR>
+                                  : a.RS <= 31 ? conv_wave_kernel<T, GATHER_TAPS1> : conv_wave_kernel<T, GATHER_TAPS2>;
+    return wave_launch<T>(kern, tiles, a.parts.parts, stream, a);
+}
+
+// 63 taps are what the mask bits hold; the images a tile touches, read and written, and its filter rows lie within 31-bit offsets.
+bool conv_wave_fits(const ConvProblem &q, int tile)
+{
+    const int64_t RS = (int64_t)q.R * q.S;
+    return (RS <= 63 || (RS == 1 && q.pad == 0)) && conv_tile_in_range(q, tile, tile) &&
+           ((int64_t)q.pad * q.W + q.pad) * 4 + (tile / ((int64_t)q.P * q.Q) + 2) * q.C * q.H * q.W * 4 < kMaxOffset;
+}
+
+hipError_t conv_wave_launch(const ConvProblem &q, int tile, int parts, hipStream_t stream)
+{
+    return tile == 64 ? conv_wave_launch_t<WaveTile<2, 2>>(q, parts, stream) : conv_wave_launch_t<WaveTile<1, 1>>(q, parts, stream);
+}
+
+}  // namespace polydl

@@ -567,6 +567,113 @@ void model_conv_thin(const ConvProblem &q, polydl_model_report *r)
     for (int i = 0; i < 4; ++i) { r->ws[i] = ws[i]; r->ws_level[i] = placed[i]; r->ws_traffic[i] = moved[i]; }
 }
 
+// ---- small problems: single waves (wave_core.hpp) --------------------------------------------------
+// Predicted microseconds.  Fitted to 12363 launches (1500 drawn problems of 2e6 .. 8e9 flops, 1 .. 16 parts of either tile): 7 % off in the
+// mean, 15 % in 95 of 100.  A step costs a workgroup of 32x32 tiles 0.53 us alone on its compute unit and 1.16 beside another one, of
+// 64x64 tiles (never two on a unit) 1.23; gathered operands cost up to 1.7 times that, and up to 1.5 us before the first step.
+enum WaveLoads { WAVE_ROWS, WAVE_POINT, WAVE_POINT_STRIDED, WAVE_TAP, WAVE_TAP_STRIDED, WAVE_TAPS, WAVE_TAPS_STRIDED };
+static double wave_us(int tile, int parts, double tiles, double steps, WaveLoads loads, double out_bytes)
+{
+    static const double per_step[] = {1, 1.28, 1.69, 1.07, 1.45, 1.15, 1.24}, before[] = {0, 0.76, 0.65, 1.14, 0.40, 1.56, 1.53};
+    const double part_steps = std::ceil(steps / parts), wgs = tiles * parts, cus = kCUs;
+    const double mean = part_steps / kWavesPerTile, most = std::ceil(mean);
+    double us = before[loads] + out_bytes / 4.0e6;
+    if (tile == 64) {
+        us += 0.7 + std::ceil(wgs / cus) * (4.5 + mean * 1.23 * per_step[loads]);
+        if (parts > 1) us += 1.6 + 0.2 * parts;
+    } else {
+        const double n = 0.25 * most + 0.75 * mean, rounds = wgs / (2 * cus);
+        if (wgs <= cus) us += 1.4 + 2.0 + n * 0.53 * per_step[loads];
+        else us += 1.4 + (rounds <= 1 ? 1 : 0.4 * std::ceil(rounds) + 0.6 * rounds) * (2.0 + n * 1.16 * per_step[loads]);
+        if (parts > 1) us += 1.24 + 0.17 * parts;
+    }
+    return us;
+}
+static WaveLoads wave_loads(const ConvProblem &q, int layout)
+{
+    const int strided = q.stride > 1;
+    if (q.R == 1 && q.S == 1 && q.pad == 0) return strided ? WAVE_POINT_STRIDED : WAVE_POINT;
+    if (layout == 2) return strided ? WAVE_TAP_STRIDED : WAVE_TAP;
+    return strided ? WAVE_TAPS_STRIDED : WAVE_TAPS;
+}
+// The best of both tiles and 1 .. 16 parts, if it is predicted below `limit`.
+template <class Fits>
+static bool wave_best(double M, double N, double K, WaveLoads loads, int layout, double limit, bool no_scratch, const ScratchArena *arena,
+                      Fits &&fits, polydl_tile_cfg *cfg)
+{
+    static const int kParts[] = {1, 2, 3, 4, 6, 8, 12, 16};
+    const double steps = std::ceil(K / 16), cus = kCUs;
+    bool found = false;
+    for (int tile : {32, 64}) {
+        if (!fits(tile)) continue;
+        const double tiles = std::ceil(M / tile) * std::ceil(N / tile);
+        // a handful of tiles of a few steps each: waves without work
+        if (tiles > 4096 || (tile == 32 && steps < kWavesPerTile && tiles < 16)) { if (tile == 32 && tiles <= 4096) return false; continue; }
+        for (int parts : kParts) {
+            if (parts > 1 && (no_scratch || parts * 4 > steps || tiles * parts > (tile == 64 ? 2 : 4) * cus)) break;
+            if (parts > 1 && arena && (tiles * parts * tile * tile * 4 > arena->partial_bytes || tiles > arena->ncounters)) break;
+            double us = wave_us(tile, parts, tiles, steps, loads, M * N * 4);
+            // parts of a reduction of few tiles are 2 .. 3 % better than the formula has it
+            if (parts == 1 && tiles <= 64) us *= 1.02;
+            if (us >= limit) continue;
+            limit = us;
+            *cfg = wave_cfg(tile, parts, layout);
+            found = true;
+        }
+    }
+    return found;
+}
+
+// Whether a small problem goes to single waves, given its pick's prediction.  Of 1500 drawn problems of 2e6 .. 8e9 flops these rules
+// send 1235 there, the time of all falls by a factor of 1.46 in the mean (1.48 with the best choice for each), and 6 were more than 3 %
+// slower.  The margin is what the two predictions are off.  Convolutions of fewer than 128 reduction rows run on the fp32 instruction
+// otherwise and are predicted too high, by up to 1.6: a wider margin.
+static const double kWaveMargin = 0.85, kWaveMarginShort = 0.6;
+bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
+{
+    const int64_t Kg = (int64_t)q.C * q.R * q.S;
+    const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
+    const double limit = pick_us * (Kg < kSplitMinReduction ? kWaveMarginShort : kWaveMargin);
+    return wave_best(q.K, (double)q.N * q.P * q.Q, (double)Kg, wave_loads(q, layout), layout, limit, no_scratch, q.arena,
+                     [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
+}
+bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
+{
+    return wave_best(q.M, q.N, q.K, WAVE_ROWS, 0, pick_us * kWaveMargin, no_scratch, q.arena,
+                     [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg);
+}
+
+static void model_wave(double M, double N, double Kg, WaveLoads loads, double in_bytes, const polydl_tile_cfg &cfg, polydl_model_report *r)
+{
+    std::memset(r, 0, sizeof(*r));
+    const double t = cfg.bm, tiles = std::ceil(M / t) * std::ceil(N / t), parts = std::max(1, cfg.split_k);
+    r->predicted_us = wave_us(cfg.bm, (int)parts, tiles, std::ceil(Kg / 16), loads, M * N * 4);
+    r->mfma_us = r->predicted_us;
+    r->mem_us = (in_bytes + M * Kg * 4 + M * N * 4) / kHbmGBs * 1e-3;
+    r->workgroups = (int)std::min(tiles * parts, 2e9);
+    r->simd_load = std::ceil(tiles * parts / kCUs) * kWavesPerTile / kSimdsPerCU;
+    // reuses: accumulators over a wave's steps; a step's operands, every row with every column; the operands by the tiles; the tensors
+    const double all = in_bytes + M * Kg * 4 + M * N * 4;
+    const double ws[4] = {2 * t * t * 4, 2 * t * 16 * 4, 2 * t * Kg * 4, all};
+    const double moved[4] = {0, tiles * 2 * t * Kg * 4, tiles * 2 * t * Kg * 4, all};
+    double sizes[4], weights[4];
+    for (int i = 0; i < 4; ++i) { sizes[i] = kLevels[i].capacity; weights[i] = 1.0 / kLevels[i].gbytes_per_s; }
+    int placed[4];
+    bucket_placed(4, ws, 4, sizes, r->level_bytes, &r->mem_bytes, placed);
+    r->eq1_cost = reuse_cost(4, r->level_bytes, r->mem_bytes, weights, 1.0 / kHbmGBs);
+    r->n_ws = 4;
+    for (int i = 0; i < 4; ++i) { r->ws[i] = ws[i]; r->ws_level[i] = placed[i]; r->ws_traffic[i] = moved[i]; }
+}
+
+void model_conv_wave(const ConvProblem &q, const polydl_tile_cfg &cfg, polydl_model_report *r)
+{
+    model_wave(q.K, (double)q.N * q.P * q.Q, (double)q.C * q.R * q.S, wave_loads(q, cfg.layout), (double)q.N * q.C * q.H * q.W * 4, cfg, r);
+}
+void model_sgemm_wave(const SgemmProblem &q, const polydl_tile_cfg &cfg, polydl_model_report *r)
+{
+    model_wave(q.M, q.N, q.K, WAVE_ROWS, (double)q.K * q.N * 4, cfg, r);
+}
+
 void conv_candidates(const ConvProblem &q, std::vector<ConvCandidate> *out)
 {
     out->clear();

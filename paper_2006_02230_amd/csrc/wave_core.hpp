@@ -1,0 +1,345 @@
+// Small products on split operands (split_core.hpp), without stages that waves share: a wave brings its own operands, splits
+// them in registers and multiplies.  The eight waves of a workgroup work on one tile of the result and take the reduction's
+// steps of 16 rows in turn; they meet once, at the end, in LDS.  No barrier in the loop, no trip through scratch memory
+// unless a tile's reduction is dealt to several workgroups.
+//
+// The staged kernels pay a barrier, an LDS round trip and a wait for every 16 rows and a hand-over through memory for every part of
+// a reduction that eight workgroups share; on a problem of a few stages per workgroup that is most of its time.  Here every wave
+// splits its operands for itself, 192 vector instructions per 24 matrix instructions with 64x64 tiles (the staged 128x128 tile: 96),
+// so large problems stay with the staged kernels.  Bound: those vector instructions.  Two waves of a SIMD take 3000 cycles a step of
+// 64x64x16 each (1536 of matrix cores; the bare splitting and products 2430); loads alone or products alone would take 2500.
+#pragma once
+#include "gemm_core.hpp"
+#include "internal.hpp"
+#include "split_core.hpp"
+
+namespace polydl {
+
+constexpr int kWaves = kWavesPerTile, kWaveThreads = 64 * kWaves;
+
+// Tile of MB x NB blocks of 32 x 32.
+template <int MB_, int NB_>
+struct WaveTile {
+    static constexpr int MB = MB_, NB = NB_, WM = 32 * MB, WN = 32 * NB;
+    static constexpr int UNITS = 4 * MB;                       // (row block, register quad) of the accumulators
+    static constexpr int A_WORDS = WM * 4, B_WORDS = WN * 4;   // 16-byte words of a step's operands in LDS
+    static constexpr int STEP = A_WORDS + B_WORDS;
+    static constexpr int SUMS = UNITS * NB * 64;               // and of a wave's accumulators
+    static constexpr int SLICE = SUMS > 2 * STEP ? SUMS : 2 * STEP;   // a wave's own part of LDS: two steps, later its sums
+    static constexpr int LDS_BYTES = kWaves * SLICE * 16;
+    static constexpr int WAVES_PER_SIMD = MB * NB == 1 ? 4 : 2;
+};
+
+// Which tile a workgroup takes: the order of tile_coords(), raster 1, without its divisions.
+struct WaveOrder {
+    uint32_t per, rem;                    // tiles of an XCD, of how many one more
+    uint32_t band, recip_band;            // tiles of eight tile rows
+    uint32_t bands, last_rows, recip_last;   // whole bands, tile rows of what is left
+};
+inline WaveOrder wave_order(uint32_t tiles_m, uint32_t tiles_n)
+{
+    WaveOrder o;
+    const uint32_t total = tiles_m * tiles_n;
+    o.per = total / 8; o.rem = total % 8;
+    o.band = 8 * tiles_n; o.recip_band = div_recip(o.band);
+    o.bands = tiles_m / 8; o.last_rows = tiles_m % 8;
+    o.recip_last = div_recip(o.last_rows ? o.last_rows : 1);
+    return o;
+}
+__device__ __forceinline__ void wave_tile(const WaveOrder &o, uint32_t pid, int &tm, int &tn)
+{
+    const uint32_t x = pid & 7, seq = x * o.per + min(x, o.rem) + (pid >> 3);
+    uint32_t in_band, r;
+    const uint32_t g = div_by(seq, o.band, o.recip_band, in_band);
+    if (g < o.bands) { tn = (int)(in_band >> 3); r = in_band & 7; }
+    else tn = (int)div_by(in_band, o.last_rows, o.recip_last, r);
+    tm = (int)(8 * g + r);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
+}
+
+// waits until at most N of the wave's vector-memory operations are still under way (encoding: wait_vmcnt0())
+template <int N>
+__device__ __forceinline__ void wait_vmcnt()
+{
+    static_assert(N < 64, "six bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4 << 14) | 0x0F70);
+}
+
+// lane i's BYTES bytes to dst + i * BYTES
+template <int BYTES>
+__device__ __forceinline__ void lds_load(__amdgpu_buffer_rsrc_t r, v4f *dst, uint32_t off, uint32_t uniform_off = 0)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (BYTES == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, (int)off, (int)uniform_off, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 4, (int)off, (int)uniform_off, 0, 0);
+#endif
+}
+
+// A operand: row-major, reduction contiguous; rows of any length and base (buffer loads need dwords only).  Lane i of the n-th load
+// brings 16 bytes of row 16 n + i / 4, so that four lanes read 64 bytes of a row together (a lane's row for itself: 15 % slower
+// on 1024^3); the four words of a row are swapped by its number, so that the lanes that read, each its row's eight
+// values, do not meet in the same banks.
+template <class T>
+struct WaveA {
+    static constexpr int LOADS = 2 * T::MB;
+    const char *base;
+    uint32_t row_bytes;
+    int rows;                         // that exist from the tile's first on, at most WM
+    uint32_t off;
+    int at0, at1;
+    static __device__ __forceinline__ int turn(int row) { return ((row >> 1) & 2) | (((row >> 3) ^ (row >> 1)) & 1); }
+    __device__ __forceinline__ void init(const float *A, int m0, int M, int K, int lane)
+    {
+        row_bytes = (uint32_t)K * 4u;
+        base = reinterpret_cast<const char *>(A) + (uint64_t)(uint32_t)m0 * row_bytes;
+        rows = min(M - m0, T::WM);
+        off = (uint32_t)(lane >> 2) * row_bytes + 16u * ((lane & 3) ^ turn(lane >> 2));
+        const int j = lane & 31, q = 2 * (lane >> 5);
+        at0 = j * 4 + (q ^ turn(j));
+        at1 = j * 4 + ((q + 1) ^ turn(j));
+    }
+    // live: the step exists (uniform); nothing is read otherwise
+    template <int N>
+    __device__ __forceinline__ void load(int t, bool live, v4f *dst) const
+    {
+        const uint32_t k = 64u * (uint32_t)t;
+        const int left = live ? min(max(rows - 16 * N, 0), 16) : 0;
+        lds_load<16>(raw_rsrc(base + (uint64_t)(16u * N) * row_bytes + k, left > 0 ? (uint32_t)left * row_bytes - k : 0u), dst + N * 64, off);
+    }
+    template <int BI>
+    __device__ __forceinline__ void fetch(const v4f *src, float (&v)[8]) const
+    {
+        const v4f x = src[BI * 128 + at0], y = src[BI * 128 + at1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[e] = x[e]; v[4 + e] = y[e]; }
+    }
+};
+
+template <class T>
+struct WaveOperands {
+    u32x4 a[3][T::MB], b[3][T::NB];
+    uint32_t seen = 0;
+    template <int N>
+    __device__ __forceinline__ void put(u32x4 (&x)[3][N], int block, const float (&v)[8])
+    {
+        SplitUnit<8> u;
+        u.seen = seen;
+        static_for<0, SplitUnit<8>::STEPS>([&](auto st) __attribute__((always_inline)) { u.template step<decltype(st)::value>(v); });
+        seen = u.seen;
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) x[pl][block] = (u32x4){u.p[pl][0], u.p[pl][1], u.p[pl][2], u.p[pl][3]};
+    }
+    __device__ __forceinline__ void multiply(SplitAcc<T> &s) const
+    {
+        constexpr int BLOCKS = T::MB * T::NB;
+        static_for<0, 6 * BLOCKS>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value, P = i / BLOCKS, bi = i % BLOCKS / T::NB, bj = i % T::NB;
+            constexpr int PA = P == 1 || P == 3 ? 1 : P == 4 ? 2 : 0, PB = P == 2 || P == 3 ? 1 : P == 5 ? 2 : 0;
+            if constexpr (P == 0) s.hi[bi][bj] = mfma_bf16(a[PA][bi], b[PB][bj], s.hi[bi][bj]);
+            else s.lo[bi][bj] = mfma_bf16(a[PA][bi], b[PB][bj], s.lo[bi][bj]);
+        });
+    }
+};
+
+// Steps t, t + 8, ... below last.  While one step is split and multiplied the next two are on their way into LDS.
+// The loaders' BL: load<N>(t, live, dst), N < LOADS, fills the [16][WN] image of a step, zeros for rows past the reduction's end (a
+// row of A goes on with the next row's values there); begin(t) comes before a step's loads; finish(v) ends a block's values.
+template <class T, class BL>
+__device__ __forceinline__ uint32_t wave_mainloop(const WaveA<T> &al, BL &bl, SplitAcc<T> &sum, int t, int last, v4f *slice, int lane)
+{
+    constexpr int LOADS = WaveA<T>::LOADS + BL::LOADS;
+    const float *b_at = reinterpret_cast<const float *>(slice + T::A_WORDS) + (lane >> 5) * 8 * T::WN + (lane & 31);
+    WaveOperands<T> w;
+    auto load = [&](int t, bool live, int buf) __attribute__((always_inline)) {
+        v4f *dst = slice + buf * T::STEP;
+        static_for<0, WaveA<T>::LOADS>([&](auto n) __attribute__((always_inline)) { al.template load<decltype(n)::value>(t, live, dst); });
+        bl.begin(t);
+        static_for<0, BL::LOADS>([&](auto n) __attribute__((always_inline)) { bl.template load<decltype(n)::value>(t, live, dst + T::A_WORDS); });
+    };
+    auto step = [&](int t, auto bufc) __attribute__((always_inline)) {
+        constexpr int buf = decltype(bufc)::value;
+        float va[T::MB][8], vb[T::NB][8];
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vmcnt<LOADS>();      // of the step after this one; its own have landed
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vb[bj][i] = b_at[buf * T::STEP * 4 + i * T::WN + 32 * bj];
+        static_for<0, T::MB>([&](auto b) __attribute__((always_inline)) { al.template fetch<decltype(b)::value>(slice + buf * T::STEP, va[decltype(b)::value]); });
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj) {
+            bl.finish(vb[bj]);
+            w.put(w.b, bj, vb[bj]);
+        }
+#pragma unroll
+        for (int bi = 0; bi < T::MB; ++bi) w.put(w.a, bi, va[bi]);
+        __builtin_amdgcn_sched_barrier(0);
+        load(t + 2 * kWaves, t + 2 * kWaves < last, buf);
+        __builtin_amdgcn_sched_barrier(0);
+        w.multiply(sum);
+    };
+    load(t, t < last, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(t + kWaves, t + kWaves < last, 1);
+    // in pairs, both unconditional; an odd last one behind them (why: gemm_core.hpp)
+    for (; t + kWaves < last; t += 2 * kWaves) {
+        step(t, std::integral_constant<int, 0>{});
+        step(t + kWaves, std::integral_constant<int, 1>{});
+    }
+    if (t < last) step(t, std::integral_constant<int, 0>{});
+    wait_vmcnt0();     // what was requested past the end still writes zeros into the slice
+    return w.seen;
+}
+
+// The same steps on the fp32 matrix cores, for values the split cannot hold.  K: length of the reduction.
+template <class T, class BL>
+__device__ __forceinline__ void wave_redo(const WaveA<T> &al, BL &bl, v16f (&acc)[T::MB][T::NB], int t, int last, int K, v4f *slice, int lane)
+{
+    const float *src = reinterpret_cast<const float *>(slice + T::A_WORDS) + (lane >> 5) * 8 * T::WN + (lane & 31);
+#pragma unroll
+    for (int bi = 0; bi < T::MB; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
+#pragma unroll 1   // a step's values have been read before the next one's arrive
+    for (; t < last; t += kWaves) {
+        static_for<0, WaveA<T>::LOADS>([&](auto n) __attribute__((always_inline)) { al.template load<decltype(n)::value>(t, true, slice); });
+        bl.begin(t);
+        static_for<0, BL::LOADS>([&](auto n) __attribute__((always_inline)) { bl.template load<decltype(n)::value>(t, true, slice + T::A_WORDS); });
+        wait_vmcnt0();
+        float a[T::MB][8], b[T::NB][8];
+        static_for<0, T::MB>([&](auto n) __attribute__((always_inline)) { al.template fetch<decltype(n)::value>(slice, a[decltype(n)::value]); });
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) b[bj][i] = src[i * T::WN + 32 * bj];
+            bl.finish(b[bj]);
+        }
+        const int rem = K - t * 16 - 8 * (lane >> 5);   // a row's values past its end are the next row's
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int bi = 0; bi < T::MB; ++bi)
+#pragma unroll
+                for (int bj = 0; bj < T::NB; ++bj)
+                    acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(i < rem ? a[bi][i] : 0.f, b[bj][i], acc[bi][bj], 0, 0, 0);
+    }
+}
+
+// The products of one wave: sums of its steps first + wave, + 8, ...
+template <class T, class BL>
+__device__ __forceinline__ void wave_products(const WaveA<T> &al, BL &bl, v16f (&acc)[T::MB][T::NB], int t, int last, int K, v4f *slice, int lane)
+{
+    SplitAcc<T> sum;
+    sum.clear();
+    const uint32_t seen = wave_mainloop<T>(al, bl, sum, t, last, slice, lane);
+    const bool bad = sum.finish(acc) || split_lossy(seen);
+    if (__builtin_expect(__ballot(bad) != 0, 0)) wave_redo<T>(al, bl, acc, t, last, K, slice, lane);
+}
+
+struct WaveParts {
+    int steps, part_steps, parts;    // of a tile's reduction; parts: workgroups that share it (blockIdx.y)
+    float *partials;                 // parts > 1: [tile][part][SUMS] sums in register order
+    unsigned *counters;              // parts > 1: per tile, how many of its parts have finished
+};
+
+// Cuts a reduction of `steps` steps, and fetches scratch memory for the parts (tiles: of the result, sums: bytes of one).
+inline hipError_t wave_parts(int K, int parts, int tiles, size_t tile_bytes, const ScratchArena *arena, hipStream_t stream, WaveParts *w)
+{
+    w->steps = (K + 15) / 16;
+    if (parts > w->steps) parts = w->steps;
+    if (parts < 1) parts = 1;
+    w->part_steps = (w->steps + parts - 1) / parts;
+    w->parts = (w->steps + w->part_steps - 1) / w->part_steps;
+    w->partials = nullptr;
+    w->counters = nullptr;
+    if (w->parts <= 1) return hipSuccess;
+    return splitk_scratch(stream, arena, (size_t)tiles * w->parts * tile_bytes, tiles, &w->partials, &w->counters);
+}
+
+// A kernel that needs more than the default window of LDS has to ask for it.
+template <class T, class... P, class... A>
+inline hipError_t wave_launch(void (*kernel)(P...), int tiles, int parts, hipStream_t stream, A... args)
+{
+    if (T::LDS_BYTES > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        if (e != hipSuccess) return e;
+    }
+    return launch_kernel(kernel, dim3((unsigned)tiles, (unsigned)parts), dim3(kWaveThreads), T::LDS_BYTES, stream, args...);
+}
+
+// The waves' sums meet in LDS, those of several workgroups in scratch memory (as in conv_finish()); each is added up in a
+// fixed order, the same for every order of arrival.  store(u, v): the lane's four rows of unit u in every column block, called by one wave for each unit.
+template <class T, class F>
+__device__ __forceinline__ void wave_finish(v4f *slices, const v16f (&acc)[T::MB][T::NB], const WaveParts &p, int wave, int lane, F &&store)
+{
+    v4f *mine = slices + wave * T::SLICE + lane;
+#pragma unroll
+    for (int u = 0; u < T::UNITS; ++u)
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj) {
+            const v16f &r = acc[u / 4][bj];
+            mine[(u * T::NB + bj) * 64] = (v4f){r[4 * (u % 4)], r[4 * (u % 4) + 1], r[4 * (u % 4) + 2], r[4 * (u % 4) + 3]};
+        }
+    __syncthreads();
+    static_assert(T::UNITS <= kWaves, "a wave takes at most one unit");
+    const int u = wave;
+    const bool mine_to_store = u < T::UNITS;   // uniform
+    v4f v[T::NB];
+#pragma unroll
+    for (int bj = 0; bj < T::NB; ++bj) v[bj] = (v4f){0.f, 0.f, 0.f, 0.f};
+    if (mine_to_store) {
+        // in pairs: three roundings deep instead of seven, so that no sum is further off than that of a staged tile's few parts
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj) {
+            v4f x[kWaves];
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) x[i] = slices[i * T::SLICE + (u * T::NB + bj) * 64 + lane];
+            v[bj] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+        }
+    }
+    if (p.parts > 1) {
+        __shared__ unsigned s_arrived;
+        constexpr uint32_t BYTES = T::SUMS * 16;
+        const char *part0 = reinterpret_cast<const char *>(p.partials) + (size_t)blockIdx.x * p.parts * BYTES;
+        const int off = 16 * lane + u * T::NB * 1024;
+        if (mine_to_store) {
+            const __amdgpu_buffer_rsrc_t r = raw_rsrc(part0 + (size_t)blockIdx.y * BYTES, BYTES);
+#pragma unroll
+            for (int bj = 0; bj < T::NB; ++bj)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v[bj]), r, off + bj * 1024, 0, kDeviceScope);
+        }
+        wait_vmcnt0();
+        __syncthreads();
+        if (threadIdx.x == 0)
+            s_arrived = __hip_atomic_fetch_add(p.counters + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(s_arrived) != (unsigned)p.parts - 1u) return;   // not the last part
+        if (threadIdx.x == 0) __hip_atomic_store(p.counters + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!mine_to_store) return;
+#pragma unroll
+        for (int bj = 0; bj < T::NB; ++bj) v[bj] = (v4f){0.f, 0.f, 0.f, 0.f};
+        constexpr int AHEAD = 4;
+        for (int q = 0; q < p.parts; q += AHEAD) {
+            const __amdgpu_buffer_rsrc_t r = raw_rsrc(part0 + (size_t)q * BYTES, AHEAD * BYTES);
+            v4f x[AHEAD][T::NB];
+#pragma unroll
+            for (int n = 0; n < AHEAD; ++n)
+#pragma unroll
+                for (int bj = 0; bj < T::NB; ++bj)   // parts past the last one are out of range: no access, zeros
+                    x[n][bj] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                                   r, q + n < p.parts ? off + bj * 1024 : (int)kOobOffset, n * (int)BYTES, kDeviceScope));
+#pragma unroll
+            for (int bj = 0; bj < T::NB; ++bj) v[bj] += (x[0][bj] + x[1][bj]) + (x[2][bj] + x[3][bj]);
+        }
+    }
+    if (mine_to_store) store(u, v);
+}
+
+}  // namespace polydl

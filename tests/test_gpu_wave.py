@@ -1,0 +1,181 @@
+"""Small problems on single waves (a tile of 64x64 or 32x32 whose reduction the eight waves of a workgroup share): edges of tiles,
+steps and parts, tap masks, values the split cannot hold, and the calls that go there, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import FP32_TOL, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2006_02230_amd as p
+    p.set_tile_override(None)
+    yield p
+    p.set_tile_override(None)
+
+
+def wave(P, tile, parts, layout=0):
+    return P.TileCfg(tile, tile, 16, tile, tile, parts, layout, 1, 0, 0)
+
+
+# rows and columns at, one below and one past the tiles, reductions at, below and past steps, waves and parts; one row, one column
+@pytest.mark.parametrize("tile", [64, 32])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 128), (63, 65, 127), (65, 31, 129), (1, 33, 16), (33, 1, 15), (130, 97, 3), (31, 200, 700),
+                                   (600, 95, 1000), (5, 3, 4100)])
+def test_sgemm(P, tile, M, N, K):
+    import torch
+    A, B, C0 = synth.sgemm_inputs(M, N, K, seed=M + N, c0="random")
+    want, ab = oracle.gemm(A, B, C0)
+    ints = synth.sgemm_inputs(M, N, K, seed=K, dist="ints")
+    for parts in (1, 2, 5):
+        P.set_tile_override(wave(P, tile, parts))
+        got = host(P.sgemm(dev(A), dev(B), dev(C0)))
+        assert oracle.scaled_error(got, want, ab) <= FP32_TOL, parts
+        out = torch.full((M, N), float("nan"), device="cuda")
+        got = host(P.sgemm(dev(ints[0]), dev(ints[1]), out, alpha=1.0, beta=0.0))
+        assert np.array_equal(got.astype(np.float64), ints[0].astype(np.float64) @ ints[1].astype(np.float64)), parts
+    P.set_tile_override(None)
+
+
+SHAPES = [synth.ConvShape("3x3", 2, 16, 9, 11, 70, 3, 3, 1, 1), synth.ConvShape("ragged", 3, 21, 13, 7, 33, 3, 3, 2, 1),
+          synth.ConvShape("tap_steps", 2, 48, 10, 9, 65, 3, 3, 1, 1), synth.ConvShape("small_images", 40, 32, 3, 3, 31, 3, 3, 1, 1),
+          synth.ConvShape("31_taps", 1, 10, 6, 40, 20, 1, 31, 1, 15), synth.ConvShape("32_taps", 1, 16, 12, 13, 40, 4, 8, 1, 3),
+          synth.ConvShape("63_taps", 1, 6, 18, 31, 33, 7, 9, 1, 4), synth.ConvShape("strided_5x5", 2, 32, 17, 15, 70, 5, 5, 3, 2),
+          synth.ConvShape("no_padding", 1, 5, 8, 8, 64, 2, 2, 2, 0), synth.ConvShape("past_the_image", 2, 7, 5, 4, 9, 9, 7, 1, 4),
+          synth.ConvShape("1x1", 3, 67, 9, 7, 100, 1, 1, 1, 0), synth.ConvShape("1x1_strided", 2, 130, 8, 9, 33, 1, 1, 2, 0),
+          synth.ConvShape("1x1_padded", 2, 20, 6, 5, 10, 1, 1, 1, 1), synth.ConvShape("one_of_each", 1, 1, 1, 1, 1, 1, 1, 1, 0),
+          synth.ConvShape("many_parts", 1, 256, 4, 4, 40, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=lambda s: s.name)
+def test_conv(P, s):
+    x, w, b = synth.conv_inputs(s, seed=11 + s.C, dist="normal", bias=True)
+    xi, wi, bi = synth.conv_inputs(s, seed=12 + s.C, dist="ints", bias=True)
+    dx, dw, db = dev(x), dev(w), dev(b)
+    tap = dict(w_tap=P.filter_tap_copy(dw))
+    applies = 2 <= s.R * s.S <= 63 and s.C % 16 == 0
+    exact, _ = oracle.conv2d_fwd(xi, wi, bias=bi, stride=s.stride, pad=s.pad)
+    for act, bias, pre, kw in (("relu6", True, None, {}), ("none", False, "relu", {}), ("relu", True, None, tap)):
+        layout = 2 if kw and applies else 0
+        want, ab = oracle.conv2d_fwd(np.maximum(x, 0) if pre else x, w, bias=b if bias else None, stride=s.stride, pad=s.pad, act=act)
+        for tile in (64, 32):
+            for parts in (1, 3):
+                P.set_tile_override(wave(P, tile, parts, layout))
+                got = host(P.conv2d_fwd(dx, dw, db if bias else None, stride=s.stride, pad=s.pad, act=act, pre_act=pre, **kw))
+                assert P.get_last_tile().wm == tile
+                assert oracle.scaled_error(got, want, ab) <= FP32_TOL, (tile, parts, act)
+                if act == "relu6":
+                    got = host(P.conv2d_fwd(dev(xi), dev(wi), dev(bi), stride=s.stride, pad=s.pad))
+                    assert np.array_equal(got.astype(np.float64), exact), (tile, parts)
+    P.set_tile_override(None)
+
+
+def test_refused(P):
+    for s, layout in ((synth.ConvShape("64_taps", 1, 3, 9, 9, 8, 8, 8, 1, 4), 0), (synth.ConvShape("no_copy", 1, 16, 9, 9, 8, 3, 3, 1, 1), 2)):
+        x, w, _ = synth.conv_inputs(s, seed=6, dist="normal")
+        P.set_tile_override(wave(P, 32, 1, layout))
+        with pytest.raises(P.PolydlError) as err:
+            P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad)
+        assert err.value.status == -3
+    P.set_tile_override(None)
+    for bad in (P.TileCfg(64, 64, 16, 64, 64, 1, 0, 0, 0, 0), P.TileCfg(32, 64, 16, 32, 64, 1, 0, 1, 0, 0)):
+        with pytest.raises(P.PolydlError):
+            P.set_tile_override(bad)
+
+
+# Values the split cannot hold: in the tile, and behind a row's end, where a ragged reduction reads the next row's first values
+@pytest.mark.parametrize("tile", [64, 32])
+@pytest.mark.parametrize("case", ["inf", "nan", "largest", "tiny", "row_ends"])
+def test_values_the_split_cannot_hold(P, tile, case):
+    M, N, K = 70, 75, 333
+    r = np.random.default_rng(5)
+    A, B = r.uniform(-1, 1, (M, K)).astype(np.float32), r.uniform(-1, 1, (K, N)).astype(np.float32)
+    if case == "inf":
+        A[3, 332] = np.inf
+    elif case == "nan":
+        B[0, 74] = np.nan
+    elif case == "largest":
+        A[69, 5] = np.finfo(np.float32).max
+        B[5] *= np.float32(1e-3)
+    elif case == "tiny":
+        A[:, 100:] *= np.float32(1e-37)
+        B[100:] *= np.float32(1e20)
+    else:                       # row 41 of A and row 0 of B begin with infinities, which no other row may see
+        A[41, :5] = -np.inf
+        B[0, :9] = np.inf
+    C0 = np.zeros((M, N), np.float32)
+    with np.errstate(all="ignore"):
+        want = A.astype(np.float64) @ B.astype(np.float64)
+        ab = np.abs(A.astype(np.float64)) @ np.abs(B.astype(np.float64))
+    for parts in (1, 2):
+        P.set_tile_override(wave(P, tile, parts))
+        got = host(P.sgemm(dev(A), dev(B), dev(C0)))
+        ok = np.isfinite(want)
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)].astype(np.float32))
+        assert (np.abs(got[ok] - want[ok]) <= FP32_TOL * ab[ok]).all(), parts
+    P.set_tile_override(None)
+
+
+@pytest.mark.parametrize("case", ["inf", "tiny", "tiny_filter"])
+def test_conv_values_the_split_cannot_hold(P, case):
+    for s in (synth.ConvShape("ragged", 2, 21, 9, 8, 40, 3, 3, 1, 1), synth.ConvShape("1x1", 2, 37, 6, 7, 70, 1, 1, 1, 0)):
+        x, w, _ = synth.conv_inputs(s, seed=9, dist="normal")
+        if case == "inf":
+            x[1, 3, 4, 5] = np.inf
+            if s.pad == 0:
+                w[5, 0, 0, 0] = -np.inf      # the value behind the end of row 4
+        elif case == "tiny":
+            x[:, 5:] *= np.float32(1e-37)
+            w *= np.float32(1e20)
+        else:
+            w[:, 7:] *= np.float32(1e-37)
+        with np.errstate(all="ignore"):
+            want, ab = oracle.conv2d_fwd(x, w, stride=s.stride, pad=s.pad)
+        ok = np.isfinite(want)
+        for tile in (64, 32):
+            P.set_tile_override(wave(P, tile, 2))
+            got = host(P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad))
+            assert np.array_equal(np.isfinite(got), ok)
+            assert (np.abs(got[ok] - want[ok]) <= FP32_TOL * ab[ok] + 1e-44).all(), (s.name, tile)
+    P.set_tile_override(None)
+
+
+def test_the_library_goes_there(P):
+    import torch
+    # by itself for small problems, aligned or not, with the fixed scratch memory, captured; not for large ones, one-step ones
+    s = synth.ConvShape("small", 1, 64, 56, 56, 64, 3, 3, 1, 1)
+    x, w, b = synth.conv_inputs(s, seed=13, dist="normal", bias=True)
+    want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad, act="relu")
+    kw = dict(stride=s.stride, pad=s.pad, act="relu")
+    dx, dw, db = dev(x), dev(w), dev(b)
+    eager = P.conv2d_fwd(dx, dw, db, **kw)
+    tile = P.get_last_tile()
+    assert tile.wm == tile.bm and tile.bm in (32, 64) and tile.algo == 0
+    assert oracle.scaled_error(host(eager), want, ab) <= FP32_TOL
+    assert P.model_conv2d(tuple(s)[1:], tile).predicted_us > 0
+
+    def skew(t):       # four bytes past the allocation's alignment
+        v = torch.empty(t.numel() + 1, device="cuda")[1:].view(t.shape)
+        return v.copy_(t)
+
+    for out in (P.conv2d_fwd(skew(dx), skew(dw), skew(db), out=skew(eager).fill_(-1.0), **kw),
+                P.conv2d_fwd_noalloc(dx, dw, db, torch.full_like(eager, -1.0), **kw)):
+        assert P.get_last_tile().as_dict() == tile.as_dict()
+        assert torch.equal(out, eager)
+    A, B, _ = synth.sgemm_inputs(500, 520, 510, seed=3)
+    C = torch.zeros(500, 520, device="cuda")
+    P.sgemm(dev(A), dev(B), C)
+    small = P.get_last_tile()
+    assert small.wm == small.bm
+    assert P.model_sgemm(500, 520, 510, small).predicted_us > 0
+    big = torch.zeros(4096, 4096, device="cuda")
+    P.sgemm(big, big, big.clone())
+    assert P.get_last_tile().bm > 64
