@@ -136,10 +136,19 @@ def _check(status, where):
         raise PolydlError(status, where)
 
 
+# A small call's kernel takes less time than its host side did: 8 us of a 64x64x64 product, 2.7 of them in
+# torch.cuda.current_stream(), which builds a Stream object, where the raw handle takes 0.1, and 1.5 in wrapping
+# arguments that argtypes converts anyway.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _dev(t, name):
@@ -148,19 +157,18 @@ def _dev(t, name):
         return None
     if not (t.is_cuda and t.is_contiguous() and t.dtype.is_floating_point and t.element_size() == 4):
         raise TypeError("%s must be a contiguous float32 tensor in device memory" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dev16(t, name):
     """Device pointer of a contiguous 2-byte-element tensor holding bfloat16 bit patterns."""
     if not (t.is_cuda and t.is_contiguous() and t.element_size() == 2):
         raise TypeError("%s must be a contiguous 16-bit tensor in device memory" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def nchw_to_nchwc_bf16(x, b=8, stream=None, out=None):
     """polydl_nchw_to_nchwc_bf16 on a 16-bit NCHW tensor: returns [N][ceil(C/b)][H][W][b]."""
-    import torch
     N, C, H, W = x.shape
     if out is None:
         out = torch.empty((N, -(-C // b), H, W, b), dtype=x.dtype, device=x.device)
@@ -173,7 +181,6 @@ def nchw_to_nchwc_bf16(x, b=8, stream=None, out=None):
 
 def kcrs_to_kcrsck_bf16(w, bc=8, bk=1, stream=None, out=None):
     """polydl_kcrs_to_kcrsck_bf16: returns [ceil(K/bk)][ceil(C/bc)][R][S][bc][bk] (16-bit elements)."""
-    import torch
     K, C, R, S = w.shape
     if out is None:
         out = torch.empty((-(-K // bk), -(-C // bc), R, S, bc, bk), dtype=w.dtype, device=w.device)
@@ -186,7 +193,6 @@ def kcrs_to_kcrsck_bf16(w, bc=8, bk=1, stream=None, out=None):
 
 def conv2d_fwd_bf16_blocked(x8c, w8c, C, bias=None, out=None, stride=1, pad=0, act=None, stream=None):
     """polydl_conv2d_fwd_bf16_blocked: x8c [N][C/8][H][W][8], w8c [K][C/8][R][S][8][1] bf16 bits."""
-    import torch
     N, _, H, W, _ = x8c.shape
     K, _, R, S = w8c.shape[:4]
     P = (H + 2 * pad - R) // stride + 1
@@ -202,7 +208,6 @@ def conv2d_fwd_bf16_blocked(x8c, w8c, C, bias=None, out=None, stride=1, pad=0, a
 
 def conv2d_fwd_bf16(x, w, bias=None, out=None, stride=1, pad=0, act=None, workspace=None, stream=None):
     """polydl_conv2d_fwd_bf16 on 16-bit NCHW / KCRS tensors; allocates the workspace when not given."""
-    import torch
     N, C, H, W = x.shape
     K, _, R, S = w.shape
     P = (H + 2 * pad - R) // stride + 1
@@ -214,7 +219,7 @@ def conv2d_fwd_bf16(x, w, bias=None, out=None, stride=1, pad=0, act=None, worksp
         out = torch.empty((N, K, max(P, 0), max(Q, 0)), dtype=torch.float32, device=x.device)
     st = lib.polydl_conv2d_fwd_bf16(N, C, H, W, K, R, S, stride, pad, _dev16(x, "x"), _dev16(w, "w"),
                                     _dev(bias, "bias"), _dev(out, "out"), ACT[act],
-                                    ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream_ptr(stream))
+                                    workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     _check(st, "polydl_conv2d_fwd_bf16")
     return out
 
@@ -230,7 +235,6 @@ def conv2d_fwd(x, w, bias=None, out=None, stride=1, pad=0, act=None, stream=None
     """polydl_conv2d_fwd_act on torch device tensors x (NCHW), w (KCRS); returns out (NKPQ).
     With pre_act given, polydl_conv2d_fwd_pre_act: the convolution of pre_act(x).
     With w_tap given (filter_tap_copy(w)), polydl_conv2d_fwd_tap."""
-    import torch
     N, C, H, W = x.shape
     K, C2, R, S = w.shape
     if C2 != C:
@@ -276,21 +280,20 @@ def sgemm(A, B, C, stream=None, alpha=None, beta=None):
     given, polydl_sgemm_ex: C = beta*C + alpha*A@B."""
     M, K = A.shape
     K2, N = B.shape
-    if K2 != K or tuple(C.shape) != (M, N):
+    if K2 != K or C.shape != (M, N):
         raise ValueError("shape mismatch")
     if alpha is None and beta is None:
         st = lib.polydl_sgemm(M, N, K, _dev(A, "A"), _dev(B, "B"), _dev(C, "C"), _stream_ptr(stream))
         _check(st, "polydl_sgemm")
         return C
-    st = lib.polydl_sgemm_ex(M, N, K, ctypes.c_float(1.0 if alpha is None else alpha), _dev(A, "A"), _dev(B, "B"),
-                             ctypes.c_float(1.0 if beta is None else beta), _dev(C, "C"), _stream_ptr(stream))
+    st = lib.polydl_sgemm_ex(M, N, K, 1.0 if alpha is None else alpha, _dev(A, "A"), _dev(B, "B"),
+                             1.0 if beta is None else beta, _dev(C, "C"), _stream_ptr(stream))
     _check(st, "polydl_sgemm_ex")
     return C
 
 
 def nchw_to_nchwc(x, b, stream=None, out=None):
     """polydl_nchw_to_nchwc: returns the [N][ceil(C/b)][H][W][b] tensor (written into out if given)."""
-    import torch
     N, C, H, W = x.shape
     if out is None:
         out = torch.empty((N, -(-C // b), H, W, b), dtype=torch.float32, device=x.device)
@@ -301,7 +304,6 @@ def nchw_to_nchwc(x, b, stream=None, out=None):
 
 def nchwc_to_nchw(xb, C, stream=None, out=None):
     """polydl_nchwc_to_nchw: returns the [N][C][H][W] tensor (written into out if given)."""
-    import torch
     N, Cb, H, W, b = xb.shape
     if out is None:
         out = torch.empty((N, C, H, W), dtype=torch.float32, device=xb.device)
@@ -312,7 +314,6 @@ def nchwc_to_nchw(xb, C, stream=None, out=None):
 
 def kcrs_to_kcrsck(w, bc, bk, stream=None, out=None):
     """polydl_kcrs_to_kcrsck: returns the [ceil(K/bk)][ceil(C/bc)][R][S][bc][bk] tensor (out if given)."""
-    import torch
     K, C, R, S = w.shape
     if out is None:
         out = torch.empty((-(-K // bk), -(-C // bc), R, S, bc, bk), dtype=torch.float32, device=w.device)
@@ -330,7 +331,6 @@ def bias_add(y, bias, stream=None):
 
 def bnorm_fwd(x, gamma, beta, mean, var, eps=1e-5, out=None, act=None, stream=None):
     """polydl_bnorm_fwd on an NKPQ tensor; out defaults to a new tensor (pass out=x for in place)."""
-    import torch
     N, K, P, Q = x.shape
     if out is None:
         out = torch.empty_like(x)
