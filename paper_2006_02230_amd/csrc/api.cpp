@@ -463,7 +463,7 @@ static void bf16_candidates(const ConvProblem &qb, std::vector<polydl_tile_cfg> 
 static int bf16_threads(const polydl_tile_cfg &c) { return (c.bm / c.wm) * (c.bn / c.wn) * 64; }
 
 // bf16 candidates are ranked with the round-by-round time model at the bf16 instruction's rate
-static bool pick_bf16(const ConvProblem &qb, polydl_tile_cfg *out)
+static bool pick_bf16(const ConvProblem &qb, polydl_tile_cfg *out, double *us = nullptr)
 {
     std::vector<polydl_tile_cfg> cands;
     bf16_candidates(qb, &cands);
@@ -473,6 +473,7 @@ static bool pick_bf16(const ConvProblem &qb, polydl_tile_cfg *out)
         const double t = model_conv_bf16(qb, c, bf16_threads(c));
         if (!have || t < best * 0.999) { best = t; *out = c; have = true; }
     }
+    if (us) *us = best;
     return have;
 }
 
@@ -497,7 +498,7 @@ int polydl_conv2d_fwd_bf16_blocked(int N, int C, int H, int W, int K, int R, int
         cfg = g_override;
     }
     if (forced) {
-        if (cfg.algo != 1) return POLYDL_ERR_UNSUPPORTED;
+        if (cfg.algo != 1 && !is_wave_cfg(cfg)) return POLYDL_ERR_UNSUPPORTED;
     } else {
         // the pick depends on the shape alone: made once per shape
         const std::array<int, 9> key = {N, cunits, H, W, K, R, S, stride, pad};
@@ -506,9 +507,23 @@ int polydl_conv2d_fwd_bf16_blocked(int N, int C, int H, int W, int K, int R, int
         if (it != g_bf16_plans.end()) {
             cfg = it->second;
         } else {
-            if (!pick_bf16(q, &cfg)) return POLYDL_ERR_UNSUPPORTED;
+            double us;
+            if (!pick_bf16(q, &cfg, &us)) return POLYDL_ERR_UNSUPPORTED;
+            conv_wave_bf16_pick(q, us, false, &cfg);
             g_bf16_plans[key] = cfg;
         }
+    }
+    if (is_wave_cfg(cfg)) {
+        if (!conv_wave_bf16_fits(q, cfg.bm)) return POLYDL_ERR_UNSUPPORTED;
+        const hipError_t we = conv_wave_bf16_launch(q, cfg.bm, cfg.split_k, (hipStream_t)stream);
+        if (we == hipSuccess) {
+            cfg.layout = 1;
+            std::lock_guard<std::mutex> lk(g_mu);
+            g_last = cfg;
+            return POLYDL_OK;
+        }
+        // the stream is being captured and has no scratch memory for the parts: the ranked pick (not cached), which may need none
+        if (forced || !refused_for_capture(we) || !pick_bf16(q, &cfg)) return launch_failed(we);
     }
     const PatchVariant *pv = find_patch_bf16_variant(cfg);
     if (!pv) return POLYDL_ERR_UNSUPPORTED;
@@ -807,6 +822,11 @@ int polydl_model_conv2d_bf16(int N, int C, int H, int W, int K, int R, int S, in
     int st = POLYDL_OK;
     if (!bf16_problem(N, C, H, W, K, R, S, stride, pad, &q, &st)) return st;
     if (!cfg || !predicted_us) return POLYDL_ERR_NULL_POINTER;
+    if (is_wave_cfg(*cfg)) {
+        if (!conv_wave_bf16_fits(q, cfg->bm) || cfg->split_k < 1) return POLYDL_ERR_UNSUPPORTED;
+        *predicted_us = model_conv_wave_bf16(q, *cfg);
+        return POLYDL_OK;
+    }
     for (int i = 0; i < kNumPatchBf16Variants; ++i) {
         const PatchVariant &v = kPatchBf16Variants[i];
         if (v.bm != cfg->bm || v.bn != cfg->bn || v.wm != cfg->wm || v.wn != cfg->wn) continue;

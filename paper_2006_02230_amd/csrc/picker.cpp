@@ -571,21 +571,27 @@ void model_conv_thin(const ConvProblem &q, polydl_model_report *r)
 // Predicted microseconds.  Fitted to 12363 launches (1500 drawn problems of 2e6 .. 8e9 flops, 1 .. 16 parts of either tile): 7 % off in the
 // mean, 15 % in 95 of 100.  A step costs a workgroup of 32x32 tiles 0.53 us alone on its compute unit and 1.16 beside another one, of
 // 64x64 tiles (never two on a unit) 1.23; gathered operands cost up to 1.7 times that, and up to 1.5 us before the first step.
-enum WaveLoads { WAVE_ROWS, WAVE_POINT, WAVE_POINT_STRIDED, WAVE_TAP, WAVE_TAP_STRIDED, WAVE_TAPS, WAVE_TAPS_STRIDED };
+// bfloat16 (a step is four units of eight channels): 7969 launches of 1000 drawn layers of 5e6 .. 3e10 flops, 9 % off in the mean.
+enum WaveLoads { WAVE_ROWS, WAVE_POINT, WAVE_POINT_STRIDED, WAVE_TAP, WAVE_TAP_STRIDED, WAVE_TAPS, WAVE_TAPS_STRIDED,
+                 WAVE_BF16_POINT, WAVE_BF16_POINT_STRIDED, WAVE_BF16_TAPS, WAVE_BF16_TAPS_STRIDED };
+struct WaveFit { double launch, round, step1, step2, parts, part; };   // step1, step2: one, two workgroups on a compute unit
 static double wave_us(int tile, int parts, double tiles, double steps, WaveLoads loads, double out_bytes)
 {
-    static const double per_step[] = {1, 1.28, 1.69, 1.07, 1.45, 1.15, 1.24}, before[] = {0, 0.76, 0.65, 1.14, 0.40, 1.56, 1.53};
-    const double part_steps = std::ceil(steps / parts), wgs = tiles * parts, cus = kCUs;
-    const double mean = part_steps / kWavesPerTile, most = std::ceil(mean);
-    double us = before[loads] + out_bytes / 4.0e6;
+    static const double per_step[] = {1, 1.28, 1.69, 1.07, 1.45, 1.15, 1.24, 1, 1.53, 1.39, 1.59};
+    static const double before[] = {0, 0.76, 0.65, 1.14, 0.40, 1.56, 1.53, 0, -0.27, -0.27, -0.60};
+    static const WaveFit fits[2][2] = {{{1.4, 2.0, 0.53, 1.16, 1.24, 0.17}, {0.7, 4.5, 1.23, 0, 1.6, 0.2}},
+                                       {{2.0, 2.4, 0.168, 0.395, 1.42, 0.19}, {2.1, 3.7, 0.381, 0, 1.77, 0.23}}};
+    const bool bf16 = loads >= WAVE_BF16_POINT;
+    const WaveFit &f = fits[bf16][tile == 64];
+    const double mean = std::ceil(steps / parts) / kWavesPerTile, most = std::ceil(mean), wgs = tiles * parts, cus = kCUs;
+    double us = before[loads] + out_bytes / 4.0e6 + f.launch + (parts > 1 ? f.parts + f.part * parts : 0);
     if (tile == 64) {
-        us += 0.7 + std::ceil(wgs / cus) * (4.5 + mean * 1.23 * per_step[loads]);
-        if (parts > 1) us += 1.6 + 0.2 * parts;
+        const double n = bf16 ? 0.33 * most + 0.67 * mean : mean;
+        us += std::ceil(wgs / cus) * (f.round + n * f.step1 * per_step[loads]);
     } else {
-        const double n = 0.25 * most + 0.75 * mean, rounds = wgs / (2 * cus);
-        if (wgs <= cus) us += 1.4 + 2.0 + n * 0.53 * per_step[loads];
-        else us += 1.4 + (rounds <= 1 ? 1 : 0.4 * std::ceil(rounds) + 0.6 * rounds) * (2.0 + n * 1.16 * per_step[loads]);
-        if (parts > 1) us += 1.24 + 0.17 * parts;
+        const double n = bf16 ? most : 0.25 * most + 0.75 * mean, rounds = wgs / (2 * cus);
+        if (wgs <= cus) us += f.round + n * f.step1 * per_step[loads];
+        else us += (rounds <= 1 ? 1 : 0.4 * std::ceil(rounds) + 0.6 * rounds) * (f.round + n * f.step2 * per_step[loads]);
     }
     return us;
 }
@@ -596,19 +602,21 @@ static WaveLoads wave_loads(const ConvProblem &q, int layout)
     if (layout == 2) return strided ? WAVE_TAP_STRIDED : WAVE_TAP;
     return strided ? WAVE_TAPS_STRIDED : WAVE_TAPS;
 }
-// The best of both tiles and 1 .. 16 parts, if it is predicted below `limit`.
+// The best of both tiles and 1 .. 16 parts, if it is predicted below `limit`, for tiles of 64x64 `limit64`.
 template <class Fits>
-static bool wave_best(double M, double N, double K, WaveLoads loads, int layout, double limit, bool no_scratch, const ScratchArena *arena,
+static bool wave_best(double M, double N, double steps, WaveLoads loads, int layout, double limit, double limit64, bool no_scratch, const ScratchArena *arena,
                       Fits &&fits, polydl_tile_cfg *cfg)
 {
     static const int kParts[] = {1, 2, 3, 4, 6, 8, 12, 16};
-    const double steps = std::ceil(K / 16), cus = kCUs;
+    const double cus = kCUs;
     bool found = false;
     for (int tile : {32, 64}) {
         if (!fits(tile)) continue;
         const double tiles = std::ceil(M / tile) * std::ceil(N / tile);
         // a handful of tiles of a few steps each: waves without work
-        if (tiles > 4096 || (tile == 32 && steps < kWavesPerTile && tiles < 16)) { if (tile == 32 && tiles <= 4096) return false; continue; }
+        if (tile == 32 && steps < kWavesPerTile && tiles < 16) return false;
+        if (tiles > 4096) continue;
+        if (tile == 64) limit = std::min(limit, limit64);
         for (int parts : kParts) {
             if (parts > 1 && (no_scratch || parts * 4 > steps || tiles * parts > (tile == 64 ? 2 : 4) * cus)) break;
             if (parts > 1 && arena && (tiles * parts * tile * tile * 4 > arena->partial_bytes || tiles > arena->ncounters)) break;
@@ -634,13 +642,39 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
     const int64_t Kg = (int64_t)q.C * q.R * q.S;
     const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
     const double limit = pick_us * (Kg < kSplitMinReduction ? kWaveMarginShort : kWaveMargin);
-    return wave_best(q.K, (double)q.N * q.P * q.Q, (double)Kg, wave_loads(q, layout), layout, limit, no_scratch, q.arena,
+    return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
 }
 bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
-    return wave_best(q.M, q.N, q.K, WAVE_ROWS, 0, pick_us * kWaveMargin, no_scratch, q.arena,
+    const double limit = pick_us * kWaveMargin;
+    return wave_best(q.M, q.N, std::ceil(q.K / 16.0), WAVE_ROWS, 0, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg);
+}
+
+// bfloat16, q.C units of eight channels.  Of 1000 drawn layers of 5e6 .. 3e10 flops about 690 go there, the time of all falls by a
+// factor of 1.39 (1.43 with the best choice for each), about ten were more than 3 % slower.  Up to eight units a row leave most waves without a
+// step; picks predicted at the floor of their model (8.8 us) take 5 us and more, which the larger tile does not undercut.
+static WaveLoads wave_bf16_loads(const ConvProblem &q)
+{
+    const bool strided = q.stride > 1;
+    if (q.R == 1 && q.S == 1) return strided ? WAVE_BF16_POINT_STRIDED : WAVE_BF16_POINT;
+    return strided ? WAVE_BF16_TAPS_STRIDED : WAVE_BF16_TAPS;
+}
+bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
+{
+    const int64_t units = (int64_t)q.C * q.R * q.S;
+    if (units <= 8) return false;
+    const double limit = 0.88 * pick_us;
+    return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(units / 4.0), wave_bf16_loads(q), 0, limit, pick_us < 9.5 ? 0.73 * pick_us : limit, no_scratch,
+                     q.arena, [&](int tile) { return conv_wave_bf16_fits(q, tile); }, cfg);
+}
+
+double model_conv_wave_bf16(const ConvProblem &q, const polydl_tile_cfg &cfg)
+{
+    const double M = q.K, N = (double)q.N * q.P * q.Q;
+    return wave_us(cfg.bm, std::max(1, cfg.split_k), std::ceil(M / cfg.bm) * std::ceil(N / cfg.bm), std::ceil(q.C * q.R * q.S / 4.0),
+                   wave_bf16_loads(q), M * N * 4);
 }
 
 static void model_wave(double M, double N, double Kg, WaveLoads loads, double in_bytes, const polydl_tile_cfg &cfg, polydl_model_report *r)

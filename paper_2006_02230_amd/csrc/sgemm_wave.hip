@@ -91,7 +91,7 @@ static hipError_t sgemm_wave_launch_t(const SgemmProblem &q, int parts, hipStrea
     a.alpha = q.alpha; a.beta = q.beta;
     const int tiles_m = (q.M + T::WM - 1) / T::WM, tiles_n = (q.N + T::WN - 1) / T::WN, tiles = tiles_m * tiles_n;
     a.order = wave_order((uint32_t)tiles_m, (uint32_t)tiles_n);
-    const hipError_t e = wave_parts(q.K, parts, tiles, sizeof(float) * T::WM * T::WN, q.arena, stream, &a.parts);
+    const hipError_t e = wave_parts((q.K + 15) / 16, parts, tiles, sizeof(float) * T::WM * T::WN, q.arena, stream, &a.parts);
     if (e != hipSuccess) return e;
     return wave_launch<T>(sgemm_wave_kernel<T>, tiles, a.parts.parts, stream, a);
 }

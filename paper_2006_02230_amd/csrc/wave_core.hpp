@@ -250,9 +250,9 @@ struct WaveParts {
 };
 
 // Cuts a reduction of `steps` steps, and fetches scratch memory for the parts (tiles: of the result, sums: bytes of one).
-inline hipError_t wave_parts(int K, int parts, int tiles, size_t tile_bytes, const ScratchArena *arena, hipStream_t stream, WaveParts *w)
+inline hipError_t wave_parts(int steps, int parts, int tiles, size_t tile_bytes, const ScratchArena *arena, hipStream_t stream, WaveParts *w)
 {
-    w->steps = (K + 15) / 16;
+    w->steps = steps;
     if (parts > w->steps) parts = w->steps;
     if (parts < 1) parts = 1;
     w->part_steps = (w->steps + parts - 1) / parts;

@@ -179,3 +179,69 @@ def test_the_library_goes_there(P):
     big = torch.zeros(4096, 4096, device="cuda")
     P.sgemm(big, big, big.clone())
     assert P.get_last_tile().bm > 64
+
+
+BF16 = SHAPES + [synth.ConvShape("two_steps", 2, 64, 5, 7, 40, 1, 1, 1, 0), synth.ConvShape("41_steps", 1, 144, 9, 9, 70, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("s", BF16, ids=lambda s: s.name)
+def test_bf16(P, s):
+    import torch
+    x, w, b = synth.conv_inputs(s, seed=14 + s.C, dist="normal", bias=True)
+    xi, wi, bi = synth.conv_inputs(s, seed=15 + s.C, dist="ints", bias=True)
+    exact, _ = oracle.conv2d_fwd(xi, wi, bias=bi, stride=s.stride, pad=s.pad)
+    tx, tw = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, w))
+    want, ab = oracle.conv2d_fwd(host(tx.float()), host(tw.float()), bias=b, stride=s.stride, pad=s.pad, act="relu")
+    blocked = lambda a, f: (P.nchw_to_nchwc_bf16(a, 8), P.kcrs_to_kcrsck_bf16(f, 8, 1))
+    for tile in (64, 32):
+        for parts in (1, 2, 5):
+            P.set_tile_override(wave(P, tile, parts))
+            got = host(P.conv2d_fwd_bf16_blocked(*blocked(tx, tw), s.C, dev(b), stride=s.stride, pad=s.pad, act="relu"))
+            assert oracle.scaled_error(got, want, ab) <= FP32_TOL, (tile, parts)      # products of bfloat16 values are exact in fp32
+            ints = [torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (xi, wi)]
+            got = host(P.conv2d_fwd_bf16_blocked(*blocked(*ints), s.C, dev(bi), stride=s.stride, pad=s.pad))
+            assert np.array_equal(got.astype(np.float64), exact), (tile, parts)
+    P.set_tile_override(None)
+
+
+def test_bf16_infinity_at_the_end_of_a_filter_row(P):
+    # the reduction ends inside a step: what lies behind a row's end is the next row, which begins with an infinity
+    import torch
+    s = synth.ConvShape("ends", 1, 40, 6, 6, 40, 1, 1, 1, 0)
+    x, w, _ = synth.conv_inputs(s, seed=16, dist="normal")
+    w[5, 0] = np.inf
+    for tile in (64, 32):
+        P.set_tile_override(wave(P, tile, 1))
+        tx, tw = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, w))
+        got = host(P.conv2d_fwd_bf16(tx, tw))
+        assert np.isfinite(got[:, :5]).all() and np.isfinite(got[:, 6:]).all() and not np.isfinite(got[:, 5]).any()
+    P.set_tile_override(None)
+
+
+def test_bf16_the_library_goes_there_and_is_captured(P):
+    import torch
+    s = synth.ConvShape("small", 1, 512, 14, 14, 128, 3, 3, 1, 1)
+    x, w, b = synth.conv_inputs(s, seed=17, dist="normal", bias=True)
+    tx, tw, tb = torch.from_numpy(x).cuda().to(torch.bfloat16), torch.from_numpy(w).cuda().to(torch.bfloat16), dev(b)
+    x8, w8 = P.nchw_to_nchwc_bf16(tx, 8), P.kcrs_to_kcrsck_bf16(tw, 8, 1)
+    out = torch.empty(1, 128, 14, 14, device="cuda")
+    call = lambda: P.conv2d_fwd_bf16_blocked(x8, w8, s.C, tb, out=out, stride=1, pad=1, act="relu")
+    eager = host(call())
+    tile = P.get_last_tile()
+    assert tile.wm == tile.bm
+    assert P.model_conv2d_bf16(tuple(s)[1:], tile) > 0
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call()                              # its scratch memory
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            call()
+    for _ in range(3):
+        out.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host(out), eager)
+        call()
+        torch.cuda.synchronize()
