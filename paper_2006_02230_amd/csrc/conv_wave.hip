@@ -35,9 +35,13 @@ struct WaveBGather {
     int half_row;                     // ROWS == 2: the lane's row of a load
     int C, HW, W, S, RS, Kg, pre_act;
     uint32_t magic_C, magic_RS, one_RS, magic_S, one_S;
-    const uint2 *tab, *row;
-    uint32_t off, koff;               // of the step being fetched
+    const uint2 *tab;
+    // of the step being fetched
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t off, koff;
     int k0;
+    bool live;
+    uint2 rows[TABLE ? LOADS : 1];
 
     static __device__ __forceinline__ void fill_table(const ConvWaveKArgs &p, int tid, uint2 *t)
     {
@@ -93,9 +97,11 @@ struct WaveBGather {
             if (col < p.Ng) pix_off += (uint32_t)(half_row * p.HW) * 4u;
         }
     }
-    __device__ __forceinline__ void begin(int t)
+    __device__ __forceinline__ void begin(int t, bool live_)
     {
         k0 = 16 * t;
+        live = live_;
+        rsrc = raw_rsrc(base, live ? bytes : 0u);
         if constexpr (TAPMAJOR) {   // one tap for the whole step
             const uint32_t tap = __umulhi((uint32_t)k0, magic_C), c0 = (uint32_t)k0 - tap * (uint32_t)C;
             const uint32_t r = fast_div(tap, magic_S, one_S), s = tap - r * (uint32_t)S;
@@ -103,27 +109,29 @@ struct WaveBGather {
             off = pix_off | (((word >> (tap & 31u)) & 1u) << 31);
             koff = (c0 * (uint32_t)HW + r * (uint32_t)W + s) * 4u;
         }
-        if constexpr (TABLE) {
+        if constexpr (TABLE) {      // the rows' entries together: one by one, each load would wait for its own
             const uint32_t period = fast_div((uint32_t)t, magic_RS, one_RS);
-            row = tab + (k0 + 16 > Kg ? (uint32_t)RS * 16u : ((uint32_t)t - period * (uint32_t)RS) * 16u) + half_row;
+            const uint2 *row = tab + (k0 + 16 > Kg ? (uint32_t)RS * 16u : ((uint32_t)t - period * (uint32_t)RS) * 16u) + half_row;
+#pragma unroll
+            for (int n = 0; n < LOADS; ++n) rows[n] = row[n * ROWS];
             koff = period * 16u * (uint32_t)HW * 4u;
         }
     }
     template <int N>
-    __device__ __forceinline__ void load(int, bool live, v4f *dst) const
+    __device__ __forceinline__ void load(v4f *dst) const
     {
         v4f *at = dst + N * 16;
         if constexpr (POINT) {
             const int k = k0 + N * ROWS;
             if constexpr (ROWS == 1) lds_load<4>(raw_rsrc(base, live && k < Kg ? bytes : 0u), at, pix_off, (uint32_t)(k * HW) * 4u);
-            else lds_load<4>(raw_rsrc(base, live ? bytes : 0u), at, k + half_row < Kg ? pix_off : kOobOffset, (uint32_t)(k * HW) * 4u);
+            else lds_load<4>(rsrc, at, k + half_row < Kg ? pix_off : kOobOffset, (uint32_t)(k * HW) * 4u);
         } else if constexpr (TAPMAJOR) {
-            lds_load<4>(raw_rsrc(base, live ? bytes : 0u), at, off, koff + (uint32_t)(N * ROWS * HW) * 4u);
+            lds_load<4>(rsrc, at, off, koff + (uint32_t)(N * ROWS * HW) * 4u);
         } else {
-            const uint2 e = row[N * ROWS];
+            const uint2 e = rows[N];
             // bit 0 counts: the shift below drops the rest
             const uint32_t outside = MODE == GATHER_TAPS1 ? lo >> e.x : (uint32_t)((((uint64_t)hi << 32) | lo) >> e.x);
-            lds_load<4>(raw_rsrc(base, live ? bytes : 0u), at, (pix_off + e.y) | (outside << 31), koff);
+            lds_load<4>(rsrc, at, (pix_off + e.y) | (outside << 31), koff);
         }
     }
     __device__ __forceinline__ void finish(float (&v)[8]) const
@@ -265,10 +273,11 @@ __global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void conv_wave_bf1
     auto load = [&](auto set, int t) __attribute__((always_inline)) {
         constexpr int SET = decltype(set)::value;
         const bool live = t < last;
-        const uint32_t keep = al.off;
-        al.off = 4 * t + quad < p.Kg ? keep : kOobOffset;      // a unit past the end of a filter row is the next row's first
-        static_for<0, A_LOADS>([&](auto n) __attribute__((always_inline)) { al.template load<decltype(n)::value>(t, live, slice + SET * T::STEP); });
-        al.off = keep;
+        al.begin(t, live);
+        const uint32_t behind = 4 * t + quad < p.Kg ? 0u : kOobOffset;      // a unit past the end of a filter row is the next row's first
+        static_for<0, A_LOADS>([&](auto n) __attribute__((always_inline)) {
+            lds_load<16>(al.rsrc, slice + SET * T::STEP + decltype(n)::value * 64, al.off[decltype(n)::value] | behind);
+        });
         const uint32_t period = fast_div((uint32_t)t, p.magic_RS, p.one_RS), koff = period * 4u * (uint32_t)p.HW * 16u;
         const uint2 *row = tab + (4 * t + 4 > p.Kg ? (uint32_t)p.RS * 4u : ((uint32_t)t - period * (uint32_t)p.RS) * 4u) + half;
         const __amdgpu_buffer_rsrc_t r = raw_rsrc(in, live ? in_bytes : 0u);

@@ -17,8 +17,9 @@ template <class T>
 struct WaveBRows {
     static constexpr int PER_ROW = T::WN / 4, ROWS = 64 / PER_ROW, LOADS = 16 / ROWS;
     const char *base;
-    uint32_t row_bytes, row_rest, off;   // row_rest: bytes from the tile's first column to the end of a row
+    uint32_t row_bytes, row_rest, off[LOADS];   // row_rest: bytes from the tile's first column to the end of a row
     int K;
+    __amdgpu_buffer_rsrc_t rsrc;                // of the step being fetched
     __device__ __forceinline__ void init(const float *B, int n0, int N, int K_, int lane)
     {
         K = K_;
@@ -26,16 +27,18 @@ struct WaveBRows {
         row_rest = (uint32_t)(N - n0) * 4u;
         row_bytes = (uint32_t)N * 4u;
         const int col = lane % PER_ROW * 4;
-        off = n0 + col < N ? (uint32_t)(lane / PER_ROW) * row_bytes + 4u * col : kOobOffset;
+#pragma unroll
+        for (int n = 0; n < LOADS; ++n) off[n] = n0 + col < N ? (uint32_t)(n * ROWS + lane / PER_ROW) * row_bytes + 4u * col : kOobOffset;
     }
-    __device__ __forceinline__ void begin(int) {}
-    __device__ __forceinline__ void finish(float (&)[8]) const {}
-    template <int N>
-    __device__ __forceinline__ void load(int t, bool live, v4f *dst) const
+    // rows past the end lie out of range
+    __device__ __forceinline__ void begin(int t, bool live)
     {
-        const int k = 16 * t + N * ROWS, left = live ? min(K - k, ROWS) : 0;
-        lds_load<16>(raw_rsrc(base + (uint64_t)(uint32_t)k * row_bytes, left > 0 ? (uint32_t)(left - 1) * row_bytes + row_rest : 0u), dst + N * 64, off);
+        const uint32_t k = live ? 16u * (uint32_t)t : 0u, rows = min((uint32_t)K - k, 16u);
+        rsrc = raw_rsrc(base + (uint64_t)k * row_bytes, live ? (rows - 1u) * row_bytes + row_rest : 0u);
     }
+    template <int N>
+    __device__ __forceinline__ void load(v4f *dst) const { lds_load<16>(rsrc, dst + N * 64, off[N]); }
+    __device__ __forceinline__ void finish(float (&)[8]) const {}
 };
 
 template <class T>

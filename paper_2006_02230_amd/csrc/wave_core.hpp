@@ -6,8 +6,8 @@
 // The staged kernels pay a barrier, an LDS round trip and a wait for every 16 rows and a hand-over through memory for every part of
 // a reduction that eight workgroups share; on a problem of a few stages per workgroup that is most of its time.  Here every wave
 // splits its operands for itself, 192 vector instructions per 24 matrix instructions with 64x64 tiles (the staged 128x128 tile: 96),
-// so large problems stay with the staged kernels.  Bound: those vector instructions.  Two waves of a SIMD take 3000 cycles a step of
-// 64x64x16 each (1536 of matrix cores; the bare splitting and products 2430); loads alone or products alone would take 2500.
+// so large problems stay with the staged kernels.  Bound: those vector instructions beside the products.  Two waves of a SIMD take
+// 2710 cycles for a step of 64x64x16 each, 1536 of matrix cores; the bare splitting and products, no loads, take 2430.
 #pragma once
 #include "gemm_core.hpp"
 #include "internal.hpp"
@@ -87,29 +87,33 @@ template <class T>
 struct WaveA {
     static constexpr int LOADS = 2 * T::MB;
     const char *base;
-    uint32_t row_bytes;
-    int rows;                         // that exist from the tile's first on, at most WM
-    uint32_t off;
+    uint32_t bytes;                   // of the rows that exist from the tile's first on, at most WM
+    uint32_t off[LOADS];
     int at0, at1;
+    __amdgpu_buffer_rsrc_t rsrc;      // of the step being fetched
     static __device__ __forceinline__ int turn(int row) { return ((row >> 1) & 2) | (((row >> 3) ^ (row >> 1)) & 1); }
     __device__ __forceinline__ void init(const float *A, int m0, int M, int K, int lane)
     {
-        row_bytes = (uint32_t)K * 4u;
+        const uint32_t row_bytes = (uint32_t)K * 4u;
         base = reinterpret_cast<const char *>(A) + (uint64_t)(uint32_t)m0 * row_bytes;
-        rows = min(M - m0, T::WM);
-        off = (uint32_t)(lane >> 2) * row_bytes + 16u * ((lane & 3) ^ turn(lane >> 2));
+        bytes = (uint32_t)min(M - m0, T::WM) * row_bytes;
+#pragma unroll
+        for (int n = 0; n < LOADS; ++n) {
+            const int row = 16 * n + (lane >> 2);
+            off[n] = m0 + row < M ? (uint32_t)row * row_bytes + 16u * ((lane & 3) ^ turn(row)) : kOobOffset;
+        }
         const int j = lane & 31, q = 2 * (lane >> 5);
         at0 = j * 4 + (q ^ turn(j));
         at1 = j * 4 + ((q + 1) ^ turn(j));
     }
     // live: the step exists (uniform); nothing is read otherwise
-    template <int N>
-    __device__ __forceinline__ void load(int t, bool live, v4f *dst) const
+    __device__ __forceinline__ void begin(int t, bool live)
     {
-        const uint32_t k = 64u * (uint32_t)t;
-        const int left = live ? min(max(rows - 16 * N, 0), 16) : 0;
-        lds_load<16>(raw_rsrc(base + (uint64_t)(16u * N) * row_bytes + k, left > 0 ? (uint32_t)left * row_bytes - k : 0u), dst + N * 64, off);
+        const uint32_t k = live ? 64u * (uint32_t)t : bytes;
+        rsrc = raw_rsrc(base + k, bytes - k);
     }
+    template <int N>
+    __device__ __forceinline__ void load(v4f *dst) const { lds_load<16>(rsrc, dst + N * 64, off[N]); }
     template <int BI>
     __device__ __forceinline__ void fetch(const v4f *src, float (&v)[8]) const
     {
@@ -133,44 +137,55 @@ struct WaveOperands {
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) x[pl][block] = (u32x4){u.p[pl][0], u.p[pl][1], u.p[pl][2], u.p[pl][3]};
     }
-    __device__ __forceinline__ void multiply(SplitAcc<T> &s) const
+    // the I-th product of a step
+    template <int I>
+    __device__ __forceinline__ void product(SplitAcc<T> &s) const
     {
-        constexpr int BLOCKS = T::MB * T::NB;
-        static_for<0, 6 * BLOCKS>([&](auto ic) __attribute__((always_inline)) {
-            constexpr int i = decltype(ic)::value, P = i / BLOCKS, bi = i % BLOCKS / T::NB, bj = i % T::NB;
-            constexpr int PA = P == 1 || P == 3 ? 1 : P == 4 ? 2 : 0, PB = P == 2 || P == 3 ? 1 : P == 5 ? 2 : 0;
-            if constexpr (P == 0) s.hi[bi][bj] = mfma_bf16(a[PA][bi], b[PB][bj], s.hi[bi][bj]);
-            else s.lo[bi][bj] = mfma_bf16(a[PA][bi], b[PB][bj], s.lo[bi][bj]);
-        });
+        constexpr int BLOCKS = T::MB * T::NB, P = I / BLOCKS, bi = I % BLOCKS / T::NB, bj = I % T::NB;
+        constexpr int PA = P == 1 || P == 3 ? 1 : P == 4 ? 2 : 0, PB = P == 2 || P == 3 ? 1 : P == 5 ? 2 : 0;
+        if constexpr (P == 0) s.hi[bi][bj] = mfma_bf16(a[PA][bi], b[PB][bj], s.hi[bi][bj]);
+        else s.lo[bi][bj] = mfma_bf16(a[PA][bi], b[PB][bj], s.lo[bi][bj]);
     }
 };
 
-// Steps t, t + 8, ... below last.  While one step is split and multiplied the next two are on their way into LDS.
-// The loaders' BL: load<N>(t, live, dst), N < LOADS, fills the [16][WN] image of a step, zeros for rows past the reduction's end (a
-// row of A goes on with the next row's values there); begin(t) comes before a step's loads; finish(v) ends a block's values.
+// Steps t, t + 8, ... below last.  A step's values are split, then multiplied; between its products the wave requests the step
+// after the next one, into the part of LDS these values came from, and reads the next one's values.  (With a descriptor per load,
+// and requests and reads ahead of the splitting, 1024^3 took 18.8 us instead of 17.8, 2048^3 135 instead of 125, 512 -> 512 3x3 on 7x7, batch
+// 32, 78 instead of 76; with those descriptors gone the order makes no difference.)
+// The loaders' BL: begin(t, live) and load<N>(dst), N < LOADS, fill the [16][WN] image of a step, zeros for rows past the reduction's
+// end (a row of A goes on with the next row's values there) and nothing where the step does not exist; finish(v) ends a block's values.
 template <class T, class BL>
-__device__ __forceinline__ uint32_t wave_mainloop(const WaveA<T> &al, BL &bl, SplitAcc<T> &sum, int t, int last, v4f *slice, int lane)
+__device__ __forceinline__ uint32_t wave_mainloop(WaveA<T> &al, BL &bl, SplitAcc<T> &sum, int t, int last, v4f *slice, int lane)
 {
-    constexpr int LOADS = WaveA<T>::LOADS + BL::LOADS;
+    constexpr int A_LOADS = WaveA<T>::LOADS, LOADS = A_LOADS + BL::LOADS;
+    constexpr int MM = 6 * T::MB * T::NB, LEAD = MM / 12, SPAN = MM * 3 / 4 - LEAD, FETCH = MM * 3 / 4;   // where requests and reads stand
     const float *b_at = reinterpret_cast<const float *>(slice + T::A_WORDS) + (lane >> 5) * 8 * T::WN + (lane & 31);
     WaveOperands<T> w;
-    auto load = [&](int t, bool live, int buf) __attribute__((always_inline)) {
-        v4f *dst = slice + buf * T::STEP;
-        static_for<0, WaveA<T>::LOADS>([&](auto n) __attribute__((always_inline)) { al.template load<decltype(n)::value>(t, live, dst); });
-        bl.begin(t);
-        static_for<0, BL::LOADS>([&](auto n) __attribute__((always_inline)) { bl.template load<decltype(n)::value>(t, live, dst + T::A_WORDS); });
+    float va[T::MB][8], vb[T::NB][8];
+    auto begin = [&](int t) __attribute__((always_inline)) {
+        al.begin(t, t < last);
+        bl.begin(t, t < last);
     };
-    auto step = [&](int t, auto bufc) __attribute__((always_inline)) {
-        constexpr int buf = decltype(bufc)::value;
-        float va[T::MB][8], vb[T::NB][8];
+    auto load = [&](auto n, int buf) __attribute__((always_inline)) {
+        constexpr int N = decltype(n)::value;
+        v4f *dst = slice + buf * T::STEP;
+        if constexpr (N < A_LOADS) al.template load<N>(dst);
+        else bl.template load<N - A_LOADS>(dst + T::A_WORDS);
+    };
+    // the values of the step in `buf`, of which at most the other step's loads may be under way
+    auto fetch = [&](int buf) __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<LOADS>();      // of the step after this one; its own have landed
+        wait_vmcnt<LOADS>();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int bj = 0; bj < T::NB; ++bj)
 #pragma unroll
             for (int i = 0; i < 8; ++i) vb[bj][i] = b_at[buf * T::STEP * 4 + i * T::WN + 32 * bj];
         static_for<0, T::MB>([&](auto b) __attribute__((always_inline)) { al.template fetch<decltype(b)::value>(slice + buf * T::STEP, va[decltype(b)::value]); });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto step = [&](int t, auto bufc) __attribute__((always_inline)) {
+        constexpr int buf = decltype(bufc)::value;
 #pragma unroll
         for (int bj = 0; bj < T::NB; ++bj) {
             bl.finish(vb[bj]);
@@ -178,14 +193,26 @@ __device__ __forceinline__ uint32_t wave_mainloop(const WaveA<T> &al, BL &bl, Sp
         }
 #pragma unroll
         for (int bi = 0; bi < T::MB; ++bi) w.put(w.a, bi, va[bi]);
+        __builtin_amdgcn_sched_barrier(0);   // the step's values are in registers: its part of LDS is free
+        begin(t + 2 * kWaves);
         __builtin_amdgcn_sched_barrier(0);
-        load(t + 2 * kWaves, t + 2 * kWaves < last, buf);
-        __builtin_amdgcn_sched_barrier(0);
-        w.multiply(sum);
+        static_for<0, MM>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            w.template product<i>(sum);
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) {
+                if constexpr (LEAD + decltype(n)::value * SPAN / LOADS == i) load(n, buf);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (i == FETCH) fetch(buf ^ 1);
+        });
     };
-    load(t, t < last, 0);
+    begin(t);
+    static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { load(n, 0); });
     __builtin_amdgcn_sched_barrier(0);
-    load(t + kWaves, t + kWaves < last, 1);
+    begin(t + kWaves);
+    static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { load(n, 1); });
+    fetch(0);
     // in pairs, both unconditional; an odd last one behind them (why: gemm_core.hpp)
     for (; t + kWaves < last; t += 2 * kWaves) {
         step(t, std::integral_constant<int, 0>{});
@@ -198,7 +225,7 @@ __device__ __forceinline__ uint32_t wave_mainloop(const WaveA<T> &al, BL &bl, Sp
 
 // The same steps on the fp32 matrix cores, for values the split cannot hold.  K: length of the reduction.
 template <class T, class BL>
-__device__ __forceinline__ void wave_redo(const WaveA<T> &al, BL &bl, v16f (&acc)[T::MB][T::NB], int t, int last, int K, v4f *slice, int lane)
+__device__ __forceinline__ void wave_redo(WaveA<T> &al, BL &bl, v16f (&acc)[T::MB][T::NB], int t, int last, int K, v4f *slice, int lane)
 {
     const float *src = reinterpret_cast<const float *>(slice + T::A_WORDS) + (lane >> 5) * 8 * T::WN + (lane & 31);
 #pragma unroll
@@ -209,9 +236,10 @@ __device__ __forceinline__ void wave_redo(const WaveA<T> &al, BL &bl, v16f (&acc
             for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
 #pragma unroll 1   // a step's values have been read before the next one's arrive
     for (; t < last; t += kWaves) {
-        static_for<0, WaveA<T>::LOADS>([&](auto n) __attribute__((always_inline)) { al.template load<decltype(n)::value>(t, true, slice); });
-        bl.begin(t);
-        static_for<0, BL::LOADS>([&](auto n) __attribute__((always_inline)) { bl.template load<decltype(n)::value>(t, true, slice + T::A_WORDS); });
+        al.begin(t, true);
+        static_for<0, WaveA<T>::LOADS>([&](auto n) __attribute__((always_inline)) { al.template load<decltype(n)::value>(slice); });
+        bl.begin(t, true);
+        static_for<0, BL::LOADS>([&](auto n) __attribute__((always_inline)) { bl.template load<decltype(n)::value>(slice + T::A_WORDS); });
         wait_vmcnt0();
         float a[T::MB][8], b[T::NB][8];
         static_for<0, T::MB>([&](auto n) __attribute__((always_inline)) { al.template fetch<decltype(n)::value>(slice, a[decltype(n)::value]); });
@@ -234,7 +262,7 @@ __device__ __forceinline__ void wave_redo(const WaveA<T> &al, BL &bl, v16f (&acc
 
 // The products of one wave: sums of its steps first + wave, + 8, ...
 template <class T, class BL>
-__device__ __forceinline__ void wave_products(const WaveA<T> &al, BL &bl, v16f (&acc)[T::MB][T::NB], int t, int last, int K, v4f *slice, int lane)
+__device__ __forceinline__ void wave_products(WaveA<T> &al, BL &bl, v16f (&acc)[T::MB][T::NB], int t, int last, int K, v4f *slice, int lane)
 {
     SplitAcc<T> sum;
     sum.clear();
