@@ -190,7 +190,7 @@ static int sgemm_impl(int M, int N, int K, float alpha, const float *A, const fl
         if (is_wave_cfg(cfg)) {
             SgemmProblem q{M, N, K, A, B, C, alpha, beta};
             if (!sgemm_wave_fits(q, cfg.bm)) return false;
-            *e = sgemm_wave_launch(q, cfg.bm, cfg.split_k, (hipStream_t)stream);
+            *e = sgemm_wave_launch(q, cfg.bm, wave_cfg_waves(cfg), cfg.split_k, (hipStream_t)stream);
             return true;
         }
         const Variant *v = find_variant(cfg);
@@ -311,7 +311,7 @@ static int conv_impl(int N, int C, int H, int W, int K, int R, int S, int stride
             q.wt_tap = wt_tap;
         }
         const int parts = cfg.split_k < 1 ? 1 : cfg.split_k;
-        hipError_t e = wave ? conv_wave_launch(q, cfg.bm, parts, (hipStream_t)stream) : v->conv(q, parts, cfg.raster, (hipStream_t)stream);
+        hipError_t e = wave ? conv_wave_launch(q, cfg.bm, wave_cfg_waves(cfg), parts, (hipStream_t)stream) : v->conv(q, parts, cfg.raster, (hipStream_t)stream);
         if (e != hipSuccess) return failed(e);
         std::lock_guard<std::mutex> lk(g_mu);
         g_last = cfg;
@@ -498,7 +498,7 @@ int polydl_conv2d_fwd_bf16_blocked(int N, int C, int H, int W, int K, int R, int
         cfg = g_override;
     }
     if (forced) {
-        if (cfg.algo != 1 && !is_wave_cfg(cfg)) return POLYDL_ERR_UNSUPPORTED;
+        if (cfg.algo != 1 && !(is_wave_cfg(cfg) && cfg.raster == 1)) return POLYDL_ERR_UNSUPPORTED;
     } else {
         // the pick depends on the shape alone: made once per shape
         const std::array<int, 9> key = {N, cunits, H, W, K, R, S, stride, pad};

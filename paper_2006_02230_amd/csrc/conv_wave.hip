@@ -48,7 +48,7 @@ struct WaveBGather {
         if constexpr (TABLE) {
             const uint32_t period = (uint32_t)p.RS * 16u, last = (uint32_t)(p.Kg - 1) & ~15u;
             const uint32_t st = last >> 4, first_of_last = (st - fast_div(st, p.magic_RS, p.one_RS) * (uint32_t)p.RS) * 16u;
-            for (uint32_t e = tid; e < period + 16u; e += kWaveThreads) {
+            for (uint32_t e = tid; e < period + 16u; e += T::THREADS) {
                 const uint32_t r16 = e < period ? e : first_of_last + (e - period);
                 const bool in = e < period || last + (e - period) < (uint32_t)p.Kg;
                 const uint32_t c = fast_div(r16, p.magic_RS, p.one_RS), rs = r16 - c * (uint32_t)p.RS;
@@ -166,7 +166,7 @@ __device__ __forceinline__ void conv_wave_store(const ConvWaveKArgs &p, int m0, 
 }
 
 template <class T, int MODE>
-__global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void conv_wave_kernel(ConvWaveKArgs p)
+__global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void conv_wave_kernel(ConvWaveKArgs p)
 {
     typedef WaveBGather<T, MODE> Gather;
     extern __shared__ __attribute__((aligned(16))) v4f slices[];
@@ -196,16 +196,16 @@ __global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void conv_wave_ker
 // are under way.  Bound on more than a few steps: the 64 bytes a cycle a compute unit loads (8 KB a step of 64x64).
 template <int MB_, int NB_>
 struct WaveTileBf16 {
-    static constexpr int MB = MB_, NB = NB_, WM = 32 * MB, WN = 32 * NB, UNITS = 4 * MB, DEPTH = 4;
+    static constexpr int MB = MB_, NB = NB_, WAVES = 8, THREADS = 512, WM = 32 * MB, WN = 32 * NB, UNITS = 4 * MB, DEPTH = 4;
     static constexpr int STEP = WM * 4, SUMS = UNITS * NB * 64;                            // 16-byte words
     static constexpr int SLICE = SUMS > DEPTH * STEP ? SUMS : DEPTH * STEP;
-    static constexpr int LDS_BYTES = kWaves * SLICE * 16;
+    static constexpr int LDS_BYTES = WAVES * SLICE * 16;
     static constexpr int WAVES_PER_SIMD = MB * NB == 1 ? 4 : 2;
 };
 
 // LONG: filters of 32 .. 63 taps
 template <class T, bool LONG>
-__global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void conv_wave_bf16_kernel(ConvWaveKArgs p)
+__global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void conv_wave_bf16_kernel(ConvWaveKArgs p)
 {
     constexpr int LAST_BIT = LONG ? 63 : 31, DEPTH = T::DEPTH, A_LOADS = 2 * T::MB, LOADS = A_LOADS + 2 * T::NB;
     extern __shared__ __attribute__((aligned(16))) v4f slices[];
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void conv_wave_bf1
     {
         const uint32_t period = (uint32_t)p.RS * 4u, end = (uint32_t)(p.Kg - 1) & ~3u, st = end >> 2;
         const uint32_t first_of_last = (st - fast_div(st, p.magic_RS, p.one_RS) * (uint32_t)p.RS) * 4u;
-        for (uint32_t e = tid; e < period + 4u; e += kWaveThreads) {
+        for (uint32_t e = tid; e < period + 4u; e += T::THREADS) {
             const uint32_t u = e < period ? e : first_of_last + (e - period);
             const bool in = e < period || end + (e - period) < (uint32_t)p.Kg;
             const uint32_t c = fast_div(u, p.magic_RS, p.one_RS), rs = u - c * (uint32_t)p.RS;
@@ -308,23 +308,23 @@ __global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void conv_wave_bf1
     };
     int t = first + wave;
     static_for<0, DEPTH>([&](auto n) __attribute__((always_inline)) {
-        load(n, t + kWaves * decltype(n)::value);
+        load(n, t + T::WAVES * decltype(n)::value);
         __builtin_amdgcn_sched_barrier(0);
     });
     // behind a step's filter rows come its pixels and the steps after it, which are the only ones left under way when it begins
-    for (; t + kWaves * (DEPTH - 1) < last; t += kWaves * DEPTH) {
+    for (; t + T::WAVES * (DEPTH - 1) < last; t += T::WAVES * DEPTH) {
         static_for<0, DEPTH>([&](auto n) __attribute__((always_inline)) {
             __builtin_amdgcn_sched_barrier(0);
             wait_vmcnt<(DEPTH - 1) * LOADS>();
             __builtin_amdgcn_sched_barrier(0);
             multiply(n);
             __builtin_amdgcn_sched_barrier(0);
-            load(n, t + kWaves * (DEPTH + decltype(n)::value));
+            load(n, t + T::WAVES * (DEPTH + decltype(n)::value));
         });
     }
     wait_vmcnt0();     // what was requested past the end still writes zeros into the slice
     static_for<0, DEPTH - 1>([&](auto n) __attribute__((always_inline)) {
-        if (t + kWaves * decltype(n)::value < last) multiply(n);   // uniform
+        if (t + T::WAVES * decltype(n)::value < last) multiply(n);   // uniform
     });
     wave_finish<T>(slices, acc, p.parts, wave, lane, [&](int u, const v4f (&v)[T::NB]) __attribute__((always_inline)) {
         conv_wave_store<T>(p, m0, n0, lane, u, v);
@@ -375,9 +375,10 @@ bool conv_wave_fits(const ConvProblem &q, int tile)
            ((int64_t)q.pad * q.W + q.pad) * 4 + (tile / ((int64_t)q.P * q.Q) + 2) * q.C * q.H * q.W * 4 < kMaxOffset;
 }
 
-hipError_t conv_wave_launch(const ConvProblem &q, int tile, int parts, hipStream_t stream)
+hipError_t conv_wave_launch(const ConvProblem &q, int tile, int waves, int parts, hipStream_t stream)
 {
-    return tile == 64 ? conv_wave_launch_t<WaveTile<2, 2>>(q, parts, stream) : conv_wave_launch_t<WaveTile<1, 1>>(q, parts, stream);
+    if (waves == 4) return conv_wave_launch_t<WaveTile<2, 2, 4>>(q, parts, stream);
+    return tile == 64 ? conv_wave_launch_t<WaveTile<2, 2, 8>>(q, parts, stream) : conv_wave_launch_t<WaveTile<1, 1, 8>>(q, parts, stream);
 }
 
 template <class T>

@@ -241,21 +241,24 @@ inline bool is_conv_thin_cfg(const polydl_tile_cfg &c)
 }
 hipError_t conv_thin_launch(const ConvProblem &q, hipStream_t stream);
 
-// sgemm_wave.hip, conv_wave.hip: small problems, the eight waves of a workgroup on one tile of 64x64 or 32x32 (wave_core.hpp).  As a
+// sgemm_wave.hip, conv_wave.hip: small problems, the eight waves of a workgroup on one tile of 64x64 or 32x32, or four on one of 64x64 (raster 0;
+// wave_core.hpp).  As a
 // configuration they are gather variants (algo 0) whose wave tile is the whole tile; split_k counts the workgroups that share a tile's
 // reduction, layout 2 reads the filter's copy.  Not ranked: they take the place of a pick where they
 // are predicted to be well below it (conv_wave_pick, sgemm_wave_pick: false where not; no_scratch: one part only).
-inline polydl_tile_cfg wave_cfg(int tile, int parts, int layout) { return polydl_tile_cfg{tile, tile, 16, tile, tile, parts, layout, 1, 0, 0}; }
+inline polydl_tile_cfg wave_cfg(int tile, int waves, int parts, int layout) { return polydl_tile_cfg{tile, tile, 16, tile, tile, parts, layout, waves == 8, 0, 0}; }
 inline bool is_wave_cfg(const polydl_tile_cfg &c)
 {
-    return c.algo == 0 && (c.bm == 64 || c.bm == 32) && c.bn == c.bm && c.bk == 16 && c.wm == c.bm && c.wn == c.bm && c.raster == 1 &&
+    return c.algo == 0 && (c.bm == 64 || c.bm == 32) && c.bn == c.bm && c.bk == 16 && c.wm == c.bm && c.wn == c.bm &&
+           (c.raster == 1 || (c.raster == 0 && c.bm == 64)) &&
            c.cb == 0 && c.split_k <= 65535;
 }
 constexpr int kWavesPerTile = 8;
+inline int wave_cfg_waves(const polydl_tile_cfg &c) { return c.raster == 0 ? 4 : kWavesPerTile; }
 bool conv_wave_fits(const ConvProblem &q, int tile);
 bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg);
 void model_conv_wave(const ConvProblem &q, const polydl_tile_cfg &cfg, polydl_model_report *r);
-hipError_t conv_wave_launch(const ConvProblem &q, int tile, int parts, hipStream_t stream);
+hipError_t conv_wave_launch(const ConvProblem &q, int tile, int waves, int parts, hipStream_t stream);
 bool conv_wave_bf16_fits(const ConvProblem &q, int tile);   // q.C counts units of eight channels
 bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg);
 double model_conv_wave_bf16(const ConvProblem &q, const polydl_tile_cfg &cfg);   // predicted microseconds
@@ -266,7 +269,7 @@ inline bool sgemm_wave_fits(const SgemmProblem &q, int tile)
 }
 bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg);
 void model_sgemm_wave(const SgemmProblem &q, const polydl_tile_cfg &cfg, polydl_model_report *r);
-hipError_t sgemm_wave_launch(const SgemmProblem &q, int tile, int parts, hipStream_t stream);
+hipError_t sgemm_wave_launch(const SgemmProblem &q, int tile, int waves, int parts, hipStream_t stream);
 
 // reuse_analyse.cpp (arguments already validated)
 int reuse_analyse(int nloops, const int *extents, const int *parallel, int nrefs, const polydl_loop_ref *refs,

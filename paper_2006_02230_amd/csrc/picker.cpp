@@ -568,32 +568,28 @@ void model_conv_thin(const ConvProblem &q, polydl_model_report *r)
 }
 
 // ---- small problems: single waves (wave_core.hpp) --------------------------------------------------
-// Predicted microseconds.  Fitted to 12363 launches (1500 drawn problems of 2e6 .. 8e9 flops, 1 .. 16 parts of either tile): 7 % off in the
-// mean, 15 % in 95 of 100.  A step costs a workgroup of 32x32 tiles 0.53 us alone on its compute unit and 1.16 beside another one, of
-// 64x64 tiles (never two on a unit) 1.23; gathered operands cost up to 1.7 times that, and up to 1.5 us before the first step.
-// bfloat16 (a step is four units of eight channels): 7969 launches of 1000 drawn layers of 5e6 .. 3e10 flops, 9 % off in the mean.
+// Predicted microseconds of tiles of 64x64 shared by eight waves (one workgroup on a compute unit) or four (two), and of 32x32 (two).
+// Fitted to 30684 launches (2700 drawn problems of 2e6 .. 3e10 flops, 1 .. 16 parts): 7.6 % off in the mean, 15 % in 95 of 100.  A step
+// costs a workgroup 0.52 (32x32) .. 1.2 us; gathered operands cost up to 1.7 times that, and up to 1.8 us before the first step.
+// bfloat16 (a step is four units of eight channels; eight waves): 7969 launches of 1000 drawn layers of 5e6 .. 3e10 flops, 9 % off in the mean.
 enum WaveLoads { WAVE_ROWS, WAVE_POINT, WAVE_POINT_STRIDED, WAVE_TAP, WAVE_TAP_STRIDED, WAVE_TAPS, WAVE_TAPS_STRIDED,
                  WAVE_BF16_POINT, WAVE_BF16_POINT_STRIDED, WAVE_BF16_TAPS, WAVE_BF16_TAPS_STRIDED };
-struct WaveFit { double launch, round, step1, step2, parts, part; };   // step1, step2: one, two workgroups on a compute unit
-static double wave_us(int tile, int parts, double tiles, double steps, WaveLoads loads, double out_bytes)
+// step1, step2: one, two workgroups on a compute unit; most: weight of the longest wave's steps against the mean; whole: of whole rounds
+struct WaveFit { double launch, round, step1, step2, parts, part, most, whole; };
+static const WaveFit kWave32 = {1.6, 2.43, 0.519, 1.127, 1.24, 0.19, 0.28, 0.37}, kWave64 = {0.9, 4.3, 1.20, 0, 1.66, 0.25, 0.1, 1},
+                     kWave64x4 = {1.2, 3.87, 0.72, 1.32, 1.78, 0.30, 0.73, 0.48}, kWaveBf16_32 = {2.0, 2.4, 0.168, 0.395, 1.42, 0.19, 1, 0.4},
+                     kWaveBf16_64 = {2.1, 3.7, 0.381, 0, 1.77, 0.23, 0.33, 1};
+static double wave_us(int tile, int waves, int parts, double tiles, double steps, WaveLoads loads, double out_bytes)
 {
-    static const double per_step[] = {1, 1.28, 1.69, 1.07, 1.45, 1.15, 1.24, 1, 1.53, 1.39, 1.59};
-    static const double before[] = {0, 0.76, 0.65, 1.14, 0.40, 1.56, 1.53, 0, -0.27, -0.27, -0.60};
-    static const WaveFit fits[2][2] = {{{1.4, 2.0, 0.53, 1.16, 1.24, 0.17}, {0.7, 4.5, 1.23, 0, 1.6, 0.2}},
-                                       {{2.0, 2.4, 0.168, 0.395, 1.42, 0.19}, {2.1, 3.7, 0.381, 0, 1.77, 0.23}}};
+    static const double per_step[] = {1, 1.26, 1.66, 1.08, 1.27, 1.14, 1.23, 1, 1.53, 1.39, 1.59};
+    static const double before[] = {0, 1.00, 0.83, 1.23, 1.30, 1.53, 1.79, 0, -0.27, -0.27, -0.60};
     const bool bf16 = loads >= WAVE_BF16_POINT;
-    const WaveFit &f = fits[bf16][tile == 64];
-    const double mean = std::ceil(steps / parts) / kWavesPerTile, most = std::ceil(mean), wgs = tiles * parts, cus = kCUs;
-    double us = before[loads] + out_bytes / 4.0e6 + f.launch + (parts > 1 ? f.parts + f.part * parts : 0);
-    if (tile == 64) {
-        const double n = bf16 ? 0.33 * most + 0.67 * mean : mean;
-        us += std::ceil(wgs / cus) * (f.round + n * f.step1 * per_step[loads]);
-    } else {
-        const double n = bf16 ? most : 0.25 * most + 0.75 * mean, rounds = wgs / (2 * cus);
-        if (wgs <= cus) us += f.round + n * f.step1 * per_step[loads];
-        else us += (rounds <= 1 ? 1 : 0.4 * std::ceil(rounds) + 0.6 * rounds) * (f.round + n * f.step2 * per_step[loads]);
-    }
-    return us;
+    const WaveFit &f = bf16 ? (tile == 64 ? kWaveBf16_64 : kWaveBf16_32) : tile == 32 ? kWave32 : waves == 4 ? kWave64x4 : kWave64;
+    const double mean = std::ceil(steps / parts) / waves, n = (f.most * std::ceil(mean) + (1 - f.most) * mean) * per_step[loads];
+    const double wgs = tiles * parts, cus = kCUs, full = wgs / (f.step2 > 0 ? 2 * cus : cus);
+    const double rounds = full <= 1 ? 1 : f.whole * std::ceil(full) + (1 - f.whole) * full;
+    return before[loads] + out_bytes / 4.0e6 + f.launch + (parts > 1 ? f.parts + f.part * parts : 0) +
+           (f.step2 > 0 && wgs > cus ? rounds * (f.round + n * f.step2) : f.step2 > 0 ? f.round + n * f.step1 : rounds * (f.round + n * f.step1));
 }
 static WaveLoads wave_loads(const ConvProblem &q, int layout)
 {
@@ -602,52 +598,53 @@ static WaveLoads wave_loads(const ConvProblem &q, int layout)
     if (layout == 2) return strided ? WAVE_TAP_STRIDED : WAVE_TAP;
     return strided ? WAVE_TAPS_STRIDED : WAVE_TAPS;
 }
-// The best of both tiles and 1 .. 16 parts, if it is predicted below `limit`, for tiles of 64x64 `limit64`.
+// The best of the tiles and 1 .. 16 parts, if it is predicted below `limit`, for tiles of 64x64 `limit64`.
 template <class Fits>
 static bool wave_best(double M, double N, double steps, WaveLoads loads, int layout, double limit, double limit64, bool no_scratch, const ScratchArena *arena,
                       Fits &&fits, polydl_tile_cfg *cfg)
 {
-    static const int kParts[] = {1, 2, 3, 4, 6, 8, 12, 16};
+    static const int kParts[] = {1, 2, 3, 4, 6, 8, 12, 16}, kTiles[][2] = {{32, 8}, {64, 8}, {64, 4}};
     const double cus = kCUs;
     bool found = false;
-    for (int tile : {32, 64}) {
-        if (!fits(tile)) continue;
+    for (const int (&tw)[2] : kTiles) {
+        const int tile = tw[0], waves = tw[1];
+        if (!fits(tile) || (waves == 4 && loads >= WAVE_BF16_POINT)) continue;
         const double tiles = std::ceil(M / tile) * std::ceil(N / tile);
         // a handful of tiles of a few steps each: waves without work
         if (tile == 32 && steps < kWavesPerTile && tiles < 16) return false;
         if (tiles > 4096) continue;
         if (tile == 64) limit = std::min(limit, limit64);
         for (int parts : kParts) {
-            if (parts > 1 && (no_scratch || parts * 4 > steps || tiles * parts > (tile == 64 ? 2 : 4) * cus)) break;
+            if (parts > 1 && (no_scratch || parts * 4 > steps || tiles * parts > (tile == 64 && waves == 8 ? 2 : 4) * cus)) break;
             if (parts > 1 && arena && (tiles * parts * tile * tile * 4 > arena->partial_bytes || tiles > arena->ncounters)) break;
-            double us = wave_us(tile, parts, tiles, steps, loads, M * N * 4);
+            double us = wave_us(tile, waves, parts, tiles, steps, loads, M * N * 4);
             // parts of a reduction of few tiles are 2 .. 3 % better than the formula has it
             if (parts == 1 && tiles <= 64) us *= 1.02;
             if (us >= limit) continue;
             limit = us;
-            *cfg = wave_cfg(tile, parts, layout);
+            *cfg = wave_cfg(tile, waves, parts, layout);
             found = true;
         }
     }
     return found;
 }
 
-// Whether a small problem goes to single waves, given its pick's prediction.  Of 1500 drawn problems of 2e6 .. 8e9 flops these rules
-// send 1235 there, the time of all falls by a factor of 1.46 in the mean (1.48 with the best choice for each), and 6 were more than 3 %
-// slower.  The margin is what the two predictions are off.  Convolutions of fewer than 128 reduction rows run on the fp32 instruction
-// otherwise and are predicted too high, by up to 1.6: a wider margin.
-static const double kWaveMargin = 0.85, kWaveMarginShort = 0.6;
+// Whether a small problem goes to single waves, given its pick's prediction: a margin for what the two predictions are off.  Of 2700
+// drawn problems of 2e6 .. 3e10 flops about 2000 go there, the time of all falls by a factor of 1.31 in the mean (1.34 with the best choice
+// for each), and about ten were more than 3 % slower, by up to 13 %.  Picks of more than 40 us gain little and are mispredicted more often.  Convolutions of
+// fewer than 128 reduction rows run on the fp32 instruction otherwise and are predicted too high, by up to 1.6.
+static double wave_limit(double pick_us, bool short_rows) { return pick_us * (short_rows ? 0.6 : pick_us <= 40 ? 0.9 : 0.83); }
 bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S;
     const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
-    const double limit = pick_us * (Kg < kSplitMinReduction ? kWaveMarginShort : kWaveMargin);
+    const double limit = wave_limit(pick_us, Kg < kSplitMinReduction);
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
 }
 bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
-    const double limit = pick_us * kWaveMargin;
+    const double limit = wave_limit(pick_us, false);
     return wave_best(q.M, q.N, std::ceil(q.K / 16.0), WAVE_ROWS, 0, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg);
 }
@@ -673,7 +670,7 @@ bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, 
 double model_conv_wave_bf16(const ConvProblem &q, const polydl_tile_cfg &cfg)
 {
     const double M = q.K, N = (double)q.N * q.P * q.Q;
-    return wave_us(cfg.bm, std::max(1, cfg.split_k), std::ceil(M / cfg.bm) * std::ceil(N / cfg.bm), std::ceil(q.C * q.R * q.S / 4.0),
+    return wave_us(cfg.bm, kWavesPerTile, std::max(1, cfg.split_k), std::ceil(M / cfg.bm) * std::ceil(N / cfg.bm), std::ceil(q.C * q.R * q.S / 4.0),
                    wave_bf16_loads(q), M * N * 4);
 }
 
@@ -681,11 +678,11 @@ static void model_wave(double M, double N, double Kg, WaveLoads loads, double in
 {
     std::memset(r, 0, sizeof(*r));
     const double t = cfg.bm, tiles = std::ceil(M / t) * std::ceil(N / t), parts = std::max(1, cfg.split_k);
-    r->predicted_us = wave_us(cfg.bm, (int)parts, tiles, std::ceil(Kg / 16), loads, M * N * 4);
+    r->predicted_us = wave_us(cfg.bm, wave_cfg_waves(cfg), (int)parts, tiles, std::ceil(Kg / 16), loads, M * N * 4);
     r->mfma_us = r->predicted_us;
     r->mem_us = (in_bytes + M * Kg * 4 + M * N * 4) / kHbmGBs * 1e-3;
     r->workgroups = (int)std::min(tiles * parts, 2e9);
-    r->simd_load = std::ceil(tiles * parts / kCUs) * kWavesPerTile / kSimdsPerCU;
+    r->simd_load = std::ceil(tiles * parts / kCUs) * wave_cfg_waves(cfg) / kSimdsPerCU;
     // reuses: accumulators over a wave's steps; a step's operands, every row with every column; the operands by the tiles; the tensors
     const double all = in_bytes + M * Kg * 4 + M * N * 4;
     const double ws[4] = {2 * t * t * 4, 2 * t * 16 * 4, 2 * t * Kg * 4, all};

@@ -42,7 +42,7 @@ struct WaveBRows {
 };
 
 template <class T>
-__global__ __launch_bounds__(kWaveThreads, T::WAVES_PER_SIMD) void sgemm_wave_kernel(SgemmWaveKArgs p)
+__global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void sgemm_wave_kernel(SgemmWaveKArgs p)
 {
     extern __shared__ __attribute__((aligned(16))) v4f slices[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -99,9 +99,10 @@ static hipError_t sgemm_wave_launch_t(const SgemmProblem &q, int parts, hipStrea
     return wave_launch<T>(sgemm_wave_kernel<T>, tiles, a.parts.parts, stream, a);
 }
 
-hipError_t sgemm_wave_launch(const SgemmProblem &q, int tile, int parts, hipStream_t stream)
+hipError_t sgemm_wave_launch(const SgemmProblem &q, int tile, int waves, int parts, hipStream_t stream)
 {
-    return tile == 64 ? sgemm_wave_launch_t<WaveTile<2, 2>>(q, parts, stream) : sgemm_wave_launch_t<WaveTile<1, 1>>(q, parts, stream);
+    if (waves == 4) return sgemm_wave_launch_t<WaveTile<2, 2, 4>>(q, parts, stream);
+    return tile == 64 ? sgemm_wave_launch_t<WaveTile<2, 2, 8>>(q, parts, stream) : sgemm_wave_launch_t<WaveTile<1, 1, 8>>(q, parts, stream);
 }
 
 }  // namespace polydl

@@ -15,18 +15,16 @@
 
 namespace polydl {
 
-constexpr int kWaves = kWavesPerTile, kWaveThreads = 64 * kWaves;
-
-// Tile of MB x NB blocks of 32 x 32.
-template <int MB_, int NB_>
+// Tile of MB x NB blocks of 32 x 32, shared by WAVES waves.
+template <int MB_, int NB_, int WAVES_>
 struct WaveTile {
-    static constexpr int MB = MB_, NB = NB_, WM = 32 * MB, WN = 32 * NB;
+    static constexpr int MB = MB_, NB = NB_, WAVES = WAVES_, THREADS = 64 * WAVES, WM = 32 * MB, WN = 32 * NB;
     static constexpr int UNITS = 4 * MB;                       // (row block, register quad) of the accumulators
     static constexpr int A_WORDS = WM * 4, B_WORDS = WN * 4;   // 16-byte words of a step's operands in LDS
     static constexpr int STEP = A_WORDS + B_WORDS;
     static constexpr int SUMS = UNITS * NB * 64;               // and of a wave's accumulators
     static constexpr int SLICE = SUMS > 2 * STEP ? SUMS : 2 * STEP;   // a wave's own part of LDS: two steps, later its sums
-    static constexpr int LDS_BYTES = kWaves * SLICE * 16;
+    static constexpr int LDS_BYTES = WAVES * SLICE * 16;
     static constexpr int WAVES_PER_SIMD = MB * NB == 1 ? 4 : 2;
 };
 
@@ -148,7 +146,7 @@ struct WaveOperands {
     }
 };
 
-// Steps t, t + 8, ... below last.  A step's values are split, then multiplied; between its products the wave requests the step
+// Steps t, t + WAVES, ... below last.  A step's values are split, then multiplied; between its products the wave requests the step
 // after the next one, into the part of LDS these values came from, and reads the next one's values.  (With a descriptor per load,
 // and requests and reads ahead of the splitting, 1024^3 took 18.8 us instead of 17.8, 2048^3 135 instead of 125, 512 -> 512 3x3 on 7x7, batch
 // 32, 78 instead of 76; with those descriptors gone the order makes no difference.)
@@ -194,7 +192,7 @@ __device__ __forceinline__ uint32_t wave_mainloop(WaveA<T> &al, BL &bl, SplitAcc
 #pragma unroll
         for (int bi = 0; bi < T::MB; ++bi) w.put(w.a, bi, va[bi]);
         __builtin_amdgcn_sched_barrier(0);   // the step's values are in registers: its part of LDS is free
-        begin(t + 2 * kWaves);
+        begin(t + 2 * T::WAVES);
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, MM>([&](auto ic) __attribute__((always_inline)) {
             constexpr int i = decltype(ic)::value;
@@ -210,13 +208,13 @@ __device__ __forceinline__ uint32_t wave_mainloop(WaveA<T> &al, BL &bl, SplitAcc
     begin(t);
     static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { load(n, 0); });
     __builtin_amdgcn_sched_barrier(0);
-    begin(t + kWaves);
+    begin(t + T::WAVES);
     static_for<0, LOADS>([&](auto n) __attribute__((always_inline)) { load(n, 1); });
     fetch(0);
     // in pairs, both unconditional; an odd last one behind them (why: gemm_core.hpp)
-    for (; t + kWaves < last; t += 2 * kWaves) {
+    for (; t + T::WAVES < last; t += 2 * T::WAVES) {
         step(t, std::integral_constant<int, 0>{});
-        step(t + kWaves, std::integral_constant<int, 1>{});
+        step(t + T::WAVES, std::integral_constant<int, 1>{});
     }
     if (t < last) step(t, std::integral_constant<int, 0>{});
     wait_vmcnt0();     // what was requested past the end still writes zeros into the slice
@@ -235,7 +233,7 @@ __device__ __forceinline__ void wave_redo(WaveA<T> &al, BL &bl, v16f (&acc)[T::M
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
 #pragma unroll 1   // a step's values have been read before the next one's arrive
-    for (; t < last; t += kWaves) {
+    for (; t < last; t += T::WAVES) {
         al.begin(t, true);
         static_for<0, WaveA<T>::LOADS>([&](auto n) __attribute__((always_inline)) { al.template load<decltype(n)::value>(slice); });
         bl.begin(t, true);
@@ -260,7 +258,7 @@ __device__ __forceinline__ void wave_redo(WaveA<T> &al, BL &bl, v16f (&acc)[T::M
     }
 }
 
-// The products of one wave: sums of its steps first + wave, + 8, ...
+// The products of one wave: sums of its steps first + wave, + WAVES, ...
 template <class T, class BL>
 __device__ __forceinline__ void wave_products(WaveA<T> &al, BL &bl, v16f (&acc)[T::MB][T::NB], int t, int last, int K, v4f *slice, int lane)
 {
@@ -299,7 +297,7 @@ inline hipError_t wave_launch(void (*kernel)(P...), int tiles, int parts, hipStr
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess) return e;
     }
-    return launch_kernel(kernel, dim3((unsigned)tiles, (unsigned)parts), dim3(kWaveThreads), T::LDS_BYTES, stream, args...);
+    return launch_kernel(kernel, dim3((unsigned)tiles, (unsigned)parts), dim3(T::THREADS), T::LDS_BYTES, stream, args...);
 }
 
 // The waves' sums meet in LDS, those of several workgroups in scratch memory (as in conv_finish()); each is added up in a
@@ -316,32 +314,39 @@ __device__ __forceinline__ void wave_finish(v4f *slices, const v16f (&acc)[T::MB
             mine[(u * T::NB + bj) * 64] = (v4f){r[4 * (u % 4)], r[4 * (u % 4) + 1], r[4 * (u % 4) + 2], r[4 * (u % 4) + 3]};
         }
     __syncthreads();
-    static_assert(T::UNITS <= kWaves, "a wave takes at most one unit");
-    const int u = wave;
-    const bool mine_to_store = u < T::UNITS;   // uniform
-    v4f v[T::NB];
+    // a wave's units: wave, wave + WAVES, ...; a tile of fewer units than waves leaves some without
+    constexpr int MINE = (T::UNITS + T::WAVES - 1) / T::WAVES;
+    static_assert(MINE == 1 || T::UNITS % T::WAVES == 0, "all waves as many units");
+    const bool any = wave < T::UNITS;   // uniform
+    v4f v[MINE][T::NB];
 #pragma unroll
-    for (int bj = 0; bj < T::NB; ++bj) v[bj] = (v4f){0.f, 0.f, 0.f, 0.f};
-    if (mine_to_store) {
-        // in pairs: three roundings deep instead of seven, so that no sum is further off than that of a staged tile's few parts
+    for (int m = 0; m < MINE; ++m)
 #pragma unroll
         for (int bj = 0; bj < T::NB; ++bj) {
-            v4f x[kWaves];
+            v[m][bj] = (v4f){0.f, 0.f, 0.f, 0.f};
+            if (!any) continue;
+            // in pairs: few roundings deep, so that no sum is further off than that of a staged tile's few parts
+            v4f x[T::WAVES];
 #pragma unroll
-            for (int i = 0; i < kWaves; ++i) x[i] = slices[i * T::SLICE + (u * T::NB + bj) * 64 + lane];
-            v[bj] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+            for (int i = 0; i < T::WAVES; ++i) x[i] = slices[i * T::SLICE + ((wave + m * T::WAVES) * T::NB + bj) * 64 + lane];
+#pragma unroll
+            for (int d = 1; d < T::WAVES; d *= 2)
+#pragma unroll
+                for (int i = 0; i < T::WAVES; i += 2 * d) x[i] += x[i + d];
+            v[m][bj] = x[0];
         }
-    }
     if (p.parts > 1) {
         __shared__ unsigned s_arrived;
         constexpr uint32_t BYTES = T::SUMS * 16;
         const char *part0 = reinterpret_cast<const char *>(p.partials) + (size_t)blockIdx.x * p.parts * BYTES;
-        const int off = 16 * lane + u * T::NB * 1024;
-        if (mine_to_store) {
+        const int off = 16 * lane + wave * T::NB * 1024;
+        if (any) {
             const __amdgpu_buffer_rsrc_t r = raw_rsrc(part0 + (size_t)blockIdx.y * BYTES, BYTES);
 #pragma unroll
-            for (int bj = 0; bj < T::NB; ++bj)
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v[bj]), r, off + bj * 1024, 0, kDeviceScope);
+            for (int m = 0; m < MINE; ++m)
+#pragma unroll
+                for (int bj = 0; bj < T::NB; ++bj)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v[m][bj]), r, off + (m * T::WAVES * T::NB + bj) * 1024, 0, kDeviceScope);
         }
         wait_vmcnt0();
         __syncthreads();
@@ -350,24 +355,32 @@ __device__ __forceinline__ void wave_finish(v4f *slices, const v16f (&acc)[T::MB
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(s_arrived) != (unsigned)p.parts - 1u) return;   // not the last part
         if (threadIdx.x == 0) __hip_atomic_store(p.counters + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!mine_to_store) return;
+        if (!any) return;
 #pragma unroll
-        for (int bj = 0; bj < T::NB; ++bj) v[bj] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < MINE; ++m)
+#pragma unroll
+            for (int bj = 0; bj < T::NB; ++bj) v[m][bj] = (v4f){0.f, 0.f, 0.f, 0.f};
         constexpr int AHEAD = 4;
         for (int q = 0; q < p.parts; q += AHEAD) {
             const __amdgpu_buffer_rsrc_t r = raw_rsrc(part0 + (size_t)q * BYTES, AHEAD * BYTES);
-            v4f x[AHEAD][T::NB];
+            v4f x[AHEAD][MINE][T::NB];
 #pragma unroll
             for (int n = 0; n < AHEAD; ++n)
 #pragma unroll
-                for (int bj = 0; bj < T::NB; ++bj)   // parts past the last one are out of range: no access, zeros
-                    x[n][bj] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
-                                   r, q + n < p.parts ? off + bj * 1024 : (int)kOobOffset, n * (int)BYTES, kDeviceScope));
+                for (int m = 0; m < MINE; ++m)
 #pragma unroll
-            for (int bj = 0; bj < T::NB; ++bj) v[bj] += (x[0][bj] + x[1][bj]) + (x[2][bj] + x[3][bj]);
+                    for (int bj = 0; bj < T::NB; ++bj)   // parts past the last one are out of range: no access, zeros
+                        x[n][m][bj] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                                          r, q + n < p.parts ? off + (m * T::WAVES * T::NB + bj) * 1024 : (int)kOobOffset, n * (int)BYTES, kDeviceScope));
+#pragma unroll
+            for (int m = 0; m < MINE; ++m)
+#pragma unroll
+                for (int bj = 0; bj < T::NB; ++bj) v[m][bj] += (x[0][m][bj] + x[1][m][bj]) + (x[2][m][bj] + x[3][m][bj]);
         }
     }
-    if (mine_to_store) store(u, v);
+    if (!any) return;
+#pragma unroll
+    for (int m = 0; m < MINE; ++m) store(wave + m * T::WAVES, v[m]);
 }
 
 }  // namespace polydl

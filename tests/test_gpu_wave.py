@@ -21,21 +21,24 @@ def P():
     p.set_tile_override(None)
 
 
-def wave(P, tile, parts, layout=0):
-    return P.TileCfg(tile, tile, 16, tile, tile, parts, layout, 1, 0, 0)
+def wave(P, tile, parts, layout=0, waves=8):
+    return P.TileCfg(tile, tile, 16, tile, tile, parts, layout, 1 if waves == 8 else 0, 0, 0)
+
+
+TILES = [(64, 8), (64, 4), (32, 8)]       # tile and the waves that share it
 
 
 # rows and columns at, one below and one past the tiles, reductions at, below and past steps, waves and parts; one row, one column
-@pytest.mark.parametrize("tile", [64, 32])
+@pytest.mark.parametrize("tile,waves", TILES)
 @pytest.mark.parametrize("M,N,K", [(64, 64, 128), (63, 65, 127), (65, 31, 129), (1, 33, 16), (33, 1, 15), (130, 97, 3), (31, 200, 700),
                                    (600, 95, 1000), (5, 3, 4100)])
-def test_sgemm(P, tile, M, N, K):
+def test_sgemm(P, tile, waves, M, N, K):
     import torch
     A, B, C0 = synth.sgemm_inputs(M, N, K, seed=M + N, c0="random")
     want, ab = oracle.gemm(A, B, C0)
     ints = synth.sgemm_inputs(M, N, K, seed=K, dist="ints")
     for parts in (1, 2, 5):
-        P.set_tile_override(wave(P, tile, parts))
+        P.set_tile_override(wave(P, tile, parts, waves=waves))
         got = host(P.sgemm(dev(A), dev(B), dev(C0)))
         assert oracle.scaled_error(got, want, ab) <= FP32_TOL, parts
         out = torch.full((M, N), float("nan"), device="cuda")
@@ -65,9 +68,9 @@ def test_conv(P, s):
     for act, bias, pre, kw in (("relu6", True, None, {}), ("none", False, "relu", {}), ("relu", True, None, tap)):
         layout = 2 if kw and applies else 0
         want, ab = oracle.conv2d_fwd(np.maximum(x, 0) if pre else x, w, bias=b if bias else None, stride=s.stride, pad=s.pad, act=act)
-        for tile in (64, 32):
+        for tile, waves in TILES:
             for parts in (1, 3):
-                P.set_tile_override(wave(P, tile, parts, layout))
+                P.set_tile_override(wave(P, tile, parts, layout, waves))
                 got = host(P.conv2d_fwd(dx, dw, db if bias else None, stride=s.stride, pad=s.pad, act=act, pre_act=pre, **kw))
                 assert P.get_last_tile().wm == tile
                 assert oracle.scaled_error(got, want, ab) <= FP32_TOL, (tile, parts, act)
@@ -85,15 +88,15 @@ def test_refused(P):
             P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad)
         assert err.value.status == -3
     P.set_tile_override(None)
-    for bad in (P.TileCfg(64, 64, 16, 64, 64, 1, 0, 0, 0, 0), P.TileCfg(32, 64, 16, 32, 64, 1, 0, 1, 0, 0)):
+    for bad in (P.TileCfg(64, 64, 16, 64, 64, 1, 0, 2, 0, 0), P.TileCfg(32, 32, 16, 32, 32, 1, 0, 0, 0, 0), P.TileCfg(32, 64, 16, 32, 64, 1, 0, 1, 0, 0)):
         with pytest.raises(P.PolydlError):
             P.set_tile_override(bad)
 
 
 # Values the split cannot hold: in the tile, and behind a row's end, where a ragged reduction reads the next row's first values
-@pytest.mark.parametrize("tile", [64, 32])
+@pytest.mark.parametrize("tile,waves", TILES)
 @pytest.mark.parametrize("case", ["inf", "nan", "largest", "tiny", "row_ends"])
-def test_values_the_split_cannot_hold(P, tile, case):
+def test_values_the_split_cannot_hold(P, tile, waves, case):
     M, N, K = 70, 75, 333
     r = np.random.default_rng(5)
     A, B = r.uniform(-1, 1, (M, K)).astype(np.float32), r.uniform(-1, 1, (K, N)).astype(np.float32)
@@ -115,7 +118,7 @@ def test_values_the_split_cannot_hold(P, tile, case):
         want = A.astype(np.float64) @ B.astype(np.float64)
         ab = np.abs(A.astype(np.float64)) @ np.abs(B.astype(np.float64))
     for parts in (1, 2):
-        P.set_tile_override(wave(P, tile, parts))
+        P.set_tile_override(wave(P, tile, parts, waves=waves))
         got = host(P.sgemm(dev(A), dev(B), dev(C0)))
         ok = np.isfinite(want)
         assert np.array_equal(np.isnan(got), np.isnan(want))
