@@ -50,9 +50,10 @@ def csrc_digest():
 def products_peak(tile, reduction, thin=False):
     """Peak of the instruction that forms the products: tiles of stage depth 16 and wave tiles up to 64x64 split
     fp32 operands for the bf16 matrix cores from a reduction of 128 on (512 for 1x1 layers of at most 64 output
-    channels: thin; 3 for SGEMM, whose caller passes no less), the pointwise and the first-layer kernel always."""
+    channels: thin; 3 for SGEMM, whose caller passes no less), the pointwise and the first-layer kernel always, and so do
+    tiles of 64x64 and 32x32 that single waves compute (a wave tile as large as the tile)."""
     split = tile.algo in (2, 3) or (tile.algo == 0 and tile.bk == 16 and tile.wm * tile.wn <= 64 * 64 and
-                               reduction >= (512 if thin else 128))
+                               ((tile.bm, tile.bn) == (tile.wm, tile.wn) or reduction >= (512 if thin else 128)))
     return SPLIT_PEAK_TFLOPS if split else FP32_MFMA_PEAK_TFLOPS
 
 

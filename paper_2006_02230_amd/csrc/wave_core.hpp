@@ -1,5 +1,5 @@
 // Small products on split operands (split_core.hpp), without stages that waves share: a wave brings its own operands, splits
-// them in registers and multiplies.  The eight waves of a workgroup work on one tile of the result and take the reduction's
+// them in registers and multiplies.  The waves of a workgroup (eight, or four) work on one tile of the result and take the reduction's
 // steps of 16 rows in turn; they meet once, at the end, in LDS.  No barrier in the loop, no trip through scratch memory
 // unless a tile's reduction is dealt to several workgroups.
 //
