@@ -245,7 +245,7 @@ hipError_t conv_thin_launch(const ConvProblem &q, hipStream_t stream);
 // wave_core.hpp).  As a
 // configuration they are gather variants (algo 0) whose wave tile is the whole tile; split_k counts the workgroups that share a tile's
 // reduction, layout 2 reads the filter's copy.  Not ranked: they take the place of a pick where they
-// are predicted to be well below it (conv_wave_pick, sgemm_wave_pick: false where not; no_scratch: one part only).
+// are predicted to be well below it (conv_wave_pick, sgemm_wave_pick, which find the pick in *cfg: false where not; no_scratch: one part only).
 inline polydl_tile_cfg wave_cfg(int tile, int waves, int parts, int layout) { return polydl_tile_cfg{tile, tile, 16, tile, tile, parts, layout, waves == 8, 0, 0}; }
 inline bool is_wave_cfg(const polydl_tile_cfg &c)
 {

@@ -633,10 +633,15 @@ static bool wave_best(double M, double N, double steps, WaveLoads loads, int lay
 // drawn problems of 2e6 .. 3e10 flops about 2000 go there, the time of all falls by a factor of 1.31 in the mean (1.34 with the best choice
 // for each), and about ten were more than 3 % slower, by up to 13 %.  Picks of more than 40 us gain little and are mispredicted more often.  Convolutions of
 // fewer than 128 reduction rows run on the fp32 instruction otherwise and are predicted too high, by up to 1.6.
+// Reductions of fewer steps than there are waves have a rounding per step and those of the meeting, which a staged tile sums in one accumulator:
+// against 64 bits they are further off, products of 32, 40, 64, 96 by 14, 22, 8, 2 %; from 112 on nearer (128: 5 %, 256: 5 .. 26 %).  Staged
+// tiles that split the reduction are the more exact up to 160 (144 in three parts: by 3 %; 192: the waves by 1 %).
+static bool wave_exact(int64_t Kg, const polydl_tile_cfg &pick) { return Kg >= (pick.split_k > 1 ? 192 : 112); }
 static double wave_limit(double pick_us, bool short_rows) { return pick_us * (short_rows ? 0.6 : pick_us <= 40 ? 0.9 : 0.83); }
 bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S;
+    if (!wave_exact(Kg, *cfg)) return false;
     const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
     const double limit = wave_limit(pick_us, Kg < kSplitMinReduction);
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit, no_scratch, q.arena,
@@ -644,6 +649,7 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
 }
 bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
+    if (!wave_exact(q.K, *cfg)) return false;
     const double limit = wave_limit(pick_us, false);
     return wave_best(q.M, q.N, std::ceil(q.K / 16.0), WAVE_ROWS, 0, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg);

@@ -184,6 +184,30 @@ def test_the_library_goes_there(P):
     assert P.get_last_tile().bm > 64
 
 
+def test_short_reductions_stay_as_exact(P):
+    # what the library does by itself is no further from 64 bits than its ranked pick (0.5 %: single sums differ in either direction)
+    import torch
+
+    def off(got, want):
+        return np.linalg.norm(host(got) - want) / np.linalg.norm(want)
+
+    for M, N, K in ((411, 1388, 32), (411, 1388, 40), (300, 500, 72), (1000, 64, 96), (300, 500, 112), (64, 64, 128), (411, 1388, 200)):
+        A, B, _ = synth.sgemm_inputs(M, N, K, seed=M + K)
+        want = A.astype(np.float64) @ B.astype(np.float64)
+        C = torch.zeros(M, N, device="cuda")
+        here = off(P.sgemm(dev(A), dev(B), C, alpha=1.0, beta=0.0), want)
+        P.set_tile_override(P.pick_sgemm(M, N, K)[0])
+        assert here <= 1.005 * off(P.sgemm(dev(A), dev(B), C, alpha=1.0, beta=0.0), want), (M, N, K)
+        P.set_tile_override(None)
+    for s in (synth.ConvShape("144", 1, 16, 7, 7, 64, 3, 3, 2, 1), synth.ConvShape("128", 2, 128, 14, 14, 128, 1, 1, 1, 0)):
+        x, w, _ = synth.conv_inputs(s, seed=21, dist="normal")
+        want, _ = oracle.conv2d_fwd(x, w, stride=s.stride, pad=s.pad)
+        here = off(P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad), want)
+        P.set_tile_override(P.pick_conv2d(tuple(s)[1:])[0])
+        assert here <= 1.005 * off(P.conv2d_fwd(dev(x), dev(w), stride=s.stride, pad=s.pad), want), s.name
+        P.set_tile_override(None)
+
+
 BF16 = SHAPES + [synth.ConvShape("two_steps", 2, 64, 5, 7, 40, 1, 1, 1, 0), synth.ConvShape("41_steps", 1, 144, 9, 9, 70, 3, 3, 1, 1)]
 
 
