@@ -73,7 +73,7 @@ typedef struct polydl_tile_cfg {
     int wm, wn;       /* wave tile (multiples of 32); the workgroup has (bm/wm)*(bn/wn) waves.
                          64x64x16 with wave tile 64x64 and 32x32x16 with 32x32 (SGEMM and algo 0,
                          raster 1; filters of at most 63 taps) are the tiles of small problems: the
-                         eight waves of a workgroup (64x64x16 with raster 0, not in bfloat16: four)
+                         eight waves of a workgroup (64x64x16 with raster 0: four)
                          share a tile's reduction and meet in LDS.  They
                          are not enumerated and not ranked: unless a variant is forced they take the
                          place of a pick where they are predicted to be well below it              */

@@ -498,7 +498,7 @@ int polydl_conv2d_fwd_bf16_blocked(int N, int C, int H, int W, int K, int R, int
         cfg = g_override;
     }
     if (forced) {
-        if (cfg.algo != 1 && !(is_wave_cfg(cfg) && cfg.raster == 1)) return POLYDL_ERR_UNSUPPORTED;
+        if (cfg.algo != 1 && !is_wave_cfg(cfg)) return POLYDL_ERR_UNSUPPORTED;
     } else {
         // the pick depends on the shape alone: made once per shape
         const std::array<int, 9> key = {N, cunits, H, W, K, R, S, stride, pad};
@@ -515,7 +515,7 @@ int polydl_conv2d_fwd_bf16_blocked(int N, int C, int H, int W, int K, int R, int
     }
     if (is_wave_cfg(cfg)) {
         if (!conv_wave_bf16_fits(q, cfg.bm)) return POLYDL_ERR_UNSUPPORTED;
-        const hipError_t we = conv_wave_bf16_launch(q, cfg.bm, cfg.split_k, (hipStream_t)stream);
+        const hipError_t we = conv_wave_bf16_launch(q, cfg.bm, wave_cfg_waves(cfg), cfg.split_k, (hipStream_t)stream);
         if (we == hipSuccess) {
             cfg.layout = 1;
             std::lock_guard<std::mutex> lk(g_mu);

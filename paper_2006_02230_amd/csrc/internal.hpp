@@ -262,7 +262,7 @@ hipError_t conv_wave_launch(const ConvProblem &q, int tile, int waves, int parts
 bool conv_wave_bf16_fits(const ConvProblem &q, int tile);   // q.C counts units of eight channels
 bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg);
 double model_conv_wave_bf16(const ConvProblem &q, const polydl_tile_cfg &cfg);   // predicted microseconds
-hipError_t conv_wave_bf16_launch(const ConvProblem &q, int tile, int parts, hipStream_t stream);
+hipError_t conv_wave_bf16_launch(const ConvProblem &q, int tile, int waves, int parts, hipStream_t stream);
 inline bool sgemm_wave_fits(const SgemmProblem &q, int tile)
 {
     return q.K >= kSgemmSplitMinReduction && sgemm_tile_in_range(q, tile, tile, 16);

@@ -571,24 +571,27 @@ void model_conv_thin(const ConvProblem &q, polydl_model_report *r)
 // Predicted microseconds of tiles of 64x64 shared by eight waves (one workgroup on a compute unit) or four (two), and of 32x32 (two).
 // Fitted to 30684 launches (2700 drawn problems of 2e6 .. 3e10 flops, 1 .. 16 parts): 7.6 % off in the mean, 15 % in 95 of 100.  A step
 // costs a workgroup 0.52 (32x32) .. 1.2 us; gathered operands cost up to 1.7 times that, and up to 1.8 us before the first step.
-// bfloat16 (a step is four units of eight channels; eight waves): 7969 launches of 1000 drawn layers of 5e6 .. 3e10 flops, 9 % off in the mean.
+// bfloat16 (a step is four units of eight channels): 7969 launches of 1000 drawn layers of 5e6 .. 3e10 flops, 9 % off in the mean; 64x64 shared by
+// four waves: 11162 launches of 3000 layers of 5e6 .. 6e10, 7.6 % off.
 enum WaveLoads { WAVE_ROWS, WAVE_POINT, WAVE_POINT_STRIDED, WAVE_TAP, WAVE_TAP_STRIDED, WAVE_TAPS, WAVE_TAPS_STRIDED,
                  WAVE_BF16_POINT, WAVE_BF16_POINT_STRIDED, WAVE_BF16_TAPS, WAVE_BF16_TAPS_STRIDED };
 // step1, step2: one, two workgroups on a compute unit; most: weight of the longest wave's steps against the mean; whole: of whole rounds
 struct WaveFit { double launch, round, step1, step2, parts, part, most, whole; };
 static const WaveFit kWave32 = {1.6, 2.43, 0.519, 1.127, 1.24, 0.19, 0.28, 0.37}, kWave64 = {0.9, 4.3, 1.20, 0, 1.66, 0.25, 0.1, 1},
                      kWave64x4 = {1.2, 3.87, 0.72, 1.32, 1.78, 0.30, 0.73, 0.48}, kWaveBf16_32 = {2.0, 2.4, 0.168, 0.395, 1.42, 0.19, 1, 0.4},
-                     kWaveBf16_64 = {2.1, 3.7, 0.381, 0, 1.77, 0.23, 0.33, 1};
+                     kWaveBf16_64 = {2.1, 3.7, 0.381, 0, 1.77, 0.23, 0.33, 1}, kWaveBf16_64x4 = {1.86, 2.99, 0.253, 0.56, 1.74, 0.295, 1, 0.60};
 static double wave_us(int tile, int waves, int parts, double tiles, double steps, WaveLoads loads, double out_bytes)
 {
-    static const double per_step[] = {1, 1.26, 1.66, 1.08, 1.27, 1.14, 1.23, 1, 1.53, 1.39, 1.59};
-    static const double before[] = {0, 1.00, 0.83, 1.23, 1.30, 1.53, 1.79, 0, -0.27, -0.27, -0.60};
+    // the last four: bfloat16 on four waves
+    static const double per_step[] = {1, 1.26, 1.66, 1.08, 1.27, 1.14, 1.23, 1, 1.53, 1.39, 1.59, 1, 1.62, 1.15, 1.27};
+    static const double before[] = {0, 1.00, 0.83, 1.23, 1.30, 1.53, 1.79, 0, -0.27, -0.27, -0.60, 0, -0.27, -0.05, -0.38};
     const bool bf16 = loads >= WAVE_BF16_POINT;
-    const WaveFit &f = bf16 ? (tile == 64 ? kWaveBf16_64 : kWaveBf16_32) : tile == 32 ? kWave32 : waves == 4 ? kWave64x4 : kWave64;
-    const double mean = std::ceil(steps / parts) / waves, n = (f.most * std::ceil(mean) + (1 - f.most) * mean) * per_step[loads];
+    const int kind = loads + (bf16 && waves == 4 ? 4 : 0);
+    const WaveFit &f = bf16 ? (tile == 32 ? kWaveBf16_32 : waves == 4 ? kWaveBf16_64x4 : kWaveBf16_64) : tile == 32 ? kWave32 : waves == 4 ? kWave64x4 : kWave64;
+    const double mean = std::ceil(steps / parts) / waves, n = (f.most * std::ceil(mean) + (1 - f.most) * mean) * per_step[kind];
     const double wgs = tiles * parts, cus = kCUs, full = wgs / (f.step2 > 0 ? 2 * cus : cus);
     const double rounds = full <= 1 ? 1 : f.whole * std::ceil(full) + (1 - f.whole) * full;
-    return before[loads] + out_bytes / 4.0e6 + f.launch + (parts > 1 ? f.parts + f.part * parts : 0) +
+    return before[kind] + out_bytes / 4.0e6 + f.launch + (parts > 1 ? f.parts + f.part * parts : 0) +
            (f.step2 > 0 && wgs > cus ? rounds * (f.round + n * f.step2) : f.step2 > 0 ? f.round + n * f.step1 : rounds * (f.round + n * f.step1));
 }
 static WaveLoads wave_loads(const ConvProblem &q, int layout)
@@ -608,7 +611,7 @@ static bool wave_best(double M, double N, double steps, WaveLoads loads, int lay
     bool found = false;
     for (const int (&tw)[2] : kTiles) {
         const int tile = tw[0], waves = tw[1];
-        if (!fits(tile) || (waves == 4 && loads >= WAVE_BF16_POINT)) continue;
+        if (!fits(tile)) continue;
         const double tiles = std::ceil(M / tile) * std::ceil(N / tile);
         // a handful of tiles of a few steps each: waves without work
         if (tile == 32 && steps < kWavesPerTile && tiles < 16) return false;
@@ -620,6 +623,8 @@ static bool wave_best(double M, double N, double steps, WaveLoads loads, int lay
             double us = wave_us(tile, waves, parts, tiles, steps, loads, M * N * 4);
             // parts of a reduction of few tiles are 2 .. 3 % better than the formula has it
             if (parts == 1 && tiles <= 64) us *= 1.02;
+            // in bfloat16 the four waves have to be well below the eight: without this one in fifty layers is 3 % slower than on those
+            if (waves == 4 && loads >= WAVE_BF16_POINT) us *= 1.03;
             if (us >= limit) continue;
             limit = us;
             *cfg = wave_cfg(tile, waves, parts, layout);
@@ -655,8 +660,10 @@ bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, pol
                      [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg);
 }
 
-// bfloat16, q.C units of eight channels.  Of 1000 drawn layers of 5e6 .. 3e10 flops about 690 go there, the time of all falls by a
-// factor of 1.39 (1.43 with the best choice for each), about ten were more than 3 % slower.  Up to eight units a row leave most waves without a
+// bfloat16, q.C units of eight channels.  The margins are the staged model's: of 3000 drawn layers of 5e6 .. 6e10 flops the picks of 1x1 ones take
+// 0.82 .. 0.92 of their prediction, of others 1.02 .. 1.17, but 0.8 where a reduction of up to 20 steps is one stage; beyond 256 steps both are off.  About
+// 1850 go there, the time of all falls by a factor of 1.33 (1.38 with the best choice for each), eleven were more than 3 % slower, by up to 8 %
+// (one margin of 0.88: 1.31, 45, 29 %).  Up to eight units a row leave most waves without a
 // step; picks predicted at the floor of their model (8.8 us) take 5 us and more, which the larger tile does not undercut.
 static WaveLoads wave_bf16_loads(const ConvProblem &q)
 {
@@ -668,15 +675,16 @@ bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, 
 {
     const int64_t units = (int64_t)q.C * q.R * q.S;
     if (units <= 8) return false;
-    const double limit = 0.88 * pick_us;
-    return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(units / 4.0), wave_bf16_loads(q), 0, limit, pick_us < 9.5 ? 0.73 * pick_us : limit, no_scratch,
+    const double steps = std::ceil(units / 4.0);
+    const double limit = (q.R == 1 && q.S == 1 ? 0.72 : steps < 20 ? 0.8 : steps > 256 ? 0.88 : 0.92) * pick_us;
+    return wave_best(q.K, (double)q.N * q.P * q.Q, steps, wave_bf16_loads(q), 0, limit, pick_us < 9.5 ? 0.73 * pick_us : limit, no_scratch,
                      q.arena, [&](int tile) { return conv_wave_bf16_fits(q, tile); }, cfg);
 }
 
 double model_conv_wave_bf16(const ConvProblem &q, const polydl_tile_cfg &cfg)
 {
     const double M = q.K, N = (double)q.N * q.P * q.Q;
-    return wave_us(cfg.bm, kWavesPerTile, std::max(1, cfg.split_k), std::ceil(M / cfg.bm) * std::ceil(N / cfg.bm), std::ceil(q.C * q.R * q.S / 4.0),
+    return wave_us(cfg.bm, wave_cfg_waves(cfg), std::max(1, cfg.split_k), std::ceil(M / cfg.bm) * std::ceil(N / cfg.bm), std::ceil(q.C * q.R * q.S / 4.0),
                    wave_bf16_loads(q), M * N * 4);
 }
 

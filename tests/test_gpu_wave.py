@@ -220,9 +220,9 @@ def test_bf16(P, s):
     tx, tw = (torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (x, w))
     want, ab = oracle.conv2d_fwd(host(tx.float()), host(tw.float()), bias=b, stride=s.stride, pad=s.pad, act="relu")
     blocked = lambda a, f: (P.nchw_to_nchwc_bf16(a, 8), P.kcrs_to_kcrsck_bf16(f, 8, 1))
-    for tile in (64, 32):
+    for tile, waves in TILES:
         for parts in (1, 2, 5):
-            P.set_tile_override(wave(P, tile, parts))
+            P.set_tile_override(wave(P, tile, parts, waves=waves))
             got = host(P.conv2d_fwd_bf16_blocked(*blocked(tx, tw), s.C, dev(b), stride=s.stride, pad=s.pad, act="relu"))
             assert oracle.scaled_error(got, want, ab) <= FP32_TOL, (tile, parts)      # products of bfloat16 values are exact in fp32
             ints = [torch.from_numpy(a).cuda().to(torch.bfloat16) for a in (xi, wi)]
