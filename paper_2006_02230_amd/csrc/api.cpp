@@ -462,14 +462,15 @@ static void bf16_candidates(const ConvProblem &qb, std::vector<polydl_tile_cfg> 
 
 static int bf16_threads(const polydl_tile_cfg &c) { return (c.bm / c.wm) * (c.bn / c.wn) * 64; }
 
-// bf16 candidates are ranked with the round-by-round time model at the bf16 instruction's rate
-static bool pick_bf16(const ConvProblem &qb, polydl_tile_cfg *out, double *us = nullptr)
+// bf16 candidates are ranked with the round-by-round time model at the bf16 instruction's rate; no_scratch: only unsplit ones
+static bool pick_bf16(const ConvProblem &qb, polydl_tile_cfg *out, double *us = nullptr, bool no_scratch = false)
 {
     std::vector<polydl_tile_cfg> cands;
     bf16_candidates(qb, &cands);
     bool have = false;
     double best = 0;
     for (const polydl_tile_cfg &c : cands) {
+        if (no_scratch && c.split_k > 1) continue;
         const double t = model_conv_bf16(qb, c, bf16_threads(c));
         if (!have || t < best * 0.999) { best = t; *out = c; have = true; }
     }
@@ -497,6 +498,13 @@ int polydl_conv2d_fwd_bf16_blocked(int N, int C, int H, int W, int K, int R, int
         forced = g_have_override;
         cfg = g_override;
     }
+    // the single waves are not among the ranked candidates: they take the place of a pick
+    auto choose = [&](bool no_scratch) {
+        double us;
+        if (!pick_bf16(q, &cfg, &us, no_scratch)) return false;
+        conv_wave_bf16_pick(q, us, no_scratch, &cfg);
+        return true;
+    };
     if (forced) {
         if (cfg.algo != 1 && !is_wave_cfg(cfg)) return POLYDL_ERR_UNSUPPORTED;
     } else {
@@ -507,39 +515,41 @@ int polydl_conv2d_fwd_bf16_blocked(int N, int C, int H, int W, int K, int R, int
         if (it != g_bf16_plans.end()) {
             cfg = it->second;
         } else {
-            double us;
-            if (!pick_bf16(q, &cfg, &us)) return POLYDL_ERR_UNSUPPORTED;
-            conv_wave_bf16_pick(q, us, false, &cfg);
+            if (!choose(false)) return POLYDL_ERR_UNSUPPORTED;
             g_bf16_plans[key] = cfg;
         }
     }
-    if (is_wave_cfg(cfg)) {
-        if (!conv_wave_bf16_fits(q, cfg.bm)) return POLYDL_ERR_UNSUPPORTED;
-        const hipError_t we = conv_wave_bf16_launch(q, cfg.bm, wave_cfg_waves(cfg), cfg.split_k, (hipStream_t)stream);
-        if (we == hipSuccess) {
-            cfg.layout = 1;
-            std::lock_guard<std::mutex> lk(g_mu);
-            g_last = cfg;
-            return POLYDL_OK;
+    bool no_scratch = false;   // the launch was refused because the stream is being captured and has no scratch memory
+    auto run = [&]() -> int {
+        hipError_t e;
+        if (is_wave_cfg(cfg)) {
+            if (!conv_wave_bf16_fits(q, cfg.bm)) return POLYDL_ERR_UNSUPPORTED;
+            e = conv_wave_bf16_launch(q, cfg.bm, wave_cfg_waves(cfg), cfg.split_k, (hipStream_t)stream);
+        } else {
+            const PatchVariant *pv = find_patch_bf16_variant(cfg);
+            if (!pv) return POLYDL_ERR_UNSUPPORTED;
+            if (cfg.cb == 0) {
+                for (int cb = 2; cb <= ((cunits + 1) & ~1) && cb <= 32; cb += 2)
+                    if (pv->conv(q, cb, 1, 0, nullptr, true) == hipSuccess) cfg.cb = cb;
+            }
+            if (cfg.cb < 2 || (cfg.cb & 1)) return POLYDL_ERR_UNSUPPORTED;
+            const int sk = cfg.split_k < 1 ? 1 : cfg.split_k;
+            if (pv->conv(q, cfg.cb, sk, cfg.raster, nullptr, true) != hipSuccess) return POLYDL_ERR_UNSUPPORTED;
+            e = pv->conv(q, cfg.cb, sk, cfg.raster, (hipStream_t)stream, false);
         }
-        // the stream is being captured and has no scratch memory for the parts: the ranked pick (not cached), which may need none
-        if (forced || !refused_for_capture(we) || !pick_bf16(q, &cfg)) return launch_failed(we);
-    }
-    const PatchVariant *pv = find_patch_bf16_variant(cfg);
-    if (!pv) return POLYDL_ERR_UNSUPPORTED;
-    if (cfg.cb == 0) {
-        for (int cb = 2; cb <= ((cunits + 1) & ~1) && cb <= 32; cb += 2)
-            if (pv->conv(q, cb, 1, 0, nullptr, true) == hipSuccess) cfg.cb = cb;
-    }
-    if (cfg.cb < 2 || (cfg.cb & 1)) return POLYDL_ERR_UNSUPPORTED;
-    const int sk = cfg.split_k < 1 ? 1 : cfg.split_k;
-    if (pv->conv(q, cfg.cb, sk, cfg.raster, nullptr, true) != hipSuccess) return POLYDL_ERR_UNSUPPORTED;
-    hipError_t e = pv->conv(q, cfg.cb, sk, cfg.raster, (hipStream_t)stream, false);
-    if (e != hipSuccess) return launch_failed(e);
-    cfg.layout = 1;
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_last = cfg;
-    return POLYDL_OK;
+        if (e != hipSuccess) {
+            no_scratch = refused_for_capture(e);
+            return launch_failed(e);
+        }
+        cfg.layout = 1;
+        std::lock_guard<std::mutex> lk(g_mu);
+        g_last = cfg;
+        return POLYDL_OK;
+    };
+    const int st = run();
+    // the best choice that needs no scratch memory (not cached); nothing was enqueued so far
+    if (st != POLYDL_OK && no_scratch && !forced && choose(true)) return run();
+    return st;
 }
 
 size_t polydl_conv2d_bf16_workspace_bytes(int N, int C, int H, int W, int K, int R, int S)

@@ -272,3 +272,40 @@ def test_bf16_the_library_goes_there_and_is_captured(P):
         assert np.array_equal(host(out), eager)
         call()
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("s", [synth.ConvShape("single_waves", 1, 512, 14, 14, 128, 3, 3, 1, 1),
+                               synth.ConvShape("ranked_64_taps", 1, 256, 12, 12, 64, 8, 8, 1, 3)], ids=lambda s: s.name)
+def test_bf16_is_captured_without_scratch_memory(P, s):
+    # a choice that splits its reduction when called eagerly, on a stream that has no scratch memory: the capture records the best
+    # choice that needs none
+    import torch
+    x, w, b = synth.conv_inputs(s, seed=18, dist="normal", bias=True)
+    tx, tw, tb = torch.from_numpy(x).cuda().to(torch.bfloat16), torch.from_numpy(w).cuda().to(torch.bfloat16), dev(b)
+    want, ab = oracle.conv2d_fwd(host(tx.float()), host(tw.float()), bias=b, stride=s.stride, pad=s.pad, act="relu")
+    x8, w8 = P.nchw_to_nchwc_bf16(tx, 8), P.kcrs_to_kcrsck_bf16(tw, 8, 1)
+    out = torch.empty(want.shape, dtype=torch.float32, device="cuda")
+
+    def call():
+        P.conv2d_fwd_bf16_blocked(x8, w8, s.C, tb, out=out, stride=s.stride, pad=s.pad, act="relu")
+    call()                                  # on the default stream: it has its own scratch memory
+    torch.cuda.synchronize()
+    eager = P.get_last_tile()
+    assert eager.split_k > 1, eager
+    fresh = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(fresh):
+        with torch.cuda.graph(graph, stream=fresh):
+            call()
+            captured = P.get_last_tile()
+    assert captured.split_k == 1, captured
+    for _ in range(3):
+        out.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert oracle.scaled_error(host(out), want, ab) <= FP32_TOL
+        call()                              # eager work in between
+        torch.cuda.synchronize()
+        assert P.get_last_tile().as_dict() == eager.as_dict()      # the choice for eager calls is unchanged
+        assert oracle.scaled_error(host(out), want, ab) <= FP32_TOL
