@@ -643,12 +643,20 @@ static bool wave_best(double M, double N, double steps, WaveLoads loads, int lay
 // tiles that split the reduction are the more exact up to 160 (144 in three parts: by 3 %; 192: the waves by 1 %).
 static bool wave_exact(int64_t Kg, const polydl_tile_cfg &pick) { return Kg >= (pick.split_k > 1 ? 192 : 112); }
 static double wave_limit(double pick_us, bool short_rows) { return pick_us * (short_rows ? 0.6 : pick_us <= 40 ? 0.9 : 0.83); }
+// Unsplit picks of 1x1 layers on the gather kernel are predicted too high: they take 0.76 of it at 128 rows, 0.86 at 500, on the fp32
+// instruction 0.72 .. 0.8, strided ones into at most 64 channels down to 0.58, and there the waves' tiles, one row of them, take up to 1.5 times
+// what they are predicted.  With the margins of other layers 42 of 74 strided ones into up to 64 channels were slower than their pick, by up to 31 %
+// (128 -> 64 on 56x45, batch 32: 13.1 us against 10.2), 40 of 183 into more, by up to 13 %, and 10 of 14 unstrided ones of 128 rows into
+// up to 64, by up to 17 %; with these one of the 393 that still go there, by 6 %.
 bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S;
     if (!wave_exact(Kg, *cfg)) return false;
+    const bool point_pick = cfg->algo == 0 && cfg->split_k <= 1 && q.R == 1 && q.S == 1 && q.pad == 0;
+    if (point_pick && q.stride > 1 && q.K <= 64) return false;
     const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
-    const double limit = wave_limit(pick_us, Kg < kSplitMinReduction);
+    double limit = wave_limit(pick_us, Kg < kSplitMinReduction || (point_pick && !split_pays(q.K, 1, Kg)));
+    if (point_pick) limit = std::min(limit, (q.stride > 1 ? 0.8 : 0.86) * pick_us);
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
 }

@@ -309,3 +309,26 @@ def test_bf16_is_captured_without_scratch_memory(P, s):
         torch.cuda.synchronize()
         assert P.get_last_tile().as_dict() == eager.as_dict()      # the choice for eager calls is unchanged
         assert oracle.scaled_error(host(out), want, ab) <= FP32_TOL
+
+
+# layers that the single waves made slower than their ranked pick (percent more time), which therefore stay with it
+SLOWER = [synth.ConvShape("few_channels_strided_29", 32, 128, 56, 45, 64, 1, 1, 2, 0), synth.ConvShape("few_channels_17", 64, 128, 7, 39, 64, 1, 1, 1, 0),
+          synth.ConvShape("few_channels_strided_25", 32, 256, 19, 104, 64, 1, 1, 2, 0), synth.ConvShape("few_channels_long_8", 32, 512, 28, 86, 64, 1, 1, 2, 0),
+          synth.ConvShape("strided_10", 32, 128, 28, 28, 128, 1, 1, 2, 0), synth.ConvShape("strided_12", 33, 128, 72, 26, 128, 1, 1, 2, 0)]
+
+
+def stays(P, s, call):
+    import torch
+    x, w = torch.zeros(s.N, s.C, s.H, s.W, device="cuda"), torch.zeros(s.K, s.C, s.R, s.S, device="cuda")
+    call(x, w)
+    torch.cuda.synchronize()
+    t = P.get_last_tile()
+    assert not (t.algo == 0 and t.wm == t.bm), t
+
+
+@pytest.mark.parametrize("s", SLOWER, ids=lambda s: s.name)
+def test_1x1_layers_that_would_be_slower_stay(P, s):
+    import torch
+    kw = dict(stride=s.stride, pad=s.pad)
+    stays(P, s, lambda x, w: P.conv2d_fwd(x, w, **kw))
+    stays(P, s, lambda x, w: P.conv2d_fwd_noalloc(x, w, None, torch.empty((s.N, s.K) + tuple(synth.out_hw(s)), device="cuda"), **kw))
