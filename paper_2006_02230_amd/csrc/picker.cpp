@@ -657,6 +657,9 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
     const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
     double limit = wave_limit(pick_us, Kg < kSplitMinReduction || (point_pick && !split_pays(q.K, 1, Kg)));
     if (point_pick) limit = std::min(limit, (q.stride > 1 ? 0.8 : 0.86) * pick_us);
+    // up to 64 channels in the KCRS order: the gather kernel's 64x128 tiles take 0.75 .. 0.82 of their prediction (1019 -> 64 3x3 on 28x28, batch
+    // 32: 212 us; waves 230).  74 of 987 such layers were slower on the waves, by up to 10 %; 7 of the 672 that still go there, by up to 9 %
+    if (layout == 0 && q.R * q.S > 1 && q.K <= 64 && cfg->algo == 0 && cfg->bn == 128) limit = std::min(limit, 0.76 * pick_us);
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
 }

@@ -332,3 +332,9 @@ def test_1x1_layers_that_would_be_slower_stay(P, s):
     kw = dict(stride=s.stride, pad=s.pad)
     stays(P, s, lambda x, w: P.conv2d_fwd(x, w, **kw))
     stays(P, s, lambda x, w: P.conv2d_fwd_noalloc(x, w, None, torch.empty((s.N, s.K) + tuple(synth.out_hw(s)), device="cuda"), **kw))
+
+
+@pytest.mark.parametrize("s", [synth.ConvShape("3x3_9", 32, 1019, 28, 28, 64, 3, 3, 1, 1), synth.ConvShape("5x5_8", 32, 256, 56, 14, 64, 5, 5, 1, 2),
+                               synth.ConvShape("7x7_leftover_10", 32, 39, 87, 63, 35, 7, 7, 1, 3)], ids=lambda s: s.name)
+def test_layers_of_few_channels_that_would_be_slower_stay(P, s):
+    stays(P, s, lambda x, w: P.conv2d_fwd(x, w, stride=s.stride, pad=s.pad))
