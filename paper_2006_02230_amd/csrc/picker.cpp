@@ -681,6 +681,11 @@ bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, pol
 // 1850 go there, the time of all falls by a factor of 1.33 (1.38 with the best choice for each), eleven were more than 3 % slower, by up to 8 %
 // (one margin of 0.88: 1.31, 45, 29 %).  Up to eight units a row leave most waves without a
 // step; picks predicted at the floor of their model (8.8 us) take 5 us and more, which the larger tile does not undercut.
+// Picks that do not split take 0.8 .. 0.9 of their prediction at 36 steps (128 input channels 3x3), and strided layers of more than 40 us cost the
+// waves 1.2 .. 1.4 times theirs: at 0.92, 29 of 696 drawn ones were slower than their pick, by up to 26 % (803 -> 256 3x3/2 on 28x28, batch 36:
+// 50 us, waves 63; 128 -> 64 3x3/2 on 56x56, batch 64: 20.4 and 23.0); with margins of their own 10 of 576, by up to 12 %.  Of 13716 layers drawn
+// anew that go there 63 are slower, eight by more than 10 and one by 20 %, half of them reductions of more than 100 steps in picks of
+// more than 15 us, where the waves take 0.74 of the time in the mean.
 static WaveLoads wave_bf16_loads(const ConvProblem &q)
 {
     const bool strided = q.stride > 1;
@@ -692,7 +697,15 @@ bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, 
     const int64_t units = (int64_t)q.C * q.R * q.S;
     if (units <= 8) return false;
     const double steps = std::ceil(units / 4.0);
-    const double limit = (q.R == 1 && q.S == 1 ? 0.72 : steps < 20 ? 0.8 : steps > 256 ? 0.88 : 0.92) * pick_us;
+    const bool unsplit = cfg->split_k <= 1;
+    const double margin = q.R == 1 && q.S == 1 ? 0.72
+                          : steps < 20         ? (q.K <= 32 ? 0.76 : 0.8)
+                          : steps > 256        ? 0.88
+                          : !unsplit           ? 0.92
+                          : q.stride == 1      ? 0.89
+                          : pick_us > 40       ? 0.88
+                                               : steps <= 48 && pick_us > 18 ? 0.84 : 0.92;
+    const double limit = margin * pick_us;
     return wave_best(q.K, (double)q.N * q.P * q.Q, steps, wave_bf16_loads(q), 0, limit, pick_us < 9.5 ? 0.73 * pick_us : limit, no_scratch,
                      q.arena, [&](int tile) { return conv_wave_bf16_fits(q, tile); }, cfg);
 }

@@ -345,3 +345,11 @@ def test_layers_of_few_channels_that_would_be_slower_stay(P, s):
                                synth.ConvShape("many_channels_12", 32, 256, 28, 16, 256, 3, 3, 2, 1)], ids=lambda s: s.name)
 def test_strided_layers_with_the_filter_copy_that_would_be_slower_stay(P, s):
     stays(P, s, lambda x, w: P.conv2d_fwd(x, w, stride=s.stride, pad=s.pad, w_tap=P.filter_tap_copy(w)))
+
+
+@pytest.mark.parametrize("s", [synth.ConvShape("strided_26", 36, 803, 28, 28, 256, 3, 3, 2, 1), synth.ConvShape("strided_short_13", 64, 128, 56, 56, 64, 3, 3, 2, 1),
+                               synth.ConvShape("few_channels_17", 14, 128, 56, 56, 17, 3, 3, 1, 1), synth.ConvShape("few_steps_13", 64, 16, 14, 23, 29, 3, 3, 1, 1)],
+                         ids=lambda s: s.name)
+def test_bf16_layers_that_would_be_slower_stay(P, s):
+    import torch
+    stays(P, s, lambda x, w: P.conv2d_fwd_bf16(x.to(torch.bfloat16), w.to(torch.bfloat16), stride=s.stride, pad=s.pad))
