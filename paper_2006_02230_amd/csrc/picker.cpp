@@ -580,7 +580,8 @@ struct WaveFit { double launch, round, step1, step2, parts, part, most, whole; }
 static const WaveFit kWave32 = {1.6, 2.43, 0.519, 1.127, 1.24, 0.19, 0.28, 0.37}, kWave64 = {0.9, 4.3, 1.20, 0, 1.66, 0.25, 0.1, 1},
                      kWave64x4 = {1.2, 3.87, 0.72, 1.32, 1.78, 0.30, 0.73, 0.48}, kWaveBf16_32 = {2.0, 2.4, 0.168, 0.395, 1.42, 0.19, 1, 0.4},
                      kWaveBf16_64 = {2.1, 3.7, 0.381, 0, 1.77, 0.23, 0.33, 1}, kWaveBf16_64x4 = {1.86, 2.99, 0.253, 0.56, 1.74, 0.295, 1, 0.60};
-static double wave_us(int tile, int waves, int parts, double tiles, double steps, WaveLoads loads, double out_bytes)
+// steps_us (may be null): the time of the steps alone
+static double wave_us(int tile, int waves, int parts, double tiles, double steps, WaveLoads loads, double out_bytes, double *steps_us = nullptr)
 {
     // the last four: bfloat16 on four waves
     static const double per_step[] = {1, 1.26, 1.66, 1.08, 1.27, 1.14, 1.23, 1, 1.53, 1.39, 1.59, 1, 1.62, 1.15, 1.27};
@@ -591,8 +592,11 @@ static double wave_us(int tile, int waves, int parts, double tiles, double steps
     const double mean = std::ceil(steps / parts) / waves, n = (f.most * std::ceil(mean) + (1 - f.most) * mean) * per_step[kind];
     const double wgs = tiles * parts, cus = kCUs, full = wgs / (f.step2 > 0 ? 2 * cus : cus);
     const double rounds = full <= 1 ? 1 : f.whole * std::ceil(full) + (1 - f.whole) * full;
-    return before[kind] + out_bytes / 4.0e6 + f.launch + (parts > 1 ? f.parts + f.part * parts : 0) +
-           (f.step2 > 0 && wgs > cus ? rounds * (f.round + n * f.step2) : f.step2 > 0 ? f.round + n * f.step1 : rounds * (f.round + n * f.step1));
+    // one round if two workgroups fit a compute unit and there is no more than one for each
+    const bool pairs = f.step2 > 0 && wgs > cus;
+    const double times = f.step2 > 0 && !pairs ? 1 : rounds, each = n * (pairs ? f.step2 : f.step1);
+    if (steps_us) *steps_us = times * each;
+    return before[kind] + out_bytes / 4.0e6 + f.launch + (parts > 1 ? f.parts + f.part * parts : 0) + times * (f.round + each);
 }
 static WaveLoads wave_loads(const ConvProblem &q, int layout)
 {
@@ -721,9 +725,10 @@ static void model_wave(double M, double N, double Kg, WaveLoads loads, double in
 {
     std::memset(r, 0, sizeof(*r));
     const double t = cfg.bm, tiles = std::ceil(M / t) * std::ceil(N / t), parts = std::max(1, cfg.split_k);
-    r->predicted_us = wave_us(cfg.bm, wave_cfg_waves(cfg), (int)parts, tiles, std::ceil(Kg / 16), loads, M * N * 4);
-    r->mfma_us = r->predicted_us;
+    r->predicted_us = wave_us(cfg.bm, wave_cfg_waves(cfg), (int)parts, tiles, std::ceil(Kg / 16), loads, M * N * 4, &r->mfma_us);
     r->mem_us = (in_bytes + M * Kg * 4 + M * N * 4) / kHbmGBs * 1e-3;
+    // launch, rounds, first loads, hand-over and stores: what neither the steps nor the tensors' bytes take
+    r->fixed_us = std::max(0.0, r->predicted_us - std::max(r->mfma_us, r->mem_us));
     r->workgroups = (int)std::min(tiles * parts, 2e9);
     r->simd_load = std::ceil(tiles * parts / kCUs) * wave_cfg_waves(cfg) / kSimdsPerCU;
     // reuses: accumulators over a wave's steps; a step's operands, every row with every column; the operands by the tiles; the tensors

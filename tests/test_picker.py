@@ -345,3 +345,12 @@ def test_products_of_three_terms_and_more_split_their_operands():
         for K in (3, 8, 32, 500, 4096):
             c, _ = P.pick_sgemm(M, N, K)
             assert c.bk == 16 and c.wm * c.wn <= 64 * 64, (M, N, K, c)
+
+
+@pytest.mark.parametrize("tile,waves,parts", [(64, 8, 1), (64, 4, 1), (64, 4, 3), (32, 8, 1), (32, 8, 4)])
+def test_single_wave_reports_split_the_predicted_time(tile, waves, parts):
+    cfg = P.TileCfg(tile, tile, 16, tile, tile, parts, 0, 1 if waves == 8 else 0, 0, 0)
+    for rep in (P.model_conv2d((1, 64, 56, 56, 64, 3, 3, 1, 1), cfg), P.model_conv2d((32, 512, 7, 7, 512, 3, 3, 1, 1), cfg),
+                P.model_conv2d((2, 128, 14, 14, 128, 1, 1, 1, 0), cfg), P.model_sgemm(128, 2048, 4096, cfg), P.model_sgemm(65, 31, 129, cfg)):
+        assert rep.mfma_us > 0 and rep.mem_us > 0 and rep.fixed_us > 0
+        assert rep.predicted_us == pytest.approx(max(rep.mfma_us, rep.mem_us) + rep.fixed_us)
