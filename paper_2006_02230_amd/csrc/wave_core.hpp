@@ -289,14 +289,13 @@ inline hipError_t wave_parts(int steps, int parts, int tiles, size_t tile_bytes,
     return splitk_scratch(stream, arena, (size_t)tiles * w->parts * tile_bytes, tiles, &w->partials, &w->counters);
 }
 
-// A kernel that needs more than the default window of LDS has to ask for it.
+// A kernel that needs more than the default window of LDS has to ask for it: all of these do, the smallest with 64 KB beside its table.
 template <class T, class... P, class... A>
 inline hipError_t wave_launch(void (*kernel)(P...), int tiles, int parts, hipStream_t stream, A... args)
 {
-    if (T::LDS_BYTES > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
-        if (e != hipSuccess) return e;
-    }
+    static_assert(T::LDS_BYTES >= 64 * 1024, "with the kernel's own arrays more than the default window");
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+    if (e != hipSuccess) return e;
     return launch_kernel(kernel, dim3((unsigned)tiles, (unsigned)parts), dim3(T::THREADS), T::LDS_BYTES, stream, args...);
 }
 
