@@ -151,9 +151,35 @@ def test_conv_values_the_split_cannot_hold(P, case):
     P.set_tile_override(None)
 
 
+@pytest.mark.parametrize("case", ["inf", "tiny", "tiny_filter"])
+def test_conv_values_the_split_cannot_hold_on_four_waves_and_tap_by_tap(P, case):
+    s = synth.ConvShape("copy", 2, 48, 9, 8, 70, 3, 3, 1, 1)
+    x, w, b = synth.conv_inputs(s, seed=23, dist="normal", bias=True)
+    if case == "inf":
+        x[1, 3, 4, 5] = np.inf
+    elif case == "tiny":
+        x[:, 5:] *= np.float32(1e-37)
+        w *= np.float32(1e20)
+    else:
+        w[:, 7:] *= np.float32(1e-37)
+    dx, dw, db = dev(x), dev(w), dev(b)
+    tap = P.filter_tap_copy(dw)
+    with np.errstate(all="ignore"):
+        want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad)
+    ok = np.isfinite(want)
+    for tile, waves in TILES:
+        for layout, kw in ((0, {}), (2, dict(w_tap=tap))):
+            for parts in (1, 3):
+                P.set_tile_override(wave(P, tile, parts, layout, waves))
+                got = host(P.conv2d_fwd(dx, dw, db, stride=s.stride, pad=s.pad, **kw))
+                assert np.array_equal(np.isfinite(got), ok), (tile, waves, layout, parts)
+                assert (np.abs(got[ok] - want[ok]) <= FP32_TOL * ab[ok] + 1e-44).all(), (tile, waves, layout, parts)
+    P.set_tile_override(None)
+
+
 def test_the_library_goes_there(P):
     import torch
-    # by itself for small problems, aligned or not, with the fixed scratch memory, captured; not for large ones, one-step ones
+    # by itself for small problems, aligned or not, and through the entry with the fixed scratch memory; not for large ones, one-step ones
     s = synth.ConvShape("small", 1, 64, 56, 56, 64, 3, 3, 1, 1)
     x, w, b = synth.conv_inputs(s, seed=13, dist="normal", bias=True)
     want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad, act="relu")
@@ -182,6 +208,52 @@ def test_the_library_goes_there(P):
     big = torch.zeros(4096, 4096, device="cuda")
     P.sgemm(big, big, big.clone())
     assert P.get_last_tile().bm > 64
+    thin = torch.zeros(500, 16, device="cuda")
+    P.sgemm(thin, thin.view(16, 500), torch.zeros(500, 500, device="cuda"))
+    last = P.get_last_tile()
+    assert last.wm < last.bm
+    P.conv2d_fwd(torch.zeros(1, 16, 20, 20, device="cuda"), torch.zeros(64, 16, 1, 1, device="cuda"))
+    last = P.get_last_tile()
+    assert not (last.algo == 0 and last.wm == last.bm)
+
+
+# parts that meet in the library's fixed array: forced ones of every tile, the larger problem first, and a choice of the library's own
+@pytest.mark.parametrize("captured", [False, True])
+def test_several_parts_on_the_fixed_scratch_memory(P, captured):
+    import torch
+    forced = [wave(P, tile, parts, waves=waves) for tile, waves in TILES for parts in (3, 5)]
+    for s, tiles in ((synth.ConvShape("a", 3, 48, 13, 11, 150, 3, 3, 1, 1), forced), (synth.ConvShape("b", 1, 32, 6, 6, 20, 3, 3, 2, 1), forced),
+                     (synth.ConvShape("long", 1, 512, 14, 14, 256, 3, 3, 1, 1), [None])):
+        x, w, b = synth.conv_inputs(s, seed=22, dist="normal", bias=True)
+        dx, dw, db = dev(x), dev(w), dev(b)
+        kw = dict(stride=s.stride, pad=s.pad, act="relu")
+        want, ab = oracle.conv2d_fwd(x, w, bias=b, stride=s.stride, pad=s.pad, act="relu")
+        for tile in tiles:
+            P.set_tile_override(tile)
+            ref = host(P.conv2d_fwd(dx, dw, db, **kw))
+            last = P.get_last_tile()
+            assert last.split_k > 1 and last.wm == last.bm and last.algo == 0, last
+            assert oracle.scaled_error(ref, want, ab) <= FP32_TOL, (s.name, last)
+            out = torch.full(ref.shape, -1.0, device="cuda")
+
+            def call():
+                P.conv2d_fwd_noalloc(dx, dw, db, out, **kw)
+            if captured:
+                side = torch.cuda.Stream()
+                graph = torch.cuda.CUDAGraph()
+                torch.cuda.synchronize()
+                with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+                    call()
+            for _ in range(3 if captured else 1):
+                out.fill_(-1.0)
+                torch.cuda.synchronize()
+                graph.replay() if captured else call()
+                assert P.get_last_tile().as_dict() == last.as_dict()
+                assert np.array_equal(host(out), ref), (s.name, last)
+                if captured:        # eager work in between, on the same array
+                    call()
+                    torch.cuda.synchronize()
+    P.set_tile_override(None)
 
 
 def test_short_reductions_stay_as_exact(P):
