@@ -57,6 +57,16 @@ def products_peak(tile, reduction, thin=False):
     return SPLIT_PEAK_TFLOPS if split else FP32_MFMA_PEAK_TFLOPS
 
 
+def unranked(tile):
+    """The first-layer kernel and the tiles of single waves: the library takes them in the place of a ranked pick."""
+    return tile["algo"] == 3 or (tile["algo"] == 0 and (tile["wm"], tile["wn"]) == (tile["bm"], tile["bn"]))
+
+
+def with_taken(P, ranked, tile):
+    """The ranked candidates and what the library took instead, if that is none of them."""
+    return list(ranked) + ([P.TileCfg(**tile)] if unranked(tile) else [])
+
+
 def conv_flops(s, P, Q):
     return 2.0 * s.N * s.K * P * Q * s.C * s.R * s.S
 
@@ -349,12 +359,12 @@ def main():
                             cold_frac_roofline=round(L["flops"] / (cms * 1e-3) / 1e12 / ceiling, 4))
             del sets
         if args.sweep:
-            # every candidate the picker ranks, and the first-layer kernel where it took their place, timed; the model's
-            # prediction beside it
+            # every candidate the picker ranks, and the first-layer kernel or the single waves where they took their place,
+            # timed; the model's prediction beside it
             shape = tuple(L["shape"])[1:]
             cands = []
             t_sweep = time.perf_counter()
-            for v in P.conv_candidates(shape, tap=L["wt"] is not None) + ([P.TileCfg(**tile)] if tile["algo"] == 3 else []):
+            for v in with_taken(P, P.conv_candidates(shape, tap=L["wt"] is not None), tile):
                 try:
                     P.set_tile_override(v)
                     run_layer(L)
@@ -378,7 +388,7 @@ def main():
             # bytes that move); the matrix-core term
             alone = {}
             for key in ("eq1_cost", "data_us", "mfma_us"):
-                c0 = min(cands, key=lambda c: (c[key], c["pred_us"]))
+                c0 = min((c for c in cands if not unranked(c["cfg"])), key=lambda c: (c[key], c["pred_us"]))
                 alone[key + "_alone_over_best"] = round(best["us"] / c0["us"], 4)
             rows[-1].update(alone)
             rows[-1].update(sweep_best_us=best["us"], sweep_best_tile=best["cfg"],
@@ -442,12 +452,13 @@ def main():
             sg.append(dict(n=n, us=round(ms * 1e3, 2), tflops=round(tf, 2),
                            frac_mfma=round(tf / products_peak(P.get_last_tile(), 128), 4), tile=P.get_last_tile().as_dict()))
             if args.sweep:
-                # every candidate the SGEMM picker ranks; candidates the model puts beyond 4x its best
-                # prediction are not timed (they would take most of the sweep's time and none is near)
+                # every candidate the SGEMM picker ranks, and the single waves where they took their place; candidates the
+                # model puts beyond 4x its best prediction are not timed (they would take most of the sweep's time and
+                # none is near)
                 pcfg, prep = P.pick_sgemm(n, n, n)
                 cands = []
                 t_sweep = time.perf_counter()
-                for v in P.sgemm_candidates(n, n, n):
+                for v in with_taken(P, P.sgemm_candidates(n, n, n), sg[-1]["tile"]):
                     pred = P.model_sgemm(n, n, n, v).predicted_us
                     if pred > 4.0 * prep.predicted_us:
                         continue
@@ -461,12 +472,13 @@ def main():
                 t_sweep = time.perf_counter() - t_sweep
                 P.set_tile_override(forced)
                 by_time = sorted(cands, key=lambda c: c["us"])
-                by_pred = sorted(cands, key=lambda c: c["pred_us"])
-                top = max(1, len(cands) // 20)   # the paper reports its GEMM picks among the top 5 % of the ranking
+                by_pred = sorted((c for c in cands if not unranked(c["cfg"])), key=lambda c: c["pred_us"])
+                top = max(1, len(by_pred) // 20)   # the paper reports its GEMM picks among the top 5 % of the ranking
                 best_in_top = min(c["us"] for c in by_pred[:top])
                 sg[-1].update(sweep_best_us=by_time[0]["us"], sweep_best_tile=by_time[0]["cfg"],
                               pick_over_best=round(by_time[0]["us"] / (ms * 1e3), 4), candidates=len(cands),
-                              predicted_us=round(prep.predicted_us, 2), sweep_seconds=round(t_sweep, 3),
+                              predicted_us=round(P.model_sgemm(n, n, n, P.TileCfg(**sg[-1]["tile"])).predicted_us, 2),
+                              sweep_seconds=round(t_sweep, 3),
                               top5pct_best_us=best_in_top,
                               top5pct_over_best=round(by_time[0]["us"] / best_in_top, 4))
             del dA, dB, dC
@@ -516,7 +528,7 @@ def main():
                 shape = tuple(s)[1:]
                 cands = []
                 t_sweep = time.perf_counter()
-                for v in P.conv_candidates_bf16(shape):
+                for v in with_taken(P, P.conv_candidates_bf16(shape), bf_rows[-1]["tile"]):
                     try:
                         P.set_tile_override(v)
                         fn()
@@ -531,6 +543,7 @@ def main():
                 t_pick = time.perf_counter()
                 pcfg, pus = P.pick_conv2d_bf16(shape)
                 t_pick = time.perf_counter() - t_pick
+                pus = P.model_conv2d_bf16(shape, P.TileCfg(**bf_rows[-1]["tile"]))     # the prediction for the variant that ran
                 bf_rows[-1].update(sweep_best_us=cands[0]["us"], sweep_best_tile=cands[0]["cfg"],
                                    pick_over_best=round(cands[0]["us"] / (ms * 1e3), 4), candidates=len(cands),
                                    predicted_us=round(pus, 2), pick_seconds=round(t_pick, 5),

@@ -36,12 +36,17 @@ ACTS = ["relu", "relu", "softsign", "relu", "softmax"]
 N_SIZES = 5
 
 
+def ranked(cfg):
+    """Whether the pickers rank the variant: not the first-layer kernel (algo 3), not single waves (a wave tile as large as the tile)."""
+    return cfg["algo"] != 3 and not (cfg["algo"] == 0 and (cfg["wm"], cfg["wn"]) == (cfg["bm"], cfg["bn"]))
+
+
 def import_sweeps(paths, out_path=DATA):
     problems = []
     for path in paths:
         for layer in json.load(open(path)):
-            # a sweep also times the first-layer kernel (algo 3) where it runs; tournaments are among the ranked candidates
-            rows = [[c["cfg"][f] for f in CFG_FIELDS] + [c["us"]] for c in layer["candidates"] if c["cfg"]["algo"] != 3]
+            # a sweep also times the first-layer kernel and single waves where they run; tournaments are among the ranked candidates
+            rows = [[c["cfg"][f] for f in CFG_FIELDS] + [c["us"]] for c in layer["candidates"] if ranked(c["cfg"])]
             problems.append({"shape": layer["shape"], "rows": rows})
     os.makedirs(os.path.dirname(out_path), exist_ok=True)
     with open(out_path, "w") as f:

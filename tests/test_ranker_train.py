@@ -78,6 +78,16 @@ def test_only_ranked_candidates_are_imported(tmp_path):
     assert list(us) == [60.0, 62.0] and [c.algo for c in got] == [0, 0]
 
 
+def test_single_waves_are_not_imported(tmp_path):
+    shape = [1, 64, 56, 56, 64, 3, 3, 1, 1]
+    cfgs = [P.TileCfg(64, 64, 16, 32, 32, 4, 0, 1, 0, 0), P.TileCfg(32, 32, 16, 32, 32, 1, 0, 1, 0, 0), P.TileCfg(64, 64, 16, 64, 64, 2, 0, 0, 0, 0),
+            P.TileCfg(64, 64, 0, 64, 64, 1, 0, 0, 3, 0)]
+    src, packed = tmp_path / "s.json", tmp_path / "packed.json"
+    src.write_text(json.dumps([{"layer": 0, "shape": shape, "picked": cfgs[1].as_dict(), "picked_us": 6.0,
+                                "candidates": [{"us": 6.0 + i, "cfg": c.as_dict()} for i, c in enumerate(cfgs)]}]))
+    assert T.import_sweeps([str(src)], str(packed)) == (1, 1)
+
+
 def test_split_is_seeded_and_about_seventy_percent():
     a, b = T.split_mask(5000, 0), T.split_mask(5000, 0)
     assert np.array_equal(a, b) and not np.array_equal(a, T.split_mask(5000, 1))
