@@ -605,17 +605,27 @@ static WaveLoads wave_loads(const ConvProblem &q, int layout)
     if (layout == 2) return strided ? WAVE_TAP_STRIDED : WAVE_TAP;
     return strided ? WAVE_TAPS_STRIDED : WAVE_TAPS;
 }
-// The best of the tiles and 1 .. 16 parts, if it is predicted below `limit`, for tiles of 64x64 `limit64`.
+// Products: the least time of what the XCDs bring in, the operands from memory and what several of them read once more from the last-level cache.
+// Each takes a run of tiles (WaveOrder) and reads the panels these touch once; row_bytes: of a row's reduction.  Of 3500 drawn products of more
+// than 8 MB the larger of this and the formula above is 17 % off in the mean, the formula alone 29 %, 2.3 times too low at
+// worst (105x236x466615).
+static double wave_panels_us(int tile, double M, double N, double row_bytes)
+{
+    const double tm = std::ceil(M / tile), tn = std::ceil(N / tile), run = std::ceil(tm * tn / 8), rows = std::min({run, tm, 8.0});
+    const double once = M + N, all = std::min(8.0, tm * tn) * (rows * M / tm + std::ceil(run / rows) * N / tn);
+    return (once / 5.0e6 + std::max(0.0, all - once) / 4.5e6) * row_bytes;
+}
+// The best of the tiles and 1 .. 16 parts, if it is predicted below `limit`, for tiles of 64x64 `limit64`.  row_bytes: of products, 0 for convolutions.
 template <class Fits>
 static bool wave_best(double M, double N, double steps, WaveLoads loads, int layout, double limit, double limit64, bool no_scratch, const ScratchArena *arena,
-                      Fits &&fits, polydl_tile_cfg *cfg)
+                      Fits &&fits, polydl_tile_cfg *cfg, double row_bytes = 0)
 {
     static const int kParts[] = {1, 2, 3, 4, 6, 8, 12, 16}, kTiles[][2] = {{32, 8}, {64, 8}, {64, 4}};
-    const double cus = kCUs;
+    const double cus = kCUs, most = limit;
     bool found = false;
     for (const int (&tw)[2] : kTiles) {
         const int tile = tw[0], waves = tw[1];
-        if (!fits(tile)) continue;
+        if (!fits(tile) || (row_bytes > 0 && wave_panels_us(tile, M, N, row_bytes) >= most)) continue;
         const double tiles = std::ceil(M / tile) * std::ceil(N / tile);
         // a handful of tiles of a few steps each: waves without work
         if (tile == 32 && steps < kWavesPerTile && tiles < 16) return false;
@@ -675,9 +685,13 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
 bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
     if (!wave_exact(q.K, *cfg)) return false;
-    const double limit = wave_limit(pick_us, false);
+    // Long reductions: picks of 48 parts and more take 0.7 of their prediction, and operands beyond 64 MB are mispredicted more often.  At the
+    // margin of the others and without the time of the panels 466 of 5727 drawn products, most of K > 16384, were slower than their
+    // pick, by up to 132 % (105x236x466615: 283 us, waves 656); of 7786 drawn anew that still go there 66, two by more than 32 %
+    const bool strict = 4.0 * q.K * ((double)q.M + q.N) > 64e6 || (cfg->split_k >= 48 && q.K > 16384);
+    const double limit = std::min(wave_limit(pick_us, false), strict ? 0.66 * pick_us : pick_us);
     return wave_best(q.M, q.N, std::ceil(q.K / 16.0), WAVE_ROWS, 0, limit, limit, no_scratch, q.arena,
-                     [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg);
+                     [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg, 4.0 * q.K);
 }
 
 // bfloat16, q.C units of eight channels.  The margins are the staged model's: of 3000 drawn layers of 5e6 .. 6e10 flops the picks of 1x1 ones take

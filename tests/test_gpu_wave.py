@@ -425,3 +425,12 @@ def test_strided_layers_with_the_filter_copy_that_would_be_slower_stay(P, s):
 def test_bf16_layers_that_would_be_slower_stay(P, s):
     import torch
     stays(P, s, lambda x, w: P.conv2d_fwd_bf16(x.to(torch.bfloat16), w.to(torch.bfloat16), stride=s.stride, pad=s.pad))
+
+
+@pytest.mark.parametrize("M,N,K", [(105, 236, 466615), (326, 58, 380505), (256, 64, 400000), (69, 59, 388422)])
+def test_long_products_that_would_be_slower_stay(P, M, N, K):
+    import torch
+    P.sgemm(torch.zeros(M, K, device="cuda"), torch.zeros(K, N, device="cuda"), torch.zeros(M, N, device="cuda"))
+    torch.cuda.synchronize()
+    t = P.get_last_tile()
+    assert t.wm < t.bm, t
