@@ -704,6 +704,9 @@ bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, pol
 // 50 us, waves 63; 128 -> 64 3x3/2 on 56x56, batch 64: 20.4 and 23.0); with margins of their own 10 of 576, by up to 12 %.  Of 13716 layers drawn
 // anew that go there 63 are slower, eight by more than 10 and one by 20 %, half of them reductions of more than 100 steps in picks of
 // more than 15 us, where the waves take 0.74 of the time in the mean.
+// Wider ranges, 1 .. 4096 channels and 1 .. 224 pixels a side: up to five steps a row (8 -> 8 3x3) the pick takes 0.55 .. 0.7 of the model's
+// floor, and 117 of 1114 were slower on the waves, by up to 20 %, at 0.8 of it; 1x1 layers of more than 15 us and operands beyond 64 MB
+// take the waves up to 2.5 times what they are predicted (20 of 284, 56 of 451 slower, by up to 22 and 70 %).
 static WaveLoads wave_bf16_loads(const ConvProblem &q)
 {
     const bool strided = q.stride > 1;
@@ -716,13 +719,15 @@ bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, 
     if (units <= 8) return false;
     const double steps = std::ceil(units / 4.0);
     const bool unsplit = cfg->split_k <= 1;
-    const double margin = q.R == 1 && q.S == 1 ? 0.72
-                          : steps < 20         ? (q.K <= 32 ? 0.76 : 0.8)
-                          : steps > 256        ? 0.88
-                          : !unsplit           ? 0.92
-                          : q.stride == 1      ? 0.89
-                          : pick_us > 40       ? 0.88
-                                               : steps <= 48 && pick_us > 18 ? 0.84 : 0.92;
+    double margin = q.R == 1 && q.S == 1 ? (pick_us > 15 ? 0.65 : 0.72)
+                    : steps < 6          ? 0.6
+                    : steps < 20         ? (q.K <= 32 ? 0.76 : 0.8)
+                    : steps > 256        ? 0.88
+                    : !unsplit           ? 0.92
+                    : q.stride == 1      ? 0.89
+                    : pick_us > 40       ? 0.88
+                                         : steps <= 48 && pick_us > 18 ? 0.84 : 0.92;
+    if (pick_us > 20 && 16.0 * ((double)q.N * q.C * q.H * q.W + (double)units * q.K) > 64e6) margin = std::min(margin, 0.72);
     const double limit = margin * pick_us;
     return wave_best(q.K, (double)q.N * q.P * q.Q, steps, wave_bf16_loads(q), 0, limit, pick_us < 9.5 ? 0.73 * pick_us : limit, no_scratch,
                      q.arena, [&](int tile) { return conv_wave_bf16_fits(q, tile); }, cfg);

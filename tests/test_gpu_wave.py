@@ -420,7 +420,9 @@ def test_strided_layers_with_the_filter_copy_that_would_be_slower_stay(P, s):
 
 
 @pytest.mark.parametrize("s", [synth.ConvShape("strided_26", 36, 803, 28, 28, 256, 3, 3, 2, 1), synth.ConvShape("strided_short_13", 64, 128, 56, 56, 64, 3, 3, 2, 1),
-                               synth.ConvShape("few_channels_17", 14, 128, 56, 56, 17, 3, 3, 1, 1), synth.ConvShape("few_steps_13", 64, 16, 14, 23, 29, 3, 3, 1, 1)],
+                               synth.ConvShape("few_channels_17", 14, 128, 56, 56, 17, 3, 3, 1, 1), synth.ConvShape("few_steps_13", 64, 16, 14, 23, 29, 3, 3, 1, 1),
+                               synth.ConvShape("five_steps_20", 49, 10, 8, 43, 2, 3, 3, 1, 1), synth.ConvShape("three_steps_16", 12, 5, 63, 26, 2, 3, 3, 1, 1),
+                               synth.ConvShape("large_70", 28, 1669, 30, 110, 28, 3, 3, 1, 1), synth.ConvShape("1x1_22", 109, 2352, 17, 20, 68, 1, 1, 1, 0)],
                          ids=lambda s: s.name)
 def test_bf16_layers_that_would_be_slower_stay(P, s):
     import torch
