@@ -674,11 +674,21 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
     // up to 64 channels in the KCRS order: the gather kernel's 64x128 tiles take 0.75 .. 0.82 of their prediction (1019 -> 64 3x3 on 28x28, batch
     // 32: 212 us; waves 230).  74 of 987 such layers were slower on the waves, by up to 10 %; 7 of the 672 that still go there, by up to 9 %
     if (layout == 0 && q.R * q.S > 1 && q.K <= 64 && cfg->algo == 0 && cfg->bn == 128) limit = std::min(limit, 0.76 * pick_us);
-    // strided layers tap by tap: a wave's loads spread over twice the cache lines, and the waves of a tile over more of them than a staged tile
-    // does; up to 64 channels of one that reads many take up to 2.5 times what they are predicted (512 -> 64 7x7 on 14x18, batch 64: 112 us, waves
-    // 214; 3x3 on 56x20: 144 and 187)
-    if (layout == 2 && q.stride > 1)
-        limit = std::min(limit, (q.K > 64 || pick_us <= 20 ? 0.77 : q.C >= 384 ? 0.64 : pick_us > 60 ? 0.73 : 0.77) * pick_us);
+    // strided layers tap by tap: a wave's loads spread over twice the cache lines, and a tile's waves come back to a line a whole tap later,
+    // when many channels have passed and it is gone: up to 2.5 times what they are predicted, 10 times on inputs beyond the caches (512 -> 64 7x7
+    // on 14x18, batch 64: 112 us, waves 214; 3264 -> 23 4x4 on 21x9, batch 74: 148 and 422).  Of 126 layers of 384 channels and more on inputs
+    // beyond 16 MB 16 were slower than their pick, at 0.5 none of 25.  Operands beyond 64 MB are off for every stride
+    const double in_bytes = 4.0 * q.N * q.C * q.H * q.W, operands = in_bytes + 4.0 * q.K * Kg;
+    if (layout == 2) {
+        const bool deep = q.C >= 384;
+        const double margin = q.stride == 1                  ? (operands > 64e6 ? 0.7 : 1)
+                              : deep && in_bytes > 16e6      ? 0.5
+                              : operands > 64e6              ? 0.62
+                              : q.K > 64 || pick_us <= 20    ? 0.77
+                              : deep                         ? 0.64
+                                                             : pick_us > 60 ? 0.73 : 0.77;
+        limit = std::min(limit, margin * pick_us);
+    }
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
 }

@@ -414,7 +414,9 @@ def test_layers_of_few_channels_that_would_be_slower_stay(P, s):
 
 @pytest.mark.parametrize("s", [synth.ConvShape("few_channels_29", 64, 512, 56, 20, 64, 3, 3, 2, 1), synth.ConvShape("few_channels_7x7_91", 64, 512, 14, 18, 64, 7, 7, 2, 3),
                                synth.ConvShape("few_channels_one_part_12", 32, 512, 47, 47, 32, 3, 3, 2, 1),
-                               synth.ConvShape("many_channels_12", 32, 256, 28, 16, 256, 3, 3, 2, 1)], ids=lambda s: s.name)
+                               synth.ConvShape("many_channels_12", 32, 256, 28, 16, 256, 3, 3, 2, 1),
+                               synth.ConvShape("large_66", 17, 3856, 51, 9, 102, 5, 5, 2, 0), synth.ConvShape("large_186", 74, 3264, 21, 9, 23, 4, 4, 2, 0)],
+                         ids=lambda s: s.name)
 def test_strided_layers_with_the_filter_copy_that_would_be_slower_stay(P, s):
     stays(P, s, lambda x, w: P.conv2d_fwd(x, w, stride=s.stride, pad=s.pad, w_tap=P.filter_tap_copy(w)))
 
