@@ -71,12 +71,11 @@ typedef enum polydl_act { POLYDL_ACT_NONE = 0, POLYDL_ACT_RELU = 1, POLYDL_ACT_R
 typedef struct polydl_tile_cfg {
     int bm, bn, bk;   /* workgroup tile: bm x bn outputs, bk reduction elements per stage      */
     int wm, wn;       /* wave tile (multiples of 32); the workgroup has (bm/wm)*(bn/wn) waves.
-                         64x64x16 with wave tile 64x64 and 32x32x16 with 32x32 (SGEMM and algo 0,
-                         raster 1; filters of at most 63 taps) are the tiles of small problems: the
-                         eight waves of a workgroup (64x64x16 with raster 0: four)
-                         share a tile's reduction and meet in LDS.  They
-                         are not enumerated and not ranked: unless a variant is forced they take the
-                         place of a pick where they are predicted to be well below it              */
+                         A wave tile as large as the tile, 64x64x16 or 32x32x16 with raster 1 (SGEMM and
+                         algo 0; filters of at most 63 taps; bfloat16 too), is a tile of small problems:
+                         the eight waves of a workgroup (64x64x16 with raster 0: four) share its reduction
+                         and meet in LDS.  Not enumerated and not ranked: unless a variant is forced
+                         they take the place of a pick where they are predicted to be well below it    */
     int split_k;      /* >= 1: the reduction is cut into this many parts (one workgroup each);  */
     int layout;       /* 0: read NCHW / KCRS directly; 1: via blocked NCHWc / KCRSck copies;
                          2: gather kernel reading the filter's [K][R][S][C] copy, reduction walked
@@ -259,7 +258,9 @@ int polydl_activation(int64_t count, float *y, int act, void *stream);
  *   sum_i levels[i]*weights[i] + mem*mem_weight.  Lower is better.
  * polydl_model_conv2d / polydl_model_sgemm: the model's report for one variant of one problem.
  * polydl_pick_conv2d / polydl_pick_sgemm: the variant with the lowest predicted time over the
- *   compiled family (what polydl_conv2d_fwd / polydl_sgemm use when no override is set).
+ *   enumerated family.  polydl_conv2d_fwd / polydl_sgemm use it when no override is set, except where
+ *   the first-layer kernel or a tile of small problems takes its place (polydl_tile_cfg: algo 3, wm);
+ *   polydl_get_last_tile tells which variant ran.
  * The report holds the working sets of the variant's reuses in bytes (accumulator tile, LDS stage,
  * one column-tile step, the workgroups resident on one XCD, the whole problem), the level each was
  * placed in by algorithm "Compute working set sizes w.r.t cache sizes" over (accumulator registers,
@@ -331,10 +332,11 @@ int polydl_model_sgemm(int M, int N, int K, const polydl_tile_cfg *cfg, polydl_m
 int polydl_pick_conv2d(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                        polydl_tile_cfg *cfg, polydl_model_report *report);
 int polydl_pick_sgemm(int M, int N, int K, polydl_tile_cfg *cfg, polydl_model_report *report);
-/* The same two for the bfloat16 convolution (C counts channels; cfg is an algo 1 variant with its
- * cb and split_k set): the predicted time in microseconds of one variant, and the variant
- * polydl_conv2d_fwd_bf16_blocked uses when no override is set.  predicted_us may be NULL in the
- * pick.  POLYDL_ERR_UNSUPPORTED for a variant that is not compiled or cannot hold the problem. */
+/* The same two for the bfloat16 convolution (C counts channels): the predicted time in microseconds of
+ * one variant (algo 1 with its cb and split_k set, or a tile of small problems with its split_k), and the
+ * algo 1 variant with the lowest, which polydl_conv2d_fwd_bf16_blocked uses when no override is set and
+ * no tile of small problems takes its place.  predicted_us may be NULL in the pick.
+ * POLYDL_ERR_UNSUPPORTED for a variant that is not compiled or cannot hold the problem. */
 int polydl_model_conv2d_bf16(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                              const polydl_tile_cfg *cfg, double *predicted_us);
 int polydl_pick_conv2d_bf16(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
@@ -390,7 +392,7 @@ int polydl_pick_conv2d_learned(int N, int C, int H, int W, int K, int R, int S, 
 /* ---- variant control (the sweep forces a variant; reports read back the one used) -----------
  * polydl_set_tile_override: cfg != NULL forces that variant for every later call of the
  * calling process (POLYDL_ERR_UNSUPPORTED if it is not a compiled variant; a later problem it
- * cannot serve returns POLYDL_ERR_UNSUPPORTED); cfg == NULL returns to the reuse-model pick.
+ * cannot serve returns POLYDL_ERR_UNSUPPORTED); cfg == NULL returns to the library's choice.
  * polydl_get_last_tile: the variant the most recent successful conv/sgemm call launched.
  * polydl_num_variants / polydl_get_variant: enumerate the compiled family
  * (kind 0 = convolution, 1 = sgemm, 2 = bfloat16 convolution). */
