@@ -657,11 +657,18 @@ static bool wave_best(double M, double N, double steps, WaveLoads loads, int lay
 // tiles that split the reduction are the more exact up to 160 (144 in three parts: by 3 %; 192: the waves by 1 %).
 static bool wave_exact(int64_t Kg, const polydl_tile_cfg &pick) { return Kg >= (pick.split_k > 1 ? 192 : 112); }
 static double wave_limit(double pick_us, bool short_rows) { return pick_us * (short_rows ? 0.6 : pick_us <= 40 ? 0.9 : 0.83); }
+// Cache lines under the values of one reduction row that 64 neighbouring pixels of the output read, unpadded.
+static double row_lines(const ConvProblem &q)
+{
+    const double PQ = (double)q.P * q.Q, pixels = std::min(64.0, q.N * PQ);
+    return std::min(pixels / q.Q * (1 + q.Q * q.stride / 32.0), std::max(1.0, pixels / PQ) * (1 + (double)q.H * q.W / 32));
+}
 // Unsplit picks of 1x1 layers on the gather kernel are predicted too high: they take 0.76 of it at 128 rows, 0.86 at 500, on the fp32
 // instruction 0.72 .. 0.8, strided ones into at most 64 channels down to 0.58, and there the waves' tiles, one row of them, take up to 1.5 times
 // what they are predicted.  With the margins of other layers 42 of 74 strided ones into up to 64 channels were slower than their pick, by up to 31 %
 // (128 -> 64 on 56x45, batch 32: 13.1 us against 10.2), 40 of 183 into more, by up to 13 %, and 10 of 14 unstrided ones of 128 rows into
-// up to 64, by up to 17 %; with these one of the 393 that still go there, by 6 %.
+// up to 64, by up to 17 %; with 0.8 and 0.86 one of the 393 that still
+// went there, by 6 %, and, drawn anew, 11 of 91 unstrided ones above 0.84.
 bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S;
@@ -670,7 +677,7 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
     if (point_pick && q.stride > 1 && q.K <= 64) return false;
     const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
     double limit = wave_limit(pick_us, Kg < kSplitMinReduction || (point_pick && !split_pays(q.K, 1, Kg)));
-    if (point_pick) limit = std::min(limit, (q.stride > 1 ? 0.8 : 0.86) * pick_us);
+    if (point_pick) limit = std::min(limit, (q.stride > 1 ? 0.8 : 0.84) * pick_us);
     // up to 64 channels in the KCRS order: the gather kernel's 64x128 tiles take 0.75 .. 0.82 of their prediction (1019 -> 64 3x3 on 28x28, batch
     // 32: 212 us; waves 230).  74 of 987 such layers were slower on the waves, by up to 10 %; 7 of the 672 that still go there, by up to 9 %
     if (layout == 0 && q.R * q.S > 1 && q.K <= 64 && cfg->algo == 0 && cfg->bn == 128) limit = std::min(limit, 0.76 * pick_us);
@@ -689,7 +696,21 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
                                                              : pick_us > 60 ? 0.73 : 0.77;
         limit = std::min(limit, margin * pick_us);
     }
-    return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit, no_scratch, q.arena,
+    double limit64 = pick_us;
+    if (q.R == 1 && q.S == 1 && q.pad == 0) {
+        // 13423 drawn 1x1 layers on the waves, 191 slower than their pick.  Strided ones whose pick splits gain nothing on tiles of 64x64 (454:
+        // 0.96 of the time in the mean, 76 slower, 3925 -> 1313 /2 on 2x2, batch 99, 38 us and 56; on 32x32 tiles 0.70, 25 of 6140 slower), those on
+        // inputs beyond the caches little (342: 0.83, 59 slower) and at stride 3 nothing; loads over many lines, and any input beyond 256 MB, cost up to
+        // 1.4 times what they are predicted.  With these margins 16 of 15567 drawn anew are slower, by up to 19 %
+        if (q.stride > 1 && cfg->split_k > 1) limit64 = 0.6 * pick_us;
+        if (q.stride > 1 && in_bytes > (cfg->split_k > 1 ? 64e6 : 32e6)) {
+            if (q.stride > 2 && cfg->split_k <= 1) return false;
+            limit = std::min(limit, 0.7 * pick_us);
+        }
+        if (row_lines(q) > 12) limit = std::min(limit, 0.75 * pick_us);
+        if (in_bytes > 256e6) limit = std::min(limit, 0.7 * pick_us);
+    }
+    return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit64, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
 }
 bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
