@@ -709,6 +709,17 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
         }
         if (row_lines(q) > 12) limit = std::min(limit, 0.75 * pick_us);
         if (in_bytes > 256e6) limit = std::min(limit, 0.7 * pick_us);
+    } else {
+        // Loads over many lines, and outputs far smaller than their input: the waves take up to three times what they are predicted, tap by tap
+        // more.  In the KCRS order 190 of 25857 drawn layers were slower than their pick, by up to 47 % (701 -> 1438 4x3 unpadded on 4x4, batch 85:
+        // 72 us, waves 99), with the copy 255 of 27543, by up to 85 % (1264 -> 1790 7x7 on 8x8, batch 7: 200 and 332); with these margins
+        // 30 of 14412 and 60 of 14629 drawn anew
+        const double PQ = (double)q.P * q.Q, HW = (double)q.H * q.W;
+        double margin = 1;
+        if (row_lines(q) >= (layout == 2 ? 16 : 23) || (q.stride == 1 && HW >= 4 * PQ)) margin = layout == 0 ? 0.66 : q.R * q.S >= 25 ? 0.45 : 0.6;
+        else if (HW > 3.1 * PQ) margin = layout == 0 ? 0.8 : 0.75;
+        if (layout == 0 && in_bytes > 256e6) margin = std::min(margin, 0.68);
+        limit = std::min(limit, margin * pick_us);
     }
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit64, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);

@@ -410,6 +410,18 @@ def test_1x1_layers_that_would_be_slower_stay(P, s):
     stays(P, s, lambda x, w: P.conv2d_fwd_noalloc(x, w, None, torch.empty((s.N, s.K) + tuple(synth.out_hw(s)), device="cuda"), **kw))
 
 
+# loads over many cache lines, outputs far smaller than their input; percent more time in the KCRS order, with the filter's copy
+@pytest.mark.parametrize("s", [synth.ConvShape("37_58", 85, 688, 4, 4, 1438, 4, 3, 1, 0), synth.ConvShape("17_15", 95, 512, 7, 7, 512, 3, 3, 3, 0),
+                               synth.ConvShape("32_31", 103, 512, 7, 7, 128, 4, 4, 2, 0), synth.ConvShape("21_21", 101, 128, 7, 7, 256, 4, 4, 2, 0)],
+                         ids=lambda s: s.name)
+def test_scattered_layers_that_would_be_slower_stay(P, s):
+    import torch
+    kw = dict(stride=s.stride, pad=s.pad)
+    stays(P, s, lambda x, w: P.conv2d_fwd(x, w, **kw))
+    stays(P, s, lambda x, w: P.conv2d_fwd(x, w, w_tap=P.filter_tap_copy(w), **kw))
+    stays(P, s, lambda x, w: P.conv2d_fwd_noalloc(x, w, None, torch.empty((s.N, s.K) + tuple(synth.out_hw(s)), device="cuda"), **kw))
+
+
 @pytest.mark.parametrize("s", [synth.ConvShape("3x3_9", 32, 1019, 28, 28, 64, 3, 3, 1, 1), synth.ConvShape("5x5_8", 32, 256, 56, 14, 64, 5, 5, 1, 2),
                                synth.ConvShape("7x7_leftover_10", 32, 39, 87, 63, 35, 7, 7, 1, 3)], ids=lambda s: s.name)
 def test_layers_of_few_channels_that_would_be_slower_stay(P, s):
