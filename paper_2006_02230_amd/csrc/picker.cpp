@@ -748,7 +748,11 @@ bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, pol
 // more than 15 us, where the waves take 0.74 of the time in the mean.
 // Wider ranges, 1 .. 4096 channels and 1 .. 224 pixels a side: up to five steps a row (8 -> 8 3x3) the pick takes 0.55 .. 0.7 of the model's
 // floor, and 117 of 1114 were slower on the waves, by up to 20 %, at 0.8 of it; 1x1 layers of more than 15 us and operands beyond 64 MB
-// take the waves up to 2.5 times what they are predicted (20 of 284, 56 of 451 slower, by up to 22 and 70 %).
+// take the waves up to 2.5 times what they are predicted (20 of 284, 56 of 451 slower, by up to 22 and 70 %).  Two and three steps a row
+// above 0.52 are even (291 of 906 layers: 0.95 of the time, 71 slower, by up to 12 %), strided layers with filters beyond 20 MB above 0.7
+// mispredicted (227 of 417: 36 slower, by up to 87 %, 2513 -> 743 3x3/3 on 100x3, batch 18, 53 us and 98).
+// Strided 1x1 layers of up to five steps on inputs beyond 16 MB are even (93: 0.955, 16 slower, by up to 30 %), other 1x1 ones of more than
+// 15 us above 0.6 nearly so (157: 0.87, 23 slower, by up to 25 %).
 static WaveLoads wave_bf16_loads(const ConvProblem &q)
 {
     const bool strided = q.stride > 1;
@@ -760,16 +764,20 @@ bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, 
     const int64_t units = (int64_t)q.C * q.R * q.S;
     if (units <= 8) return false;
     const double steps = std::ceil(units / 4.0);
-    const bool unsplit = cfg->split_k <= 1;
-    double margin = q.R == 1 && q.S == 1 ? (pick_us > 15 ? 0.65 : 0.72)
-                    : steps < 6          ? 0.6
-                    : steps < 20         ? (q.K <= 32 ? 0.76 : 0.8)
-                    : steps > 256        ? 0.88
-                    : !unsplit           ? 0.92
-                    : q.stride == 1      ? 0.89
-                    : pick_us > 40       ? 0.88
-                                         : steps <= 48 && pick_us > 18 ? 0.84 : 0.92;
-    if (pick_us > 20 && 16.0 * ((double)q.N * q.C * q.H * q.W + (double)units * q.K) > 64e6) margin = std::min(margin, 0.72);
+    const bool unsplit = cfg->split_k <= 1, point = q.R == 1 && q.S == 1, strided = q.stride > 1;
+    const double in_bytes = 16.0 * q.N * q.C * q.H * q.W, filter_bytes = 16.0 * units * q.K;
+    double margin = point           ? (pick_us > 15 ? 0.6 : 0.72)
+                    : steps < 4     ? 0.52
+                    : steps < 6     ? 0.6
+                    : steps < 20    ? (q.K <= 32 ? 0.76 : 0.8)
+                    : steps > 256   ? 0.88
+                    : !unsplit      ? 0.92
+                    : q.stride == 1 ? 0.89
+                    : pick_us > 40  ? 0.88
+                                    : steps <= 48 && pick_us > 18 ? 0.84 : 0.92;
+    if (strided && !point && filter_bytes > 20e6) margin = std::min(margin, 0.7);
+    if (strided && point && unsplit && steps <= 5 && in_bytes > 16e6) margin = 0.4;
+    if (pick_us > 20 && in_bytes + filter_bytes > 64e6) margin = std::min(margin, 0.72);
     const double limit = margin * pick_us;
     return wave_best(q.K, (double)q.N * q.P * q.Q, steps, wave_bf16_loads(q), 0, limit, pick_us < 9.5 ? 0.73 * pick_us : limit, no_scratch,
                      q.arena, [&](int tile) { return conv_wave_bf16_fits(q, tile); }, cfg);

@@ -440,7 +440,10 @@ def test_strided_layers_with_the_filter_copy_that_would_be_slower_stay(P, s):
 @pytest.mark.parametrize("s", [synth.ConvShape("strided_26", 36, 803, 28, 28, 256, 3, 3, 2, 1), synth.ConvShape("strided_short_13", 64, 128, 56, 56, 64, 3, 3, 2, 1),
                                synth.ConvShape("few_channels_17", 14, 128, 56, 56, 17, 3, 3, 1, 1), synth.ConvShape("few_steps_13", 64, 16, 14, 23, 29, 3, 3, 1, 1),
                                synth.ConvShape("five_steps_20", 49, 10, 8, 43, 2, 3, 3, 1, 1), synth.ConvShape("three_steps_16", 12, 5, 63, 26, 2, 3, 3, 1, 1),
-                               synth.ConvShape("large_70", 28, 1669, 30, 110, 28, 3, 3, 1, 1), synth.ConvShape("1x1_22", 109, 2352, 17, 20, 68, 1, 1, 1, 0)],
+                               synth.ConvShape("large_70", 28, 1669, 30, 110, 28, 3, 3, 1, 1), synth.ConvShape("1x1_22", 109, 2352, 17, 20, 68, 1, 1, 1, 0),
+                               synth.ConvShape("large_filter_87", 18, 2513, 100, 3, 743, 3, 3, 3, 0), synth.ConvShape("large_filter_75", 19, 3217, 100, 3, 367, 3, 3, 3, 0),
+                               synth.ConvShape("1x1_strided_30", 105, 94, 173, 19, 34, 1, 1, 3, 0), synth.ConvShape("1x1_long_24", 58, 3077, 34, 18, 176, 1, 1, 1, 0),
+                               synth.ConvShape("three_steps_10", 3, 7, 32, 32, 142, 3, 3, 1, 1), synth.ConvShape("three_steps_11", 126, 1, 20, 2, 64, 3, 3, 1, 1)],
                          ids=lambda s: s.name)
 def test_bf16_layers_that_would_be_slower_stay(P, s):
     import torch
