@@ -648,9 +648,11 @@ static bool wave_best(double M, double N, double steps, WaveLoads loads, int lay
     return found;
 }
 
-// Whether a small problem goes to single waves, given its pick's prediction: a margin for what the two predictions are off.  Of 2700
-// drawn problems of 2e6 .. 3e10 flops about 2000 go there, the time of all falls by a factor of 1.31 in the mean (1.34 with the best choice
-// for each), and about ten were more than 3 % slower, by up to 13 %.  Picks of more than 40 us gain little and are mispredicted more often.  Convolutions of
+// Whether a small problem goes to single waves, given its pick's prediction: a margin for what the two predictions are off, and further down lower
+// ones where one of them is further off.  Drawn over 1 .. 4096 channels, 1 .. 224 pixels a side, batches of 1 .. 128 and 2e6 .. 4e10 flops, 12505 of
+// 22675 layers in the KCRS order go there and take 0.70 of the pick's time in sum, 57 of them more than 3 % longer; with the filter's copy 13006 of
+// 23808, 0.70, 85; 1x1 layers 13759 of 46613, 0.69, 33; products of up to 8192 x 8192 x 200000 14051 of 18919, 0.59, 14.
+// Picks of more than 40 us gain little and are mispredicted more often.  Convolutions of
 // fewer than 128 reduction rows run on the fp32 instruction otherwise and are predicted too high, by up to 1.6.
 // Reductions of fewer steps than there are waves have a rounding per step and those of the meeting, which a staged tile sums in one accumulator:
 // against 64 bits they are further off, products of 32, 40, 64, 96 by 14, 22, 8, 2 %; from 112 on nearer (128: 5 %, 256: 5 .. 26 %).  Staged
@@ -696,30 +698,22 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
                                                              : pick_us > 60 ? 0.73 : 0.77;
         limit = std::min(limit, margin * pick_us);
     }
+    // Loads that spread over many lines, and inputs beyond 256 MB, cost the waves up to three times what they are predicted.  In the KCRS order they
+    // are even from 23 lines on above 0.8 (87 drawn layers: 1.02 of the pick's time, 34 slower, by up to 38 %; 0.75 .. 0.8: 0.88, 14 of 123), large inputs
+    // above 0.7 (70: 0.97, 20 slower); with the copy from 16 lines on above 0.66 (634: 0.91, 83 slower, by up to 58 %)
+    const bool point = q.R == 1 && q.S == 1 && q.pad == 0;
+    const double lines = row_lines(q);
+    if (layout == 0 && lines >= 23) limit = std::min(limit, 0.75 * pick_us);
+    if (layout == 2 && lines >= 16) limit = std::min(limit, 0.66 * pick_us);
+    if (layout == 0 && in_bytes > 256e6) limit = std::min(limit, 0.7 * pick_us);
+    // Strided 1x1 layers whose pick splits gain nothing on tiles of 64x64 (454: 0.96, 76 slower; on 32x32 0.70, 25 of 6140), nor at all above 0.7
+    // on inputs beyond 64 MB (42: 1.0, 19 slower); unsplit ones on inputs beyond 32 MB not above 0.75, at stride 3 not above 0.4 (31: 0.98, 10 slower,
+    // and 106: 0.96, 42, by up to 26 %, 128 -> 128 on 68x68, batch 53, 18.4 us and 23.1)
     double limit64 = pick_us;
-    if (q.R == 1 && q.S == 1 && q.pad == 0) {
-        // 13423 drawn 1x1 layers on the waves, 191 slower than their pick.  Strided ones whose pick splits gain nothing on tiles of 64x64 (454:
-        // 0.96 of the time in the mean, 76 slower, 3925 -> 1313 /2 on 2x2, batch 99, 38 us and 56; on 32x32 tiles 0.70, 25 of 6140 slower), those on
-        // inputs beyond the caches little (342: 0.83, 59 slower) and at stride 3 nothing; loads over many lines, and any input beyond 256 MB, cost up to
-        // 1.4 times what they are predicted.  With these margins 16 of 15567 drawn anew are slower, by up to 19 %
-        if (q.stride > 1 && cfg->split_k > 1) limit64 = 0.6 * pick_us;
-        if (q.stride > 1 && in_bytes > (cfg->split_k > 1 ? 64e6 : 32e6)) {
-            if (q.stride > 2 && cfg->split_k <= 1) return false;
-            limit = std::min(limit, 0.7 * pick_us);
-        }
-        if (row_lines(q) > 12) limit = std::min(limit, 0.75 * pick_us);
-        if (in_bytes > 256e6) limit = std::min(limit, 0.7 * pick_us);
-    } else {
-        // Loads over many lines, and outputs far smaller than their input: the waves take up to three times what they are predicted, tap by tap
-        // more.  In the KCRS order 190 of 25857 drawn layers were slower than their pick, by up to 47 % (701 -> 1438 4x3 unpadded on 4x4, batch 85:
-        // 72 us, waves 99), with the copy 255 of 27543, by up to 85 % (1264 -> 1790 7x7 on 8x8, batch 7: 200 and 332); with these margins
-        // 30 of 14412 and 60 of 14629 drawn anew
-        const double PQ = (double)q.P * q.Q, HW = (double)q.H * q.W;
-        double margin = 1;
-        if (row_lines(q) >= (layout == 2 ? 16 : 23) || (q.stride == 1 && HW >= 4 * PQ)) margin = layout == 0 ? 0.66 : q.R * q.S >= 25 ? 0.45 : 0.6;
-        else if (HW > 3.1 * PQ) margin = layout == 0 ? 0.8 : 0.75;
-        if (layout == 0 && in_bytes > 256e6) margin = std::min(margin, 0.68);
-        limit = std::min(limit, margin * pick_us);
+    if (point && q.stride > 1) {
+        const bool split = cfg->split_k > 1;
+        if (split) limit64 = 0.6 * pick_us;
+        if (in_bytes > (split ? 64e6 : 32e6)) limit = std::min(limit, (split ? 0.7 : q.stride == 2 ? 0.75 : 0.4) * pick_us);
     }
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit64, no_scratch, q.arena,
                      [&](int tile) { return conv_wave_fits(q, tile); }, cfg);
@@ -737,22 +731,20 @@ bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, pol
 }
 
 // bfloat16, q.C units of eight channels.  The margins are the staged model's: of 3000 drawn layers of 5e6 .. 6e10 flops the picks of 1x1 ones take
-// 0.82 .. 0.92 of their prediction, of others 1.02 .. 1.17, but 0.8 where a reduction of up to 20 steps is one stage; beyond 256 steps both are off.  About
-// 1850 go there, the time of all falls by a factor of 1.33 (1.38 with the best choice for each), eleven were more than 3 % slower, by up to 8 %
-// (one margin of 0.88: 1.31, 45, 29 %).  Up to eight units a row leave most waves without a
+// 0.82 .. 0.92 of their prediction, of others 1.02 .. 1.17, but 0.8 where a reduction of up to 20 steps is one stage; beyond 256 steps both are off.  Over
+// the ranges above 16266 of 24958 layers go there and take 0.61 of the pick's time in sum, 74 of them more than 3 % longer; 1x1 layers 17088 of 38766,
+// 0.62, 27.  Up to eight units a row leave most waves without a
 // step; picks predicted at the floor of their model (8.8 us) take 5 us and more, which the larger tile does not undercut.
 // Picks that do not split take 0.8 .. 0.9 of their prediction at 36 steps (128 input channels 3x3), and strided layers of more than 40 us cost the
 // waves 1.2 .. 1.4 times theirs: at 0.92, 29 of 696 drawn ones were slower than their pick, by up to 26 % (803 -> 256 3x3/2 on 28x28, batch 36:
-// 50 us, waves 63; 128 -> 64 3x3/2 on 56x56, batch 64: 20.4 and 23.0); with margins of their own 10 of 576, by up to 12 %.  Of 13716 layers drawn
-// anew that go there 63 are slower, eight by more than 10 and one by 20 %, half of them reductions of more than 100 steps in picks of
-// more than 15 us, where the waves take 0.74 of the time in the mean.
-// Wider ranges, 1 .. 4096 channels and 1 .. 224 pixels a side: up to five steps a row (8 -> 8 3x3) the pick takes 0.55 .. 0.7 of the model's
+// 50 us, waves 63; 128 -> 64 3x3/2 on 56x56, batch 64: 20.4 and 23.0); with margins of their own 10 of 576, by up to 12 %.
+// Up to five steps a row (8 -> 8 3x3) the pick takes 0.55 .. 0.7 of the model's
 // floor, and 117 of 1114 were slower on the waves, by up to 20 %, at 0.8 of it; 1x1 layers of more than 15 us and operands beyond 64 MB
 // take the waves up to 2.5 times what they are predicted (20 of 284, 56 of 451 slower, by up to 22 and 70 %).  Two and three steps a row
 // above 0.52 are even (291 of 906 layers: 0.95 of the time, 71 slower, by up to 12 %), strided layers with filters beyond 20 MB above 0.7
 // mispredicted (227 of 417: 36 slower, by up to 87 %, 2513 -> 743 3x3/3 on 100x3, batch 18, 53 us and 98).
-// Strided 1x1 layers of up to five steps on inputs beyond 16 MB are even (93: 0.955, 16 slower, by up to 30 %), other 1x1 ones of more than
-// 15 us above 0.6 nearly so (157: 0.87, 23 slower, by up to 25 %).
+// Strided 1x1 layers of up to five steps on inputs beyond 16 MB are even (93: 0.955, 16 slower, by up to 30 %), 1x1 ones of more than 15 us and
+// 64 steps above 0.6 nearly so (51: 0.93, 13 slower, by up to 24 %).
 static WaveLoads wave_bf16_loads(const ConvProblem &q)
 {
     const bool strided = q.stride > 1;
@@ -766,7 +758,7 @@ bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, 
     const double steps = std::ceil(units / 4.0);
     const bool unsplit = cfg->split_k <= 1, point = q.R == 1 && q.S == 1, strided = q.stride > 1;
     const double in_bytes = 16.0 * q.N * q.C * q.H * q.W, filter_bytes = 16.0 * units * q.K;
-    double margin = point           ? (pick_us > 15 ? 0.6 : 0.72)
+    double margin = point           ? (pick_us <= 15 ? 0.72 : units > 256 ? 0.6 : 0.65)
                     : steps < 4     ? 0.52
                     : steps < 6     ? 0.6
                     : steps < 20    ? (q.K <= 32 ? 0.76 : 0.8)
