@@ -559,7 +559,7 @@ def main():
                             "peak": round(bf_flops / (ideal_ms * 1e-3) / 1e12, 1), "unit": "TFLOP/s",
                             "frac": round(ideal_ms / bf_ms, 4),
                             "note": "peak = suite flops / sum over layers of flops / min(2500 TFLOP/s, AI * 8 TB/s)"},
-                  workload="configs[4]: the same eight layers, bf16 inputs in NCHW8c / KCRS8c, fp32 accumulate "
+                  workload="the same eight layers, bf16 inputs in NCHW8c / KCRS8c, fp32 accumulate "
                            "and output, N=64, bias+ReLU fused",
                   tflops=round(tf, 2), frac_of_bf16_mfma_peak=round(tf / BF16_MFMA_PEAK_TFLOPS, 4),
                   us_per_pass=round(bf_ms * 1e3, 1), layout_transform_us_per_pass=round(tr_ms * 1e3, 1),
@@ -590,7 +590,7 @@ def main():
             samples["c"].append(time_calls(torch, conv_only, 20, batches=1))
         t_f, t_s, t_c = (sorted(samples[k])[2] for k in ("f", "s", "c"))
         ob = 4.0 * s.N * s.K * Pq * Qq
-        fusion = dict(workload="configs[3]: conv+bias+ReLU, N=%d C=K=%d %dx%d 3x3" % (s.N, s.C, s.H, s.W),
+        fusion = dict(workload="conv+bias+ReLU, N=%d C=K=%d %dx%d 3x3" % (s.N, s.C, s.H, s.W),
                       fused_us=round(t_f * 1e3, 2), separate_us=round(t_s * 1e3, 2), conv_only_us=round(t_c * 1e3, 2),
                       speedup=round(t_s / t_f, 3),
                       output_bytes=ob, algorithmic_bytes_saved=4 * ob,
@@ -717,7 +717,7 @@ def main():
         fn()
         ms = time_calls(torch, fn, 200)
         fl = conv_flops(s, Pq, Qq)
-        cfg1 = dict(workload="configs[0]: N=1 C=K=64 56x56 3x3 s1 p1, no bias, U[-1,1), seed 0",
+        cfg1 = dict(workload="N=1 C=K=64 56x56 3x3 s1 p1, no bias, U[-1,1), seed 0",
                     us=round(ms * 1e3, 2), tflops=round(fl / (ms * 1e-3) / 1e12, 2),
                     frac_mfma=round(fl / (ms * 1e-3) / 1e12 / products_peak(P.get_last_tile(), 64 * 9), 4),
                     mfma_time_at_peak_us=round(fl / (products_peak(P.get_last_tile(), 64 * 9) * 1e12) * 1e6, 2),
@@ -772,7 +772,7 @@ def main():
         "value": round(value, 3), "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
-        "config": {"workload": ("configs[2]: ResNet-50-shaped conv suite, fp32 NCHW, N=%d, layers %s, "
+        "config": {"workload": ("ResNet-50-shaped conv suite, fp32 NCHW, N=%d, layers %s, "
                                 "in N(0,1), wt N(0,2/(CRS)), bias U[-0.1,0.1), ReLU"
                                 % (args.batch, "0-7 (all eight)" if len(chosen) == 8 else str(chosen)))
                                if args.suite == "resnet" else
