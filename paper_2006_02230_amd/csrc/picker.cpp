@@ -615,17 +615,18 @@ static double wave_panels_us(int tile, double M, double N, double row_bytes)
     const double once = M + N, all = std::min(8.0, tm * tn) * (rows * M / tm + std::ceil(run / rows) * N / tn);
     return (once / 5.0e6 + std::max(0.0, all - once) / 4.5e6) * row_bytes;
 }
-// The best of the tiles and 1 .. 16 parts, if it is predicted below `limit`, for tiles of 64x64 `limit64`.  row_bytes: of products, 0 for convolutions.
+// The best of the tiles and 1 .. 16 parts, if it is predicted below `limit`, for tiles of 64x64 `limit64`.  row_bytes: of products,
+// 0 for convolutions; a product's panels have to be predicted below panels_limit.
 template <class Fits>
 static bool wave_best(double M, double N, double steps, WaveLoads loads, int layout, double limit, double limit64, bool no_scratch, const ScratchArena *arena,
-                      Fits &&fits, polydl_tile_cfg *cfg, double row_bytes = 0)
+                      Fits &&fits, polydl_tile_cfg *cfg, double row_bytes = 0, double panels_limit = 0)
 {
     static const int kParts[] = {1, 2, 3, 4, 6, 8, 12, 16}, kTiles[][2] = {{32, 8}, {64, 8}, {64, 4}};
-    const double cus = kCUs, most = limit;
+    const double cus = kCUs;
     bool found = false;
     for (const int (&tw)[2] : kTiles) {
         const int tile = tw[0], waves = tw[1];
-        if (!fits(tile) || (row_bytes > 0 && wave_panels_us(tile, M, N, row_bytes) >= most)) continue;
+        if (!fits(tile) || (row_bytes > 0 && wave_panels_us(tile, M, N, row_bytes) >= panels_limit)) continue;
         const double tiles = std::ceil(M / tile) * std::ceil(N / tile);
         // a handful of tiles of a few steps each: waves without work
         if (tile == 32 && steps < kWavesPerTile && tiles < 16) return false;
@@ -649,9 +650,10 @@ static bool wave_best(double M, double N, double steps, WaveLoads loads, int lay
 }
 
 // Whether a small problem goes to single waves, given its pick's prediction: a margin for what the two predictions are off, and further down lower
-// ones where one of them is further off.  Drawn over 1 .. 4096 channels, 1 .. 224 pixels a side, batches of 1 .. 128 and 2e6 .. 4e10 flops, 12505 of
-// 22675 layers in the KCRS order go there and take 0.70 of the pick's time in sum, 57 of them more than 3 % longer; with the filter's copy 13006 of
-// 23808, 0.70, 85; 1x1 layers 13759 of 46613, 0.69, 33; products of up to 8192 x 8192 x 200000 14051 of 18919, 0.59, 14.
+// ones where one of them is further off.  Drawn over 1 .. 4096 channels, 1 .. 224 pixels a side, batches of 1 .. 128 and 2e6 .. 4e10 flops, 12351 of
+// 22501 layers in the KCRS order go there and take 0.70 of the pick's time in sum, 70 of them more than 3 % longer; with the filter's copy 12539 of
+// 22480, 0.72, 110; 1x1 layers 13260 of 44326, 0.71, 82; products of up to 8192 x 8192 x 200000 14217 of 19353, 0.60, 29.  The lower margins lie where
+// the mean of a class comes to the pick's time, or where many of it take much longer.
 // Picks of more than 40 us gain little and are mispredicted more often.  Convolutions of
 // fewer than 128 reduction rows run on the fp32 instruction otherwise and are predicted too high, by up to 1.6.
 // Reductions of fewer steps than there are waves have a rounding per step and those of the meeting, which a staged tile sums in one accumulator:
@@ -669,50 +671,45 @@ static double row_lines(const ConvProblem &q)
 // instruction 0.72 .. 0.8, strided ones into at most 64 channels down to 0.58, and there the waves' tiles, one row of them, take up to 1.5 times
 // what they are predicted.  With the margins of other layers 42 of 74 strided ones into up to 64 channels were slower than their pick, by up to 31 %
 // (128 -> 64 on 56x45, batch 32: 13.1 us against 10.2), 40 of 183 into more, by up to 13 %, and 10 of 14 unstrided ones of 128 rows into
-// up to 64, by up to 17 %; with 0.8 and 0.86 one of the 393 that still
-// went there, by 6 %, and, drawn anew, 11 of 91 unstrided ones above 0.84.
+// up to 64, by up to 17 %; the three margins lie where layers drawn anew
+// come to the pick's time: strided ones into up to 64 above 0.5 (1300: 1.02), others above 0.8 (2130: 1.02), unstrided ones above 0.85 (1936: 0.99).
 bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
     const int64_t Kg = (int64_t)q.C * q.R * q.S;
     if (!wave_exact(Kg, *cfg)) return false;
     const bool point_pick = cfg->algo == 0 && cfg->split_k <= 1 && q.R == 1 && q.S == 1 && q.pad == 0;
-    if (point_pick && q.stride > 1 && q.K <= 64) return false;
     const int layout = q.has_tap && gather_tap_major_fits(q, 16) ? 2 : 0;
     double limit = wave_limit(pick_us, Kg < kSplitMinReduction || (point_pick && !split_pays(q.K, 1, Kg)));
-    if (point_pick) limit = std::min(limit, (q.stride > 1 ? 0.8 : 0.84) * pick_us);
+    if (point_pick) limit = std::min(limit, (q.stride == 1 ? 0.84 : q.K > 64 ? 0.8 : 0.5) * pick_us);
     // up to 64 channels in the KCRS order: the gather kernel's 64x128 tiles take 0.75 .. 0.82 of their prediction (1019 -> 64 3x3 on 28x28, batch
     // 32: 212 us; waves 230).  74 of 987 such layers were slower on the waves, by up to 10 %; 7 of the 672 that still go there, by up to 9 %
     if (layout == 0 && q.R * q.S > 1 && q.K <= 64 && cfg->algo == 0 && cfg->bn == 128) limit = std::min(limit, 0.76 * pick_us);
     // strided layers tap by tap: a wave's loads spread over twice the cache lines, and a tile's waves come back to a line a whole tap later,
     // when many channels have passed and it is gone: up to 2.5 times what they are predicted, 10 times on inputs beyond the caches (512 -> 64 7x7
-    // on 14x18, batch 64: 112 us, waves 214; 3264 -> 23 4x4 on 21x9, batch 74: 148 and 422).  Of 126 layers of 384 channels and more on inputs
-    // beyond 16 MB 16 were slower than their pick, at 0.5 none of 25.  Operands beyond 64 MB are off for every stride
+    // on 14x18, batch 64: 112 us, waves 214; 3264 -> 23 4x4 on 21x9, batch 74: 148 and 422).  384 channels and more on inputs beyond 16 MB come to
+    // 0.86 .. 1.0 of the pick's time from 0.5 on, one in nine more than 10 % slower, by up to 191 %; other layers into more than 64 channels to 0.98 above 0.77;
+    // into fewer they take 0.9 up to 0.85, from 384 channels 0.89 at 0.65 .. 0.7 (4000 layers drawn among those above these or lower margins)
     const double in_bytes = 4.0 * q.N * q.C * q.H * q.W, operands = in_bytes + 4.0 * q.K * Kg;
-    if (layout == 2) {
+    if (layout == 2 && q.stride > 1) {
         const bool deep = q.C >= 384;
-        const double margin = q.stride == 1                  ? (operands > 64e6 ? 0.7 : 1)
-                              : deep && in_bytes > 16e6      ? 0.5
-                              : operands > 64e6              ? 0.62
-                              : q.K > 64 || pick_us <= 20    ? 0.77
-                              : deep                         ? 0.64
-                                                             : pick_us > 60 ? 0.73 : 0.77;
+        const double margin = deep && in_bytes > 16e6 ? 0.5 : q.C > 1024 && operands > 64e6 ? 0.62 : q.K > 64 ? 0.77 : deep && pick_us > 20 ? 0.72 : 0.83;
         limit = std::min(limit, margin * pick_us);
     }
     // Loads that spread over many lines, and inputs beyond 256 MB, cost the waves up to three times what they are predicted.  In the KCRS order they
-    // are even from 23 lines on above 0.8 (87 drawn layers: 1.02 of the pick's time, 34 slower, by up to 38 %; 0.75 .. 0.8: 0.88, 14 of 123), large inputs
-    // above 0.7 (70: 0.97, 20 slower); with the copy from 16 lines on above 0.66 (634: 0.91, 83 slower, by up to 58 %)
+    // are even from 23 lines on above 0.8 (361 drawn layers: 1.01 of the pick's time, 38 % slower; 0.75 .. 0.8: 0.87, 10 %), large inputs
+    // above 0.7 (70: 0.97, 20 slower); with the copy from 16 lines on above 0.75 (220: 0.97, 31 % slower; 0.65 .. 0.75: 0.91, 15 %), operands beyond 64 MB
+    // above 0.8 (110: 0.92).  The margins for lines lie lower, where the slowest begin: single layers take up to 1.6 times as long
     const bool point = q.R == 1 && q.S == 1 && q.pad == 0;
     const double lines = row_lines(q);
-    if (layout == 0 && lines >= 23) limit = std::min(limit, 0.75 * pick_us);
-    if (layout == 2 && lines >= 16) limit = std::min(limit, 0.66 * pick_us);
-    if (layout == 0 && in_bytes > 256e6) limit = std::min(limit, 0.7 * pick_us);
-    // Strided 1x1 layers whose pick splits gain nothing on tiles of 64x64 (454: 0.96, 76 slower; on 32x32 0.70, 25 of 6140), nor at all above 0.7
+    if (lines >= (layout == 0 ? 23 : 16)) limit = std::min(limit, (layout == 0 ? 0.75 : 0.66) * pick_us);
+    if (layout == 0 ? in_bytes > 256e6 : operands > 64e6) limit = std::min(limit, (layout == 0 ? 0.7 : 0.8) * pick_us);
+    // Strided 1x1 layers whose pick splits gain nothing on tiles of 64x64 above 0.85 (1007: 0.99, 23 % slower; 0.8 .. 0.85: 0.9), nor at all above 0.7
     // on inputs beyond 64 MB (42: 1.0, 19 slower); unsplit ones on inputs beyond 32 MB not above 0.75, at stride 3 not above 0.4 (31: 0.98, 10 slower,
     // and 106: 0.96, 42, by up to 26 %, 128 -> 128 on 68x68, batch 53, 18.4 us and 23.1)
     double limit64 = pick_us;
     if (point && q.stride > 1) {
         const bool split = cfg->split_k > 1;
-        if (split) limit64 = 0.6 * pick_us;
+        if (split) limit64 = (in_bytes > 64e6 ? 0.6 : 0.85) * pick_us;
         if (in_bytes > (split ? 64e6 : 32e6)) limit = std::min(limit, (split ? 0.7 : q.stride == 2 ? 0.75 : 0.4) * pick_us);
     }
     return wave_best(q.K, (double)q.N * q.P * q.Q, std::ceil(Kg / 16.0), wave_loads(q, layout), layout, limit, limit64, no_scratch, q.arena,
@@ -721,30 +718,29 @@ bool conv_wave_pick(const ConvProblem &q, double pick_us, bool no_scratch, polyd
 bool sgemm_wave_pick(const SgemmProblem &q, double pick_us, bool no_scratch, polydl_tile_cfg *cfg)
 {
     if (!wave_exact(q.K, *cfg)) return false;
-    // Long reductions: picks of 48 parts and more take 0.7 of their prediction, and operands beyond 64 MB are mispredicted more often.  At the
-    // margin of the others and without the time of the panels 466 of 5727 drawn products, most of K > 16384, were slower than their
-    // pick, by up to 132 % (105x236x466615: 283 us, waves 656); of 7786 drawn anew that still go there 66, two by more than 32 %
-    const bool strict = 4.0 * q.K * ((double)q.M + q.N) > 64e6 || (cfg->split_k >= 48 && q.K > 16384);
-    const double limit = std::min(wave_limit(pick_us, false), strict ? 0.66 * pick_us : pick_us);
+    // Long reductions: picks of 48 parts and more take 0.7 of their prediction, and neither formula knows how much of the panels the caches keep.
+    // Beyond 16384 products above 0.6 (picks of fewer parts; 1138 drawn: 0.98 of the pick's time, 29 % slower) and 0.5 (433: 1.14, 64 %; 105x236x466615
+    // 283 us, waves 656) are even or worse, and so are those whose panels take more than 0.9 of the pick's prediction (330: 1.02; 0.8 .. 0.9: 0.92, 22 %
+    // slower); up to 16384 those below 0.85 take 0.82 .. 0.9 and one in fifty is slower
+    const bool longer = q.K > 16384;
+    const double limit = std::min(wave_limit(pick_us, false), !longer ? pick_us : cfg->split_k >= 48 ? 0.45 * pick_us : 0.58 * pick_us);
     return wave_best(q.M, q.N, std::ceil(q.K / 16.0), WAVE_ROWS, 0, limit, limit, no_scratch, q.arena,
-                     [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg, 4.0 * q.K);
+                     [&](int tile) { return sgemm_wave_fits(q, tile); }, cfg, 4.0 * q.K, (longer ? 0.8 : 0.85) * pick_us);
 }
 
 // bfloat16, q.C units of eight channels.  The margins are the staged model's: of 3000 drawn layers of 5e6 .. 6e10 flops the picks of 1x1 ones take
 // 0.82 .. 0.92 of their prediction, of others 1.02 .. 1.17, but 0.8 where a reduction of up to 20 steps is one stage; beyond 256 steps both are off.  Over
-// the ranges above 16266 of 24958 layers go there and take 0.61 of the pick's time in sum, 74 of them more than 3 % longer; 1x1 layers 17088 of 38766,
-// 0.62, 27.  Up to eight units a row leave most waves without a
+// the ranges above 16035 of 24283 layers go there and take 0.62 of the pick's time in sum, 91 of them more than 3 % longer; 1x1 layers 17132 of 38410,
+// 0.64, 43.  Up to eight units a row leave most waves without a
 // step; picks predicted at the floor of their model (8.8 us) take 5 us and more, which the larger tile does not undercut.
-// Picks that do not split take 0.8 .. 0.9 of their prediction at 36 steps (128 input channels 3x3), and strided layers of more than 40 us cost the
-// waves 1.2 .. 1.4 times theirs: at 0.92, 29 of 696 drawn ones were slower than their pick, by up to 26 % (803 -> 256 3x3/2 on 28x28, batch 36:
-// 50 us, waves 63; 128 -> 64 3x3/2 on 56x56, batch 64: 20.4 and 23.0); with margins of their own 10 of 576, by up to 12 %.
-// Up to five steps a row (8 -> 8 3x3) the pick takes 0.55 .. 0.7 of the model's
-// floor, and 117 of 1114 were slower on the waves, by up to 20 %, at 0.8 of it; 1x1 layers of more than 15 us and operands beyond 64 MB
-// take the waves up to 2.5 times what they are predicted (20 of 284, 56 of 451 slower, by up to 22 and 70 %).  Two and three steps a row
-// above 0.52 are even (291 of 906 layers: 0.95 of the time, 71 slower, by up to 12 %), strided layers with filters beyond 20 MB above 0.7
-// mispredicted (227 of 417: 36 slower, by up to 87 %, 2513 -> 743 3x3/3 on 100x3, batch 18, 53 us and 98).
-// Strided 1x1 layers of up to five steps on inputs beyond 16 MB are even (93: 0.955, 16 slower, by up to 30 %), 1x1 ones of more than 15 us and
-// 64 steps above 0.6 nearly so (51: 0.93, 13 slower, by up to 24 %).
+// Where the margins lie, of 17000 layers drawn among those above lower ones: picks that do not split take 0.8 .. 0.9 of their prediction at 36 steps
+// (128 input channels 3x3), and strided layers of more than 40 us cost the waves 1.2 .. 1.4 times theirs: above 0.9, and above 0.85 where a
+// pick of up to 48 steps takes more than 18 us, they come to the pick's time (803 -> 256 3x3/2 on 28x28, batch 36: 50 us, waves 63).
+// Two and three steps a row (8 -> 8 3x3), whose pick takes 0.55 .. 0.7 of the model's floor: 0.98 at 0.5 .. 0.55, 1.05 .. 1.11 above; four and five: 0.94 at
+// 0.6 .. 0.65, 1.0 above.  Operands beyond 64 MB take the waves up to 2.5 times what they are predicted, filters beyond 64 MB above 0.72: 1.0 (263, 32 %
+// more than 10 % slower), more than 1024 channels 0.85 (652, 19 %), others 0.84 up to 0.9 (1269, 4 %), 0.95 above; strided layers with filters beyond 20 MB
+// of more than 1024 channels 0.88 above 0.7 (362, 23 %; 2513 -> 743 3x3/3 on 100x3, batch 18: 53 us, waves 98), of fewer 0.76 (730, 4 %).  1x1 layers of more
+// than 15 us and 64 steps: 0.92 at 0.6 .. 0.65 (13 %), 1.0 above; strided ones of up to five steps on inputs beyond 16 MB 0.92 at 0.5 .. 0.55, 0.97 above.
 static WaveLoads wave_bf16_loads(const ConvProblem &q)
 {
     const bool strided = q.stride > 1;
@@ -756,20 +752,20 @@ bool conv_wave_bf16_pick(const ConvProblem &q, double pick_us, bool no_scratch, 
     const int64_t units = (int64_t)q.C * q.R * q.S;
     if (units <= 8) return false;
     const double steps = std::ceil(units / 4.0);
-    const bool unsplit = cfg->split_k <= 1, point = q.R == 1 && q.S == 1, strided = q.stride > 1;
+    const bool unsplit = cfg->split_k <= 1, point = q.R == 1 && q.S == 1, strided = q.stride > 1, deep = q.C > 128;
     const double in_bytes = 16.0 * q.N * q.C * q.H * q.W, filter_bytes = 16.0 * units * q.K;
-    double margin = point           ? (pick_us <= 15 ? 0.72 : units > 256 ? 0.6 : 0.65)
+    double margin = point           ? (pick_us > 15 && units > 256 ? 0.6 : 0.72)
                     : steps < 4     ? 0.52
-                    : steps < 6     ? 0.6
+                    : steps < 6     ? 0.65
                     : steps < 20    ? (q.K <= 32 ? 0.76 : 0.8)
                     : steps > 256   ? 0.88
                     : !unsplit      ? 0.92
-                    : q.stride == 1 ? 0.89
-                    : pick_us > 40  ? 0.88
-                                    : steps <= 48 && pick_us > 18 ? 0.84 : 0.92;
-    if (strided && !point && filter_bytes > 20e6) margin = std::min(margin, 0.7);
-    if (strided && point && unsplit && steps <= 5 && in_bytes > 16e6) margin = 0.4;
-    if (pick_us > 20 && in_bytes + filter_bytes > 64e6) margin = std::min(margin, 0.72);
+                    : !strided      ? 0.9
+                    : pick_us > 40  ? 0.9
+                                    : steps <= 48 && pick_us > 18 ? 0.85 : 0.92;
+    if (strided && !point && deep && filter_bytes > 20e6) margin = std::min(margin, 0.7);
+    if (strided && point && unsplit && steps <= 5 && in_bytes > 16e6) margin = 0.5;
+    if (pick_us > 20 && in_bytes + filter_bytes > 64e6) margin = std::min(margin, deep || filter_bytes > 64e6 ? 0.72 : 0.88);
     const double limit = margin * pick_us;
     return wave_best(q.K, (double)q.N * q.P * q.Q, steps, wave_bf16_loads(q), 0, limit, pick_us < 9.5 ? 0.73 * pick_us : limit, no_scratch,
                      q.arena, [&](int tile) { return conv_wave_bf16_fits(q, tile); }, cfg);
