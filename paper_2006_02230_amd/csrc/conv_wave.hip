@@ -363,10 +363,10 @@ static hipError_t conv_wave_launch_t(const ConvProblem &q, int parts, hipStream_
     int tiles;
     const hipError_t e = conv_wave_args<T>(q, 4, 16, parts, stream, &a, &tiles);
     if (e != hipSuccess) return e;
-    void (*kern)(ConvWaveKArgs) = q.R == 1 && q.S == 1 && q.pad == 0 ? conv_wave_kernel<T, GATHER_POINT>
-                                  : q.wt_tap ? conv_wave_kernel<T, GATHER_TAPMAJOR>
-                                  : a.RS <= 31 ? conv_wave_kernel<T, GATHER_TAPS1> : conv_wave_kernel<T, GATHER_TAPS2>;
-    return wave_launch<T>(kern, tiles, a.parts.parts, stream, a);
+    if (q.R == 1 && q.S == 1 && q.pad == 0) return wave_launch<T, conv_wave_kernel<T, GATHER_POINT>>(tiles, a.parts.parts, stream, a);
+    if (q.wt_tap) return wave_launch<T, conv_wave_kernel<T, GATHER_TAPMAJOR>>(tiles, a.parts.parts, stream, a);
+    if (a.RS <= 31) return wave_launch<T, conv_wave_kernel<T, GATHER_TAPS1>>(tiles, a.parts.parts, stream, a);
+    return wave_launch<T, conv_wave_kernel<T, GATHER_TAPS2>>(tiles, a.parts.parts, stream, a);
 }
 
 // 63 taps are what the mask bits hold; the images a tile touches, read and written, and its filter rows lie within 31-bit offsets.
@@ -390,8 +390,8 @@ static hipError_t conv_wave_bf16_launch_t(const ConvProblem &q, int parts, hipSt
     int tiles;
     const hipError_t e = conv_wave_args<T>(q, 16, 4, parts, stream, &a, &tiles);
     if (e != hipSuccess) return e;
-    void (*kern)(ConvWaveKArgs) = a.RS <= 31 ? conv_wave_bf16_kernel<T, false> : conv_wave_bf16_kernel<T, true>;
-    return wave_launch<T>(kern, tiles, a.parts.parts, stream, a);
+    if (a.RS <= 31) return wave_launch<T, conv_wave_bf16_kernel<T, false>>(tiles, a.parts.parts, stream, a);
+    return wave_launch<T, conv_wave_bf16_kernel<T, true>>(tiles, a.parts.parts, stream, a);
 }
 
 // q.C counts units of eight channels

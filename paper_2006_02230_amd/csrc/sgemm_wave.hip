@@ -96,7 +96,7 @@ static hipError_t sgemm_wave_launch_t(const SgemmProblem &q, int parts, hipStrea
     a.order = wave_order((uint32_t)tiles_m, (uint32_t)tiles_n);
     const hipError_t e = wave_parts((q.K + 15) / 16, parts, tiles, sizeof(float) * T::WM * T::WN, q.arena, stream, &a.parts);
     if (e != hipSuccess) return e;
-    return wave_launch<T>(sgemm_wave_kernel<T>, tiles, a.parts.parts, stream, a);
+    return wave_launch<T, sgemm_wave_kernel<T>>(tiles, a.parts.parts, stream, a);
 }
 
 hipError_t sgemm_wave_launch(const SgemmProblem &q, int tile, int waves, int parts, hipStream_t stream)
