@@ -26,12 +26,12 @@ HBM_PEAK_GBS = 8000.0
 # fetch and write-back counters of two rocprofv3 --pmc runs, each scaled by what the same counter
 # reads for a plain 256 MiB elementwise copy.  Valid only for the kernel sources they were taken
 # with: their digest is kept beside them and the bench line reports null when it no longer matches.
-HBM_TRAFFIC = {"csrc_sha256": "307ab6610a4d3b05432aff8f1c9595327c673d4fc47fd4830df36f9ab8e9ad82", "batch": 32, "filters": "tap", "fetch_bytes": 568791879, "write_bytes": 408603412}
+HBM_TRAFFIC = {"csrc_sha256": "bcd9a350a253a845e5d0b9eed4419be2fe111b9a98bed7e449d43daaff337eba", "batch": 32, "filters": "tap", "fetch_bytes": 568582168, "write_bytes": 408611853}
 
 
 # L2 fetch + write-back bytes of config 4 from two rocprofv3 --pmc runs of `bench.py --copy-probe --counter-pass
 # fusion` (same scaling as above): the fused launch, and the convolution + bias + activation launches it replaces.
-FUSION_TRAFFIC = {"csrc_sha256": "307ab6610a4d3b05432aff8f1c9595327c673d4fc47fd4830df36f9ab8e9ad82", "fused_bytes": 84575956, "separate_bytes": 110415799}
+FUSION_TRAFFIC = {"csrc_sha256": "bcd9a350a253a845e5d0b9eed4419be2fe111b9a98bed7e449d43daaff337eba", "fused_bytes": 84528908, "separate_bytes": 110357798}
 
 COLD_ROTATION_BYTES = 640 * 1000 * 1000
 
